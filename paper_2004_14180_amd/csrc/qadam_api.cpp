@@ -116,6 +116,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.num_segments = h->num_segments;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
+    L.ticket = h->d_status + 32;
     L.need_amax = h->need_amax; L.need_reduce = h->need_reduce;
     return L;
 }

@@ -92,6 +92,7 @@ struct Launch {
     const int32_t* sample_tiles;    // device: indices of the sampled tiles
     int32_t     num_sample_tiles;
     uint32_t*   status;     // device status word
+    uint32_t*   ticket;     // device work counter of the fused kernel, zero between launches
     bool        need_amax;   // server-moments path: some layer is neither small nor empty (else no tile-maxima launch)
     bool        need_reduce; // some layer has more than kMediumLayerTiles tiles, or is empty (else no scale-folding launch)
     hipStream_t stream;

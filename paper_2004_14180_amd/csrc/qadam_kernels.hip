@@ -544,6 +544,8 @@ struct FusedArgs {
     const uint32_t* tile_max;     // [N][num_tiles]
     const int32_t* seg_tile_begin;
     int num_segments;
+    uint32_t* ticket;             // work counter of the launch (see take_ticket); null: take blockIdx
+    int parts;                    // pieces a tile is cut into, one workgroup each: 1, 2 or 4
     StepScalars S;
     ServerPtrs sp;
     const float* grad[QADAM_MAX_WORKERS];
@@ -569,6 +571,26 @@ struct WorkerArgs {        // one worker
     int worker;
     int64_t seg_len;           // tiles == null only: length of the single segment
 };
+
+// Position of this workgroup in the launch's work order: a device-wide counter, not blockIdx.  The eight
+// XCDs each start their share of a grid in order, but they drift apart, and then the workgroups in flight
+// are spread over a wide stretch of every one of the step's 2N+4 read and N+5 written streams, which costs
+// DRAM page hits.  With tickets the bare access pattern of the main pass (20 reads, 13 writes, buffers packed
+// one behind the other) goes from 3.12 to 2.96 ms (5.5 -> 5.8 TB/s) and the whole step of 1.3 G parameters,
+// 4 workers, from 23.1 to 20.9 ms.  A ticket costs about 12 ns of the counter's time (85 per microsecond
+// over the whole chip), so a work item has to move more than some 70 KB.
+// The last ticket of a launch puts the counter back to zero for the next.
+__device__ __forceinline__ uint32_t take_ticket(uint32_t* counter)
+{
+    __shared__ uint32_t mine;
+    if (threadIdx.x == 0) {
+        const uint32_t t = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == gridDim.x - 1) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine = t;
+    }
+    __syncthreads();
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
+}
 
 // Tile record of workgroup `ti`: from the handle's table, or, for the handle-free single-segment
 // call (tiles == null), computed from the segment length: tile ti covers elements
@@ -1317,7 +1339,8 @@ __global__ void __launch_bounds__(kBlockThreads) k_weight_dequantize(DequantArgs
 // (the first pass left p_i = alpha m_i / sqrt(v_i + eps) + e_i in the error buffers; the server
 // only subtracts the mean message).
 template <int V, int ROUNDING, int U, bool W, bool INLINE = false, bool SH = false>
-__device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, const SmallLayerShared* sh = nullptr)
+__device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, const SmallLayerShared* sh = nullptr,
+                                           int part_begin = 0, int part_len = kDefaultTileElems)
 {
     constexpr int WAVE_ELEMS = 64 * V, BLOCK_ELEMS = (kBlockThreads / 64) * WAVE_ELEMS;
     const StepScalars& S = A.S;
@@ -1325,7 +1348,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, co
     const QgConst c = make_qg(S.k_g);
     const int N = S.num_workers;
     const Shift sf = make_shift(t);
-    for (int base = wave * WAVE_ELEMS; base < t.len; base += BLOCK_ELEMS) {
+    for (int base = part_begin + wave * WAVE_ELEMS; base < min(t.len, part_begin + part_len); base += BLOCK_ELEMS) {
         const int off = base + lane * V;
         const int nvalid = min(max(t.len - off, 0), V);
         const int64_t gi = t.start + off;
@@ -1430,9 +1453,16 @@ __device__ __forceinline__ void fused_small_layer(const FusedArgs& A, const Tile
 template <int ROUNDING, int U, bool W>
 __global__ void __launch_bounds__(kBlockThreads) k_fused(FusedArgs A)
 {
-    const int ti = blockIdx.x;
+    int ti = blockIdx.x, part_begin = 0, part_len = kDefaultTileElems;
+    if constexpr (!W) {
+        const uint32_t item = A.ticket ? take_ticket(A.ticket) : blockIdx.x;
+        ti = (int)(item / (uint32_t)A.parts);
+        part_len = kDefaultTileElems / A.parts;
+        part_begin = (int)(item % (uint32_t)A.parts) * part_len;
+    }
     const Tile t = A.tiles[ti];
     if constexpr (!W) {
+        if (part_begin > 0 && (part_begin >= t.len || (t.flags & kTileSmallHead))) return;
         // small layers: the workgroup of the first tile does the whole layer, scales included
         if (t.flags & kTileSmallBody) return;
         if (t.flags & kTileSmallHead) {
@@ -1450,13 +1480,13 @@ __global__ void __launch_bounds__(kBlockThreads) k_fused(FusedArgs A)
             if ((threadIdx.x & 63) == 0) sh.part[i][threadIdx.x >> 6] = wm;
         }
         small_layer_finish(sh, 0, N, t.seg, A.num_segments, A.scales, A.inv_scales, A.err_bound, A.bound_factor, false,
-                           ti == t0);
-        if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, true, true>(A, t, &sh);
-        else fused_tile<4, ROUNDING, U, W, true, false>(A, t, &sh);
+                           ti == t0 && part_begin == 0);
+        if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, true, true>(A, t, &sh, part_begin, part_len);
+        else fused_tile<4, ROUNDING, U, W, true, false>(A, t, &sh, part_begin, part_len);
         return;
     }
-    if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, false, true>(A, t);
-    else fused_tile<4, ROUNDING, U, W, false, false>(A, t);
+    if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, false, true>(A, t, nullptr, part_begin, part_len);
+    else fused_tile<4, ROUNDING, U, W, false, false>(A, t, nullptr, part_begin, part_len);
 }
 
 // ---- Q_g = identity: the messages are fp32 values ------------------------------------------------
@@ -1845,6 +1875,17 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
     return hipGetLastError();
 }
 
+// Pieces a tile is cut into by the ticketed main pass.  Half tiles keep the workgroups in flight on a
+// narrower stretch of every buffer (124 M parameters, 8 workers: 3.90 ms per step with whole tiles, 3.78 with
+// halves, 3.78 with quarters) at half the tickets of quarters; a vector that would give the chip fewer than
+// four workgroups per CU is cut into quarters (11.7 M parameters: 257 -> 255 us).  Beyond 2^22 tiles the grid
+// limit (work items x 256 threads below 2^32) leaves whole tiles only.
+static int pieces_per_tile(int num_tiles)
+{
+    if (num_tiles >= 1 << 22) return 1;
+    return num_tiles < 4096 ? 4 : 2;
+}
+
 static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
                                    bool variant_w)
 {
@@ -1857,8 +1898,12 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    const dim3 grid(L.num_tiles), block(kBlockThreads);
     const int N = S.num_workers;
+    // a launch that fits the chip at once has no order to keep: there the ticket is 2 us of latency for nothing
+    // (51 k parameters, 4 workers: 81 us per step without, 85 with)
+    A.ticket = L.num_tiles >= 1024 ? L.ticket : nullptr;
+    A.parts = variant_w ? 1 : pieces_per_tile(L.num_tiles);
+    const dim3 grid((unsigned)L.num_tiles * (unsigned)A.parts), block(kBlockThreads);
     // loads of up to four workers in flight per lane: more (eight) costs registers and occupancy
     // without a measurable gain
 #define QADAM_LAUNCH_FUSED(R, WV)                                                                     \
