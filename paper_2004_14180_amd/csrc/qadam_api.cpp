@@ -31,7 +31,7 @@ struct qadam_ctx {
     uint32_t* d_thr;            // [num_workers][num_segments]
     int32_t*  d_sample_tiles;   // indices of the sampled tiles
     int32_t   num_sample_tiles;
-    bool      need_amax, need_reduce;   // which launches of the scale pass this layer list needs at all
+    bool      empty_layers;     // some layer has no element
     int       trust_errs;                       // qadam_trust_error_buffers: 0 off, 1 when it pays, 2 always, 3 verify
     bool      bound_valid[QADAM_MAX_WORKERS];   // d_err_bound row i describes what bound_err[i] now holds
     const float* bound_err[QADAM_MAX_WORKERS];  // the error buffer that row was recorded for
@@ -115,9 +115,8 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.num_segments = h->num_segments;
+    L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
-    L.ticket = h->d_status + 32;
-    L.need_amax = h->need_amax; L.need_reduce = h->need_reduce;
     return L;
 }
 
@@ -273,15 +272,12 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     std::vector<int32_t> sample_tiles;
     std::vector<int32_t> seg_tile_begin(num_segments + 1, 0);
     int64_t word_off = 0;
-    bool need_amax = false, need_reduce = false;
     for (int l = 0; l < num_segments; ++l) {
         seg_tile_begin[l] = (int32_t)tiles.size();
         const int64_t a = seg_offsets[l], n = seg_offsets[l + 1] - a;
         const int64_t seg_words = segment_code_words(h->code_bits, n);
         const int64_t used_words = (n + 31) / 32 * h->code_bits;
-        const int64_t layer_tiles = (n + h->tile_elems - 1) / h->tile_elems;
-        if (n == 0 || layer_tiles > kMediumLayerTiles) need_reduce = true;   // an empty layer's scale (0) comes from there too
-        if (n > kSmallLayerElems) need_amax = true;
+        if (n == 0) h->empty_layers = true;
         for (int64_t o = 0; o < n; o += h->tile_elems) {
             Tile t;
             t.start = a + o;
@@ -290,17 +286,10 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             t.seg = l;
             t.flags = (a % 4 != 0) ? kTileUnaligned : 0;
             if (o + h->tile_elems >= n) t.flags |= (int32_t)(seg_words - used_words) << 8;
-            t.layer_len = 0;
-            if (layer_tiles <= kMediumLayerTiles) t.flags |= kTileMedium;
-            if (n <= kSmallLayerElems) {
-                // one workgroup (that of the first tile) handles the whole layer; never a sampled tile
-                t.flags |= o == 0 ? kTileSmallHead : kTileSmallBody;
-                if (o == 0) t.layer_len = (int32_t)n;
-            } else {
-                if ((o / h->tile_elems) % kSampleStride == 0) {
-                    t.flags |= kTileSampled;
-                    sample_tiles.push_back((int32_t)tiles.size());
-                }
+            t.reserved = 0;
+            if ((o / h->tile_elems) % kSampleStride == 0) {
+                t.flags |= kTileSampled;
+                sample_tiles.push_back((int32_t)tiles.size());
             }
             tiles.push_back(t);
         }
@@ -311,8 +300,6 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     seg_tile_begin[num_segments] = (int32_t)tiles.size();
     h->num_tiles = (int32_t)tiles.size();
     h->num_sample_tiles = (int32_t)sample_tiles.size();
-    h->need_amax = need_amax;
-    h->need_reduce = need_reduce;
 
     hipError_t e = hipGetDevice(&h->device);
     // set-up of the allocation-free entry point for this device (address of its static array), so that
@@ -326,7 +313,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     if (e == hipSuccess)
         e = hipMemcpy(h->d_seg_tile_begin, seg_tile_begin.data(), sizeof(int32_t) * (num_segments + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess && h->num_tiles > 0)
-        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->num_tiles * num_workers);
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->num_tiles * num_workers * kMomentParts);
     if (e == hipSuccess && h->num_tiles > 0)
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_sum), sizeof(double) * (size_t)h->num_tiles);
     if (e == hipSuccess && num_segments > 0)
@@ -578,7 +565,7 @@ int qadam_worker_step_w(qadam_handle_t h, int32_t worker, int64_t step, float lr
     // pass 1: local moments, p = alpha m / sqrt(v + eps) + e parked in the error buffer, tile maxima
     BoundRecord record(h, worker, 1, W);
     QADAM_HIP(launch_worker_moments_w(L, S, W, worker, 1));
-    QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1));
+    QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1, moment_parts(L.num_tiles)));
     // pass 2: quantize the parked p
     W.grad[worker] = nullptr;
     QADAM_HIP(launch_worker_quantize(L, S, W, worker));
@@ -616,7 +603,7 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     // pass 1 (all workers): local moments, p parked in the error buffers, tile maxima; then scales
     BoundRecord record(h, 0, h->num_workers, W);
     QADAM_HIP(launch_worker_moments_w(L, S, W, 0, h->num_workers));
-    if (!idg) QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers));
+    if (!idg) QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers, moment_parts(L.num_tiles)));
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
     // pass 2: quantize every worker's parked p, subtract the mean message, Q_x
     if (idg) QADAM_HIP(launch_plain_messages(L, S, W, sp, true));

@@ -19,29 +19,19 @@ struct Tile {
     int32_t seg;        // layer segment the tile belongs to
     int32_t flags;      // bit 0: start is not a multiple of 4 (no 128-bit accesses);
                         // bit 1: sampled tile of the filtered scale pass;
-                        // bit 2: first tile of a small layer (see below); bit 3: a later tile of one;
                         // bits 8..9: zero words to append after the tile's codes (segment padding)
-    int32_t layer_len;  // first tile of a small layer: elements of the whole layer; else 0
+    int32_t reserved;
 };
 static_assert(sizeof(Tile) == 32, "tile records are read as two 128-bit scalar loads");
 
 constexpr int kTileUnaligned = 1;
 constexpr int kTileSampled = 2;
-// A small layer (at most kSmallLayerElems elements) is handled by ONE workgroup in the kernels of the
-// server-moments path: the workgroup of the layer's first tile takes the layer's scales itself (one read
-// of g and e, which stay in cache) and then quantizes all of the layer's tiles, so these layers make a
-// single trip through HBM and need no scale pass; the workgroups of the layer's other tiles exit at once.
-// The worker-moments path (whose first pass produces the tile maxima anyway) ignores the two flags.
-constexpr int kTileSmallHead = 4;
-constexpr int kTileSmallBody = 8;
-constexpr int kSmallLayerElems = 4 * 4096;
-// A layer of at most kMediumLayerTiles tiles (small layers included) needs no launch of the kernel that
-// folds tile maxima into scales: every workgroup that quantizes one of its tiles folds the layer's few
-// tile maxima itself (they sit in L2), and the workgroup of the layer's first tile writes the scale out.
-constexpr int kTileMedium = 16;
-constexpr int kMediumLayerTiles = 640;
 constexpr int kSampleStride = 64;   // every 64th tile of a layer (from its first) is a sampled tile
 constexpr int kBlockThreads = 256;
+constexpr int kReduceThreads = 1024;
+// pieces a tile is cut into by the first pass of variant W, each with a maximum of its own
+constexpr int kMomentParts = 1;
+inline int moment_parts(int num_tiles) { return num_tiles < (1 << 22) ? kMomentParts : 1; }
 constexpr int kDefaultTileElems = 4096;   // elements per tile (16 per lane of a 256-thread workgroup)
 
 // Scalars of one launch, identical for every kernel.
@@ -91,10 +81,8 @@ struct Launch {
     uint32_t*   thr;        // device, [num_workers][num_segments]: thresholds of the filtered scale pass
     const int32_t* sample_tiles;    // device: indices of the sampled tiles
     int32_t     num_sample_tiles;
+    bool        empty_layers;   // some layer has no element: its scale (0) has no quantizing workgroup to write it
     uint32_t*   status;     // device status word
-    uint32_t*   ticket;     // device work counter of the fused kernel, zero between launches
-    bool        need_amax;   // server-moments path: some layer is neither small nor empty (else no tile-maxima launch)
-    bool        need_reduce; // some layer has more than kMediumLayerTiles tiles, or is empty (else no scale-folding launch)
     hipStream_t stream;
 };
 
@@ -102,7 +90,8 @@ struct Launch {
 // scales in two stages without atomics: per-tile maxima, then one workgroup per (worker, layer)
 // reduces its tiles and also writes the reciprocal used by the fast quotient
 hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
-hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
+hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
+                                int max_per_tile = 1);
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker);

@@ -7,19 +7,17 @@
 //   * 64-wide wavefronts, 256-thread workgroups; a lane owns 4 consecutive fp32 values so every
 //     global access is a 128-bit load/store and a wavefront touches 1 KiB of contiguous memory;
 //     all buffers are touched once per pass, so loads and stores carry the non-temporal hint;
-//   * a workgroup owns one tile (<= 4096 elements of one layer), so all per-layer quantities
-//     (scales, code offsets) are wave-uniform and live in scalar registers;
-//   * the loads of a group of workers are issued together before any arithmetic, so a wavefront
-//     keeps 16-20 KiB in flight and few wavefronts per SIMD suffice to cover HBM latency;
+//   * work is cut along tiles (<= 4096 elements of one layer), so all per-layer quantities (scales, code
+//     offsets) are wave-uniform and live in scalar registers;
+//   * the main pass, the worker quantizer and the server run as workgroups of ONE wavefront each, which drift
+//     apart and so mix their reads and writes (see Items); the loads of a group of workers are issued together
+//     before any arithmetic;
 //   * the per-layer scale is a max over |g+e|: lanes reduce with integer max on the bit pattern
 //     (non-negative floats order like integers; NaN/Inf sort above every finite value and so
 //     surface in the scale), wavefront reduction by cross-lane shuffles, LDS across the four
 //     wavefronts, one plain store of the tile's maximum; the tile maxima of a layer are folded by a
-//     second small kernel (layers of more than 640 tiles) or by the quantizing workgroups themselves
-//     (smaller layers: the few maxima sit in L2, and the launch is saved).  No atomics: thousands of
-//     workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole pass;
-//   * a layer of at most 16384 elements is done by ONE workgroup, scale included: g and e are read
-//     once from memory (the quantizing phase finds them in cache), no scale pass is needed for it;
+//     second small kernel, or on short vectors by the quantizing wavefronts themselves.  No atomics: thousands
+//     of workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole pass;
 //   * a segment that starts off the 16-byte grid keeps the same lane-to-element mapping (the codes are
 //     anchored at the segment start) and moves its data with dword-aligned 128-bit accesses;
 //   * when the error buffers are what the previous step wrote, |e| <= s/4 (half the widest gap of
@@ -262,14 +260,12 @@ __device__ __forceinline__ uint32_t load_planes(const uint32_t* __restrict__ chu
 // guarded vector access: one 128-bit non-temporal access when the lane's V=4 elements are all
 // inside the tile (every buffer is streamed exactly once per pass)
 // ------------------------------------------------------------------------------------------------
-template <int V, bool STREAMING = true>
+template <int V>
 __device__ __forceinline__ void load_v(const float* __restrict__ p, int nvalid, float (&out)[V])
 {
     if constexpr (V == 4) {
         if (nvalid == 4) {
-            // STREAMING = false: the data is read again shortly (small layers), so no non-temporal hint
-            const f4 t = STREAMING ? __builtin_nontemporal_load(reinterpret_cast<const f4*>(p))
-                                   : *reinterpret_cast<const f4*>(p);
+            const f4 t = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
             out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
         } else {
 #pragma unroll
@@ -518,6 +514,28 @@ __device__ __forceinline__ void weight_lane(const StepScalars& S, const float (&
 // ------------------------------------------------------------------------------------------------
 // kernel argument blocks
 // ------------------------------------------------------------------------------------------------
+// Work items of the kernels whose workgroups are single wavefronts (the main pass, the worker quantizer, the
+// server): a tile is cut into `parts` pieces and each is one workgroup.  Wavefronts that share a workgroup start
+// together and then load and store in step, and the next four start when the last of them has ended; on their own
+// they drift apart, so reads and writes mix, and the workgroups in flight cover a narrower stretch of each of the
+// 2N+4 read and N+5 written streams (main pass with four wavefronts per workgroup -> one: 11.7 M parameters,
+// 4 workers 204 -> 172 us; 124 M, 8 workers 3.29 -> 3.04 ms; 1.3 G, 4 workers 19.5 -> 18.4 ms).
+//
+// Workgroups go to the eight XCDs in turn.  wave_item gives the workgroups of one XCD runs of consecutive items, so
+// that the pieces of a line of packed codes, which neighbouring items write, meet in one L2.
+struct Items {
+    uint32_t count;             // tiles * parts
+    uint32_t parts;             // pieces per tile
+    uint32_t run_shift;         // log2 of the items in a row that go to one XCD
+};
+
+__device__ __forceinline__ uint32_t wave_item(const Items& I)
+{
+    const uint32_t xcd = blockIdx.x & 7u, k = blockIdx.x >> 3;
+    const uint32_t mask = (1u << I.run_shift) - 1u;
+    return (((k & ~mask) << 3) | (xcd << I.run_shift)) + (k & mask);
+}
+
 struct AmaxArgs {
     const Tile* tiles;
     int num_tiles;
@@ -531,21 +549,26 @@ struct AmaxArgs {
     const float* err_bound;     // verification only: [N][L] bounds the error buffers must respect
     uint32_t* status;
     int64_t seg_len;            // tiles == null only: length of the single segment
-    int skip_small;             // non-zero: tiles of small layers are left to the quantizing kernel
+};
+
+// How a quantizing kernel comes by the scales.  tile_max == null: k_reduce_scales has written scales and reciprocals.
+// Else every wavefront folds the maxima of its layer itself, and the first one of the layer writes out what
+// k_reduce_scales would have written.
+struct Fold {
+    const uint32_t* tile_max;       // rows of `row` maxima, `per_tile` to a tile
+    const int32_t* seg_tile_begin;  // null: one segment that owns the whole row
+    int row, per_tile;
+    int num_segments;
+    float* inv_scales;              // [N][L]
+    float* err_bound;               // [N][L]
+    float bound_factor;
 };
 
 struct FusedArgs {
     const Tile* tiles;
-    int num_tiles;
+    Items items;
     uint32_t* status;
-    float* inv_scales;            // [N][L]
-    float* err_bound;             // [N][L], written for small and medium layers (the scale kernel writes the others)
-    float bound_factor;
-    const uint32_t* tile_max;     // [N][num_tiles]
-    const int32_t* seg_tile_begin;
-    int num_segments;
-    uint32_t* ticket;             // work counter of the launch (see take_ticket); null: take blockIdx
-    int parts;                    // pieces a tile is cut into, one workgroup each: 1, 2 or 4
+    Fold fold;
     StepScalars S;
     ServerPtrs sp;
     const float* grad[QADAM_MAX_WORKERS];
@@ -556,41 +579,17 @@ struct FusedArgs {
 
 struct WorkerArgs {        // one worker
     const Tile* tiles;
-    int num_tiles;
+    Items items;
     uint32_t* status;
     StepScalars S;
     const float* grad;     // variant S: g;  variant W second pass: null (p was parked in err)
     float* err;
     uint32_t* codes;
     float* scales;
-    float* inv_scales;         // this worker's row
-    float* err_bound;          // this worker's row, written for small and medium layers
-    float bound_factor;
-    const uint32_t* tile_max;  // this worker's row
-    const int32_t* seg_tile_begin;
+    Fold fold;                 // its tables start at this worker's rows
     int worker;
     int64_t seg_len;           // tiles == null only: length of the single segment
 };
-
-// Position of this workgroup in the launch's work order: a device-wide counter, not blockIdx.  The eight
-// XCDs each start their share of a grid in order, but they drift apart, and then the workgroups in flight
-// are spread over a wide stretch of every one of the step's 2N+4 read and N+5 written streams, which costs
-// DRAM page hits.  With tickets the bare access pattern of the main pass (20 reads, 13 writes, buffers packed
-// one behind the other) goes from 3.12 to 2.96 ms (5.5 -> 5.8 TB/s) and the whole step of 1.3 G parameters,
-// 4 workers, from 23.1 to 20.9 ms.  A ticket costs about 12 ns of the counter's time (85 per microsecond
-// over the whole chip), so a work item has to move more than some 70 KB.
-// The last ticket of a launch puts the counter back to zero for the next.
-__device__ __forceinline__ uint32_t take_ticket(uint32_t* counter)
-{
-    __shared__ uint32_t mine;
-    if (threadIdx.x == 0) {
-        const uint32_t t = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (t == gridDim.x - 1) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        mine = t;
-    }
-    __syncthreads();
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
-}
 
 // Tile record of workgroup `ti`: from the handle's table, or, for the handle-free single-segment
 // call (tiles == null), computed from the segment length: tile ti covers elements
@@ -609,7 +608,7 @@ __device__ __forceinline__ Tile tile_at(const Tile* __restrict__ tiles, int ti, 
         const int64_t used = (seg_len + 31) / 32 * code_bits;
         t.flags = (int32_t)((used + 3) / 4 * 4 - used) << 8;     // zero words up to a multiple of 16 bytes
     }
-    t.layer_len = 0;
+    t.reserved = 0;
     return t;
 }
 
@@ -619,11 +618,11 @@ struct ScaleArgs {
     const uint32_t* tile_max;
     const int32_t* seg_tile_begin;
     int first_worker, num_segments, num_tiles;
+    int max_per_tile;       // maxima the pass before left per tile
     float* err_bound;       // [N][L]: bound on |e'| after the step that uses these scales
     uint32_t* thr;          // [N][L]: thresholds of the filtered pass (written by k_reduce_lower_bounds)
     float bound_factor;     // |e'| <= bound_factor * s for this quantizer and rounding mode
     int sample_stride;      // every sample_stride-th tile of a layer is a sampled tile
-    const Tile* tiles;      // to recognise the layers whose scales the quantizing kernel folds itself (null: none)
 };
 
 // ------------------------------------------------------------------------------------------------
@@ -641,16 +640,17 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 }
 
 // block-wide max of the lanes' values; thread 0 gets the result
+template <int THREADS = kBlockThreads>
 __device__ __forceinline__ uint32_t block_max(uint32_t local)
 {
-    __shared__ uint32_t wave_part[kBlockThreads / 64];
+    __shared__ uint32_t wave_part[THREADS / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t wm = wave_max_u32(local);
     if (lane == 0) wave_part[wave] = wm;
     __syncthreads();
     uint32_t bm = wave_part[0];
 #pragma unroll
-    for (int w = 1; w < kBlockThreads / 64; ++w) bm = wave_part[w] > bm ? wave_part[w] : bm;
+    for (int w = 1; w < THREADS / 64; ++w) bm = wave_part[w] > bm ? wave_part[w] : bm;
     return bm;
 }
 
@@ -658,7 +658,6 @@ __device__ __forceinline__ uint32_t block_max(uint32_t local)
 // maximum does not care which lane sees which element, so the range is walked as the aligned quads of
 // memory it contains plus at most three single elements at either end.  thr != 0: e is read only for
 // quads (elements) whose |g| reaches thr (filtered scale pass).
-template <bool STREAMING>
 __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, const float* __restrict__ e,
                                                int64_t start, int len, uint32_t thr)
 {
@@ -687,8 +686,8 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
             live[k] = q < a1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { gv[k][j] = 0.0f; ev[k][j] = 0.0f; }
-            if (live[k] && g) load_v<4, STREAMING>(g + q, 4, gv[k]);
-            if (live[k] && thr == 0u) load_v<4, STREAMING>(e + q, 4, ev[k]);
+            if (live[k] && g) load_v<4>(g + q, 4, gv[k]);
+            if (live[k] && thr == 0u) load_v<4>(e + q, 4, ev[k]);
         }
         if (thr != 0u) {
 #pragma unroll
@@ -700,7 +699,7 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
                     top = ab > top ? ab : top;
                 }
                 cand[k] = live[k] && top >= thr;
-                if (cand[k]) load_v<4, STREAMING>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
+                if (cand[k]) load_v<4>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
             }
         }
 #pragma unroll
@@ -717,99 +716,82 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
     return local;
 }
 
-// ---- small layers: the scales are taken by the quantizing workgroup itself -----------------------
-struct SmallLayerShared {
-    uint32_t part[QADAM_MAX_WORKERS][kBlockThreads / 64];
-    float scale[QADAM_MAX_WORKERS];
-    float inv[QADAM_MAX_WORKERS];
+struct Scale {
+    float s, inv;
 };
 
-// max |g + e| over the n elements of a layer that start at flat index `start`, over this wavefront's
-// share; the loads carry no streaming hint because the quantizing phase reads the same lines again
-template <int V>
-__device__ __forceinline__ uint32_t small_layer_wave_max(const float* __restrict__ g, const float* __restrict__ e,
-                                                         int64_t start, int n)
+// 1/s must be a normal number with full precision for the error bound of the fast quotient, else 0
+__device__ __forceinline__ Scale make_scale(uint32_t max_bits)
 {
-    uint32_t local = 0;
-    for (int off = threadIdx.x * V; off < n; off += kBlockThreads * V) {
-        const int nvalid = min(n - off, V);
-        float gv[V], ev[V];
-        load_v<V, false>(g + start + off, nvalid, gv);
-        load_v<V, false>(e + start + off, nvalid, ev);
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const uint32_t ab = f2u(gv[j] + ev[j]) & 0x7fffffffu;
-            local = ab > local ? ab : local;
-        }
-    }
-    return wave_max_u32(local);
+    Scale r;
+    r.s = u2f(max_bits);
+    const bool ok = r.s >= 0x1p-100f && r.s <= 0x1p100f;
+    r.inv = ok ? 1.0f / r.s : 0.0f;
+    return r;
 }
 
-// After every wavefront has stored its part for workers first..first+count-1: thread k folds the parts of
-// worker first+k into the scale and its reciprocal (the same two operations k_reduce_scales performs),
-// keeps them in LDS for the workgroup and writes scale, reciprocal and residual bound to global memory.
-__device__ __forceinline__ void small_layer_finish(SmallLayerShared& sh, int first, int count, int seg, int num_segments,
-                                                   float* const* scales, float* inv_scales, float* err_bound,
-                                                   float bound_factor, bool per_worker_rows, bool write_global = true)
+// what the residual p - Q_g(p) of a step with this scale can reach (a non-finite scale gives a non-finite
+// bound, which switches the next step's filter off); the added 2^-140 covers scales so small that s * level
+// itself is rounded
+__device__ __forceinline__ float residual_bound(float s, float bound_factor) { return s * bound_factor + 0x1p-140f; }
+
+// Scale of the tile's layer for the worker of table row `row`, from where k_reduce_scales left it.
+__device__ __forceinline__ Scale stored_scale(const Fold& F, int row, const Tile& t, const float* scales)
 {
-    __syncthreads();
-    if ((int)threadIdx.x < count) {
-        const int i = first + (int)threadIdx.x;
-        uint32_t bm = sh.part[i][0];
-#pragma unroll
-        for (int w = 1; w < kBlockThreads / 64; ++w) bm = sh.part[i][w] > bm ? sh.part[i][w] : bm;
-        const float s = u2f(bm);
-        const bool ok = s >= 0x1p-100f && s <= 0x1p100f;
-        const float inv = ok ? 1.0f / s : 0.0f;
-        sh.scale[i] = s;
-        sh.inv[i] = inv;
-        if (write_global) {
-            // per_worker_rows: the table pointers address worker i's row; else row i of an [N][L] table
-            const size_t row = per_worker_rows ? 0 : (size_t)i * num_segments;
-            scales[per_worker_rows ? 0 : i][seg] = s;
-            inv_scales[row + seg] = inv;
-            err_bound[row + seg] = s * bound_factor + 0x1p-140f;
-        }
-    }
-    __syncthreads();
+    Scale r;
+    r.s = scales[t.seg];
+    r.inv = F.inv_scales[(size_t)row * F.num_segments + t.seg];
+    return r;
 }
 
-// this wavefront's share of the max over the tile maxima [t0, t1) of one worker (medium layers)
-__device__ __forceinline__ uint32_t medium_layer_wave_max(const uint32_t* __restrict__ tile_max_row, int t0, int t1)
+// The same, folded by one wavefront; `first`: the wavefront writes it out if its tile `ti` is the layer's first.
+__device__ __forceinline__ Scale folded_scale(const Fold& F, int row, const Tile& t, int ti, bool first, float* scales)
 {
+    const int t0 = F.seg_tile_begin ? F.seg_tile_begin[t.seg] * F.per_tile : 0;
+    const int t1 = F.seg_tile_begin ? F.seg_tile_begin[t.seg + 1] * F.per_tile : F.row;
+    const uint32_t* part = F.tile_max + (size_t)row * F.row;
     uint32_t local = 0;
-    for (int t = t0 + (int)threadIdx.x; t < t1; t += kBlockThreads) {
-        const uint32_t v = tile_max_row[t];
+    for (int k = t0 + (int)threadIdx.x; k < t1; k += 64) {
+        const uint32_t v = part[k];
         local = v > local ? v : local;
     }
-    return wave_max_u32(local);
+    const Scale r = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(local)));
+    if (first && ti * F.per_tile == t0 && threadIdx.x == 0) {
+        scales[t.seg] = r.s;
+        F.inv_scales[(size_t)row * F.num_segments + t.seg] = r.inv;
+        F.err_bound[(size_t)row * F.num_segments + t.seg] = residual_bound(r.s, F.bound_factor);
+    }
+    return r;
 }
 
-// grid: (layers, workers).  One workgroup folds the tile maxima of its (worker, layer).
-__global__ void __launch_bounds__(kBlockThreads) k_reduce_scales(ScaleArgs A)
+__device__ __forceinline__ void check_scale(float s, uint32_t* status)
+{
+    if (!(s >= 0.0f && s < __builtin_inff()) && threadIdx.x == 0) atomicOr(status, QADAM_STATUS_NONFINITE_SCALE);
+}
+
+// grid: (layers, workers).  One workgroup folds the maxima of its (worker, layer).  The maxima come from L2 and
+// what bounds the kernel is the chain of loads of one thread, hence 1024 threads and eight loads in flight each.
+__global__ void __launch_bounds__(kReduceThreads) k_reduce_scales(ScaleArgs A)
 {
     const int l = blockIdx.x, w = A.first_worker + blockIdx.y;
     // no table: a single segment that owns every tile
-    const int t0 = A.seg_tile_begin ? A.seg_tile_begin[l] : 0;
-    const int t1 = A.seg_tile_begin ? A.seg_tile_begin[l + 1] : A.num_tiles;
-    if (A.tiles && t1 > t0 && (A.tiles[t0].flags & kTileMedium)) return;
-    const uint32_t* part = A.tile_max + (size_t)w * A.num_tiles;
+    const int t0 = (A.seg_tile_begin ? A.seg_tile_begin[l] : 0) * A.max_per_tile;
+    const int t1 = (A.seg_tile_begin ? A.seg_tile_begin[l + 1] : A.num_tiles) * A.max_per_tile;
+    const uint32_t* part = A.tile_max + (size_t)w * A.num_tiles * A.max_per_tile;
     uint32_t local = 0;
-    for (int t = t0 + threadIdx.x; t < t1; t += kBlockThreads) {
-        const uint32_t v = part[t];
-        local = v > local ? v : local;
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += kReduceThreads * 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = t + k * kReduceThreads < t1 ? part[t + k * kReduceThreads] : 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) local = v[k] > local ? v[k] : local;
     }
-    const uint32_t bm = block_max(local);
+    const uint32_t bm = block_max<kReduceThreads>(local);
     if (threadIdx.x == 0) {
-        const float s = u2f(bm);
-        A.scales[w][l] = s;
-        // 1/s must be a normal number with full precision for the error bound of the fast quotient
-        const bool ok = s >= 0x1p-100f && s <= 0x1p100f;
-        A.inv_scales[(size_t)w * A.num_segments + l] = ok ? 1.0f / s : 0.0f;
-        // what the residual p - Q_g(p) of this step can reach (a non-finite scale gives a non-finite
-        // bound, which switches the next step's filter off)
-        // bound on the next |e|; the added 2^-140 covers scales so small that s * level itself is rounded
-        A.err_bound[(size_t)w * A.num_segments + l] = s * A.bound_factor + 0x1p-140f;
+        const Scale r = make_scale(bm);
+        A.scales[w][l] = r.s;
+        A.inv_scales[(size_t)w * A.num_segments + l] = r.inv;
+        A.err_bound[(size_t)w * A.num_segments + l] = residual_bound(r.s, A.bound_factor);
     }
 }
 
@@ -822,7 +804,6 @@ __global__ void __launch_bounds__(kBlockThreads) k_reduce_lower_bounds(ScaleArgs
 {
     const int l = blockIdx.x, w = A.first_worker + blockIdx.y;
     const int t0 = A.seg_tile_begin[l], t1 = A.seg_tile_begin[l + 1];
-    if (t1 > t0 && (A.tiles[t0].flags & kTileSmallHead)) return;
     const uint32_t* part = A.tile_max + (size_t)w * A.num_tiles;
     uint32_t local = 0;
     for (int t = t0 + (int)threadIdx.x * A.sample_stride; t < t1; t += kBlockThreads * A.sample_stride) {
@@ -882,12 +863,11 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax(AmaxArgs A)
 {
     const int ti = A.tile_list ? A.tile_list[blockIdx.x] : (int)blockIdx.x;
     const Tile t = tile_at(A.tiles, ti, A.seg_len, 0);
-    if (A.skip_small && (t.flags & (kTileSmallHead | kTileSmallBody))) return;
     const int w = A.first_worker + blockIdx.y;
     const float* g = A.grad[w];
     const float* e = A.err[w];
     uint32_t local;
-    if (t.flags & kTileUnaligned) local = amax_range<true>(g, e, t.start, t.len, 0u);
+    if (t.flags & kTileUnaligned) local = amax_range(g, e, t.start, t.len, 0u);
     else local = amax_tile<4>(g, e, t);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles + ti] = bm;
@@ -956,13 +936,12 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax_filtered(AmaxArgs A)
     const int ti = blockIdx.x;
     const Tile t = A.tiles[ti];
     if (t.flags & kTileSampled) return;
-    if (A.skip_small && (t.flags & (kTileSmallHead | kTileSmallBody))) return;
     const int w = A.first_worker + blockIdx.y;
     const float* g = A.grad[w];
     const float* e = A.err[w];
     const uint32_t thr = A.thr[(size_t)w * A.num_segments + t.seg];
     uint32_t local;
-    if (t.flags & kTileUnaligned) local = amax_range<true>(g, e, t.start, t.len, thr);
+    if (t.flags & kTileUnaligned) local = amax_range(g, e, t.start, t.len, thr);
     else if (thr == 0u) local = amax_tile<4>(g, e, t);
     else local = amax_tile_filtered<4>(g, e, t, thr);
     const uint32_t bm = block_max(local);
@@ -995,7 +974,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_check_error_bounds(AmaxArgs A
     const Tile t = A.tiles[ti];
     const int w = A.first_worker + blockIdx.y;
     const float* e = A.err[w];
-    const uint32_t local = (t.flags & kTileUnaligned) ? amax_range<true>(nullptr, e, t.start, t.len, 0u) : emax_tile<4>(e, t);
+    const uint32_t local = (t.flags & kTileUnaligned) ? amax_range(nullptr, e, t.start, t.len, 0u) : emax_tile<4>(e, t);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) {
         const float bound = A.err_bound[(size_t)w * A.num_segments + t.seg];
@@ -1026,116 +1005,93 @@ __device__ __forceinline__ void store_chunk_words(uint32_t* __restrict__ codes, 
     const bool group_live = base + grp * 32 < t.len;
     if (writes && group_live) {
         const int64_t cw = t.code_word + (int64_t)(base >> 5) * code_bits;
-        __builtin_nontemporal_store(word, codes + cw + word_slot);
+        // an ordinary store: a wavefront's words are 64..128 bytes, less than a line, and L2 puts the pieces of
+        // a line together before it goes out (with the non-temporal hint they leave one by one: main pass of
+        // 11.7 M parameters, 4 workers, 178 us against 167)
+        codes[cw + word_slot] = word;
     }
 }
 
+// Two runs of 256 elements per wavefront: one leaves too little in flight behind one wavefront's start-up, four
+// start too late (124 M parameters, 4 workers through the separate calls: 2294 / 2246 / 2313 us per step; 2^24
+// elements, one worker: 61.3 / 57.5 / 59.9 us).
+constexpr int kQuantizeRuns = 2;
+constexpr uint32_t kQuantizeParts = kDefaultTileElems / (256 * kQuantizeRuns);
+
 // ---- worker side alone (qadam_worker_quantize, second pass of variant W) -------------------------
-template <int V, int ROUNDING, bool PARKED, bool INLINE = false, bool SH = false>
-__device__ __forceinline__ void worker_tile(const WorkerArgs& A, const Tile& t, const SmallLayerShared* sh = nullptr)
+// One wavefront's share: C runs of 64 V consecutive elements of a tile from `part_begin`, their loads issued
+// together.  FULL: the share is whole, so that no access needs a guard.
+template <int V, int ROUNDING, bool PARKED, bool SH, int C, bool FULL>
+__device__ __forceinline__ void worker_part(const WorkerArgs& A, const Tile& t, int ti, int part_begin)
 {
-    constexpr int WAVE_ELEMS = 64 * V, BLOCK_ELEMS = (kBlockThreads / 64) * WAVE_ELEMS;
+    constexpr int WAVE_ELEMS = 64 * V;
     const StepScalars& S = A.S;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x;
     const QgConst c = make_qg(S.k_g);
-    const float s = INLINE ? sh->scale[0] : A.scales[t.seg];
-    const float inv_s = INLINE ? sh->inv[0] : A.inv_scales[t.seg];
-    if (!(s >= 0.0f && s < __builtin_inff()) && threadIdx.x == 0) atomicOr(A.status, QADAM_STATUS_NONFINITE_SCALE);
     const Shift sf = make_shift(t);
-    for (int base = wave * WAVE_ELEMS; base < t.len; base += BLOCK_ELEMS) {
-        const int off = base + lane * V;
-        const int nvalid = min(max(t.len - off, 0), V);
-        const int64_t gi = t.start + off;
-        float g[V], e[V], q[V], en[V], U[V];
+    float g[C][V], e[C][V];
 #pragma unroll
-        for (int j = 0; j < V; ++j) U[j] = 0.0f;
+    for (int k = 0; k < C; ++k) {
+        const int off = part_begin + k * WAVE_ELEMS + lane * V;
+        const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
         if constexpr (PARKED) {
             // the first pass left p = u + e in the error buffer; p + 0 reproduces it
-            ld<V, SH>(A.err, gi, nvalid, sf, g);
+            ld<V, SH>(A.err, t.start + off, nvalid, sf, g[k]);
 #pragma unroll
-            for (int j = 0; j < V; ++j) e[j] = 0.0f;
+            for (int j = 0; j < V; ++j) e[k][j] = 0.0f;
         } else {
-            ld<V, SH>(A.grad, gi, nvalid, sf, g);
-            ld<V, SH>(A.err, gi, nvalid, sf, e);
+            ld<V, SH>(A.grad, t.start + off, nvalid, sf, g[k]);
+            ld<V, SH>(A.err, t.start + off, nvalid, sf, e[k]);
         }
+    }
+    const Scale sc = A.fold.tile_max ? folded_scale(A.fold, 0, t, ti, part_begin == 0, A.scales)
+                                     : stored_scale(A.fold, 0, t, A.scales);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const int base = part_begin + k * WAVE_ELEMS;
+        if (!FULL && base >= t.len) break;
+        const int off = base + lane * V;
+        const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
+        const int64_t gi = t.start + off;
+        float q[V], en[V], U[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) U[j] = 0.0f;
         if constexpr (ROUNDING == 1) unif<V, SH>(S, gi, (uint32_t)A.worker, 0u, sf, U);
         uint32_t codes;
-        worker_lane<V, ROUNDING>(g, e, s, inv_s, c, S.mu_bits, U, q, en, codes);
+        worker_lane<V, ROUNDING>(g[k], e[k], sc.s, sc.inv, c, S.mu_bits, U, q, en, codes);
         st<V, SH>(A.err, gi, nvalid, sf, en);
         int slot; bool writes;
         const uint32_t word = pack_planes<V>(codes, S.code_bits, lane, slot, writes);
         store_chunk_words(A.codes, t, base, S.code_bits, word, slot, writes);
     }
-    write_pad_words(A.codes, t, S.code_bits);
-}
-
-// the tiles of a small layer, one after the other, with the flags each would carry in the table
-__device__ __forceinline__ Tile small_layer_tile(const Tile& head, int o, int code_bits)
-{
-    const int n = head.layer_len;
-    Tile t = head;
-    t.start = head.start + o;
-    t.code_word = head.code_word + (int64_t)(o / 32) * code_bits;
-    t.len = min(n - o, kDefaultTileElems);
-    t.flags = head.flags & kTileUnaligned;
-    if (o + kDefaultTileElems >= n) {
-        const int used = (n + 31) / 32 * code_bits;
-        t.flags |= ((used + 3) / 4 * 4 - used) << 8;
-    }
-    return t;
-}
-
-template <int ROUNDING>
-__device__ __forceinline__ void worker_small_layer(const WorkerArgs& A, const Tile& head)
-{
-    __shared__ SmallLayerShared sh;
-    const int n = head.layer_len;
-    const bool unaligned = head.flags & kTileUnaligned;
-    const uint32_t wm = unaligned ? wave_max_u32(amax_range<false>(A.grad, A.err, head.start, n, 0u))
-                                  : small_layer_wave_max<4>(A.grad, A.err, head.start, n);
-    if ((threadIdx.x & 63) == 0) sh.part[0][threadIdx.x >> 6] = wm;
-    float* scales_row[1] = {A.scales};
-    small_layer_finish(sh, 0, 1, head.seg, 1, scales_row, A.inv_scales, A.err_bound, A.bound_factor, true);
-    for (int o = 0; o < n; o += kDefaultTileElems) {
-        const Tile t = small_layer_tile(head, o, A.S.code_bits);
-        if (unaligned) worker_tile<4, ROUNDING, false, true, true>(A, t, &sh);
-        else worker_tile<4, ROUNDING, false, true, false>(A, t, &sh);
-    }
+    if (part_begin + C * WAVE_ELEMS >= t.len) write_pad_words(A.codes, t, S.code_bits);
+    if (part_begin == 0) check_scale(sc.s, A.status);
 }
 
 template <int ROUNDING, bool PARKED>
-__global__ void __launch_bounds__(kBlockThreads) k_worker_quantize(WorkerArgs A)
+__global__ void __launch_bounds__(64) k_worker_quantize(WorkerArgs A)
 {
-    const int ti = blockIdx.x;
+    constexpr int C = kQuantizeRuns;
+    const uint32_t item = wave_item(A.items);
+    if (item >= A.items.count) return;
+    const int ti = (int)(item / A.items.parts);
     const Tile t = tile_at(A.tiles, ti, A.seg_len, A.S.code_bits);
-    if constexpr (!PARKED) {
-        // small layers: the workgroup of the first tile does the whole layer, scale included
-        if (t.flags & kTileSmallBody) return;
-        if (t.flags & kTileSmallHead) {
-            worker_small_layer<ROUNDING>(A, t);
-            return;
-        }
+    const int part_begin = (int)(item % A.items.parts) * (C * 256);
+    if (part_begin >= t.len) return;
+    const bool full = part_begin + C * 256 <= t.len;
+    if (t.flags & kTileUnaligned) {
+        if (full) worker_part<4, ROUNDING, PARKED, true, C, true>(A, t, ti, part_begin);
+        else worker_part<4, ROUNDING, PARKED, true, C, false>(A, t, ti, part_begin);
+    } else {
+        if (full) worker_part<4, ROUNDING, PARKED, false, C, true>(A, t, ti, part_begin);
+        else worker_part<4, ROUNDING, PARKED, false, C, false>(A, t, ti, part_begin);
     }
-    if (t.flags & kTileMedium) {
-        // the layer has few tiles: fold their maxima here instead of in a launch of its own
-        __shared__ SmallLayerShared sh;
-        const int t0 = A.seg_tile_begin[t.seg], t1 = A.seg_tile_begin[t.seg + 1];
-        const uint32_t wm = medium_layer_wave_max(A.tile_max, t0, t1);
-        if ((threadIdx.x & 63) == 0) sh.part[0][threadIdx.x >> 6] = wm;
-        float* scales_row[1] = {A.scales};
-        small_layer_finish(sh, 0, 1, t.seg, 1, scales_row, A.inv_scales, A.err_bound, A.bound_factor, true, ti == t0);
-        if (t.flags & kTileUnaligned) worker_tile<4, ROUNDING, PARKED, true, true>(A, t, &sh);
-        else worker_tile<4, ROUNDING, PARKED, true, false>(A, t, &sh);
-        return;
-    }
-    if (t.flags & kTileUnaligned) worker_tile<4, ROUNDING, PARKED, false, true>(A, t);
-    else worker_tile<4, ROUNDING, PARKED, false, false>(A, t);
 }
 
 // ---- server side alone (qadam_server_step) -------------------------------------------------------
 struct ServerArgs {
     const Tile* tiles;
-    int num_tiles;
+    Items items;
     StepScalars S;
     float* x; float* m; float* v;
     const uint32_t* codes[QADAM_MAX_WORKERS];
@@ -1146,14 +1102,15 @@ struct ServerArgs {
 // U = number of workers whose code words are loaded together (N must be a multiple of U);
 // MU_BITS = bits of the level index (code bits minus the sign)
 template <int V, int U, int MU_BITS, bool SH = false>
-__device__ __forceinline__ void server_tile(const ServerArgs& A, const Tile& t)
+__device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, int part_begin, int part_len)
 {
-    constexpr int WAVE_ELEMS = 64 * V, BLOCK_ELEMS = (kBlockThreads / 64) * WAVE_ELEMS;
+    constexpr int WAVE_ELEMS = 64 * V;
     const StepScalars& S = A.S;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x;
+    const int part_end = min(t.len, part_begin + part_len);
     const QgConst c = make_qg(S.k_g);
     const Shift sf = make_shift(t);
-    for (int base = wave * WAVE_ELEMS; base < t.len; base += BLOCK_ELEMS) {
+    for (int base = part_begin; base < part_end; base += WAVE_ELEMS) {
         const int off = base + lane * V;
         const int nvalid = min(max(t.len - off, 0), V);
         if (nvalid == 0) continue;
@@ -1199,12 +1156,16 @@ __device__ __forceinline__ void server_tile(const ServerArgs& A, const Tile& t)
 }
 
 template <int U, int MU_BITS>
-__global__ void __launch_bounds__(kBlockThreads) k_server_step(ServerArgs A)
+__global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 {
-    const int ti = blockIdx.x;
-    const Tile t = A.tiles[ti];
-    if (t.flags & kTileUnaligned) server_tile<4, U, MU_BITS, true>(A, t);
-    else server_tile<4, U, MU_BITS, false>(A, t);
+    const uint32_t item = wave_item(A.items);
+    if (item >= A.items.count) return;
+    const Tile t = A.tiles[item / A.items.parts];
+    const int part_len = kDefaultTileElems / (int)A.items.parts;
+    const int part_begin = (int)(item % A.items.parts) * part_len;
+    if (part_begin >= t.len) return;
+    if (t.flags & kTileUnaligned) server_part<4, U, MU_BITS, true>(A, t, part_begin, part_len);
+    else server_part<4, U, MU_BITS, false>(A, t, part_begin, part_len);
 }
 
 // ---- weight quantizer alone (qadam_weight_quantize) ----------------------------------------------
@@ -1334,23 +1295,24 @@ __global__ void __launch_bounds__(kBlockThreads) k_weight_dequantize(DequantArgs
 }
 
 // ---- the whole step in one pass (qadam_step_fused) -----------------------------------------------
-// U = number of workers whose loads are issued together (N must be a multiple of U).
+// One wavefront's share: `part_len` elements of a tile from `part_begin`, 64 V at a time, the workers' g and e
+// loaded U workers at a time.  FULL: the share is whole, so that no access needs a guard.
 // W = false: variant S (workers' g and e in, server moments).  W = true: second pass of variant W
 // (the first pass left p_i = alpha m_i / sqrt(v_i + eps) + e_i in the error buffers; the server
 // only subtracts the mean message).
-template <int V, int ROUNDING, int U, bool W, bool INLINE = false, bool SH = false>
-__device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, const SmallLayerShared* sh = nullptr,
-                                           int part_begin = 0, int part_len = kDefaultTileElems)
+template <int ROUNDING, int V, bool W, bool SH, bool FOLD, int U, bool FULL>
+__device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, int ti, int part_begin, int part_len)
 {
-    constexpr int WAVE_ELEMS = 64 * V, BLOCK_ELEMS = (kBlockThreads / 64) * WAVE_ELEMS;
+    constexpr int WAVE_ELEMS = 64 * V;
     const StepScalars& S = A.S;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x;
     const QgConst c = make_qg(S.k_g);
     const int N = S.num_workers;
     const Shift sf = make_shift(t);
-    for (int base = part_begin + wave * WAVE_ELEMS; base < min(t.len, part_begin + part_len); base += BLOCK_ELEMS) {
+    const int part_end = min(t.len, part_begin + part_len);
+    for (int base = part_begin; base < part_end; base += WAVE_ELEMS) {
         const int off = base + lane * V;
-        const int nvalid = min(max(t.len - off, 0), V);
+        const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
         const int64_t gi = t.start + off;
         // server state first: its latency hides behind the workers' arithmetic
         float xv[V], mv[V], vv[V], wi[V], wo[V];
@@ -1371,6 +1333,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, co
             float g[U][V], e[U][V];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (U > 1 && i0 + u >= N) break;
                 if constexpr (W) {
                     ld<V, SH>(A.err[i0 + u], gi, nvalid, sf, g[u]);       // parked p; p + 0 reproduces it
 #pragma unroll
@@ -1383,8 +1346,15 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, co
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = i0 + u;
-                const float s = INLINE ? sh->scale[i] : A.scales[i][t.seg];
-                const float inv_s = INLINE ? sh->inv[i] : A.inv_scales[(size_t)i * A.num_segments + t.seg];
+                if (U > 1 && i >= N) break;
+                Scale sc;
+                if constexpr (FOLD) {
+                    sc = folded_scale(A.fold, i, t, ti, base == 0, A.scales[i]);
+                    if (base == 0) check_scale(sc.s, A.status);
+                } else {
+                    sc = stored_scale(A.fold, i, t, A.scales[i]);
+                }
+                const float s = sc.s, inv_s = sc.inv;
                 float q[V], en[V], Ur[V];
 #pragma unroll
                 for (int j = 0; j < V; ++j) Ur[j] = 0.0f;
@@ -1421,72 +1391,31 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& A, const Tile& t, co
             stw<V, SH>(A.sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
         }
     }
-    for (int i = 0; i < N; ++i) {
-        write_pad_words(A.codes[i], t, S.code_bits);
-        const float s = INLINE ? sh->scale[i] : A.scales[i][t.seg];
-        if (!(s >= 0.0f && s < __builtin_inff()) && threadIdx.x == 0)
-            atomicOr(A.status, QADAM_STATUS_NONFINITE_SCALE);
-    }
-}
-
-// One workgroup does a whole small layer: the scales of all workers first (g and e read once, kept in
-// cache), then the layer's tiles exactly as the separate workgroups would have done them.
-template <int ROUNDING, int U>
-__device__ __forceinline__ void fused_small_layer(const FusedArgs& A, const Tile& head)
-{
-    __shared__ SmallLayerShared sh;
-    const int n = head.layer_len, N = A.S.num_workers;
-    const bool unaligned = head.flags & kTileUnaligned;
-    for (int i = 0; i < N; ++i) {
-        const uint32_t wm = unaligned ? wave_max_u32(amax_range<false>(A.grad[i], A.err[i], head.start, n, 0u))
-                                      : small_layer_wave_max<4>(A.grad[i], A.err[i], head.start, n);
-        if ((threadIdx.x & 63) == 0) sh.part[i][threadIdx.x >> 6] = wm;
-    }
-    small_layer_finish(sh, 0, N, head.seg, A.num_segments, A.scales, A.inv_scales, A.err_bound, A.bound_factor, false);
-    for (int o = 0; o < n; o += kDefaultTileElems) {
-        const Tile t = small_layer_tile(head, o, A.S.code_bits);
-        if (unaligned) fused_tile<4, ROUNDING, U, false, true, true>(A, t, &sh);
-        else fused_tile<4, ROUNDING, U, false, true, false>(A, t, &sh);
-    }
+    if (part_begin + part_len >= t.len)
+        for (int i = 0; i < N; ++i) write_pad_words(A.codes[i], t, S.code_bits);
+    if (!FOLD && part_begin == 0)
+        for (int i = 0; i < N; ++i) check_scale(A.scales[i][t.seg], A.status);
 }
 
 template <int ROUNDING, int U, bool W>
-__global__ void __launch_bounds__(kBlockThreads) k_fused(FusedArgs A)
+__global__ void __launch_bounds__(64) k_fused(FusedArgs A)
 {
-    int ti = blockIdx.x, part_begin = 0, part_len = kDefaultTileElems;
-    if constexpr (!W) {
-        const uint32_t item = A.ticket ? take_ticket(A.ticket) : blockIdx.x;
-        ti = (int)(item / (uint32_t)A.parts);
-        part_len = kDefaultTileElems / A.parts;
-        part_begin = (int)(item % (uint32_t)A.parts) * part_len;
-    }
+    constexpr bool FOLD = U == 1;
+    const uint32_t item = wave_item(A.items);
+    if (item >= A.items.count) return;
+    const int ti = (int)(item / A.items.parts);
     const Tile t = A.tiles[ti];
-    if constexpr (!W) {
-        if (part_begin > 0 && (part_begin >= t.len || (t.flags & kTileSmallHead))) return;
-        // small layers: the workgroup of the first tile does the whole layer, scales included
-        if (t.flags & kTileSmallBody) return;
-        if (t.flags & kTileSmallHead) {
-            fused_small_layer<ROUNDING, U>(A, t);
-            return;
-        }
+    const int part_len = kDefaultTileElems / (int)A.items.parts;
+    const int part_begin = (int)(item % A.items.parts) * part_len;
+    if (part_begin >= t.len) return;
+    const bool full = part_begin + part_len <= t.len;
+    if (t.flags & kTileUnaligned) {
+        if (full) fused_part<ROUNDING, 4, W, true, FOLD, U, true>(A, t, ti, part_begin, part_len);
+        else fused_part<ROUNDING, 4, W, true, FOLD, 1, false>(A, t, ti, part_begin, part_len);
+    } else {
+        if (full) fused_part<ROUNDING, 4, W, false, FOLD, U, true>(A, t, ti, part_begin, part_len);
+        else fused_part<ROUNDING, 4, W, false, FOLD, 1, false>(A, t, ti, part_begin, part_len);
     }
-    if (t.flags & kTileMedium) {
-        // the layer has few tiles: fold their maxima here instead of in a launch of its own
-        __shared__ SmallLayerShared sh;
-        const int N = A.S.num_workers;
-        const int t0 = A.seg_tile_begin[t.seg], t1 = A.seg_tile_begin[t.seg + 1];
-        for (int i = 0; i < N; ++i) {
-            const uint32_t wm = medium_layer_wave_max(A.tile_max + (size_t)i * A.num_tiles, t0, t1);
-            if ((threadIdx.x & 63) == 0) sh.part[i][threadIdx.x >> 6] = wm;
-        }
-        small_layer_finish(sh, 0, N, t.seg, A.num_segments, A.scales, A.inv_scales, A.err_bound, A.bound_factor, false,
-                           ti == t0 && part_begin == 0);
-        if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, true, true>(A, t, &sh, part_begin, part_len);
-        else fused_tile<4, ROUNDING, U, W, true, false>(A, t, &sh, part_begin, part_len);
-        return;
-    }
-    if (t.flags & kTileUnaligned) fused_tile<4, ROUNDING, U, W, false, true>(A, t, nullptr, part_begin, part_len);
-    else fused_tile<4, ROUNDING, U, W, false, false>(A, t, nullptr, part_begin, part_len);
 }
 
 // ---- Q_g = identity: the messages are fp32 values ------------------------------------------------
@@ -1570,19 +1499,20 @@ struct MomentsWArgs {
     float* mw[QADAM_MAX_WORKERS];
     float* vw[QADAM_MAX_WORKERS];
     float* err[QADAM_MAX_WORKERS];
-    uint32_t* tile_max;     // [N][num_tiles]
+    uint32_t* tile_max;     // [N][num_tiles * parts]
+    int parts;              // pieces per tile
     int first_worker;
 };
 
 template <int V, bool SH = false>
-__device__ __forceinline__ uint32_t moments_w_tile(const StepScalars& S, const float* __restrict__ grad,
+__device__ __forceinline__ uint32_t moments_w_part(const StepScalars& S, const float* __restrict__ grad,
                                                    float* __restrict__ mw, float* __restrict__ vw,
-                                                   float* __restrict__ err, const Tile& t)
+                                                   float* __restrict__ err, const Tile& t, int part_begin, int part_len)
 {
     constexpr int BLOCK_ELEMS = kBlockThreads * V;
     uint32_t local = 0;
     const Shift sf = make_shift(t);
-    for (int base = 0; base < t.len; base += BLOCK_ELEMS) {
+    for (int base = part_begin; base < min(t.len, part_begin + part_len); base += BLOCK_ELEMS) {
         const int off = base + threadIdx.x * V;
         const int nvalid = min(max(t.len - off, 0), V);
         const int64_t gi = t.start + off;
@@ -1605,17 +1535,20 @@ __device__ __forceinline__ uint32_t moments_w_tile(const StepScalars& S, const f
     return local;
 }
 
-// grid: (tiles, workers)
+// grid: (tiles * parts, workers)
 __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
 {
-    const int ti = blockIdx.x;
+    const int ti = (int)(blockIdx.x / (unsigned)A.parts);
     const Tile t = A.tiles[ti];
+    const int part_len = kDefaultTileElems / A.parts, part_begin = (int)(blockIdx.x % (unsigned)A.parts) * part_len;
     const int w = A.first_worker + blockIdx.y;
     uint32_t local;
-    if (t.flags & kTileUnaligned) local = moments_w_tile<4, true>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t);
-    else local = moments_w_tile<4, false>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t);
+    if (t.flags & kTileUnaligned)
+        local = moments_w_part<4, true>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
+    else
+        local = moments_w_part<4, false>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
     const uint32_t bm = block_max(local);
-    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles + ti] = bm;
+    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles * A.parts + blockIdx.x] = bm;
 }
 
 // ---- diagnostic: per-layer sum of squares in fp64, fixed order ---------------------------------
@@ -1708,7 +1641,6 @@ static float residual_bound_factor(const StepScalars& S)
 
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
-    A.tiles = L.tiles;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) A.scales[i] = W.scales[i];
     A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.seg_tile_begin = L.seg_tile_begin;
     A.first_worker = first_worker; A.num_segments = L.num_segments; A.num_tiles = L.num_tiles;
@@ -1717,13 +1649,42 @@ static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S,
     A.sample_stride = kSampleStride;
 }
 
-hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
+// On a short vector the quantizing kernel folds the maxima itself: its wavefronts are all on the chip at once and the
+// launch of k_reduce_scales (2.5 us) costs more than one more load, or a few, at the head of each.  Beyond that every
+// wavefront pays again: 4 workers of 2^19 elements 35.3 us per step with the launch, 32.8 without; 2^20 35.3 / 32.8;
+// 2^21 47.7 / 55.4; 16 workers of 2^19 79.9 / 77.4, of 2^20 79.9 / 85.6; one worker's call in a row of four, 2^21
+// elements, 23.8 / 21.6.
+static bool fold_in_quantizer(int num_tiles, int num_workers)
 {
-    if (L.num_segments == 0 || num == 0) return hipSuccess;
-    if (!L.need_reduce) return hipSuccess;      // every scale is folded by the quantizing kernel
+    return num_tiles <= 128 || (int64_t)num_tiles * num_workers <= 1024;
+}
+
+static bool fold_in_quantizer(const Launch& L, int num_workers)
+{
+    return fold_in_quantizer(L.num_tiles, num_workers) && !L.empty_layers;
+}
+
+static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
+{
+    Fold F;
+    F.row = L.num_tiles * max_per_tile; F.per_tile = max_per_tile;
+    F.tile_max = fold_in_quantizer(L, num) ? L.tile_max + (size_t)worker * F.row : nullptr;
+    F.seg_tile_begin = L.seg_tile_begin;
+    F.num_segments = L.num_segments;
+    F.inv_scales = L.inv_scales + (size_t)worker * L.num_segments;
+    F.err_bound = L.err_bound + (size_t)worker * L.num_segments;
+    F.bound_factor = residual_bound_factor(S);
+    return F;
+}
+
+hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
+                                int max_per_tile)
+{
+    if (L.num_segments == 0 || num == 0 || fold_in_quantizer(L, num)) return hipSuccess;
     ScaleArgs A;
     fill_scale_args(A, L, S, W, first_worker);
-    hipLaunchKernelGGL(k_reduce_scales, dim3(L.num_segments, num), dim3(kBlockThreads), 0, L.stream, A);
+    A.max_per_tile = max_per_tile;
+    hipLaunchKernelGGL(k_reduce_scales, dim3(L.num_segments, num), dim3(kReduceThreads), 0, L.stream, A);
     return hipGetLastError();
 }
 
@@ -1736,7 +1697,6 @@ static void fill_amax_args(AmaxArgs& A, const Launch& L, const WorkerPtrs& W, in
     A.tile_list = nullptr; A.thr = L.thr; A.num_segments = L.num_segments;
     A.err_bound = L.err_bound; A.status = L.status;
     A.seg_len = 0;
-    A.skip_small = 1;       // only the server-moments path uses these kernels
 }
 
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num)
@@ -1744,7 +1704,6 @@ hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int f
     if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
-    A.skip_small = 0;       // the check covers every tile
     hipLaunchKernelGGL(k_check_error_bounds, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
     return hipGetLastError();
 }
@@ -1752,7 +1711,7 @@ hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int f
 hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
     (void)S;
-    if (L.num_tiles == 0 || num == 0 || !L.need_amax) return hipSuccess;
+    if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
     hipLaunchKernelGGL(k_amax, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
@@ -1764,7 +1723,7 @@ hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& 
 // where |g| reaches the threshold.  launch_reduce_scales follows as usual.
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
-    if (L.num_tiles == 0 || num == 0 || !L.need_amax) return hipSuccess;
+    if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
     A.tile_list = L.sample_tiles;
@@ -1777,22 +1736,39 @@ hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const Wor
     return hipGetLastError();
 }
 
+// `parts` pieces per tile, fewer where the launch would reach 2^32 work-items.  Runs are 256 items (256 KiB of
+// every stream) where that leaves each XCD eight or more of them (1.3 G parameters, 4 workers: 18.97 ms with runs
+// of 16, 18.41 with 64, 18.8 with 256; 124 M, 3 workers: 1.765 / 1.728 / 1.702 ms), shorter on short vectors.
+static Items wave_items(int num_tiles, uint32_t parts)
+{
+    Items I;
+    while ((int64_t)num_tiles * parts > ((int64_t)1 << 26) - 4096) parts /= 2;
+    I.parts = parts;
+    I.count = (uint32_t)num_tiles * parts;
+    I.run_shift = 0;
+    while (I.run_shift < 8 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
+    return I;
+}
+
+static dim3 wave_grid(const Items& I)
+{
+    const uint32_t round = 8u << I.run_shift;
+    return dim3((I.count + round - 1) / round * round);
+}
+
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker)
 {
     if (L.num_tiles == 0) return hipSuccess;
     WorkerArgs A;
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles;
+    A.tiles = L.tiles;
     A.status = L.status; A.S = S;
     A.grad = W.grad[worker]; A.err = W.err[worker]; A.codes = W.codes[worker]; A.scales = W.scales[worker];
-    A.inv_scales = L.inv_scales + (size_t)worker * L.num_segments;
-    A.err_bound = L.err_bound + (size_t)worker * L.num_segments;
-    A.bound_factor = residual_bound_factor(S);
-    A.tile_max = L.tile_max + (size_t)worker * L.num_tiles;
-    A.seg_tile_begin = L.seg_tile_begin;
+    A.fold = make_fold(L, S, worker, 1, A.grad ? 1 : moment_parts(L.num_tiles));
     A.worker = worker;
     A.seg_len = 0;
     const bool parked = (A.grad == nullptr);
-    const dim3 grid(L.num_tiles), block(kBlockThreads);
+    A.items = wave_items(L.num_tiles, kQuantizeParts);
+    const dim3 grid = wave_grid(A.items), block(64);
     if (S.rounding == 0) {
         if (parked) hipLaunchKernelGGL((k_worker_quantize<0, true>), grid, block, 0, L.stream, A);
         else hipLaunchKernelGGL((k_worker_quantize<0, false>), grid, block, 0, L.stream, A);
@@ -1805,13 +1781,14 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
 
 static void fill_server_args(ServerArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W)
 {
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles; A.S = S;
+    A.tiles = L.tiles; A.S = S;
+    A.items = wave_items(L.num_tiles, 16);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
 static void launch_server_kernel(const Launch& L, const ServerArgs& A)
 {
-    const dim3 grid(L.num_tiles), block(kBlockThreads);
+    const dim3 grid = wave_grid(A.items), block(64);
     const bool four = A.S.num_workers % 4 == 0;
 #define QADAM_LAUNCH_SERVER(MB)                                                                       \
     do {                                                                                              \
@@ -1875,42 +1852,30 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
     return hipGetLastError();
 }
 
-// Pieces a tile is cut into by the ticketed main pass.  Half tiles keep the workgroups in flight on a
-// narrower stretch of every buffer (124 M parameters, 8 workers: 3.90 ms per step with whole tiles, 3.78 with
-// halves, 3.78 with quarters) at half the tickets of quarters; a vector that would give the chip fewer than
-// four workgroups per CU is cut into quarters (11.7 M parameters: 257 -> 255 us).  Beyond 2^22 tiles the grid
-// limit (work items x 256 threads below 2^32) leaves whole tiles only.
-static int pieces_per_tile(int num_tiles)
-{
-    if (num_tiles >= 1 << 22) return 1;
-    return num_tiles < 4096 ? 4 : 2;
-}
+// LDS that a workgroup of the main pass reserves and does not use: it holds the pass to 16 wavefronts per CU, each
+// with the loads of four workers in flight.  More of them only spread the accesses over more DRAM pages, fewer
+// leave the memory idle (1.3 G parameters, 4 workers, whole step: 20 per CU 22.0 ms, 16 21.7, 12 21.6, 8 22.5;
+// 124 M, 8 workers: 3.95 / 3.89 / 3.87 / 4.09; 11.7 M, 4 workers: 229 / 227 / 236 / 250 us).
+constexpr unsigned kMainPassLds = 10240;
 
 static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
                                    bool variant_w)
 {
     if (L.num_tiles == 0) return hipSuccess;
     FusedArgs A;
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles;
-    A.status = L.status; A.inv_scales = L.inv_scales; A.num_segments = L.num_segments; A.S = S; A.sp = sp;
-    A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
-    A.tile_max = L.tile_max; A.seg_tile_begin = L.seg_tile_begin;
+    A.tiles = L.tiles;
+    A.status = L.status; A.S = S; A.sp = sp;
+    A.fold = make_fold(L, S, 0, S.num_workers, variant_w ? moment_parts(L.num_tiles) : 1);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    const int N = S.num_workers;
-    // a launch that fits the chip at once has no order to keep: there the ticket is 2 us of latency for nothing
-    // (51 k parameters, 4 workers: 81 us per step without, 85 with)
-    A.ticket = L.num_tiles >= 1024 ? L.ticket : nullptr;
-    A.parts = variant_w ? 1 : pieces_per_tile(L.num_tiles);
-    const dim3 grid((unsigned)L.num_tiles * (unsigned)A.parts), block(kBlockThreads);
-    // loads of up to four workers in flight per lane: more (eight) costs registers and occupancy
-    // without a measurable gain
-#define QADAM_LAUNCH_FUSED(R, WV)                                                                     \
-    do {                                                                                              \
-        if (N % 4 == 0) hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, 0, L.stream, A);         \
-        else if (N % 2 == 0 && R == 0) hipLaunchKernelGGL((k_fused<R, 2, WV>), grid, block, 0, L.stream, A); \
-        else hipLaunchKernelGGL((k_fused<R, 1, WV>), grid, block, 0, L.stream, A);                    \
+    A.items = wave_items(L.num_tiles, 16);
+    const dim3 grid = wave_grid(A.items), block(64);
+    // U = 4, or the variant that folds the scales, one worker at a time
+#define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
+    do {                                                                                                           \
+        if (A.fold.tile_max) hipLaunchKernelGGL((k_fused<R, 1, WV>), grid, block, 0, L.stream, A);                 \
+        else hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, kMainPassLds, L.stream, A);                      \
     } while (0)
     if (S.rounding == 0) {
         if (variant_w) QADAM_LAUNCH_FUSED(0, true); else QADAM_LAUNCH_FUSED(0, false);
@@ -1931,10 +1896,8 @@ hipError_t launch_plain_messages(const Launch& L, const StepScalars& S, const Wo
 {
     if (L.num_tiles == 0) return hipSuccess;
     FusedArgs A;
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles;
-    A.status = L.status; A.inv_scales = L.inv_scales; A.num_segments = L.num_segments; A.S = S; A.sp = sp;
-    A.err_bound = L.err_bound; A.bound_factor = 0.0f;
-    A.tile_max = L.tile_max; A.seg_tile_begin = L.seg_tile_begin;
+    A.tiles = L.tiles; A.items = Items{};
+    A.status = L.status; A.fold = Fold{}; A.S = S; A.sp = sp;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = nullptr; A.scales[i] = nullptr;
     }
@@ -1980,7 +1943,8 @@ hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const 
     }
     A.tile_max = L.tile_max;
     A.first_worker = first_worker;
-    hipLaunchKernelGGL(k_moments_w, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
+    A.parts = moment_parts(L.num_tiles);
+    hipLaunchKernelGGL(k_moments_w, dim3((unsigned)L.num_tiles * (unsigned)A.parts, num), dim3(kBlockThreads), 0, L.stream, A);
     return hipGetLastError();
 }
 
@@ -2048,25 +2012,31 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         A.tile_max = tile_max; A.first_worker = 0; A.num_segments = 1; A.status = status;
         hipLaunchKernelGGL(k_amax, dim3(num_tiles, 1), dim3(kBlockThreads), 0, stream, A);
     }
-    ScaleArgs R;
-    std::memset(&R, 0, sizeof R);
-    R.scales[0] = scale_out; R.inv_scales = inv_scale; R.tile_max = tile_max; R.seg_tile_begin = nullptr;
-    R.first_worker = 0; R.num_segments = 1; R.num_tiles = num_tiles;
-    R.err_bound = err_bound; R.thr = nullptr;
-    R.bound_factor = residual_bound_factor(S);
-    R.sample_stride = kSampleStride;
-    R.tiles = nullptr;
-    hipLaunchKernelGGL(k_reduce_scales, dim3(1, 1), dim3(kBlockThreads), 0, stream, R);
+    Fold F;
+    std::memset(&F, 0, sizeof F);
+    F.row = num_tiles; F.per_tile = 1; F.num_segments = 1;
+    F.inv_scales = inv_scale; F.err_bound = err_bound; F.bound_factor = residual_bound_factor(S);
+    if (num_tiles > 0 && fold_in_quantizer(num_tiles, 1)) {
+        F.tile_max = tile_max;
+    } else {
+        ScaleArgs R;
+        std::memset(&R, 0, sizeof R);
+        R.scales[0] = scale_out; R.inv_scales = inv_scale; R.tile_max = tile_max; R.seg_tile_begin = nullptr;
+        R.first_worker = 0; R.num_segments = 1; R.num_tiles = num_tiles; R.max_per_tile = 1;
+        R.err_bound = err_bound; R.thr = nullptr;
+        R.bound_factor = residual_bound_factor(S);
+        R.sample_stride = kSampleStride;
+        hipLaunchKernelGGL(k_reduce_scales, dim3(1, 1), dim3(kReduceThreads), 0, stream, R);
+    }
     if (num_tiles > 0) {
         WorkerArgs W;
         std::memset(&W, 0, sizeof W);
-        W.tiles = nullptr; W.num_tiles = num_tiles; W.seg_len = n;
+        W.tiles = nullptr; W.seg_len = n;
         W.status = status; W.S = S;
-        W.grad = grad; W.err = err; W.codes = codes; W.scales = scale_out; W.inv_scales = inv_scale;
-        W.err_bound = err_bound; W.bound_factor = residual_bound_factor(S);
-        W.tile_max = tile_max; W.seg_tile_begin = nullptr;
+        W.grad = grad; W.err = err; W.codes = codes; W.scales = scale_out; W.fold = F;
         W.worker = 0;
-        hipLaunchKernelGGL((k_worker_quantize<0, false>), dim3(num_tiles), dim3(kBlockThreads), 0, stream, W);
+        W.items = wave_items(num_tiles, kQuantizeParts);
+        hipLaunchKernelGGL((k_worker_quantize<0, false>), wave_grid(W.items), dim3(64), 0, stream, W);
     }
     return hipGetLastError();
 }
