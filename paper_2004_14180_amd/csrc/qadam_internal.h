@@ -29,8 +29,9 @@ constexpr int kTileSampled = 2;
 constexpr int kSampleStride = 64;   // every 64th tile of a layer (from its first) is a sampled tile
 constexpr int kBlockThreads = 256;
 constexpr int kReduceThreads = 1024;
-// pieces a tile is cut into by the first pass of variant W, each with a maximum of its own
-constexpr int kMomentParts = 1;
+// pieces a tile is cut into by the first pass of variant W, each with a maximum of its own: one turn of a workgroup,
+// or the whole tile where quarters would bring the launch to 2^32 work-items
+constexpr int kMomentParts = 4;
 inline int moment_parts(int num_tiles) { return num_tiles < (1 << 22) ? kMomentParts : 1; }
 constexpr int kDefaultTileElems = 4096;   // elements per tile (16 per lane of a 256-thread workgroup)
 

@@ -24,6 +24,35 @@ def test_each_side_of_the_fold(N, tiles, fused):
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
+@pytest.mark.parametrize("N,tiles", [(2, 128), (8, 129), (4, 255), (4, 257)])
+def test_worker_moments_each_side_of_the_fold(N, tiles):
+    """Variant W leaves four maxima per tile: ends of a layer in each quarter of its last tile."""
+    from oracle import qadam_oracle as oracle
+    gcfg, ocfg = configs()
+    sizes = [(tiles - 5) * T, 1000, T + 1025, 3, 2049]
+    seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    P, rng = int(seg[-1]), np.random.default_rng(tiles)
+    f32 = lambda s: (rng.standard_normal(P) * s).astype(np.float32)  # noqa: E731
+    hx, hw = f32(0.02), np.zeros(P, np.float32)
+    he, hm, hv = ([np.zeros(P, np.float32) for _ in range(N)] for _ in range(3))
+    dev = lambda a: torch.from_numpy(a.copy()).cuda()  # noqa: E731
+    x, werr, e, m, v = dev(hx), dev(hw), [dev(a) for a in he], [dev(a) for a in hm], [dev(a) for a in hv]
+    q = QAdam(gcfg, seg, N)
+    codes = [torch.zeros(q.grad_code_bytes() // 4, dtype=torch.int32, device="cuda") for _ in range(N)]
+    scales = [torch.zeros(len(sizes), device="cuda") for _ in range(N)]
+    wcodes = torch.zeros(P, dtype=torch.int8, device="cuda")
+    for t in (1, 2):
+        g = [f32(1e-2) for _ in range(N)]
+        q.step_fused_w(t, 1e-3, 0.999, [dev(a) for a in g], m, v, e, codes, scales, x, werr, wcodes)
+        torch.cuda.synchronize()
+        oracle.step_w(ocfg, seg, t, 1e-3, 0.999, g, he, hm, hv, hx, hw)
+    same = lambda d, h: np.array_equal(d.cpu().numpy().view(np.uint32), h.view(np.uint32))  # noqa: E731
+    assert same(x, hx) and same(werr, hw)
+    for i in range(N):
+        assert same(e[i], he[i]) and same(m[i], hm[i]) and same(v[i], hv[i]), i
+    q.close()
+
+
 @pytest.mark.parametrize("k_g", [0, 2, 6])
 @pytest.mark.parametrize("n", [1, 33, 255, 257, 4095, 4097, 16383, 16384, 16385, 128 * T + 1, 1024 * T, 1024 * T + 1])
 def test_segment_call(n, k_g):
