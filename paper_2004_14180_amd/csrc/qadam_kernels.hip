@@ -541,7 +541,8 @@ struct AmaxArgs {
     int num_tiles;
     const float* grad[QADAM_MAX_WORKERS];
     const float* err[QADAM_MAX_WORKERS];
-    uint32_t* tile_max;     // [N][num_tiles]
+    uint32_t* tile_max;     // rows of `row` maxima, one row per worker
+    int row;
     int first_worker;
     const int32_t* tile_list;   // null: workgroup b takes tile b; else tile tile_list[b] (the sampled tiles)
     const uint32_t* thr;        // filtered pass only: [N][L] thresholds on |g| as bit patterns (0: read everything)
@@ -618,6 +619,7 @@ struct ScaleArgs {
     const uint32_t* tile_max;
     const int32_t* seg_tile_begin;
     int first_worker, num_segments, num_tiles;
+    int row;                // maxima from one worker's to the next's
     int max_per_tile;       // maxima the pass before left per tile
     float* err_bound;       // [N][L]: bound on |e'| after the step that uses these scales
     uint32_t* thr;          // [N][L]: thresholds of the filtered pass (written by k_reduce_lower_bounds)
@@ -777,7 +779,7 @@ __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales(ScaleArgs A)
     // no table: a single segment that owns every tile
     const int t0 = (A.seg_tile_begin ? A.seg_tile_begin[l] : 0) * A.max_per_tile;
     const int t1 = (A.seg_tile_begin ? A.seg_tile_begin[l + 1] : A.num_tiles) * A.max_per_tile;
-    const uint32_t* part = A.tile_max + (size_t)w * A.num_tiles * A.max_per_tile;
+    const uint32_t* part = A.tile_max + (size_t)w * A.row;
     uint32_t local = 0;
     for (int t = t0 + (int)threadIdx.x; t < t1; t += kReduceThreads * 8) {
         uint32_t v[8];
@@ -804,7 +806,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_reduce_lower_bounds(ScaleArgs
 {
     const int l = blockIdx.x, w = A.first_worker + blockIdx.y;
     const int t0 = A.seg_tile_begin[l], t1 = A.seg_tile_begin[l + 1];
-    const uint32_t* part = A.tile_max + (size_t)w * A.num_tiles;
+    const uint32_t* part = A.tile_max + (size_t)w * A.row;
     uint32_t local = 0;
     for (int t = t0 + (int)threadIdx.x * A.sample_stride; t < t1; t += kBlockThreads * A.sample_stride) {
         const uint32_t v = part[t];
@@ -870,7 +872,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax(AmaxArgs A)
     if (t.flags & kTileUnaligned) local = amax_range(g, e, t.start, t.len, 0u);
     else local = amax_tile<4>(g, e, t);
     const uint32_t bm = block_max(local);
-    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles + ti] = bm;
+    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.row + ti] = bm;
 }
 
 // Filtered scale pass, stage 3 of 4: max |g + e| over the elements of a tile that can still be the
@@ -945,7 +947,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax_filtered(AmaxArgs A)
     else if (thr == 0u) local = amax_tile<4>(g, e, t);
     else local = amax_tile_filtered<4>(g, e, t, thr);
     const uint32_t bm = block_max(local);
-    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles + ti] = bm;
+    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.row + ti] = bm;
 }
 
 // max |e| over a tile
@@ -1700,10 +1702,14 @@ static float residual_bound_factor(const StepScalars& S)
     return (S.rounding == 0 ? half_gap : 2.0f * half_gap) * (1.0f + 0x1p-20f);
 }
 
+// Every pass gives worker w the same row of the maxima, whether it leaves one per tile or `moment_parts`: calls for
+// different workers may run on different streams.
+static int max_row(const Launch& L) { return L.num_tiles * moment_parts(L.num_tiles); }
+
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) A.scales[i] = W.scales[i];
-    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.seg_tile_begin = L.seg_tile_begin;
+    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.row = max_row(L); A.seg_tile_begin = L.seg_tile_begin;
     A.first_worker = first_worker; A.num_segments = L.num_segments; A.num_tiles = L.num_tiles;
     A.err_bound = L.err_bound; A.thr = L.thr;
     A.bound_factor = residual_bound_factor(S);
@@ -1728,7 +1734,7 @@ static bool fold_in_quantizer(const Launch& L, int num_workers)
 static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
 {
     Fold F;
-    F.row = L.num_tiles * max_per_tile; F.per_tile = max_per_tile;
+    F.row = max_row(L); F.per_tile = max_per_tile;
     F.tile_max = fold_in_quantizer(L, num) ? L.tile_max + (size_t)worker * F.row : nullptr;
     F.seg_tile_begin = L.seg_tile_begin;
     F.num_segments = L.num_segments;
@@ -1753,7 +1759,7 @@ static void fill_amax_args(AmaxArgs& A, const Launch& L, const WorkerPtrs& W, in
 {
     A.tiles = L.tiles; A.num_tiles = L.num_tiles;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; }
-    A.tile_max = L.tile_max;
+    A.tile_max = L.tile_max; A.row = max_row(L);
     A.first_worker = first_worker;
     A.tile_list = nullptr; A.thr = L.thr; A.num_segments = L.num_segments;
     A.err_bound = L.err_bound; A.status = L.status;
@@ -2076,7 +2082,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         std::memset(&A, 0, sizeof A);
         A.tiles = nullptr; A.num_tiles = num_tiles; A.seg_len = n;
         A.grad[0] = grad; A.err[0] = err;
-        A.tile_max = tile_max; A.first_worker = 0; A.num_segments = 1; A.status = status;
+        A.tile_max = tile_max; A.row = num_tiles; A.first_worker = 0; A.num_segments = 1; A.status = status;
         hipLaunchKernelGGL(k_amax, dim3(num_tiles, 1), dim3(kBlockThreads), 0, stream, A);
     }
     Fold F;
@@ -2089,7 +2095,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         ScaleArgs R;
         std::memset(&R, 0, sizeof R);
         R.scales[0] = scale_out; R.inv_scales = inv_scale; R.tile_max = tile_max; R.seg_tile_begin = nullptr;
-        R.first_worker = 0; R.num_segments = 1; R.num_tiles = num_tiles; R.max_per_tile = 1;
+        R.first_worker = 0; R.num_segments = 1; R.num_tiles = num_tiles; R.row = num_tiles; R.max_per_tile = 1;
         R.err_bound = err_bound; R.thr = nullptr;
         R.bound_factor = residual_bound_factor(S);
         R.sample_stride = kSampleStride;
