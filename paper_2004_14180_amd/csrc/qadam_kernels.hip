@@ -1230,6 +1230,10 @@ __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 }
 
 // ---- weight quantizer alone (qadam_weight_quantize) ----------------------------------------------
+// Index of a single-wavefront workgroup of a flat launch (flat_grid): one dimension of a grid holds fewer than 2^32
+// work-items, so a very long vector takes several rows.
+__device__ __forceinline__ int64_t wave_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 struct WeightArgs {
     StepScalars S;
     const float* x;
@@ -1238,36 +1242,24 @@ struct WeightArgs {
     int64_t n;
 };
 
-// One workgroup per 4096 consecutive elements; a lane owns four quads, quad k being elements
-// 4 * (lane + 256 k) .. + 3, and issues the loads of all four before any arithmetic.
+// A single wavefront per 256 consecutive elements, one quad per lane, in memory order.  Bound by HBM (x, e^x in; e^x,
+// codes out).  Wavefronts that start and end on their own keep reads and writes mixed: 124 M parameters, 4 workers
+// through the separate calls, whole step 2302 us with 256 threads and four quads per lane, 2280 with 64 threads and
+// two, 2267 with 64 and one.
 template <int ROUNDING>
-__global__ void __launch_bounds__(kBlockThreads) k_weight_quantize(WeightArgs A)
+__global__ void __launch_bounds__(64) k_weight_quantize(WeightArgs A)
 {
     const StepScalars& S = A.S;
-    const int64_t base = (int64_t)blockIdx.x * (kBlockThreads * 16);
-    float xv[4][4], wi[4][4];
-    int nvalid[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t gi = base + 4 * ((int64_t)threadIdx.x + kBlockThreads * k);
-        nvalid[k] = (int)max((int64_t)0, min((int64_t)4, A.n - gi));
-#pragma unroll
-        for (int t = 0; t < 4; ++t) wi[k][t] = 0.0f;
-        if (nvalid[k] > 0) {
-            load_v<4>(A.x + gi, nvalid[k], xv[k]);
-            if (S.weight_ef) load_v<4>(A.werr + gi, nvalid[k], wi[k]);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (nvalid[k] == 0) continue;
-        const int64_t gi = base + 4 * ((int64_t)threadIdx.x + kBlockThreads * k);
-        float wo[4];
-        int j[4];
-        weight_lane<4, ROUNDING>(S, xv[k], wi[k], gi, Shift{}, wo, j);
-        if (A.werr) store_v<4>(A.werr + gi, nvalid[k], wo);
-        store_wcodes<4>(A.wcodes, S.wcode_bytes, gi, nvalid[k], j);
-    }
+    const int64_t gi = 4 * (wave_index() * 64 + threadIdx.x);
+    if (gi >= A.n) return;
+    const int nvalid = (int)min((int64_t)4, A.n - gi);
+    float xv[4], wi[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wo[4];
+    int j[4];
+    load_v<4>(A.x + gi, nvalid, xv);
+    if (S.weight_ef) load_v<4>(A.werr + gi, nvalid, wi);
+    weight_lane<4, ROUNDING>(S, xv, wi, gi, Shift{}, wo, j);
+    if (A.werr) store_v<4>(A.werr + gi, nvalid, wo);
+    store_wcodes<4>(A.wcodes, S.wcode_bytes, gi, nvalid, j);
 }
 
 struct DequantArgs {
@@ -1278,79 +1270,71 @@ struct DequantArgs {
     float inv_two_kx1;
 };
 
-// A lane owns four pieces of E consecutive codes (E = 4 for fp32 output, 8 for binary16, so that an output
-// store is always 128 bits), piece k being elements E * (lane + 256 k) .. of the workgroup's 1024 E codes:
-// every store of a wavefront is one contiguous 1 KiB run and the four code loads are issued together.
+// A single wavefront per 64 E consecutive codes, E per lane (E = 4 for fp32 output, 8 for binary16, so that an output
+// store is always 128 bits and a wavefront's is one contiguous 1 KiB run).  Bound by the memory's write side; more
+// codes per lane and more wavefronts per workgroup only bunch the stores: 124 M codes to binary16 60.7 us with 256
+// threads and four pieces of E per lane; with 64 threads 58.7 with four, 58.6 with two, 57.7 with one.
 template <bool HALF, int CODE_BYTES>
-__global__ void __launch_bounds__(kBlockThreads) k_weight_dequantize(DequantArgs A)
+__global__ void __launch_bounds__(64) k_weight_dequantize(DequantArgs A)
 {
     constexpr int E = HALF ? 8 : 4;
-    constexpr int WORDS = E * CODE_BYTES / 4;           // code words per piece: 1, 2 or 4
-    const int64_t base = (int64_t)blockIdx.x * (kBlockThreads * E * 4);
-    uint32_t w[4][WORDS];
-    bool full[4];
+    constexpr int WORDS = E * CODE_BYTES / 4;           // code words per lane: 1, 2 or 4
+    const int64_t i = E * (wave_index() * 64 + threadIdx.x);
+    const bool full = i + E <= A.n;
+    uint32_t w[WORDS];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t i = base + E * ((int64_t)threadIdx.x + kBlockThreads * k);
-        full[k] = i + E <= A.n;
-#pragma unroll
-        for (int t = 0; t < WORDS; ++t) w[k][t] = 0u;
-        const char* src = static_cast<const char*>(A.wcodes) + i * CODE_BYTES;
-        if (full[k]) {
-            if constexpr (WORDS == 1) {
-                w[k][0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
-            } else if constexpr (WORDS == 2) {
-                const u2 v = __builtin_nontemporal_load(reinterpret_cast<const u2*>(src));
-                w[k][0] = v.x; w[k][1] = v.y;
-            } else {
-                const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(src));
-                w[k][0] = v.x; w[k][1] = v.y; w[k][2] = v.z; w[k][3] = v.w;
-            }
+    for (int t = 0; t < WORDS; ++t) w[t] = 0u;
+    const char* src = static_cast<const char*>(A.wcodes) + i * CODE_BYTES;
+    if (full) {
+        if constexpr (WORDS == 1) {
+            w[0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
+        } else if constexpr (WORDS == 2) {
+            const u2 v = __builtin_nontemporal_load(reinterpret_cast<const u2*>(src));
+            w[0] = v.x; w[1] = v.y;
         } else {
-            // ragged end of the vector: code by code
+            const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(src));
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        }
+    } else {
+        // ragged end of the vector: code by code
 #pragma unroll
-            for (int t = 0; t < E; ++t) {
-                if (i + t < A.n) {
-                    const uint32_t c = CODE_BYTES == 1 ? (uint32_t)(uint8_t)src[t]
-                                                       : (uint32_t)reinterpret_cast<const uint16_t*>(src)[t];
-                    w[k][t * CODE_BYTES / 4] |= c << (8 * ((t * CODE_BYTES) & 3));
-                }
+        for (int t = 0; t < E; ++t) {
+            if (i + t < A.n) {
+                const uint32_t c = CODE_BYTES == 1 ? (uint32_t)(uint8_t)src[t]
+                                                   : (uint32_t)reinterpret_cast<const uint16_t*>(src)[t];
+                w[t * CODE_BYTES / 4] |= c << (8 * ((t * CODE_BYTES) & 3));
             }
         }
     }
+    float xh[E];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t i = base + E * ((int64_t)threadIdx.x + kBlockThreads * k);
-        float xh[E];
-#pragma unroll
-        for (int t = 0; t < E; ++t) {
-            const uint32_t c = w[k][t * CODE_BYTES / 4] >> (8 * ((t * CODE_BYTES) & 3));
-            const int j = CODE_BYTES == 1 ? (int)(int8_t)c : (int)(int16_t)c;
-            xh[t] = (float)j * A.inv_two_kx1;
-        }
-        if constexpr (HALF) {
-            __half* out = static_cast<__half*>(A.xhat) + i;
-            if (full[k]) {
-                u4 v;
-                v.x = (uint32_t)__half_as_ushort(__float2half_rn(xh[0])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[1])) << 16);
-                v.y = (uint32_t)__half_as_ushort(__float2half_rn(xh[2])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[3])) << 16);
-                v.z = (uint32_t)__half_as_ushort(__float2half_rn(xh[4])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[5])) << 16);
-                v.w = (uint32_t)__half_as_ushort(__float2half_rn(xh[6])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[7])) << 16);
-                __builtin_nontemporal_store(v, reinterpret_cast<u4*>(out));
-            } else {
-#pragma unroll
-                for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = __float2half_rn(xh[t]);
-            }
+    for (int t = 0; t < E; ++t) {
+        const uint32_t c = w[t * CODE_BYTES / 4] >> (8 * ((t * CODE_BYTES) & 3));
+        const int j = CODE_BYTES == 1 ? (int)(int8_t)c : (int)(int16_t)c;
+        xh[t] = (float)j * A.inv_two_kx1;
+    }
+    if constexpr (HALF) {
+        __half* out = static_cast<__half*>(A.xhat) + i;
+        if (full) {
+            u4 v;
+            v.x = (uint32_t)__half_as_ushort(__float2half_rn(xh[0])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[1])) << 16);
+            v.y = (uint32_t)__half_as_ushort(__float2half_rn(xh[2])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[3])) << 16);
+            v.z = (uint32_t)__half_as_ushort(__float2half_rn(xh[4])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[5])) << 16);
+            v.w = (uint32_t)__half_as_ushort(__float2half_rn(xh[6])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[7])) << 16);
+            __builtin_nontemporal_store(v, reinterpret_cast<u4*>(out));
         } else {
-            float* out = static_cast<float*>(A.xhat) + i;
-            if (full[k]) {
-                f4 v;
-                v.x = xh[0]; v.y = xh[1]; v.z = xh[2]; v.w = xh[3];
-                __builtin_nontemporal_store(v, reinterpret_cast<f4*>(out));
-            } else {
 #pragma unroll
-                for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = xh[t];
-            }
+            for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = __float2half_rn(xh[t]);
+        }
+    } else {
+        float* out = static_cast<float*>(A.xhat) + i;
+        if (full) {
+            f4 v;
+            v.x = xh[0]; v.y = xh[1]; v.z = xh[2]; v.w = xh[3];
+            __builtin_nontemporal_store(v, reinterpret_cast<f4*>(out));
+        } else {
+#pragma unroll
+            for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = xh[t];
         }
     }
 }
@@ -1888,12 +1872,20 @@ hipError_t launch_server_apply_w(const Launch& L, const StepScalars& S, const Wo
     return hipGetLastError();
 }
 
+// single-wavefront workgroups of `per_wave` consecutive elements each
+static dim3 flat_grid(int64_t n, int per_wave)
+{
+    constexpr int64_t kRow = (int64_t)1 << 25;
+    const int64_t waves = (n + per_wave - 1) / per_wave;
+    return dim3((unsigned)(waves < kRow ? waves : kRow), (unsigned)((waves + kRow - 1) / kRow));
+}
+
 hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const float* x, float* werr, void* wcodes)
 {
     if (L.num_params == 0) return hipSuccess;
     WeightArgs A;
     A.S = S; A.x = x; A.werr = werr; A.wcodes = wcodes; A.n = L.num_params;
-    const dim3 grid((unsigned)((L.num_params + kBlockThreads * 16 - 1) / (kBlockThreads * 16))), block(kBlockThreads);
+    const dim3 grid = flat_grid(L.num_params, 256), block(64);
     if (S.rounding == 0) hipLaunchKernelGGL(k_weight_quantize<0>, grid, block, 0, L.stream, A);
     else hipLaunchKernelGGL(k_weight_quantize<1>, grid, block, 0, L.stream, A);
     return hipGetLastError();
@@ -1907,8 +1899,7 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
     union { uint32_t u; float f; } cv;
     cv.u = (uint32_t)(127 - S.k_x - 1) << 23;
     A.inv_two_kx1 = cv.f;
-    const int64_t per_block = (int64_t)kBlockThreads * 4 * (half ? 8 : 4);
-    const dim3 grid((unsigned)((L.num_params + per_block - 1) / per_block)), block(kBlockThreads);
+    const dim3 grid = flat_grid(L.num_params, 64 * (half ? 8 : 4)), block(64);
     if (S.wcode_bytes == 1) {
         if (half) hipLaunchKernelGGL((k_weight_dequantize<true, 1>), grid, block, 0, L.stream, A);
         else hipLaunchKernelGGL((k_weight_dequantize<false, 1>), grid, block, 0, L.stream, A);
