@@ -6,7 +6,8 @@
 // rules are the ones that matter for that regime on CDNA4:
 //   * 64-wide wavefronts, 256-thread workgroups; a lane owns 4 consecutive fp32 values so every
 //     global access is a 128-bit load/store and a wavefront touches 1 KiB of contiguous memory;
-//     all buffers are touched once per pass, so loads and stores carry the non-temporal hint;
+//     all buffers are touched once per pass, so loads and stores carry the non-temporal hint, except where the next
+//     pass finds the data in the memory-side cache (keep_scanned, keep_parked);
 //   * work is cut along tiles (<= 4096 elements of one layer), so all per-layer quantities (scales, code
 //     offsets) are wave-uniform and live in scalar registers;
 //   * the main pass, the worker quantizer and the server run as workgroups of ONE wavefront each, which drift
@@ -656,10 +657,24 @@ __device__ __forceinline__ uint32_t block_max(uint32_t local)
     return bm;
 }
 
+// load_v of the scale pass.  KEEP: an ordinary load, so that the lines stay in the 256 MB cache in front of the memory
+// for the pass that quantizes them (keep_scanned says when); else the non-temporal one, which leaves no copy behind.
+template <int V, bool KEEP>
+__device__ __forceinline__ void load_scan(const float* __restrict__ p, int nvalid, float (&out)[V])
+{
+    if (KEEP && nvalid == 4) {
+        const f4 t = *reinterpret_cast<const f4*>(p);
+        out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
+    } else {
+        load_v<V>(p, nvalid, out);
+    }
+}
+
 // max |g + e| (g == null: max |e|) over the flat range [start, start + len) wherever it begins: a
 // maximum does not care which lane sees which element, so the range is walked as the aligned quads of
 // memory it contains plus at most three single elements at either end.  thr != 0: e is read only for
 // quads (elements) whose |g| reaches thr (filtered scale pass).
+template <bool KEEP>
 __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, const float* __restrict__ e,
                                                int64_t start, int len, uint32_t thr)
 {
@@ -688,8 +703,8 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
             live[k] = q < a1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { gv[k][j] = 0.0f; ev[k][j] = 0.0f; }
-            if (live[k] && g) load_v<4>(g + q, 4, gv[k]);
-            if (live[k] && thr == 0u) load_v<4>(e + q, 4, ev[k]);
+            if (live[k] && g) load_scan<4, KEEP>(g + q, 4, gv[k]);
+            if (live[k] && thr == 0u) load_scan<4, KEEP>(e + q, 4, ev[k]);
         }
         if (thr != 0u) {
 #pragma unroll
@@ -701,7 +716,7 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
                     top = ab > top ? ab : top;
                 }
                 cand[k] = live[k] && top >= thr;
-                if (cand[k]) load_v<4>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
+                if (cand[k]) load_scan<4, KEEP>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
             }
         }
 #pragma unroll
@@ -822,7 +837,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_reduce_lower_bounds(ScaleArgs
     }
 }
 
-template <int V>
+template <int V, bool KEEP>
 __device__ __forceinline__ uint32_t amax_tile(const float* __restrict__ g, const float* __restrict__ e, const Tile& t)
 {
     constexpr int BLOCK_ELEMS = kBlockThreads * V;
@@ -833,8 +848,8 @@ __device__ __forceinline__ uint32_t amax_tile(const float* __restrict__ g, const
             float gv[4][4], ev[4][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                load_v<4>(g + t.start + k * BLOCK_ELEMS + threadIdx.x * 4, 4, gv[k]);
-                load_v<4>(e + t.start + k * BLOCK_ELEMS + threadIdx.x * 4, 4, ev[k]);
+                load_scan<4, KEEP>(g + t.start + k * BLOCK_ELEMS + threadIdx.x * 4, 4, gv[k]);
+                load_scan<4, KEEP>(e + t.start + k * BLOCK_ELEMS + threadIdx.x * 4, 4, ev[k]);
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -849,8 +864,8 @@ __device__ __forceinline__ uint32_t amax_tile(const float* __restrict__ g, const
     for (int off = threadIdx.x * V; off < t.len; off += BLOCK_ELEMS) {
         const int nvalid = min(t.len - off, V);
         float gv[V], ev[V];
-        load_v<V>(g + t.start + off, nvalid, gv);
-        load_v<V>(e + t.start + off, nvalid, ev);
+        load_scan<V, KEEP>(g + t.start + off, nvalid, gv);
+        load_scan<V, KEEP>(e + t.start + off, nvalid, ev);
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const uint32_t ab = f2u(gv[j] + ev[j]) & 0x7fffffffu;
@@ -861,6 +876,7 @@ __device__ __forceinline__ uint32_t amax_tile(const float* __restrict__ g, const
 }
 
 // grid: (tiles, workers)
+template <bool KEEP>
 __global__ void __launch_bounds__(kBlockThreads) k_amax(AmaxArgs A)
 {
     const int ti = A.tile_list ? A.tile_list[blockIdx.x] : (int)blockIdx.x;
@@ -869,8 +885,8 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax(AmaxArgs A)
     const float* g = A.grad[w];
     const float* e = A.err[w];
     uint32_t local;
-    if (t.flags & kTileUnaligned) local = amax_range(g, e, t.start, t.len, 0u);
-    else local = amax_tile<4>(g, e, t);
+    if (t.flags & kTileUnaligned) local = amax_range<KEEP>(g, e, t.start, t.len, 0u);
+    else local = amax_tile<4, KEEP>(g, e, t);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) A.tile_max[(size_t)w * A.row + ti] = bm;
 }
@@ -943,8 +959,8 @@ __global__ void __launch_bounds__(kBlockThreads) k_amax_filtered(AmaxArgs A)
     const float* e = A.err[w];
     const uint32_t thr = A.thr[(size_t)w * A.num_segments + t.seg];
     uint32_t local;
-    if (t.flags & kTileUnaligned) local = amax_range(g, e, t.start, t.len, thr);
-    else if (thr == 0u) local = amax_tile<4>(g, e, t);
+    if (t.flags & kTileUnaligned) local = amax_range<false>(g, e, t.start, t.len, thr);
+    else if (thr == 0u) local = amax_tile<4, false>(g, e, t);
     else local = amax_tile_filtered<4>(g, e, t, thr);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) A.tile_max[(size_t)w * A.row + ti] = bm;
@@ -976,7 +992,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_check_error_bounds(AmaxArgs A
     const Tile t = A.tiles[ti];
     const int w = A.first_worker + blockIdx.y;
     const float* e = A.err[w];
-    const uint32_t local = (t.flags & kTileUnaligned) ? amax_range(nullptr, e, t.start, t.len, 0u) : emax_tile<4>(e, t);
+    const uint32_t local = (t.flags & kTileUnaligned) ? amax_range<false>(nullptr, e, t.start, t.len, 0u) : emax_tile<4>(e, t);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) {
         const float bound = A.err_bound[(size_t)w * A.num_segments + t.seg];
@@ -1549,7 +1565,22 @@ struct MomentsWArgs {
     int first_worker;
 };
 
-template <int V, bool SH = false>
+// an ordinary store: the lines stay in the cache in front of the memory for the next pass
+template <bool SH>
+__device__ __forceinline__ void store_keep(float* __restrict__ p, int nvalid, const float (&in)[4])
+{
+    if (nvalid == 4) {
+        f4 t;
+        t.x = in[0]; t.y = in[1]; t.z = in[2]; t.w = in[3];
+        if constexpr (SH) *reinterpret_cast<f4_a4*>(p) = t;
+        else *reinterpret_cast<f4*>(p) = t;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) if (j < nvalid) p[j] = in[j];
+    }
+}
+
+template <int V, bool SH, bool KEEP>
 __device__ __forceinline__ uint32_t moments_w_part(const StepScalars& S, const float* __restrict__ grad,
                                                    float* __restrict__ mw, float* __restrict__ vw,
                                                    float* __restrict__ err, const Tile& t, int part_begin, int part_len)
@@ -1575,7 +1606,8 @@ __device__ __forceinline__ uint32_t moments_w_part(const StepScalars& S, const f
         }
         st<V, SH>(mw, gi, nvalid, sf, mv);
         st<V, SH>(vw, gi, nvalid, sf, vv);
-        st<V, SH>(err, gi, nvalid, sf, p);
+        if constexpr (KEEP) store_keep<SH>(err + gi, nvalid, p);
+        else st<V, SH>(err, gi, nvalid, sf, p);
     }
     return local;
 }
@@ -1583,6 +1615,7 @@ __device__ __forceinline__ uint32_t moments_w_part(const StepScalars& S, const f
 // grid: (tiles * parts, workers), one 1024-element turn per workgroup: a workgroup that does a whole tile turn by
 // turn leaves the memory idle between a turn's stores and the next one's loads (11.7 M parameters, 4 workers:
 // 240 us with whole tiles, 226 with quarters).
+template <bool KEEP>
 __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
 {
     const int ti = (int)(blockIdx.x / (unsigned)A.parts);
@@ -1591,9 +1624,9 @@ __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
     const int w = A.first_worker + blockIdx.y;
     uint32_t local;
     if (t.flags & kTileUnaligned)
-        local = moments_w_part<4, true>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
+        local = moments_w_part<4, true, KEEP>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
     else
-        local = moments_w_part<4, false>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
+        local = moments_w_part<4, false, KEEP>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
     const uint32_t bm = block_max(local);
     if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles * A.parts + blockIdx.x] = bm;
 }
@@ -1728,6 +1761,23 @@ static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num
     return F;
 }
 
+// Whether the scale pass over n elements of num workers leaves g and e in the cache for the quantizing pass.  A hit
+// costs the memory nothing, a line kept in vain pushes out another's.  us per step, non-temporal / ordinary loads:
+// 4 workers of 2 M (2^20) elements 48.9 / 47.4, 8 M 165.3 / 158.3, 16 M 317.6 / 304.4, 24 M 470.5 / 457.4, 32 M 618 / 611;
+// 8 workers of 12 M 407 / 401; the handle-free call on 24 M 83.4 / 82.4.  One worker's separate call has little else
+// to push out, and gains less: four calls of 8 M in a row 188.4 / 185.5, one of 16 M 159.8 / 159.3, of 24 M 232.0 /
+// 233.2, of 40 M 375.6 / 379.7; four of 119 M 2299 / 2342.
+static bool keep_scanned(int64_t n, int num)
+{
+    const int64_t bytes = 8 * n * num;
+    return bytes <= (num > 1 ? (int64_t)768 << 20 : (int64_t)192 << 20);
+}
+
+// Whether the first pass of variant W leaves the parked p of num workers in the cache for the pass that quantizes it.
+// us per step, non-temporal / ordinary stores: 4 workers of 4 M (2^20) elements 125.7 / 123.4, 16 M 480 / 458, 24 M
+// 709 / 685, 30 M 874 / 866, 48 M 1374 / 1407; one worker of 64 M 601 / 577.
+static bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)512 << 20; }
+
 hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
                                 int max_per_tile)
 {
@@ -1765,7 +1815,9 @@ hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& 
     if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
-    hipLaunchKernelGGL(k_amax, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
+    const dim3 grid(L.num_tiles, num), block(kBlockThreads);
+    if (keep_scanned(L.num_params, num)) hipLaunchKernelGGL(k_amax<true>, grid, block, 0, L.stream, A);
+    else hipLaunchKernelGGL(k_amax<false>, grid, block, 0, L.stream, A);
     return hipGetLastError();
 }
 
@@ -1778,7 +1830,7 @@ hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const Wor
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
     A.tile_list = L.sample_tiles;
-    hipLaunchKernelGGL(k_amax, dim3(L.num_sample_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
+    hipLaunchKernelGGL(k_amax<false>, dim3(L.num_sample_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
     ScaleArgs R;
     fill_scale_args(R, L, S, W, first_worker);
     hipLaunchKernelGGL(k_reduce_lower_bounds, dim3(L.num_segments, num), dim3(kBlockThreads), 0, L.stream, R);
@@ -2002,7 +2054,9 @@ hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const 
     A.tile_max = L.tile_max;
     A.first_worker = first_worker;
     A.parts = moment_parts(L.num_tiles);
-    hipLaunchKernelGGL(k_moments_w, dim3((unsigned)L.num_tiles * (unsigned)A.parts, num), dim3(kBlockThreads), 0, L.stream, A);
+    const dim3 grid((unsigned)L.num_tiles * (unsigned)A.parts, num), block(kBlockThreads);
+    if (keep_parked(L.num_params, num)) hipLaunchKernelGGL(k_moments_w<true>, grid, block, 0, L.stream, A);
+    else hipLaunchKernelGGL(k_moments_w<false>, grid, block, 0, L.stream, A);
     return hipGetLastError();
 }
 
@@ -2074,7 +2128,9 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         A.tiles = nullptr; A.num_tiles = num_tiles; A.seg_len = n;
         A.grad[0] = grad; A.err[0] = err;
         A.tile_max = tile_max; A.row = num_tiles; A.first_worker = 0; A.num_segments = 1; A.status = status;
-        hipLaunchKernelGGL(k_amax, dim3(num_tiles, 1), dim3(kBlockThreads), 0, stream, A);
+        const dim3 grid(num_tiles, 1), block(kBlockThreads);
+        if (keep_scanned(n, 1)) hipLaunchKernelGGL(k_amax<true>, grid, block, 0, stream, A);
+        else hipLaunchKernelGGL(k_amax<false>, grid, block, 0, stream, A);
     }
     Fold F;
     std::memset(&F, 0, sizeof F);
