@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/qadam.h"
+#include "qadam_work.h"
 
 namespace qadam {
 
@@ -28,7 +29,6 @@ constexpr int kTileUnaligned = 1;
 constexpr int kTileSampled = 2;
 constexpr int kSampleStride = 64;   // every 64th tile of a layer (from its first) is a sampled tile
 constexpr int kBlockThreads = 256;
-constexpr int kReduceThreads = 1024;
 // pieces a tile is cut into by the first pass of variant W, each with a maximum of its own: one turn of a workgroup,
 // or the whole tile where quarters would bring the launch to 2^32 work-items
 constexpr int kMomentParts = 4;

@@ -642,7 +642,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return v;
 }
 
-// block-wide max of the lanes' values; thread 0 gets the result
+// block-wide max of the lanes' values; every thread gets the result
 template <int THREADS = kBlockThreads>
 __device__ __forceinline__ uint32_t block_max(uint32_t local)
 {
@@ -786,6 +786,29 @@ __device__ __forceinline__ void check_scale(float s, uint32_t* status)
     if (!(s >= 0.0f && s < __builtin_inff()) && threadIdx.x == 0) atomicOr(status, QADAM_STATUS_NONFINITE_SCALE);
 }
 
+// Maximum of part[t0 .. t1) over THREADS threads, this one's share: eight loads in flight each.
+template <int THREADS>
+__device__ __forceinline__ uint32_t fold_maxima(const uint32_t* __restrict__ part, int t0, int t1, int thread)
+{
+    uint32_t local = 0;
+    for (int t = t0 + thread; t < t1; t += THREADS * 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = t + k * THREADS < t1 ? part[t + k * THREADS] : 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) local = v[k] > local ? v[k] : local;
+    }
+    return local;
+}
+
+__device__ __forceinline__ void write_scale(const ScaleArgs& A, int w, int l, uint32_t max_bits)
+{
+    const Scale r = make_scale(max_bits);
+    A.scales[w][l] = r.s;
+    A.inv_scales[(size_t)w * A.num_segments + l] = r.inv;
+    A.err_bound[(size_t)w * A.num_segments + l] = residual_bound(r.s, A.bound_factor);
+}
+
 // grid: (layers, workers).  One workgroup folds the maxima of its (worker, layer).  The maxima come from L2 and
 // what bounds the kernel is the chain of loads of one thread, hence 1024 threads and eight loads in flight each.
 __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales(ScaleArgs A)
@@ -794,21 +817,33 @@ __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales(ScaleArgs A)
     // no table: a single segment that owns every tile
     const int t0 = (A.seg_tile_begin ? A.seg_tile_begin[l] : 0) * A.max_per_tile;
     const int t1 = (A.seg_tile_begin ? A.seg_tile_begin[l + 1] : A.num_tiles) * A.max_per_tile;
-    const uint32_t* part = A.tile_max + (size_t)w * A.row;
-    uint32_t local = 0;
-    for (int t = t0 + (int)threadIdx.x; t < t1; t += kReduceThreads * 8) {
-        uint32_t v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = t + k * kReduceThreads < t1 ? part[t + k * kReduceThreads] : 0u;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) local = v[k] > local ? v[k] : local;
-    }
+    const uint32_t local = fold_maxima<kReduceThreads>(A.tile_max + (size_t)w * A.row, t0, t1, (int)threadIdx.x);
     const uint32_t bm = block_max<kReduceThreads>(local);
-    if (threadIdx.x == 0) {
-        const Scale r = make_scale(bm);
-        A.scales[w][l] = r.s;
-        A.inv_scales[(size_t)w * A.num_segments + l] = r.inv;
-        A.err_bound[(size_t)w * A.num_segments + l] = residual_bound(r.s, A.bound_factor);
+    if (threadIdx.x == 0) write_scale(A, w, l, bm);
+}
+
+// The same for lists of many layers.  grid: (layers / kListLayers, workers).  Each wavefront folds one layer if its
+// maxima are one turn of it (kListMaxima); the longer layers among the workgroup's are folded by all of it afterwards,
+// one by one, so that no mix of short and long layers leaves it with one wavefront at work.
+__global__ void __launch_bounds__(kReduceThreads) k_reduce_scales_list(ScaleArgs A)
+{
+    const int first = blockIdx.x * kListLayers, w = A.first_worker + blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t* part = A.tile_max + (size_t)w * A.row;
+    // lane k holds where layer first + k begins (past the last layer: its end, an empty range)
+    const int begin = lane <= kListLayers ? A.seg_tile_begin[min(first + lane, A.num_segments)] * A.max_per_tile : 0;
+    const int t0 = __shfl(begin, wave, 64), t1 = __shfl(begin, wave + 1, 64);
+    if (first + wave < A.num_segments && t1 - t0 <= kListMaxima) {
+        const uint32_t m = wave_max_u32(fold_maxima<64>(part, t0, t1, lane));
+        if (lane == 0) write_scale(A, w, first + wave, m);
+    }
+#pragma unroll 1
+    for (int k = 0; k < kListLayers; ++k) {
+        const int a = __builtin_amdgcn_readlane(begin, k), b = __builtin_amdgcn_readlane(begin, k + 1);
+        if (b - a <= kListMaxima) continue;         // the same in every wavefront of the workgroup
+        const uint32_t bm = block_max<kReduceThreads>(fold_maxima<kReduceThreads>(part, a, b, (int)threadIdx.x));
+        if (threadIdx.x == 0) write_scale(A, w, first + k, bm);
+        __syncthreads();                            // block_max's parts are read before the next round writes them
     }
 }
 
@@ -1785,7 +1820,9 @@ hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const Wor
     ScaleArgs A;
     fill_scale_args(A, L, S, W, first_worker);
     A.max_per_tile = max_per_tile;
-    hipLaunchKernelGGL(k_reduce_scales, dim3(L.num_segments, num), dim3(kReduceThreads), 0, L.stream, A);
+    const dim3 grid(reduce_blocks(L.num_segments, num), num), block(kReduceThreads);
+    if (reduce_by_list(L.num_segments, num)) hipLaunchKernelGGL(k_reduce_scales_list, grid, block, 0, L.stream, A);
+    else hipLaunchKernelGGL(k_reduce_scales, grid, block, 0, L.stream, A);
     return hipGetLastError();
 }
 

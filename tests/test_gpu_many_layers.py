@@ -1,0 +1,71 @@
+"""GPU parity on lists of very many layers, where the scales are found a workgroup per 16 layers and the launches come
+near their largest size.  Bit for bit against the oracle, which takes such a list in one call."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qadam_oracle as oracle
+from paper_2004_14180_amd import QAdam
+from parity_util import configs
+
+pytestmark = pytest.mark.gpu
+
+
+def _same(dev, host):
+    return np.array_equal(dev.cpu().numpy().view(np.uint8), np.ascontiguousarray(host).view(np.uint8))
+
+
+def _step(sizes, N, call, seed):
+    """One step from a state that is nowhere zero; every output compared with the oracle's."""
+    gcfg, ocfg = configs()
+    seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    P, L, rng = int(seg[-1]), len(sizes), np.random.default_rng(seed)
+    f32 = lambda s: rng.standard_normal(P, dtype=np.float32) * np.float32(s)  # noqa: E731
+    dev = lambda a: torch.from_numpy(a.copy()).cuda()  # noqa: E731
+    hg, he = [f32(1e-2) for _ in range(N)], [f32(1e-3) for _ in range(N)]
+    hx, hw = f32(0.02), f32(1e-3)
+    nm = N if call == "w" else 1
+    hm, hv = [f32(1e-3) for _ in range(nm)], [f32(1e-3) ** 2 for _ in range(nm)]
+    g, e, m, v = ([dev(a) for a in b] for b in (hg, he, hm, hv))
+    x, werr, wcodes = dev(hx), dev(hw), torch.full((P,), 77, dtype=torch.int8, device="cuda")
+    q = QAdam(gcfg, seg.tolist(), N)
+    codes = [torch.full((q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(N)]
+    scales = [torch.full((L,), -1.0, device="cuda") for _ in range(N)]
+    if call == "fused":
+        q.step_fused(1, 1e-3, 0.999, g, e, codes, scales, x, m[0], v[0], werr, wcodes)
+    elif call == "calls":
+        for i in range(N):
+            q.worker_quantize(i, 1, g[i], e[i], codes[i], scales[i])
+        q.server_step(1, 1e-3, 0.999, codes, scales, x, m[0], v[0])
+        q.weight_quantize(1, x, werr, wcodes)
+    elif call == "w":
+        q.step_fused_w(1, 1e-3, 0.999, g, m, v, e, codes, scales, x, werr, wcodes)
+    if call == "w":
+        out = oracle.step_w(ocfg, seg, 1, 1e-3, 0.999, hg, he, hm, hv, hx, hw, want_tie=False)
+    else:
+        out = oracle.step_s(ocfg, seg, 1, 1e-3, 0.999, hg, he, hx, hm[0], hv[0], hw, want_tie=False)
+    assert q.get_status() == 0
+    for i in range(N):
+        assert _same(scales[i], out["scales"][i]) and _same(codes[i], out["words"][i]) and _same(e[i], he[i]), (call, i)
+    assert all(_same(a, b) for a, b in zip(m + v + [x, werr, wcodes], hm + hv + [hx, hw, out["wcodes"]])), call
+    q.close()
+
+
+T = 4096
+
+
+@pytest.mark.parametrize("call", ["fused", "calls", "w"])
+@pytest.mark.parametrize("N", [1, 3])
+def test_layers_each_side_of_a_wavefronts_turn(call, N):
+    """Layers of 511 to 513 maxima (one per tile, four in variant W) among short and empty ones; 1025 layers or more, so
+    that a workgroup takes 16 layers also with one worker, the last one fewer."""
+    long = [T * 512 - 3, T * 512 + 1, T * 128, T * 128 + 5] if N == 1 else [T * 512 + 1, T * 128, T * 128 + 1]
+    sizes = [1, 33, 0, 1000, 5] * 100 + long + [7, 255, 1025, 0, 3] * 105
+    assert len(sizes) > 1024 and len(sizes) % 16
+    _step(sizes, N, call, seed=11 + N)
+
+
+@pytest.mark.parametrize("call", ["fused", "calls", "w"])
+def test_more_layers_than_workgroups_of_1024_threads_fit(call):
+    """2^22 + 5 layers: a workgroup of 1024 threads for each would be a launch of 2^32 work-items."""
+    _step([1] * ((1 << 22) + 4) + [3 * T + 1], 1, call, seed=3)
