@@ -255,7 +255,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     h->mu_bits = cfg->k_g == QADAM_IDENTITY ? 0 : mu_bits_for(cfg->k_g);
     h->code_bits = cfg->k_g == QADAM_IDENTITY ? 0 : 1 + h->mu_bits;       /* 0: no codes are stored */
     h->wcode_bytes = cfg->k_x == QADAM_IDENTITY ? 0 : (cfg->k_x <= 6 ? 1 : 2);
-    h->tile_elems = kDefaultTileElems;
+    h->tile_elems = kTileElems;
 
     // one workgroup per tile: a launch needs tiles * threads per workgroup below 2^32
     int64_t tile_count = 0;

@@ -33,7 +33,6 @@ constexpr int kBlockThreads = 256;
 // or the whole tile where quarters would bring the launch to 2^32 work-items
 constexpr int kMomentParts = 4;
 inline int moment_parts(int num_tiles) { return num_tiles < (1 << 22) ? kMomentParts : 1; }
-constexpr int kDefaultTileElems = 4096;   // elements per tile (16 per lane of a 256-thread workgroup)
 
 // Scalars of one launch, identical for every kernel.
 struct StepScalars {

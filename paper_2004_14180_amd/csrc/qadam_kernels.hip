@@ -515,27 +515,8 @@ __device__ __forceinline__ void weight_lane(const StepScalars& S, const float (&
 // ------------------------------------------------------------------------------------------------
 // kernel argument blocks
 // ------------------------------------------------------------------------------------------------
-// Work items of the kernels whose workgroups are single wavefronts (the main pass, the worker quantizer, the
-// server): a tile is cut into `parts` pieces and each is one workgroup.  Wavefronts that share a workgroup start
-// together and then load and store in step, and the next four start when the last of them has ended; on their own
-// they drift apart, so reads and writes mix, and the workgroups in flight cover a narrower stretch of each of the
-// 2N+4 read and N+5 written streams (main pass with four wavefronts per workgroup -> one: 11.7 M parameters,
-// 4 workers 204 -> 172 us; 124 M, 8 workers 3.29 -> 3.04 ms; 1.3 G, 4 workers 19.5 -> 18.4 ms).
-//
-// Workgroups go to the eight XCDs in turn.  wave_item gives the workgroups of one XCD runs of consecutive items, so
-// that the pieces of a line of packed codes, which neighbouring items write, meet in one L2.
-struct Items {
-    uint32_t count;             // tiles * parts
-    uint32_t parts;             // pieces per tile
-    uint32_t run_shift;         // log2 of the items in a row that go to one XCD
-};
-
-__device__ __forceinline__ uint32_t wave_item(const Items& I)
-{
-    const uint32_t xcd = blockIdx.x & 7u, k = blockIdx.x >> 3;
-    const uint32_t mask = (1u << I.run_shift) - 1u;
-    return (((k & ~mask) << 3) | (xcd << I.run_shift)) + (k & mask);
-}
+// the item of this workgroup (see Items)
+__device__ __forceinline__ uint32_t wave_item(const Items& I) { return item_of(I, blockIdx.x); }
 
 struct AmaxArgs {
     const Tile* tiles;
@@ -595,18 +576,18 @@ struct WorkerArgs {        // one worker
 
 // Tile record of workgroup `ti`: from the handle's table, or, for the handle-free single-segment
 // call (tiles == null), computed from the segment length: tile ti covers elements
-// [ti * kDefaultTileElems, ...) of a segment that starts 16-byte aligned at element 0.
+// [ti * kTileElems, ...) of a segment that starts 16-byte aligned at element 0.
 __device__ __forceinline__ Tile tile_at(const Tile* __restrict__ tiles, int ti, int64_t seg_len, int code_bits)
 {
     if (tiles) return tiles[ti];
     Tile t;
-    t.start = (int64_t)ti * kDefaultTileElems;
-    t.code_word = (int64_t)ti * (kDefaultTileElems / 32) * code_bits;
+    t.start = (int64_t)ti * kTileElems;
+    t.code_word = (int64_t)ti * (kTileElems / 32) * code_bits;
     const int64_t left = seg_len - t.start;
-    t.len = (int32_t)(left < kDefaultTileElems ? left : kDefaultTileElems);
+    t.len = (int32_t)(left < kTileElems ? left : kTileElems);
     t.seg = 0;
     t.flags = 0;
-    if (left <= kDefaultTileElems) {
+    if (left <= kTileElems) {
         const int64_t used = (seg_len + 31) / 32 * code_bits;
         t.flags = (int32_t)((used + 3) / 4 * 4 - used) << 8;     // zero words up to a multiple of 16 bytes
     }
@@ -1069,11 +1050,11 @@ __device__ __forceinline__ void store_chunk_words(uint32_t* __restrict__ codes, 
 // start too late (124 M parameters, 4 workers through the separate calls: 2294 / 2246 / 2313 us per step; 2^24
 // elements, one worker: 61.3 / 57.5 / 59.9 us).
 constexpr int kQuantizeRuns = 2;
-constexpr uint32_t kQuantizeParts = kDefaultTileElems / (256 * kQuantizeRuns);
+constexpr int kQuantizeElems = 256 * kQuantizeRuns;
 
 // ---- worker side alone (qadam_worker_quantize, second pass of variant W) -------------------------
-// One wavefront's share: C runs of 64 V consecutive elements of a tile from `part_begin`, their loads issued
-// together.  FULL: the share is whole, so that no access needs a guard.
+// One turn of a wavefront: C runs of 64 V consecutive elements of a tile from `part_begin`, their loads issued
+// together.  FULL: the turn is whole, so that no access needs a guard.
 template <int V, int ROUNDING, bool PARKED, bool SH, int C, bool FULL>
 __device__ __forceinline__ void worker_part(const WorkerArgs& A, const Tile& t, int ti, int part_begin)
 {
@@ -1124,20 +1105,21 @@ __device__ __forceinline__ void worker_part(const WorkerArgs& A, const Tile& t, 
 template <int ROUNDING, bool PARKED>
 __global__ void __launch_bounds__(64) k_worker_quantize(WorkerArgs A)
 {
-    constexpr int C = kQuantizeRuns;
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
     const int ti = (int)(item / A.items.parts);
     const Tile t = tile_at(A.tiles, ti, A.seg_len, A.S.code_bits);
-    const int part_begin = (int)(item % A.items.parts) * (C * 256);
-    if (part_begin >= t.len) return;
-    const bool full = part_begin + C * 256 <= t.len;
-    if (t.flags & kTileUnaligned) {
-        if (full) worker_part<4, ROUNDING, PARKED, true, C, true>(A, t, ti, part_begin);
-        else worker_part<4, ROUNDING, PARKED, true, C, false>(A, t, ti, part_begin);
-    } else {
-        if (full) worker_part<4, ROUNDING, PARKED, false, C, true>(A, t, ti, part_begin);
-        else worker_part<4, ROUNDING, PARKED, false, C, false>(A, t, ti, part_begin);
+    const int part_begin = (int)(item % A.items.parts) * A.items.part_len;
+    const int part_end = min(t.len, part_begin + A.items.part_len);
+    for (int begin = part_begin; begin < part_end; begin += kQuantizeElems) {
+        const bool full = begin + kQuantizeElems <= t.len;
+        if (t.flags & kTileUnaligned) {
+            if (full) worker_part<4, ROUNDING, PARKED, true, kQuantizeRuns, true>(A, t, ti, begin);
+            else worker_part<4, ROUNDING, PARKED, true, kQuantizeRuns, false>(A, t, ti, begin);
+        } else {
+            if (full) worker_part<4, ROUNDING, PARKED, false, kQuantizeRuns, true>(A, t, ti, begin);
+            else worker_part<4, ROUNDING, PARKED, false, kQuantizeRuns, false>(A, t, ti, begin);
+        }
     }
 }
 
@@ -1273,7 +1255,7 @@ __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
     const Tile t = A.tiles[item / A.items.parts];
-    const int part_len = kDefaultTileElems / (int)A.items.parts;
+    const int part_len = A.items.part_len;
     const int part_begin = (int)(item % A.items.parts) * part_len;
     if (part_begin >= t.len) return;
     if (t.flags & kTileUnaligned) server_part<4, U, MU_BITS, true>(A, t, part_begin, part_len);
@@ -1501,7 +1483,7 @@ __global__ void __launch_bounds__(64) k_fused(FusedArgs A)
     if (item >= A.items.count) return;
     const int ti = (int)(item / A.items.parts);
     const Tile t = A.tiles[ti];
-    const int part_len = kDefaultTileElems / (int)A.items.parts;
+    const int part_len = A.items.part_len;
     const int part_begin = (int)(item % A.items.parts) * part_len;
     if (part_begin >= t.len) return;
     const bool full = part_begin + part_len <= t.len;
@@ -1655,7 +1637,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
 {
     const int ti = (int)(blockIdx.x / (unsigned)A.parts);
     const Tile t = A.tiles[ti];
-    const int part_len = kDefaultTileElems / A.parts, part_begin = (int)(blockIdx.x % (unsigned)A.parts) * part_len;
+    const int part_len = kTileElems / A.parts, part_begin = (int)(blockIdx.x % (unsigned)A.parts) * part_len;
     const int w = A.first_worker + blockIdx.y;
     uint32_t local;
     if (t.flags & kTileUnaligned)
@@ -1876,25 +1858,7 @@ hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const Wor
     return hipGetLastError();
 }
 
-// `parts` pieces per tile, fewer where the launch would reach 2^32 work-items.  Runs are 256 items (256 KiB of
-// every stream) where that leaves each XCD eight or more of them (1.3 G parameters, 4 workers: 18.97 ms with runs
-// of 16, 18.41 with 64, 18.8 with 256; 124 M, 3 workers: 1.765 / 1.728 / 1.702 ms), shorter on short vectors.
-static Items wave_items(int num_tiles, uint32_t parts)
-{
-    Items I;
-    while ((int64_t)num_tiles * parts > ((int64_t)1 << 26) - 4096) parts /= 2;
-    I.parts = parts;
-    I.count = (uint32_t)num_tiles * parts;
-    I.run_shift = 0;
-    while (I.run_shift < 8 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
-    return I;
-}
-
-static dim3 wave_grid(const Items& I)
-{
-    const uint32_t round = 8u << I.run_shift;
-    return dim3((I.count + round - 1) / round * round);
-}
+static dim3 wave_grid(const Items& I) { return dim3(wave_blocks(I)); }
 
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker)
 {
@@ -1907,7 +1871,7 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
     A.worker = worker;
     A.seg_len = 0;
     const bool parked = (A.grad == nullptr);
-    A.items = wave_items(L.num_tiles, kQuantizeParts);
+    A.items = wave_items(L.num_tiles, kQuantizeElems);
     const dim3 grid = wave_grid(A.items), block(64);
     if (S.rounding == 0) {
         if (parked) hipLaunchKernelGGL((k_worker_quantize<0, true>), grid, block, 0, L.stream, A);
@@ -1922,7 +1886,7 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
 static void fill_server_args(ServerArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W)
 {
     A.tiles = L.tiles; A.S = S;
-    A.items = wave_items(L.num_tiles, 16);
+    A.items = wave_items(L.num_tiles, 256);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
@@ -2016,7 +1980,7 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    A.items = wave_items(L.num_tiles, 16);
+    A.items = wave_items(L.num_tiles, 256);
     const dim3 grid = wave_grid(A.items), block(64);
     // U = 4, or the variant that folds the scales, one worker at a time
 #define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
@@ -2105,7 +2069,7 @@ hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const 
 // or a HIP call (on the host it is only a stand-in for the symbol): it uses the address that
 // hipGetSymbolAddress returned for the current device.
 // ================================================================================================
-constexpr int kNoallocMaxTiles = (int)(kNoallocMaxElems / kDefaultTileElems);
+constexpr int kNoallocMaxTiles = (int)(kNoallocMaxElems / kTileElems);
 constexpr int kNoallocExtraWords = 64;      // [0] reciprocal scale, [1] residual bound, [2] status, rest unused
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) uint32_t scratch[kNoallocMaxTiles + kNoallocExtraWords];
@@ -2153,7 +2117,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         hipLaunchKernelGGL(k_segment, dim3(1), dim3(kSegmentThreads), 0, stream, A);
         return hipGetLastError();
     }
-    const int num_tiles = (int)((n + kDefaultTileElems - 1) / kDefaultTileElems);
+    const int num_tiles = (int)((n + kTileElems - 1) / kTileElems);
     uint32_t* tile_max = sc;
     float* inv_scale = reinterpret_cast<float*>(sc + kNoallocMaxTiles);
     float* err_bound = reinterpret_cast<float*>(sc + kNoallocMaxTiles + 1);
@@ -2192,7 +2156,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         W.status = status; W.S = S;
         W.grad = grad; W.err = err; W.codes = codes; W.scales = scale_out; W.fold = F;
         W.worker = 0;
-        W.items = wave_items(num_tiles, kQuantizeParts);
+        W.items = wave_items(num_tiles, kQuantizeElems);
         hipLaunchKernelGGL((k_worker_quantize<0, false>), wave_grid(W.items), dim3(64), 0, stream, W);
     }
     return hipGetLastError();

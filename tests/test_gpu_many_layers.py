@@ -24,7 +24,7 @@ def _step(sizes, N, call, seed):
     dev = lambda a: torch.from_numpy(a.copy()).cuda()  # noqa: E731
     hg, he = [f32(1e-2) for _ in range(N)], [f32(1e-3) for _ in range(N)]
     hx, hw = f32(0.02), f32(1e-3)
-    nm = N if call == "w" else 1
+    nm = N if call[0] == "w" else 1
     hm, hv = [f32(1e-3) for _ in range(nm)], [f32(1e-3) ** 2 for _ in range(nm)]
     g, e, m, v = ([dev(a) for a in b] for b in (hg, he, hm, hv))
     x, werr, wcodes = dev(hx), dev(hw), torch.full((P,), 77, dtype=torch.int8, device="cuda")
@@ -40,7 +40,12 @@ def _step(sizes, N, call, seed):
         q.weight_quantize(1, x, werr, wcodes)
     elif call == "w":
         q.step_fused_w(1, 1e-3, 0.999, g, m, v, e, codes, scales, x, werr, wcodes)
-    if call == "w":
+    elif call == "w_calls":
+        for i in range(N):
+            q.worker_step_w(i, 1, 1e-3, 0.999, g[i], m[i], v[i], e[i], codes[i], scales[i])
+        q.server_apply_w(1, codes, scales, x)
+        q.weight_quantize(1, x, werr, wcodes)
+    if call[0] == "w":
         out = oracle.step_w(ocfg, seg, 1, 1e-3, 0.999, hg, he, hm, hv, hx, hw, want_tie=False)
     else:
         out = oracle.step_s(ocfg, seg, 1, 1e-3, 0.999, hg, he, hx, hm[0], hv[0], hw, want_tie=False)
@@ -69,3 +74,10 @@ def test_layers_each_side_of_a_wavefronts_turn(call, N):
 def test_more_layers_than_workgroups_of_1024_threads_fit(call):
     """2^22 + 5 layers: a workgroup of 1024 threads for each would be a launch of 2^32 work-items."""
     _step([1] * ((1 << 22) + 4) + [3 * T + 1], 1, call, seed=3)
+
+
+@pytest.mark.parametrize("call", ["calls", "w_calls"])
+def test_whole_tiles_where_the_quantizers_pieces_are_longer_than_a_turn(call):
+    """2^23 tiles: the worker quantizer's launch then holds four pieces per tile, each two turns of a wavefront.  Most
+    tiles are layers of one element; two layers have whole tiles, one of them off the 16-byte grid."""
+    _step([3 * T + 700, 1025] + [1] * (1 << 23) + [2 * T + 2600], 1, call, seed=4)
