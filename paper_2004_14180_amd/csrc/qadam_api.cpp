@@ -22,6 +22,7 @@ struct qadam_ctx {
     int     device;
     Tile*     d_tiles;
     int32_t   num_tiles;
+    ListShape shape;
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
     uint32_t* d_tile_max;       // [num_workers][num_tiles]
@@ -114,7 +115,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.tile_max = h->d_tile_max; L.seg_tile_begin = h->d_seg_tile_begin; L.tile_sum = h->d_tile_sum;
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
-    L.num_tiles = h->num_tiles; L.num_segments = h->num_segments;
+    L.num_tiles = h->num_tiles; L.shape = h->shape; L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
     return L;
@@ -292,6 +293,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
                 sample_tiles.push_back((int32_t)tiles.size());
             }
             tiles.push_back(t);
+            add_tiles(h->shape, 1, t.len);
         }
         word_off += seg_words;
     }
@@ -313,7 +315,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     if (e == hipSuccess)
         e = hipMemcpy(h->d_seg_tile_begin, seg_tile_begin.data(), sizeof(int32_t) * (num_segments + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess && h->num_tiles > 0)
-        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->num_tiles * num_workers * moment_parts(h->num_tiles));
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->num_tiles * num_workers * moment_cut(h->shape).parts);
     if (e == hipSuccess && h->num_tiles > 0)
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_sum), sizeof(double) * (size_t)h->num_tiles);
     if (e == hipSuccess && num_segments > 0)
@@ -565,7 +567,7 @@ int qadam_worker_step_w(qadam_handle_t h, int32_t worker, int64_t step, float lr
     // pass 1: local moments, p = alpha m / sqrt(v + eps) + e parked in the error buffer, tile maxima
     BoundRecord record(h, worker, 1, W);
     QADAM_HIP(launch_worker_moments_w(L, S, W, worker, 1));
-    QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1, moment_parts(L.num_tiles)));
+    QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1, moment_parts(L)));
     // pass 2: quantize the parked p
     W.grad[worker] = nullptr;
     QADAM_HIP(launch_worker_quantize(L, S, W, worker));
@@ -603,7 +605,7 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     // pass 1 (all workers): local moments, p parked in the error buffers, tile maxima; then scales
     BoundRecord record(h, 0, h->num_workers, W);
     QADAM_HIP(launch_worker_moments_w(L, S, W, 0, h->num_workers));
-    if (!idg) QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers, moment_parts(L.num_tiles)));
+    if (!idg) QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers, moment_parts(L)));
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
     // pass 2: quantize every worker's parked p, subtract the mean message, Q_x
     if (idg) QADAM_HIP(launch_plain_messages(L, S, W, sp, true));

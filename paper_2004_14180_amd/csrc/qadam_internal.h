@@ -29,10 +29,6 @@ constexpr int kTileUnaligned = 1;
 constexpr int kTileSampled = 2;
 constexpr int kSampleStride = 64;   // every 64th tile of a layer (from its first) is a sampled tile
 constexpr int kBlockThreads = 256;
-// pieces a tile is cut into by the first pass of variant W, each with a maximum of its own: one turn of a workgroup,
-// or the whole tile where quarters would bring the launch to 2^32 work-items
-constexpr int kMomentParts = 4;
-inline int moment_parts(int num_tiles) { return num_tiles < (1 << 22) ? kMomentParts : 1; }
 
 // Scalars of one launch, identical for every kernel.
 struct StepScalars {
@@ -74,6 +70,7 @@ struct Launch {
     uint32_t*   tile_max;   // device, [num_workers][num_tiles]: per-tile max |p| as a bit pattern
     const int32_t* seg_tile_begin;  // device, [num_segments + 1]: first tile of every segment
     int32_t     num_tiles;
+    ListShape   shape;
     int32_t     num_segments;
     int64_t     num_params;
     double*     tile_sum;   // device, [num_tiles]: per-tile partial sums of the norm diagnostic
@@ -85,6 +82,9 @@ struct Launch {
     uint32_t*   status;     // device status word
     hipStream_t stream;
 };
+
+// maxima per tile that the first pass of variant W leaves
+inline int moment_parts(const Launch& L) { return (int)moment_cut(L.shape).parts; }
 
 // Launchers (defined in qadam_kernels.hip).  `first_worker`/`num` select the workers a launch covers.
 // scales in two stages without atomics: per-tile maxima, then one workgroup per (worker, layer)

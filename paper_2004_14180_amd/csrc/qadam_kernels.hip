@@ -1107,10 +1107,10 @@ __global__ void __launch_bounds__(64) k_worker_quantize(WorkerArgs A)
 {
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
-    const int ti = (int)(item / A.items.parts);
+    const int ti = (int)(item / A.items.cut.parts);
     const Tile t = tile_at(A.tiles, ti, A.seg_len, A.S.code_bits);
-    const int part_begin = (int)(item % A.items.parts) * A.items.part_len;
-    const int part_end = min(t.len, part_begin + A.items.part_len);
+    const int part_begin = (int)(item % A.items.cut.parts) * A.items.cut.part_len;
+    const int part_end = min(t.len, part_begin + A.items.cut.part_len);
     for (int begin = part_begin; begin < part_end; begin += kQuantizeElems) {
         const bool full = begin + kQuantizeElems <= t.len;
         if (t.flags & kTileUnaligned) {
@@ -1254,9 +1254,9 @@ __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 {
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
-    const Tile t = A.tiles[item / A.items.parts];
-    const int part_len = A.items.part_len;
-    const int part_begin = (int)(item % A.items.parts) * part_len;
+    const Tile t = A.tiles[item / A.items.cut.parts];
+    const int part_len = A.items.cut.part_len;
+    const int part_begin = (int)(item % A.items.cut.parts) * part_len;
     if (part_begin >= t.len) return;
     if (t.flags & kTileUnaligned) server_part<4, U, MU_BITS, true>(A, t, part_begin, part_len);
     else server_part<4, U, MU_BITS, false>(A, t, part_begin, part_len);
@@ -1481,10 +1481,10 @@ __global__ void __launch_bounds__(64) k_fused(FusedArgs A)
     constexpr bool FOLD = U == 1;
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
-    const int ti = (int)(item / A.items.parts);
+    const int ti = (int)(item / A.items.cut.parts);
     const Tile t = A.tiles[ti];
-    const int part_len = A.items.part_len;
-    const int part_begin = (int)(item % A.items.parts) * part_len;
+    const int part_len = A.items.cut.part_len;
+    const int part_begin = (int)(item % A.items.cut.parts) * part_len;
     if (part_begin >= t.len) return;
     const bool full = part_begin + part_len <= t.len;
     if (t.flags & kTileUnaligned) {
@@ -1577,8 +1577,8 @@ struct MomentsWArgs {
     float* mw[QADAM_MAX_WORKERS];
     float* vw[QADAM_MAX_WORKERS];
     float* err[QADAM_MAX_WORKERS];
-    uint32_t* tile_max;     // [N][num_tiles * parts]
-    int parts;              // pieces per tile
+    uint32_t* tile_max;     // [N][num_tiles * cut.parts]
+    Cut cut;
     int first_worker;
 };
 
@@ -1629,15 +1629,15 @@ __device__ __forceinline__ uint32_t moments_w_part(const StepScalars& S, const f
     return local;
 }
 
-// grid: (tiles * parts, workers), one 1024-element turn per workgroup: a workgroup that does a whole tile turn by
+// grid: (tiles * cut.parts, workers), one 1024-element turn per workgroup: a workgroup that does a whole tile turn by
 // turn leaves the memory idle between a turn's stores and the next one's loads (11.7 M parameters, 4 workers:
 // 240 us with whole tiles, 226 with quarters).
 template <bool KEEP>
 __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
 {
-    const int ti = (int)(blockIdx.x / (unsigned)A.parts);
+    const int ti = (int)(blockIdx.x / A.cut.parts);
     const Tile t = A.tiles[ti];
-    const int part_len = kTileElems / A.parts, part_begin = (int)(blockIdx.x % (unsigned)A.parts) * part_len;
+    const int part_len = A.cut.part_len, part_begin = (int)(blockIdx.x % A.cut.parts) * part_len;
     const int w = A.first_worker + blockIdx.y;
     uint32_t local;
     if (t.flags & kTileUnaligned)
@@ -1645,7 +1645,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
     else
         local = moments_w_part<4, false, KEEP>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
     const uint32_t bm = block_max(local);
-    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles * A.parts + blockIdx.x] = bm;
+    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles * A.cut.parts + blockIdx.x] = bm;
 }
 
 // ---- diagnostic: per-layer sum of squares in fp64, fixed order ---------------------------------
@@ -1738,7 +1738,7 @@ static float residual_bound_factor(const StepScalars& S)
 
 // Every pass gives worker w the same row of the maxima, whether it leaves one per tile or `moment_parts`: calls for
 // different workers may run on different streams.
-static int max_row(const Launch& L) { return L.num_tiles * moment_parts(L.num_tiles); }
+static int max_row(const Launch& L) { return L.num_tiles * moment_parts(L); }
 
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
@@ -1867,11 +1867,11 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
     A.tiles = L.tiles;
     A.status = L.status; A.S = S;
     A.grad = W.grad[worker]; A.err = W.err[worker]; A.codes = W.codes[worker]; A.scales = W.scales[worker];
-    A.fold = make_fold(L, S, worker, 1, A.grad ? 1 : moment_parts(L.num_tiles));
+    A.fold = make_fold(L, S, worker, 1, A.grad ? 1 : moment_parts(L));
     A.worker = worker;
     A.seg_len = 0;
     const bool parked = (A.grad == nullptr);
-    A.items = wave_items(L.num_tiles, kQuantizeElems);
+    A.items = wave_items(L.shape, kQuantizeElems);
     const dim3 grid = wave_grid(A.items), block(64);
     if (S.rounding == 0) {
         if (parked) hipLaunchKernelGGL((k_worker_quantize<0, true>), grid, block, 0, L.stream, A);
@@ -1886,7 +1886,7 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
 static void fill_server_args(ServerArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W)
 {
     A.tiles = L.tiles; A.S = S;
-    A.items = wave_items(L.num_tiles, 256);
+    A.items = wave_items(L.shape, 256);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
@@ -1976,11 +1976,11 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     FusedArgs A;
     A.tiles = L.tiles;
     A.status = L.status; A.S = S; A.sp = sp;
-    A.fold = make_fold(L, S, 0, S.num_workers, variant_w ? moment_parts(L.num_tiles) : 1);
+    A.fold = make_fold(L, S, 0, S.num_workers, variant_w ? moment_parts(L) : 1);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    A.items = wave_items(L.num_tiles, 256);
+    A.items = wave_items(L.shape, 256);
     const dim3 grid = wave_grid(A.items), block(64);
     // U = 4, or the variant that folds the scales, one worker at a time
 #define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
@@ -2054,8 +2054,8 @@ hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const 
     }
     A.tile_max = L.tile_max;
     A.first_worker = first_worker;
-    A.parts = moment_parts(L.num_tiles);
-    const dim3 grid((unsigned)L.num_tiles * (unsigned)A.parts, num), block(kBlockThreads);
+    A.cut = moment_cut(L.shape);
+    const dim3 grid((unsigned)L.num_tiles * A.cut.parts, num), block(kBlockThreads);
     if (keep_parked(L.num_params, num)) hipLaunchKernelGGL(k_moments_w<true>, grid, block, 0, L.stream, A);
     else hipLaunchKernelGGL(k_moments_w<false>, grid, block, 0, L.stream, A);
     return hipGetLastError();
@@ -2156,7 +2156,10 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         W.status = status; W.S = S;
         W.grad = grad; W.err = err; W.codes = codes; W.scales = scale_out; W.fold = F;
         W.worker = 0;
-        W.items = wave_items(num_tiles, kQuantizeElems);
+        ListShape shape{};
+        add_tiles(shape, num_tiles - 1, kTileElems);
+        add_tiles(shape, 1, (int)(n - (int64_t)(num_tiles - 1) * kTileElems));
+        W.items = wave_items(shape, kQuantizeElems);
         hipLaunchKernelGGL((k_worker_quantize<0, false>), wave_grid(W.items), dim3(64), 0, stream, W);
     }
     return hipGetLastError();

@@ -9,20 +9,69 @@ namespace qadam {
 constexpr int64_t kMaxTiles = (int64_t)1 << 24;     // a handle has fewer: one 256-thread workgroup per tile must fit a launch
 constexpr int kTileElems = 4096;                     // elements per tile (16 per lane of a 256-thread workgroup)
 
+// ---- how a list of layers is cut into pieces -------------------------------------------------------------------------
+// What the cut depends on.  Tiles are not all whole: the last one of a layer holds the rest, and a list of short layers
+// has no other.
+struct ListShape {
+    int32_t num_tiles;
+    int32_t longest;            // elements of the longest tile
+    int64_t pieces[5];          // [k]: pieces of 256 << k elements, counted from the beginning of each tile, with an element
+};
+
+constexpr void add_tiles(ListShape& s, int64_t tiles, int len)
+{
+    s.num_tiles += (int32_t)tiles;
+    if (tiles > 0 && len > s.longest) s.longest = len;
+    for (int k = 0; k < 5; ++k) s.pieces[k] += tiles * ((len + (256 << k) - 1) / (256 << k));
+}
+
+// A launch gives every tile the same number of pieces of the same length.
+struct Cut {
+    uint32_t parts;             // pieces per tile
+    int32_t  part_len;          // elements per piece; parts * part_len covers the longest tile
+};
+
+constexpr int64_t kFullChip = 8192;     // pieces that fill the chip: 256 CUs with 16 wavefronts, twice
+
+// Pieces of `turn` elements (256 << k), as many as the longest tile has.  They are twice as long where the launch would
+// have more than `most` of them, and where its empty ones, behind the end of shorter tiles, cost more than the rest while
+// longer ones still fill the chip (`empty_cost`: of an empty piece against one with elements).  us per step of 4 workers,
+// pieces of `turn` / this rule / whole tiles: GPT-2 small 2292 / 2292 / 2584; 5000 times layers of 4096 and 64 elements
+// 435 / 434 / 597; 4000 times 4096 and four of 64 484 / 417 / 432; 3000 times 4096 and eight of 64 580 / 448 / 430; one of
+// 40 M and 20000 of 100 1040 / 1000 / 967.  With sixteen pieces for every tile, however short the longest is:
+// 100000 layers of 100 1565, with one 719.
+constexpr Cut cut_tiles(const ListShape& s, int turn, int64_t most, double empty_cost)
+{
+    Cut c{1, turn};
+    int k = 0;
+    while ((256 << k) < turn) ++k;
+    for (;; ++k, c.part_len *= 2) {
+        c.parts = s.longest > c.part_len ? (uint32_t)((s.longest + c.part_len - 1) / c.part_len) : 1u;
+        if (c.part_len >= kTileElems) return c;
+        const int64_t items = (int64_t)s.num_tiles * c.parts;
+        const bool sparse = (double)(items - s.pieces[k]) * empty_cost > (double)s.pieces[k] && s.pieces[k + 1] >= kFullChip;
+        if (items <= most && !sparse) return c;
+    }
+}
+
+// The pieces of the first pass of variant W: one 256-thread workgroup and one maximum each.  An empty one is four
+// wavefronts and a barrier.  us per step of 4 workers, pieces of 1024 / 2048 elements: 5000 times layers of 4096 and 64
+// (0.6 empty pieces of 1024 to one with elements) 728 / 770, 4000 of 5000 elements (0.6) 646 / 671; of 2048 / 4096: 4000
+// times 4096 and four of 64 (0.67) 661 / 615, 3000 times 4096 and eight of 64 (0.8) 720 / 613.
+constexpr Cut moment_cut(const ListShape& s) { return cut_tiles(s, 1024, kMaxTiles - 1, 1.6); }
+
 // ---- work items of the kernels whose workgroups are single wavefronts ------------------------------------------------
-// (the main pass, the worker quantizer, the server): a tile is cut into `parts` pieces of `part_len` elements and each is
-// one workgroup.  Wavefronts that share a workgroup start together and then load and store in step, and the next four
-// start when the last of them has ended; on their own they drift apart, so reads and writes mix, and the workgroups in
-// flight cover a narrower stretch of each of the 2N+4 read and N+5 written streams (main pass with four wavefronts per
-// workgroup -> one: 11.7 M parameters, 4 workers 204 -> 172 us; 124 M, 8 workers 3.29 -> 3.04 ms; 1.3 G, 4 workers
-// 19.5 -> 18.4 ms).
+// (the main pass, the worker quantizer, the server): every piece of a tile is one workgroup.  Wavefronts that share a
+// workgroup start together and then load and store in step, and the next four start when the last of them has ended; on
+// their own they drift apart, so reads and writes mix, and the workgroups in flight cover a narrower stretch of each of
+// the 2N+4 read and N+5 written streams (main pass with four wavefronts per workgroup -> one: 11.7 M parameters, 4 workers
+// 204 -> 172 us; 124 M, 8 workers 3.29 -> 3.04 ms; 1.3 G, 4 workers 19.5 -> 18.4 ms).
 //
 // Workgroups go to the eight XCDs in turn.  item_of gives the workgroups of one XCD runs of consecutive items, so
 // that the pieces of a line of packed codes, which neighbouring items write, meet in one L2.
 struct Items {
-    uint32_t count;             // tiles * parts
-    uint32_t parts;             // pieces per tile
-    int32_t  part_len;          // elements per piece; parts * part_len covers a tile
+    uint32_t count;             // tiles * cut.parts
+    Cut      cut;
     uint32_t run_shift;         // log2 of the items in a row that go to one XCD
 };
 
@@ -33,16 +82,14 @@ constexpr uint32_t item_of(const Items& I, uint32_t block)
     return (((k & ~mask) << 3) | (xcd << I.run_shift)) + (k & mask);
 }
 
-// Pieces of `part_len` elements, longer where the launch would reach 2^32 work-items.  Runs are 256 items (256 KiB of
-// every stream) where that leaves each XCD eight or more of them (1.3 G parameters, 4 workers: 18.97 ms with runs
-// of 16, 18.41 with 64, 18.8 with 256; 124 M, 3 workers: 1.765 / 1.728 / 1.702 ms), shorter on short vectors.
-constexpr Items wave_items(int num_tiles, int part_len)
+// Runs are 256 items (of whole tiles: 256 KiB of every stream in the main pass and the server, 512 KiB in the worker
+// quantizer) where that leaves each XCD eight or more of them (1.3 G parameters, 4 workers: 18.97 ms with runs of 16, 18.41
+// with 64, 18.8 with 256; 124 M, 3 workers: 1.765 / 1.728 / 1.702 ms), shorter on short vectors.
+constexpr Items wave_items(const ListShape& s, int turn)
 {
     Items I{};
-    I.parts = (uint32_t)(kTileElems / part_len);
-    while ((int64_t)num_tiles * I.parts > ((int64_t)1 << 26) - 4096) I.parts /= 2;
-    I.part_len = kTileElems / (int)I.parts;
-    I.count = (uint32_t)num_tiles * I.parts;
+    I.cut = cut_tiles(s, turn, ((int64_t)1 << 26) - 4096, 1);
+    I.count = (uint32_t)s.num_tiles * I.cut.parts;
     while (I.run_shift < 8 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
     return I;
 }

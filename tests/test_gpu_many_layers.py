@@ -81,3 +81,14 @@ def test_whole_tiles_where_the_quantizers_pieces_are_longer_than_a_turn(call):
     """2^23 tiles: the worker quantizer's launch then holds four pieces per tile, each two turns of a wavefront.  Most
     tiles are layers of one element; two layers have whole tiles, one of them off the 16-byte grid."""
     _step([3 * T + 700, 1025] + [1] * (1 << 23) + [2 * T + 2600], 1, call, seed=4)
+
+
+@pytest.mark.parametrize("call", ["fused", "calls", "w", "w_calls"])
+@pytest.mark.parametrize("sizes,N", [
+    ([600] * 800 + [3], 2),                                     # three pieces of 256, two of 512, one of 1024
+    ([1023, 513, 1025, 7] * 300, 3),                            # five pieces of 256: one more than a quarter of a tile
+    ([T, 64, 64, 64, 64, 64, 64, 64, 65] * 1100, 1),            # sparse: longer pieces, on and off the 16-byte grid
+    ([T * 2000 + 5] + [100] * 9000, 1),                         # one long layer and many short ones
+])
+def test_pieces_of_short_and_mixed_layers(call, sizes, N):
+    _step(sizes, N, call, seed=len(sizes))

@@ -14,7 +14,7 @@ def _run(tmp_path, body):
                    '#define CHECK(c, ...) do { if (!(c)) { std::puts(#c); std::printf(__VA_ARGS__); std::exit(1); } } while (0)\n'
                    "int main() {\n" + body + "\nreturn 0; }\n")
     inc = os.path.join(ROOT, "paper_2004_14180_amd", "csrc")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", inc, "-o", str(exe), str(src)], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused", "-I", inc, "-o", str(exe), str(src)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
 
@@ -34,29 +34,69 @@ def test_every_layer_has_a_workgroup_in_a_launch_that_fits(tmp_path):
         }""")
 
 
-def test_pieces_cover_every_tile_and_every_workgroup_has_its_own(tmp_path):
-    """Both sides of every size at which tiles are cut into fewer pieces, for the two piece lengths in use (256: the main
-    pass and the server; 512: the worker quantizer, whose turns the kernel repeats over a longer piece)."""
-    _run(tmp_path, """
-    for (int turn : {256, 512}) {
-        uint32_t most = kTileElems / turn, before = most;
-        bool fewer = false;
-        for (long long n = 1; n < kMaxTiles; n = n < 70000 ? n + 1 + n / 50 : n + 997) {
-            const Items I = wave_items((int)n, turn);
-            CHECK(I.parts >= 1 && (long long)I.parts * I.part_len >= kTileElems, "%lld", n);
-            CHECK((long long)(I.parts - 1) * I.part_len < kTileElems && I.part_len % turn == 0, "%lld", n);
-            CHECK(I.count == (unsigned long long)n * I.parts && I.parts <= before, "%lld", n);
-            const unsigned long long blocks = wave_blocks(I);
-            CHECK(blocks >= I.count && blocks * 64 < (1ull << 32), "%lld", n);
-            fewer = fewer || I.parts < most;
-            before = I.parts;
+SHAPES = """
+    // n tiles of `len` elements, and the same behind n / 100 whole ones
+    const int lens[] = {1, 10, 255, 256, 257, 600, 1000, 1024, 1025, 2048, 2049, 4095, 4096};
+    auto shape = [](long long n, int len, bool mixed) {
+        ListShape s{};
+        const long long whole = mixed ? n / 100 : 0;
+        add_tiles(s, whole, kTileElems);
+        add_tiles(s, n - whole, len);
+        return s;
+    };
+    auto next = [](long long n) { return n < 70000 ? n + 1 + n / 20 : n + 9973; };
+"""
+
+
+def test_pieces_cover_every_tile_in_a_launch_that_fits(tmp_path):
+    """For the piece lengths in use (256: the main pass and the server; 512: the worker quantizer, whose turns the kernel
+    repeats over a longer piece; 1024: variant W's first pass), over both sides of every size at which pieces change."""
+    _run(tmp_path, SHAPES + """
+    int fewest = 16, most = 0;
+    for (int len : lens) for (int mixed = 0; mixed < 2; ++mixed)
+        for (long long n = 1; n < kMaxTiles; n = next(n)) {
+            const ListShape s = shape(n, len, mixed);
+            CHECK(s.num_tiles == n && (n < 100 || !mixed || s.longest == kTileElems), "%lld x %d", n, len);
+            for (int turn : {256, 512, 1024}) {
+                const Items I = wave_items(s, turn);
+                const Cut c = turn == 1024 ? moment_cut(s) : I.cut;
+                CHECK(c.parts >= 1 && (long long)c.parts * c.part_len >= s.longest, "%lld x %d, turn %d", n, len, turn);
+                CHECK(((long long)c.parts - 1) * c.part_len < s.longest && c.part_len % turn == 0 && c.part_len <= kTileElems,
+                      "%lld x %d, turn %d", n, len, turn);
+                if (turn == 1024) {
+                    CHECK((unsigned long long)n * c.parts * 256 < (1ull << 32), "%lld x %d", n, len);
+                    continue;
+                }
+                const unsigned long long blocks = wave_blocks(I);
+                CHECK(I.count == (unsigned long long)n * c.parts && blocks >= I.count && blocks * 64 < (1ull << 32),
+                      "%lld x %d, turn %d", n, len, turn);
+                if (len == kTileElems && turn == 256) {
+                    fewest = c.parts < (uint32_t)fewest ? (int)c.parts : fewest;
+                    most = (int)c.parts > most ? (int)c.parts : most;
+                }
+            }
         }
-        const Items last = wave_items((int)kMaxTiles - 1, turn);
-        CHECK(fewer && last.parts < most && last.parts * last.part_len >= kTileElems, "the sizes do not reach fewer pieces");
-    }
-    // every item is some workgroup's, and no two workgroups have the same one
+    CHECK(most == 16 && fewest < 8, "the sizes do not reach fewer pieces");""")
+
+
+def test_no_launch_is_mostly_empty(tmp_path):
+    """Beyond what fills the chip, at most every second wavefront finds nothing to do."""
+    _run(tmp_path, SHAPES + """
+    for (int len : lens) for (int mixed = 0; mixed < 2; ++mixed)
+        for (long long n = 1; n < kMaxTiles; n = next(n))
+            for (int turn : {256, 512}) {
+                const ListShape s = shape(n, len, mixed);
+                const Items I = wave_items(s, turn);
+                int k = 0;
+                while ((256 << k) < I.cut.part_len) ++k;
+                CHECK(I.count <= 2 * s.pieces[k] || s.pieces[k + 1] < kFullChip, "%lld x %d, turn %d", n, len, turn);
+            }""")
+
+
+def test_every_workgroup_has_an_item_of_its_own(tmp_path):
+    _run(tmp_path, SHAPES + """
     for (int n : {1, 3, 7, 8, 9, 63, 64, 127, 129, 1000, 4095, 4096, 4097, 70001, 300007}) {
-        const Items I = wave_items(n, 256);
+        const Items I = wave_items(shape(n, kTileElems, false), 256);
         const uint32_t blocks = wave_blocks(I);
         unsigned char* seen = (unsigned char*)std::calloc(blocks, 1);
         for (uint32_t b = 0; b < blocks; ++b) {
