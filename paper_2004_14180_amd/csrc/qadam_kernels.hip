@@ -1263,9 +1263,9 @@ __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 }
 
 // ---- weight quantizer alone (qadam_weight_quantize) ----------------------------------------------
-// Index of a single-wavefront workgroup of a flat launch (flat_grid): one dimension of a grid holds fewer than 2^32
-// work-items, so a very long vector takes several rows.
-__device__ __forceinline__ int64_t wave_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+// Index of a workgroup of a flat launch (flat_grid): one dimension of a grid holds fewer than 2^32 work-items, so a very
+// long vector takes several rows.
+__device__ __forceinline__ int64_t flat_index() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 struct WeightArgs {
     StepScalars S;
@@ -1283,7 +1283,7 @@ template <int ROUNDING>
 __global__ void __launch_bounds__(64) k_weight_quantize(WeightArgs A)
 {
     const StepScalars& S = A.S;
-    const int64_t gi = 4 * (wave_index() * 64 + threadIdx.x);
+    const int64_t gi = 4 * (flat_index() * 64 + threadIdx.x);
     if (gi >= A.n) return;
     const int nvalid = (int)min((int64_t)4, A.n - gi);
     float xv[4], wi[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wo[4];
@@ -1303,71 +1303,78 @@ struct DequantArgs {
     float inv_two_kx1;
 };
 
-// A single wavefront per 64 E consecutive codes, E per lane (E = 4 for fp32 output, 8 for binary16, so that an output
-// store is always 128 bits and a wavefront's is one contiguous 1 KiB run).  Bound by the memory's write side; more
-// codes per lane and more wavefronts per workgroup only bunch the stores: 124 M codes to binary16 60.7 us with 256
-// threads and four pieces of E per lane; with 64 threads 58.7 with four, 58.6 with two, 57.7 with one.
-template <bool HALF, int CODE_BYTES>
-__global__ void __launch_bounds__(64) k_weight_dequantize(DequantArgs A)
+// A workgroup per THREADS * PIECES * E consecutive codes, E per lane and piece (E = 4 for fp32 output, 8 for binary16, so
+// that an output store is always 128 bits and a wavefront's is one contiguous 1 KiB run).  Bound by the memory's write side
+// on long vectors, by the rate at which workgroups start where the data is in the memory-side cache (decode_shape).
+template <bool HALF, int CODE_BYTES, int THREADS, int PIECES>
+__global__ void __launch_bounds__(THREADS) k_weight_dequantize(DequantArgs A)
 {
     constexpr int E = HALF ? 8 : 4;
-    constexpr int WORDS = E * CODE_BYTES / 4;           // code words per lane: 1, 2 or 4
-    const int64_t i = E * (wave_index() * 64 + threadIdx.x);
-    const bool full = i + E <= A.n;
-    uint32_t w[WORDS];
+    constexpr int WORDS = E * CODE_BYTES / 4;           // code words per lane and piece: 1, 2 or 4
+    const int64_t base = E * (flat_index() * (THREADS * PIECES) + threadIdx.x);
+    uint32_t w[PIECES][WORDS];
 #pragma unroll
-    for (int t = 0; t < WORDS; ++t) w[t] = 0u;
-    const char* src = static_cast<const char*>(A.wcodes) + i * CODE_BYTES;
-    if (full) {
-        if constexpr (WORDS == 1) {
-            w[0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
-        } else if constexpr (WORDS == 2) {
-            const u2 v = __builtin_nontemporal_load(reinterpret_cast<const u2*>(src));
-            w[0] = v.x; w[1] = v.y;
+    for (int k = 0; k < PIECES; ++k) {
+        const int64_t i = base + k * THREADS * E;
+        const char* src = static_cast<const char*>(A.wcodes) + i * CODE_BYTES;
+#pragma unroll
+        for (int t = 0; t < WORDS; ++t) w[k][t] = 0u;
+        if (i + E <= A.n) {
+            if constexpr (WORDS == 1) {
+                w[k][0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
+            } else if constexpr (WORDS == 2) {
+                const u2 v = __builtin_nontemporal_load(reinterpret_cast<const u2*>(src));
+                w[k][0] = v.x; w[k][1] = v.y;
+            } else {
+                const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(src));
+                w[k][0] = v.x; w[k][1] = v.y; w[k][2] = v.z; w[k][3] = v.w;
+            }
         } else {
-            const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(src));
-            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-        }
-    } else {
-        // ragged end of the vector: code by code
+            // ragged end of the vector: code by code
 #pragma unroll
-        for (int t = 0; t < E; ++t) {
-            if (i + t < A.n) {
-                const uint32_t c = CODE_BYTES == 1 ? (uint32_t)(uint8_t)src[t]
-                                                   : (uint32_t)reinterpret_cast<const uint16_t*>(src)[t];
-                w[t * CODE_BYTES / 4] |= c << (8 * ((t * CODE_BYTES) & 3));
+            for (int t = 0; t < E; ++t) {
+                if (i + t < A.n) {
+                    const uint32_t c = CODE_BYTES == 1 ? (uint32_t)(uint8_t)src[t]
+                                                       : (uint32_t)reinterpret_cast<const uint16_t*>(src)[t];
+                    w[k][t * CODE_BYTES / 4] |= c << (8 * ((t * CODE_BYTES) & 3));
+                }
             }
         }
     }
-    float xh[E];
 #pragma unroll
-    for (int t = 0; t < E; ++t) {
-        const uint32_t c = w[t * CODE_BYTES / 4] >> (8 * ((t * CODE_BYTES) & 3));
-        const int j = CODE_BYTES == 1 ? (int)(int8_t)c : (int)(int16_t)c;
-        xh[t] = (float)j * A.inv_two_kx1;
-    }
-    if constexpr (HALF) {
-        __half* out = static_cast<__half*>(A.xhat) + i;
-        if (full) {
-            u4 v;
-            v.x = (uint32_t)__half_as_ushort(__float2half_rn(xh[0])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[1])) << 16);
-            v.y = (uint32_t)__half_as_ushort(__float2half_rn(xh[2])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[3])) << 16);
-            v.z = (uint32_t)__half_as_ushort(__float2half_rn(xh[4])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[5])) << 16);
-            v.w = (uint32_t)__half_as_ushort(__float2half_rn(xh[6])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[7])) << 16);
-            __builtin_nontemporal_store(v, reinterpret_cast<u4*>(out));
-        } else {
+    for (int k = 0; k < PIECES; ++k) {
+        const int64_t i = base + k * THREADS * E;
+        const bool full = i + E <= A.n;
+        float xh[E];
 #pragma unroll
-            for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = __float2half_rn(xh[t]);
+        for (int t = 0; t < E; ++t) {
+            const uint32_t c = w[k][t * CODE_BYTES / 4] >> (8 * ((t * CODE_BYTES) & 3));
+            const int j = CODE_BYTES == 1 ? (int)(int8_t)c : (int)(int16_t)c;
+            xh[t] = (float)j * A.inv_two_kx1;
         }
-    } else {
-        float* out = static_cast<float*>(A.xhat) + i;
-        if (full) {
-            f4 v;
-            v.x = xh[0]; v.y = xh[1]; v.z = xh[2]; v.w = xh[3];
-            __builtin_nontemporal_store(v, reinterpret_cast<f4*>(out));
-        } else {
+        if constexpr (HALF) {
+            __half* out = static_cast<__half*>(A.xhat) + i;
+            if (full) {
+                u4 v;
+                v.x = (uint32_t)__half_as_ushort(__float2half_rn(xh[0])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[1])) << 16);
+                v.y = (uint32_t)__half_as_ushort(__float2half_rn(xh[2])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[3])) << 16);
+                v.z = (uint32_t)__half_as_ushort(__float2half_rn(xh[4])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[5])) << 16);
+                v.w = (uint32_t)__half_as_ushort(__float2half_rn(xh[6])) | ((uint32_t)__half_as_ushort(__float2half_rn(xh[7])) << 16);
+                __builtin_nontemporal_store(v, reinterpret_cast<u4*>(out));
+            } else {
 #pragma unroll
-            for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = xh[t];
+                for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = __float2half_rn(xh[t]);
+            }
+        } else {
+            float* out = static_cast<float*>(A.xhat) + i;
+            if (full) {
+                f4 v;
+                v.x = xh[0]; v.y = xh[1]; v.z = xh[2]; v.w = xh[3];
+                __builtin_nontemporal_store(v, reinterpret_cast<f4*>(out));
+            } else {
+#pragma unroll
+                for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = xh[t];
+            }
         }
     }
 }
@@ -1925,12 +1932,10 @@ hipError_t launch_server_apply_w(const Launch& L, const StepScalars& S, const Wo
     return hipGetLastError();
 }
 
-// single-wavefront workgroups of `per_wave` consecutive elements each
-static dim3 flat_grid(int64_t n, int per_wave)
+static dim3 flat_grid(int64_t n, int threads, int per_block)
 {
-    constexpr int64_t kRow = (int64_t)1 << 25;
-    const int64_t waves = (n + per_wave - 1) / per_wave;
-    return dim3((unsigned)(waves < kRow ? waves : kRow), (unsigned)((waves + kRow - 1) / kRow));
+    const FlatGrid g = flat_blocks(n, threads, per_block);
+    return dim3(g.x, g.y);
 }
 
 hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const float* x, float* werr, void* wcodes)
@@ -1938,27 +1943,46 @@ hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const f
     if (L.num_params == 0) return hipSuccess;
     WeightArgs A;
     A.S = S; A.x = x; A.werr = werr; A.wcodes = wcodes; A.n = L.num_params;
-    const dim3 grid = flat_grid(L.num_params, 256), block(64);
+    const dim3 grid = flat_grid(L.num_params, 64, 256), block(64);
     if (S.rounding == 0) hipLaunchKernelGGL(k_weight_quantize<0>, grid, block, 0, L.stream, A);
     else hipLaunchKernelGGL(k_weight_quantize<1>, grid, block, 0, L.stream, A);
     return hipGetLastError();
+}
+
+template <bool HALF, int CODE_BYTES, int THREADS, int PIECES>
+static void launch_decoder(const Launch& L, const DequantArgs& A)
+{
+    hipLaunchKernelGGL((k_weight_dequantize<HALF, CODE_BYTES, THREADS, PIECES>),
+                       flat_grid(A.n, THREADS, THREADS * PIECES * (HALF ? 8 : 4)), dim3(THREADS), 0, L.stream, A);
+}
+
+// Workgroups of 256 threads with four pieces per lane where codes and output stay in the memory-side cache, else smaller
+// ones.  us, 256 x 4 / the other, outputs in the cache where they fit: int8 to fp32 (256 x 2) 8 M 7.4 / 7.9, 11.7 M
+// 9.9 / 10.7, 24 M 20.4 / 19.4, 124 M 115 / 94, 400 M 372 / 302; the others (64 x 1) int8 to binary16 2 M 3.7 / 2.8, 4 M
+// 3.7 / 3.9, 11.7 M 6.2 / 8.0, 40 M 20.2 / 21.2, 124 M 60.3 / 59.0, 400 M 197 / 181; int16 to fp32 1 M 2.8 / 2.7, 4 M
+// 4.0 / 6.0, 11.7 M 11.7 / 13.5, 40 M 38.8 / 38.6, 400 M 406 / 354; int16 to binary16 4 M 3.8 / 4.0, 8 M 5.1 / 6.1, 11.7 M
+// 8.7 / 8.2, 400 M 252 / 237.
+static bool decode_in_cache(int64_t n, int code_bytes, bool half)
+{
+    const int64_t bytes = n * (code_bytes + (half ? 2 : 4));
+    return bytes >= (int64_t)8 << 20 && bytes <= (int64_t)(half && code_bytes == 2 ? 40 : 160) << 20;
 }
 
 hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const void* wcodes, void* xhat, bool half)
 {
     if (L.num_params == 0) return hipSuccess;
     DequantArgs A;
-    A.wcodes = wcodes; A.xhat = xhat; A.n = L.num_params; A.wcode_bytes = S.wcode_bytes;
+    A.wcodes = wcodes; A.xhat = xhat; A.n = L.num_params;
     union { uint32_t u; float f; } cv;
     cv.u = (uint32_t)(127 - S.k_x - 1) << 23;
     A.inv_two_kx1 = cv.f;
-    const dim3 grid = flat_grid(L.num_params, 64 * (half ? 8 : 4)), block(64);
+    const bool cached = decode_in_cache(A.n, S.wcode_bytes, half);
     if (S.wcode_bytes == 1) {
-        if (half) hipLaunchKernelGGL((k_weight_dequantize<true, 1>), grid, block, 0, L.stream, A);
-        else hipLaunchKernelGGL((k_weight_dequantize<false, 1>), grid, block, 0, L.stream, A);
+        if (half) cached ? launch_decoder<true, 1, 256, 4>(L, A) : launch_decoder<true, 1, 64, 1>(L, A);
+        else cached ? launch_decoder<false, 1, 256, 4>(L, A) : launch_decoder<false, 1, 256, 2>(L, A);
     } else {
-        if (half) hipLaunchKernelGGL((k_weight_dequantize<true, 2>), grid, block, 0, L.stream, A);
-        else hipLaunchKernelGGL((k_weight_dequantize<false, 2>), grid, block, 0, L.stream, A);
+        if (half) cached ? launch_decoder<true, 2, 256, 4>(L, A) : launch_decoder<true, 2, 64, 1>(L, A);
+        else cached ? launch_decoder<false, 2, 256, 4>(L, A) : launch_decoder<false, 2, 64, 1>(L, A);
     }
     return hipGetLastError();
 }

@@ -101,6 +101,18 @@ constexpr uint32_t wave_blocks(const Items& I)
     return (I.count + round - 1) / round * round;
 }
 
+// ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
+// Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
+struct FlatGrid {
+    uint32_t x, y;
+};
+
+constexpr FlatGrid flat_blocks(int64_t n, int threads, int per_block)
+{
+    const int64_t row = ((int64_t)1 << 31) / threads, blocks = (n + per_block - 1) / per_block;
+    return {(uint32_t)(blocks < row ? blocks : row), (uint32_t)((blocks + row - 1) / row)};
+}
+
 // ---- folding the maxima of the layers (k_reduce_scales, k_reduce_scales_list) ----------------------------------------
 constexpr int kReduceThreads = 1024;
 constexpr int kListLayers = kReduceThreads / 64;    // layers per workgroup of k_reduce_scales_list, one per wavefront

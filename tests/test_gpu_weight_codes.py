@@ -35,3 +35,20 @@ def test_lengths(n, k_x, weight_ef, rounding):
     assert np.array_equal(half[:n].cpu().numpy(), want["xhat"].astype(np.float16))
     assert (wc[n:] == 77).all() and (err[n:] == 7).all() and (full[n:] == 7).all() and (half[n:] == 7).all()
     q.close()
+
+
+@pytest.mark.parametrize("k_x,half", [(6, False), (6, True), (14, False), (14, True)])
+def test_decoder_each_side_of_its_rule(k_x, half):
+    """The vector lengths on both sides of the two lines between the decoder's launch shapes (8 MiB, and 160 or 40 MiB of
+    codes and output), each with a ragged end."""
+    size = (1 if k_x <= 6 else 2) + (2 if half else 4)
+    for line in (8 << 20, (40 if half and k_x > 6 else 160) << 20):
+        for n in (line // size, line // size + 1, line // size + 4099):
+            q = QAdam(configs(k_x=k_x)[0], [0, n], 1)
+            wt, top = (torch.int8, 64) if k_x <= 6 else (torch.int16, 1 << 14)
+            wc = torch.randint(-top, top + 1, (n,), dtype=wt, device="cuda")
+            out = torch.full((n + 16,), 7.0, dtype=torch.float16 if half else torch.float32, device="cuda")
+            (q.weight_dequantize_f16 if half else q.weight_dequantize)(wc, out[:n])
+            want = (wc.to(torch.float32) * 2.0 ** -(k_x + 1)).to(out.dtype)      # exact, then one rounding
+            assert torch.equal(out[:n], want) and (out[n:] == 7).all(), n
+            q.close()

@@ -106,3 +106,15 @@ def test_every_workgroup_has_an_item_of_its_own(tmp_path):
         }
         std::free(seen);
     }""")
+
+
+def test_flat_launches_cover_the_longest_vector(tmp_path):
+    """Vectors have up to 2^36 elements (tiles of 4096 below 2^24); x counts work-items below 2^32, y stays below 2^16."""
+    _run(tmp_path, """
+    for (int threads : {64, 256}) for (int per : {256, 512, 2048, 4096, 8192})
+        for (long long n : {1ll, 255ll, 256ll, 257ll, (1ll << 31) - 1, (1ll << 33) - 1, 1ll << 33, (1ll << 33) + 1, (1ll << 36) - 1}) {
+            const FlatGrid g = flat_blocks(n, threads, per);
+            const unsigned long long blocks = (unsigned long long)g.x * g.y;
+            CHECK(g.x >= 1 && (unsigned long long)g.x * threads < (1ull << 32) && g.y < (1u << 16), "%lld", n);
+            CHECK(blocks * per >= (unsigned long long)n && blocks * per < n + (unsigned long long)g.x * per, "%lld", n);
+        }""")
