@@ -23,6 +23,7 @@ struct qadam_ctx {
     Tile*     d_tiles;
     int32_t   num_tiles;
     ListShape shape;
+    int32_t   longest_layer;    // tiles of the longest layer
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
     uint32_t* d_tile_max;       // [num_workers][num_tiles]
@@ -115,7 +116,8 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.tile_max = h->d_tile_max; L.seg_tile_begin = h->d_seg_tile_begin; L.tile_sum = h->d_tile_sum;
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
-    L.num_tiles = h->num_tiles; L.shape = h->shape; L.num_segments = h->num_segments;
+    L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
+    L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
     return L;
@@ -295,6 +297,8 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             tiles.push_back(t);
             add_tiles(h->shape, 1, t.len);
         }
+        const int32_t layer_tiles = (int32_t)tiles.size() - seg_tile_begin[l];
+        if (layer_tiles > h->longest_layer) h->longest_layer = layer_tiles;
         word_off += seg_words;
     }
     h->code_words = word_off;

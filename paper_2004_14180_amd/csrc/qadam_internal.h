@@ -71,6 +71,7 @@ struct Launch {
     const int32_t* seg_tile_begin;  // device, [num_segments + 1]: first tile of every segment
     int32_t     num_tiles;
     ListShape   shape;
+    int32_t     longest_layer;  // tiles of the longest layer
     int32_t     num_segments;
     int64_t     num_params;
     double*     tile_sum;   // device, [num_tiles]: per-tile partial sums of the norm diagnostic

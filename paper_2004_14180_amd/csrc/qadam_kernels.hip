@@ -1757,26 +1757,16 @@ static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S,
     A.sample_stride = kSampleStride;
 }
 
-// On a short vector the quantizing kernel folds the maxima itself: its wavefronts are all on the chip at once and the
-// launch of k_reduce_scales (2.5 us) costs more than one more load, or a few, at the head of each.  Beyond that every
-// wavefront pays again: 4 workers of 2^19 elements 35.3 us per step with the launch, 32.8 without; 2^20 35.3 / 32.8;
-// 2^21 47.7 / 55.4; 16 workers of 2^19 79.9 / 77.4, of 2^20 79.9 / 85.6; one worker's call in a row of four, 2^21
-// elements, 23.8 / 21.6.
-static bool fold_in_quantizer(int num_tiles, int num_workers)
+static bool fold_in_quantizer(const Launch& L, int num, int max_per_tile)
 {
-    return num_tiles <= 128 || (int64_t)num_tiles * num_workers <= 1024;
-}
-
-static bool fold_in_quantizer(const Launch& L, int num_workers)
-{
-    return fold_in_quantizer(L.num_tiles, num_workers) && !L.empty_layers;
+    return !L.empty_layers && fold_in_quantizer(L.num_tiles, L.longest_layer * max_per_tile, num);
 }
 
 static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
 {
     Fold F;
     F.row = max_row(L); F.per_tile = max_per_tile;
-    F.tile_max = fold_in_quantizer(L, num) ? L.tile_max + (size_t)worker * F.row : nullptr;
+    F.tile_max = fold_in_quantizer(L, num, max_per_tile) ? L.tile_max + (size_t)worker * F.row : nullptr;
     F.seg_tile_begin = L.seg_tile_begin;
     F.num_segments = L.num_segments;
     F.inv_scales = L.inv_scales + (size_t)worker * L.num_segments;
@@ -1805,7 +1795,7 @@ static bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)512
 hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
                                 int max_per_tile)
 {
-    if (L.num_segments == 0 || num == 0 || fold_in_quantizer(L, num)) return hipSuccess;
+    if (L.num_segments == 0 || num == 0 || fold_in_quantizer(L, num, max_per_tile)) return hipSuccess;
     ScaleArgs A;
     fill_scale_args(A, L, S, W, first_worker);
     A.max_per_tile = max_per_tile;
@@ -2161,7 +2151,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
     std::memset(&F, 0, sizeof F);
     F.row = num_tiles; F.per_tile = 1; F.num_segments = 1;
     F.inv_scales = inv_scale; F.err_bound = err_bound; F.bound_factor = residual_bound_factor(S);
-    if (num_tiles > 0 && fold_in_quantizer(num_tiles, 1)) {
+    if (num_tiles > 0 && fold_in_quantizer(num_tiles, num_tiles, 1)) {
         F.tile_max = tile_max;
     } else {
         ScaleArgs R;

@@ -133,4 +133,16 @@ constexpr unsigned reduce_blocks(int num_segments, int num)
                                              : (unsigned)num_segments;
 }
 
+// Whether the quantizing kernel folds the maxima itself: every wavefront those of its layer (`longest`: most maxima of one
+// layer) for each of its workers, one after the other, which saves the launch of k_reduce_scales, about 2.5 us with its gap.
+// GPU time of a step, us, with the launch / folded.  One layer, one worker: 512 tiles 26.1 / 24.5, 768 36.5 / 35.6, 1024
+// 47.0 / 50.3; two workers: 192 tiles 15.7 / 15.1, 384 27.2 / 24.2, 512 33.7 / 34.4; four: 64 13.3 / 12.8, 128 16.2 / 17.6,
+// 256 26.4 / 27.9; sixteen: 16 24.1 / 29.2.  Eight layers, one worker: 1024 tiles (128 each) 46.1 / 41.6; 64 layers of 4
+// tiles, four workers 26.6 / 25.9.  Four maxima per tile (variant W), one layer, one worker: 128 tiles (512) 12.7 / 12.2,
+// 192 (768) 14.0 / 14.7, 512 26.1 / 33.2, 1024 46.0 / 69.0.  One worker's call: 512 tiles 14.4 / 14.3, 1024 20.8 / 24.9.
+constexpr bool fold_in_quantizer(int num_tiles, int longest, int num_workers)
+{
+    return num_workers <= 10 && longest <= (1536 >> num_workers) && (int64_t)num_tiles * num_workers <= 1024;
+}
+
 }  // namespace qadam

@@ -24,12 +24,30 @@ def test_each_side_of_the_fold(N, tiles, fused):
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
+@pytest.mark.parametrize("N,longest,others", [(1, 768, 0), (1, 769, 0), (1, 700, 324), (1, 700, 325), (2, 384, 0), (2, 385, 0),
+                                              (4, 96, 160), (4, 97, 0), (10, 1, 101), (10, 1, 102), (11, 1, 50)])
+@pytest.mark.parametrize("fused", [True, False])
+def test_each_side_of_the_longest_folded_layer(N, longest, others, fused):
+    """The limits on the longest layer's tiles (halved with every worker more) and on tiles times workers."""
+    sizes = [3] + [T - 1] * (others - 1) + [longest * T - 6] if others else [longest * T - 6]
+    rep, st = _custom(sizes, N, 2, seed=longest + N, fused=fused, trust=2)
+    assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+
+
 @pytest.mark.parametrize("N,tiles", [(2, 128), (8, 129), (4, 255), (4, 257)])
 def test_worker_moments_each_side_of_the_fold(N, tiles):
     """Variant W leaves four maxima per tile: ends of a layer in each quarter of its last tile."""
+    _worker_moments(N, tiles, [(tiles - 5) * T, 1000, T + 1025, 3, 2049])
+
+
+@pytest.mark.parametrize("N,tiles", [(1, 192), (1, 193), (2, 96), (2, 97), (4, 24), (4, 25)])
+def test_worker_moments_each_side_of_the_longest_folded_layer(N, tiles):
+    _worker_moments(N, tiles, [tiles * T, 1000, T + 1025, 3, 2049])
+
+
+def _worker_moments(N, tiles, sizes):
     from oracle import qadam_oracle as oracle
     gcfg, ocfg = configs()
-    sizes = [(tiles - 5) * T, 1000, T + 1025, 3, 2049]
     seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     P, rng = int(seg[-1]), np.random.default_rng(tiles)
     f32 = lambda s: (rng.standard_normal(P) * s).astype(np.float32)  # noqa: E731
@@ -54,7 +72,7 @@ def test_worker_moments_each_side_of_the_fold(N, tiles):
 
 
 @pytest.mark.parametrize("k_g", [0, 2, 6])
-@pytest.mark.parametrize("n", [1, 33, 255, 257, 4095, 4097, 16383, 16384, 16385, 128 * T + 1, 1024 * T, 1024 * T + 1])
+@pytest.mark.parametrize("n", [1, 33, 255, 257, 4095, 4097, 16383, 16384, 16385, 128 * T + 1, 768 * T, 768 * T + 1, 1024 * T, 1024 * T + 1])
 def test_segment_call(n, k_g):
     from oracle import qadam_oracle as oracle
     rng = np.random.default_rng(n)
