@@ -1,8 +1,8 @@
 """GPU parity: the HIP library (through its C boundary) against the CPU oracle, element by element,
 on the seeded synthetic workloads and on edge cases.  Sizes are chosen so the oracle finishes in
 seconds while every tile shape occurs: full 4096-element tiles, ragged tails, segments that start
-off a 16-byte boundary (dword-aligned wide accesses), tiny and empty segments, small layers (one
-workgroup, no scale pass) and layers whose tile maxima the quantizing kernel folds itself."""
+off a 16-byte boundary (dword-aligned wide accesses), tiny and empty segments, and vectors whose tile maxima
+the quantizing kernel folds itself."""
 import numpy as np
 import pytest
 import torch
@@ -95,7 +95,7 @@ def test_every_misalignment_and_code_width(shift, cfgkw):
 @pytest.mark.parametrize("seed", range(24))
 def test_random_layer_lists_and_settings(seed):
     """Seeded random layer lists (empty, tiny, odd and tile-multiple sizes, so every alignment and every
-    kind of layer -- small, folded-by-the-quantizer, large -- occurs in changing order) under random
+    way to the scales -- folded by the quantizer, by a launch of their own -- occurs in changing order) under random
     settings of N, k_g, k_x, rounding, weight feedback, fused or separate calls, filtered scale pass."""
     rng = np.random.default_rng(1000 + seed)
     pool = [0, 1, 2, 3, 5, 31, 32, 33, 64, 255, 1000, 1001, 4095, 4096, 4097, 8192, 12289, 16384, 16385, 20000,
