@@ -167,11 +167,12 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step,
  * library runs on holds until the process ends; n > QADAM_NOALLOC_MAX_ELEMS returns QADAM_ERANGE.  The array's
  * address on the current device is looked up once per device: by qadam_init, else by the first call of this
  * function on that device (only that first call should stay outside a graph capture).
- * ALL calls on one GPU share the array: two calls that may overlap on one GPU (different streams without an
+ * Calls on one GPU share the array: two calls that may overlap on one GPU (different streams without an
  * ordering event, or two host threads on different streams) race and give wrong results; calls on one stream
- * are ordered and need nothing.  Nothing in the array has to be cleared between calls (every word is written
+ * are ordered and need nothing.  (Today a segment of up to 16384 elements does not touch the array; do not build
+ * on it.)  Nothing in the array has to be cleared between calls (every word is written
  * before it is read).  A non-finite ||g+e||_inf is visible in scale_dev (codes are then all zero); there is no
- * status word to read for this call.  Enqueues three kernels on `stream`; does not synchronise. */
+ * status word to read for this call.  Enqueues one to three kernels on `stream`; does not synchronise. */
 #define QADAM_NOALLOC_MAX_ELEMS (1 << 28)
 int qadam_quantize_segment_noalloc(int32_t k_g, int64_t n, const float* grad_dev, float* err_dev,
                                    void* codes_dev, float* scale_dev, void* stream);

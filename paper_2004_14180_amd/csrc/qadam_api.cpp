@@ -26,7 +26,7 @@ struct qadam_ctx {
     int32_t   longest_layer;    // tiles of the longest layer
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
-    uint32_t* d_tile_max;       // [num_workers][num_tiles]
+    uint32_t* d_tile_max;       // [num_workers][num_tiles * pieces of a tile in variant W's first pass]
     int32_t*  d_seg_tile_begin; // [num_segments + 1]
     double*   d_tile_sum;       // [num_tiles]
     float*    d_err_bound;      // [num_workers][num_segments]

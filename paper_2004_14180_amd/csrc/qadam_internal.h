@@ -67,7 +67,8 @@ struct ServerPtrs {
 struct Launch {
     const Tile* tiles;      // device
     float*      inv_scales; // device, [num_workers][num_segments]: 1/s where the fast quotient is safe, else 0
-    uint32_t*   tile_max;   // device, [num_workers][num_tiles]: per-tile max |p| as a bit pattern
+    uint32_t*   tile_max;   // device, [num_workers][num_tiles * moment_parts]: max |p| per tile (variant W: per piece of a
+                            // tile) as a bit pattern; a worker's row begins at the same place in every call
     const int32_t* seg_tile_begin;  // device, [num_segments + 1]: first tile of every segment
     int32_t     num_tiles;
     ListShape   shape;
@@ -89,7 +90,7 @@ inline int moment_parts(const Launch& L) { return (int)moment_cut(L.shape).parts
 
 // Launchers (defined in qadam_kernels.hip).  `first_worker`/`num` select the workers a launch covers.
 // scales in two stages without atomics: per-tile maxima, then one workgroup per (worker, layer)
-// reduces its tiles and also writes the reciprocal used by the fast quotient
+// (of long lists: per 16 layers) reduces its tiles and also writes the reciprocal used by the fast quotient
 hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
                                 int max_per_tile = 1);

@@ -4,20 +4,20 @@
 //
 // Everything here is a streaming pass bound by HBM bandwidth: no contraction, no MFMA.  The design
 // rules are the ones that matter for that regime on CDNA4:
-//   * 64-wide wavefronts, 256-thread workgroups; a lane owns 4 consecutive fp32 values so every
-//     global access is a 128-bit load/store and a wavefront touches 1 KiB of contiguous memory;
+//   * 64-wide wavefronts; a lane owns 4 consecutive fp32 values so every global access is a 128-bit
+//     load/store and a wavefront touches 1 KiB of contiguous memory;
 //     all buffers are touched once per pass, so loads and stores carry the non-temporal hint, except where the next
 //     pass finds the data in the memory-side cache (keep_scanned, keep_parked);
 //   * work is cut along tiles (<= 4096 elements of one layer), so all per-layer quantities (scales, code
 //     offsets) are wave-uniform and live in scalar registers;
-//   * the main pass, the worker quantizer and the server run as workgroups of ONE wavefront each, which drift
-//     apart and so mix their reads and writes (see Items); the loads of a group of workers are issued together
-//     before any arithmetic;
+//   * the scale pass and variant W's first pass run as 256-thread workgroups; the main pass, both quantizers and
+//     the server as workgroups of ONE wavefront each, which drift apart and so mix their reads and writes (see
+//     Items); the loads of a group of workers are issued together before any arithmetic;
 //   * the per-layer scale is a max over |g+e|: lanes reduce with integer max on the bit pattern
 //     (non-negative floats order like integers; NaN/Inf sort above every finite value and so
 //     surface in the scale), wavefront reduction by cross-lane shuffles, LDS across the four
 //     wavefronts, one plain store of the tile's maximum; the tile maxima of a layer are folded by a
-//     second small kernel, or on short vectors by the quantizing wavefronts themselves.  No atomics: thousands
+//     second small kernel, or where they are few by the quantizing wavefronts themselves.  No atomics: thousands
 //     of workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole pass;
 //   * a segment that starts off the 16-byte grid keeps the same lane-to-element mapping (the codes are
 //     anchored at the segment start) and moves its data with dword-aligned 128-bit accesses;
@@ -2132,8 +2132,8 @@ hipError_t noalloc_prepare()
     return scratch_for_current_device(&p);
 }
 
-// The three launches of qadam_worker_quantize for worker 0 of a one-segment vector of n elements,
-// with tile records computed in the kernels and the scratch rows taken from the static array.
+// qadam_worker_quantize for worker 0 of a one-segment vector of n elements: one launch up to kSegmentElems, beyond that
+// its two or three, with tile records computed in the kernels and the scratch rows taken from the static array.
 // Nothing of the array has to start at zero: every tile maximum, the reciprocal and the bound are
 // written before they are read, and the status word is only ever OR-ed into and never read here.
 hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float* grad, float* err, uint32_t* codes,

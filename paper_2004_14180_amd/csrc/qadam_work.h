@@ -64,8 +64,9 @@ constexpr Cut moment_cut(const ListShape& s) { return cut_tiles(s, 1024, kMaxTil
 // (the main pass, the worker quantizer, the server): every piece of a tile is one workgroup.  Wavefronts that share a
 // workgroup start together and then load and store in step, and the next four start when the last of them has ended; on
 // their own they drift apart, so reads and writes mix, and the workgroups in flight cover a narrower stretch of each of
-// the 2N+4 read and N+5 written streams (main pass with four wavefronts per workgroup -> one: 11.7 M parameters, 4 workers
-// 204 -> 172 us; 124 M, 8 workers 3.29 -> 3.04 ms; 1.3 G, 4 workers 19.5 -> 18.4 ms).
+// the 2N+4 read and N+5 written streams (whole step on the same buffers, workgroups of four wavefronts tile by tile -> of
+// one, with the scale paths that came with them: 11.7 M parameters, 4 workers 264 -> 215 us; 124 M, 8 workers 4.12 ->
+// 3.84 ms; 1.3 G, 4 workers 22.7 -> 21.3 ms).
 //
 // Workgroups go to the eight XCDs in turn.  item_of gives the workgroups of one XCD runs of consecutive items, so
 // that the pieces of a line of packed codes, which neighbouring items write, meet in one L2.
@@ -83,8 +84,10 @@ constexpr uint32_t item_of(const Items& I, uint32_t block)
 }
 
 // Runs are 256 items (of whole tiles: 256 KiB of every stream in the main pass and the server, 512 KiB in the worker
-// quantizer) where that leaves each XCD eight or more of them (1.3 G parameters, 4 workers: 18.97 ms with runs of 16, 18.41
-// with 64, 18.8 with 256; 124 M, 3 workers: 1.765 / 1.728 / 1.702 ms), shorter on short vectors.
+// quantizer) where that leaves each XCD eight or more of them, shorter on short vectors.  Runs of 16 / 64 / 256 items, ms per
+// step on the same buffers (medians of 9 turns within 1 %): 124 M parameters, 8 workers 4.00 / 3.88 / 3.83, 3 workers off
+// the grid 2.30 / 2.22 / 2.24; 1.3 G, 4 workers 22.3 / 21.6 / 21.9; 2^28, 16 workers 14.2 / 14.3 / 15.3 where its buffers
+// lay in that run, and 14.3 with 256 where they lay in another.
 constexpr Items wave_items(const ListShape& s, int turn)
 {
     Items I{};
