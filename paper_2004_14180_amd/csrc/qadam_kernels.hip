@@ -521,6 +521,7 @@ __device__ __forceinline__ uint32_t wave_item(const Items& I) { return item_of(I
 struct AmaxArgs {
     const Tile* tiles;
     int num_tiles;
+    Items items;            // k_amax<true>: one tile each
     const float* grad[QADAM_MAX_WORKERS];
     const float* err[QADAM_MAX_WORKERS];
     uint32_t* tile_max;     // rows of `row` maxima, one row per worker
@@ -895,7 +896,13 @@ __device__ __forceinline__ uint32_t amax_tile(const float* __restrict__ g, const
 template <bool KEEP>
 __global__ void __launch_bounds__(kBlockThreads) k_amax(AmaxArgs A)
 {
-    const int ti = A.tile_list ? A.tile_list[blockIdx.x] : (int)blockIdx.x;
+    int ti = (int)blockIdx.x;
+    if (KEEP) {
+        ti = (int)wave_item(A.items);
+        if (ti >= A.num_tiles) return;
+    } else if (A.tile_list) {
+        ti = A.tile_list[blockIdx.x];
+    }
     const Tile t = tile_at(A.tiles, ti, A.seg_len, 0);
     const int w = A.first_worker + blockIdx.y;
     const float* g = A.grad[w];
@@ -1852,15 +1859,23 @@ hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int f
     return hipGetLastError();
 }
 
+static void launch_scan(AmaxArgs& A, const ListShape& shape, int64_t n, int num, hipStream_t stream)
+{
+    A.items = scan_items(shape);
+    if (keep_scanned(n, num) && scan_fits(A.items)) {
+        hipLaunchKernelGGL(k_amax<true>, dim3(wave_blocks(A.items), num), dim3(kBlockThreads), 0, stream, A);
+    } else {
+        hipLaunchKernelGGL(k_amax<false>, dim3(A.num_tiles, num), dim3(kBlockThreads), 0, stream, A);
+    }
+}
+
 hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
     (void)S;
     if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
-    const dim3 grid(L.num_tiles, num), block(kBlockThreads);
-    if (keep_scanned(L.num_params, num)) hipLaunchKernelGGL(k_amax<true>, grid, block, 0, L.stream, A);
-    else hipLaunchKernelGGL(k_amax<false>, grid, block, 0, L.stream, A);
+    launch_scan(A, L.shape, L.num_params, num, L.stream);
     return hipGetLastError();
 }
 
@@ -2154,15 +2169,16 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
     float* err_bound = reinterpret_cast<float*>(sc + kNoallocMaxTiles + 1);
     uint32_t* status = sc + kNoallocMaxTiles + 2;
 
+    ListShape shape{};
     if (num_tiles > 0) {
+        add_tiles(shape, num_tiles - 1, kTileElems);
+        add_tiles(shape, 1, (int)(n - (int64_t)(num_tiles - 1) * kTileElems));
         AmaxArgs A;
         std::memset(&A, 0, sizeof A);
         A.tiles = nullptr; A.num_tiles = num_tiles; A.seg_len = n;
         A.grad[0] = grad; A.err[0] = err;
         A.tile_max = tile_max; A.row = num_tiles; A.first_worker = 0; A.num_segments = 1; A.status = status;
-        const dim3 grid(num_tiles, 1), block(kBlockThreads);
-        if (keep_scanned(n, 1)) hipLaunchKernelGGL(k_amax<true>, grid, block, 0, stream, A);
-        else hipLaunchKernelGGL(k_amax<false>, grid, block, 0, stream, A);
+        launch_scan(A, shape, n, 1, stream);
     }
     Fold F;
     std::memset(&F, 0, sizeof F);
@@ -2187,9 +2203,6 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
         W.status = status; W.S = S;
         W.grad = grad; W.err = err; W.codes = codes; W.scales = scale_out; W.fold = F;
         W.worker = 0;
-        ListShape shape{};
-        add_tiles(shape, num_tiles - 1, kTileElems);
-        add_tiles(shape, 1, (int)(n - (int64_t)(num_tiles - 1) * kTileElems));
         W.items = wave_items(shape, kQuantizeElems);
         launch_quantizer(W, stream);
     }

@@ -104,6 +104,23 @@ constexpr uint32_t wave_blocks(const Items& I)
     return (I.count + round - 1) / round * round;
 }
 
+// Tiles of the scale pass, a workgroup each, on the XCD whose wavefronts quantize them (the worker quantizer's and the main
+// pass's runs are the same elements where they are short enough to matter): what the pass leaves in an L2 is then found
+// there.  us, tiles round the XCDs in turn / this way: one worker's call, 128 tiles 8.5 / 7.3, 512 12.4 / 10.5, 1024
+// 20.1 / 15.2, 2048 33.5 / 32.2; step of 4 workers, 256 tiles 26.3 / 22.7, 512 47.7 / 45.0, 1024 85.5 / 84.0, 2048 158 / 157.
+constexpr Items scan_items(const ListShape& s)
+{
+    const Items q = wave_items(s, 512);
+    Items I{};
+    I.cut = Cut{1, kTileElems};
+    I.count = (uint32_t)s.num_tiles;
+    while ((q.cut.parts << (I.run_shift + 1)) <= (1u << q.run_shift)) ++I.run_shift;
+    return I;
+}
+
+// one dimension of a launch holds fewer than 2^32 work-items
+constexpr bool scan_fits(const Items& I) { return (uint64_t)wave_blocks(I) * 256 < ((uint64_t)1 << 32); }
+
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
 // Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
 struct FlatGrid {

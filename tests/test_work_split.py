@@ -108,6 +108,34 @@ def test_every_workgroup_has_an_item_of_its_own(tmp_path):
     }""")
 
 
+def test_scale_pass_has_a_workgroup_for_every_tile(tmp_path):
+    """And the tile's workgroup is on the XCD of the wavefronts that quantize it, where those of one tile are on one."""
+    _run(tmp_path, SHAPES + """
+    for (int n : {1, 7, 8, 16, 17, 127, 128, 129, 512, 1000, 4095, 4097, 70001}) {
+        const ListShape s = shape(n, kTileElems, false);
+        const Items I = scan_items(s), q = wave_items(s, 512), f = wave_items(s, 256);
+        const uint32_t blocks = wave_blocks(I);
+        CHECK(scan_fits(I) && I.count == (uint32_t)n, "%d", n);
+        unsigned char* seen = (unsigned char*)std::calloc(blocks, 1);
+        int* xcd = (int*)std::calloc(n, sizeof(int));
+        for (uint32_t b = 0; b < blocks; ++b) {
+            const uint32_t tile = item_of(I, b);
+            CHECK(tile < blocks && !seen[tile], "%d", n);
+            seen[tile] = 1;
+            if (tile < I.count) xcd[tile] = (int)(b & 7);
+        }
+        for (const Items& w : {q, f})
+            for (uint32_t b = 0; b < wave_blocks(w); ++b) {
+                const uint32_t item = item_of(w, b);
+                if (item < w.count && n >= 128 && n <= 2048)
+                    CHECK(xcd[item / w.cut.parts] == (int)(b & 7), "%d tiles, item %u", n, item);
+            }
+        std::free(seen);
+        std::free(xcd);
+    }
+    CHECK(!scan_fits(scan_items(shape(kMaxTiles - 1, 1, false))), "the largest list");""")
+
+
 def test_flat_launches_cover_the_longest_vector(tmp_path):
     """Vectors have up to 2^36 elements (tiles of 4096 below 2^24); x counts work-items below 2^32, y stays below 2^16."""
     _run(tmp_path, """
