@@ -20,10 +20,14 @@ struct qadam_ctx {
     int64_t code_words;         // uint32 words of one worker's packed codes
     int32_t tile_elems;
     int     device;
-    Tile*     d_tiles;
+    Tile*     d_tiles;          // all tiles; with short layers apart, scaled.tiles and the short layers behind them
     int32_t   num_tiles;
     ListShape shape;
     int32_t   longest_layer;    // tiles of the longest layer
+    Section   scaled;           // see Launch
+    int32_t*  d_scaled;         // with short layers apart: scaled.seg_tile_begin and scaled.layers, one behind the other
+    const Tile* short_layers;
+    ShortLayers apart;
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
     uint32_t* d_tile_max;       // [num_workers][num_tiles * pieces of a tile in variant W's first pass]
@@ -117,6 +121,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
+    L.scaled = h->scaled; L.short_layers = h->short_layers; L.apart = h->apart;
     L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
@@ -272,7 +277,15 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     // tile table: segments cut into runs of tile_elems elements
     std::vector<Tile> tiles;
     tiles.reserve((size_t)tile_count);
-    std::vector<int32_t> sample_tiles;
+    ShortLayers shorts{};
+    for (int l = 0; l < num_segments; ++l) {
+        const int64_t n = seg_offsets[l + 1] - seg_offsets[l];
+        if (n > 0 && n <= kTileElems) ++shorts.num[short_size((int)n)];
+    }
+    if (h->code_bits > 0) h->apart = short_layers_apart(shorts, tile_count, num_workers);
+    const bool split = h->apart.any();
+    std::vector<Tile> scaled_tiles, short_layers[kShortSizes];
+    std::vector<int32_t> sample_tiles, scaled_begin, scaled_layers;
     std::vector<int32_t> seg_tile_begin(num_segments + 1, 0);
     int64_t word_off = 0;
     for (int l = 0; l < num_segments; ++l) {
@@ -281,6 +294,13 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         const int64_t seg_words = segment_code_words(h->code_bits, n);
         const int64_t used_words = (n + 31) / 32 * h->code_bits;
         if (n == 0) h->empty_layers = true;
+        const bool apart = split && n > 0 && n <= kTileElems;
+        if (split) scaled_begin.push_back((int32_t)scaled_tiles.size());
+        if (!apart) {
+            if (split) scaled_layers.push_back(l);
+            ++h->scaled.num_layers;
+            h->scaled.num_elems += n;
+        }
         for (int64_t o = 0; o < n; o += h->tile_elems) {
             Tile t;
             t.start = a + o;
@@ -290,11 +310,14 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             t.flags = (a % 4 != 0) ? kTileUnaligned : 0;
             if (o + h->tile_elems >= n) t.flags |= (int32_t)(seg_words - used_words) << 8;
             t.reserved = 0;
-            if ((o / h->tile_elems) % kSampleStride == 0) {
+            if (!apart && (o / h->tile_elems) % kSampleStride == 0) {
                 t.flags |= kTileSampled;
-                sample_tiles.push_back((int32_t)tiles.size());
+                sample_tiles.push_back(h->scaled.shape.num_tiles);
             }
             tiles.push_back(t);
+            if (apart) short_layers[h->apart.size_of((int)n)].push_back(t);
+            else if (split) scaled_tiles.push_back(t);
+            if (!apart) add_tiles(h->scaled.shape, 1, t.len);
             add_tiles(h->shape, 1, t.len);
         }
         const int32_t layer_tiles = (int32_t)tiles.size() - seg_tile_begin[l];
@@ -318,8 +341,8 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->d_seg_tile_begin), sizeof(int32_t) * (num_segments + 1));
     if (e == hipSuccess)
         e = hipMemcpy(h->d_seg_tile_begin, seg_tile_begin.data(), sizeof(int32_t) * (num_segments + 1), hipMemcpyHostToDevice);
-    if (e == hipSuccess && h->num_tiles > 0)
-        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->num_tiles * num_workers * moment_cut(h->shape).parts);
+    if (e == hipSuccess && h->scaled.shape.num_tiles > 0)
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->scaled.shape.num_tiles * num_workers * moment_cut(h->scaled.shape).parts);
     if (e == hipSuccess && h->num_tiles > 0)
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_sum), sizeof(double) * (size_t)h->num_tiles);
     if (e == hipSuccess && num_segments > 0)
@@ -331,6 +354,15 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         if (e == hipSuccess)
             e = hipMemcpy(h->d_sample_tiles, sample_tiles.data(), sizeof(int32_t) * sample_tiles.size(),
                           hipMemcpyHostToDevice);
+    }
+    if (e == hipSuccess && split) {
+        scaled_begin.push_back((int32_t)scaled_tiles.size());
+        scaled_begin.insert(scaled_begin.end(), scaled_layers.begin(), scaled_layers.end());
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_scaled), sizeof(int32_t) * scaled_begin.size());
+        if (e == hipSuccess)
+            e = hipMemcpy(h->d_scaled, scaled_begin.data(), sizeof(int32_t) * scaled_begin.size(), hipMemcpyHostToDevice);
+        tiles.insert(tiles.end(), scaled_tiles.begin(), scaled_tiles.end());
+        for (const std::vector<Tile>& s : short_layers) tiles.insert(tiles.end(), s.begin(), s.end());
     }
     if (e == hipSuccess && h->num_tiles > 0) {
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tiles), sizeof(Tile) * tiles.size());
@@ -347,9 +379,14 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         if (h->d_err_bound) (void)hipFree(h->d_err_bound);
         if (h->d_thr) (void)hipFree(h->d_thr);
         if (h->d_sample_tiles) (void)hipFree(h->d_sample_tiles);
+        if (h->d_scaled) (void)hipFree(h->d_scaled);
         delete h;
         return hip_fail(e, "qadam_init device tables");
     }
+    h->scaled.tiles = split ? h->d_tiles + h->num_tiles : h->d_tiles;
+    h->scaled.seg_tile_begin = split ? h->d_scaled : h->d_seg_tile_begin;
+    h->scaled.layers = split ? h->d_scaled + num_segments + 1 : nullptr;
+    h->short_layers = split ? h->scaled.tiles + h->scaled.shape.num_tiles : nullptr;
     *out = h;
     return QADAM_OK;
 }
@@ -368,6 +405,7 @@ int qadam_destroy(qadam_handle_t h)
     if (h->d_err_bound) (void)hipFree(h->d_err_bound);
     if (h->d_thr) (void)hipFree(h->d_thr);
     if (h->d_sample_tiles) (void)hipFree(h->d_sample_tiles);
+    if (h->d_scaled) (void)hipFree(h->d_scaled);
     delete h;
     return QADAM_OK;
 }
@@ -398,12 +436,13 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step, const 
     QADAM_CHECK(check_capture(h, stream, &capturing));
     // a recorded call always takes the full scale pass: a replay must not depend on what ran before it
     const bool recorded = !capturing && bound_usable(h, worker, err_dev);
-    const bool filtered = recorded && (h->trust_errs == 2 || (h->trust_errs == 1 && h->num_tiles >= kFilterMinTiles));
+    const bool filtered = recorded && (h->trust_errs == 2 || (h->trust_errs == 1 && h->scaled.shape.num_tiles >= kFilterMinTiles));
     if (h->trust_errs == 3 && recorded) QADAM_HIP(launch_check_error_bounds(L, W, worker, 1));
     BoundRecord record(h, worker, 1, W);
     if (filtered) QADAM_HIP(launch_amax_filtered(L, S, W, worker, 1));
     else QADAM_HIP(launch_amax(L, S, W, worker, 1));
     QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1));
+    QADAM_HIP(launch_short_layers(L, S, W, worker, false));
     QADAM_HIP(launch_worker_quantize(L, S, W, worker));
     record.complete = !capturing;       // nothing has run yet when the call was only recorded
     return QADAM_OK;
@@ -524,7 +563,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     } else {
         // the filtered pass costs two more (small) launches: only worth it from about 10^8 worker-elements on
         bool filtered = h->trust_errs == 2 ||
-                        (h->trust_errs == 1 && (int64_t)h->num_tiles * h->num_workers >= kFilterMinTiles);
+                        (h->trust_errs == 1 && (int64_t)h->scaled.shape.num_tiles * h->num_workers >= kFilterMinTiles);
         bool all_recorded = true;
         for (int i = 0; i < h->num_workers; ++i) all_recorded = all_recorded && bound_usable(h, i, W.err[i]);
         all_recorded = all_recorded && !capturing;     // a recorded call always takes the full scale pass
@@ -535,6 +574,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
         else QADAM_HIP(launch_amax(L, S, W, 0, h->num_workers));
         QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers));
         if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
+        QADAM_HIP(launch_short_layers(L, S, W, sp, false));
         QADAM_HIP(launch_fused(L, S, W, sp));
         record.complete = !capturing;
     }
@@ -572,6 +612,7 @@ int qadam_worker_step_w(qadam_handle_t h, int32_t worker, int64_t step, float lr
     BoundRecord record(h, worker, 1, W);
     QADAM_HIP(launch_worker_moments_w(L, S, W, worker, 1));
     QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1, moment_parts(L)));
+    QADAM_HIP(launch_short_layers(L, S, W, worker, true));
     // pass 2: quantize the parked p
     W.grad[worker] = nullptr;
     QADAM_HIP(launch_worker_quantize(L, S, W, worker));
@@ -613,7 +654,10 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
     // pass 2: quantize every worker's parked p, subtract the mean message, Q_x
     if (idg) QADAM_HIP(launch_plain_messages(L, S, W, sp, true));
-    else QADAM_HIP(launch_fused_w(L, S, W, sp));
+    else {
+        QADAM_HIP(launch_short_layers(L, S, W, sp, true));
+        QADAM_HIP(launch_fused_w(L, S, W, sp));
+    }
     record.complete = !idg && !capturing;   // with the identity quantizer no scale, hence no bound, was produced
     if (h->profile && !capturing) {
         QADAM_HIP(hipEventRecord(h->ev[2], L.stream));

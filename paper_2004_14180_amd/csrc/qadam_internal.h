@@ -64,15 +64,29 @@ struct ServerPtrs {
     void*  wcodes;
 };
 
+// Those of a handle's layers whose scales come from a pass of their own: all, or all but short_layers.  Tiles are counted
+// within the section.
+struct Section {
+    const Tile* tiles;      // device
+    const int32_t* seg_tile_begin;  // device, [num_segments + 1]: first tile of every layer
+    const int32_t* layers;  // device: the layers, empty ones included; null: all
+    int32_t     num_layers;
+    int64_t     num_elems;
+    ListShape   shape;
+};
+
 struct Launch {
     const Tile* tiles;      // device
     float*      inv_scales; // device, [num_workers][num_segments]: 1/s where the fast quotient is safe, else 0
-    uint32_t*   tile_max;   // device, [num_workers][num_tiles * moment_parts]: max |p| per tile (variant W: per piece of a
-                            // tile) as a bit pattern; a worker's row begins at the same place in every call
+    uint32_t*   tile_max;   // device, [num_workers][scaled tiles * moment_parts]: max |p| per tile (variant W: per piece of
+                            // a tile) as a bit pattern; a worker's row begins at the same place in every call
     const int32_t* seg_tile_begin;  // device, [num_segments + 1]: first tile of every segment
     int32_t     num_tiles;
     ListShape   shape;
+    Section     scaled;
     int32_t     longest_layer;  // tiles of the longest layer
+    const Tile* short_layers;   // device: the layers that k_layers does, one tile each, by size; null: none
+    ShortLayers apart;          // how many of each size
     int32_t     num_segments;
     int64_t     num_params;
     double*     tile_sum;   // device, [num_tiles]: per-tile partial sums of the norm diagnostic
@@ -86,7 +100,7 @@ struct Launch {
 };
 
 // maxima per tile that the first pass of variant W leaves
-inline int moment_parts(const Launch& L) { return (int)moment_cut(L.shape).parts; }
+inline int moment_parts(const Launch& L) { return (int)moment_cut(L.scaled.shape).parts; }
 
 // Launchers (defined in qadam_kernels.hip).  `first_worker`/`num` select the workers a launch covers.
 // scales in two stages without atomics: per-tile maxima, then one workgroup per (worker, layer)
@@ -97,6 +111,10 @@ hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const Wor
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker);
+// the short layers of the list, from the gradient (variant_w: through the local moments) to the codes, for one worker; or
+// the whole step of all workers
+hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker, bool variant_w);
+hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w);
 hipError_t launch_server_step(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp);
 hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const float* x, float* werr, void* wcodes);
 hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const void* wcodes, void* xhat, bool half);

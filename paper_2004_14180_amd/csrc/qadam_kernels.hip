@@ -601,7 +601,8 @@ struct ScaleArgs {
     float* inv_scales;
     const uint32_t* tile_max;
     const int32_t* seg_tile_begin;
-    int first_worker, num_segments, num_tiles;
+    const int32_t* layers;  // null: all
+    int first_worker, num_layers, num_segments, num_tiles;
     int row;                // maxima from one worker's to the next's
     int max_per_tile;       // maxima the pass before left per tile
     float* err_bound;       // [N][L]: bound on |e'| after the step that uses these scales
@@ -795,7 +796,7 @@ __device__ __forceinline__ void write_scale(const ScaleArgs& A, int w, int l, ui
 // what bounds the kernel is the chain of loads of one thread, hence 1024 threads and eight loads in flight each.
 __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales(ScaleArgs A)
 {
-    const int l = blockIdx.x, w = A.first_worker + blockIdx.y;
+    const int l = A.layers ? A.layers[blockIdx.x] : (int)blockIdx.x, w = A.first_worker + blockIdx.y;
     // no table: a single segment that owns every tile
     const int t0 = (A.seg_tile_begin ? A.seg_tile_begin[l] : 0) * A.max_per_tile;
     const int t1 = (A.seg_tile_begin ? A.seg_tile_begin[l + 1] : A.num_tiles) * A.max_per_tile;
@@ -812,19 +813,22 @@ __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales_list(ScaleArgs
     const int first = blockIdx.x * kListLayers, w = A.first_worker + blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t* part = A.tile_max + (size_t)w * A.row;
-    // lane k holds where layer first + k begins (past the last layer: its end, an empty range)
-    const int begin = lane <= kListLayers ? A.seg_tile_begin[min(first + lane, A.num_segments)] * A.max_per_tile : 0;
-    const int t0 = __shfl(begin, wave, 64), t1 = __shfl(begin, wave + 1, 64);
-    if (first + wave < A.num_segments && t1 - t0 <= kListMaxima) {
+    // lane k holds layer first + k and its range (past the last layer: an empty one)
+    const bool live = lane < kListLayers && first + lane < A.num_layers;
+    const int layer = !live ? 0 : A.layers ? A.layers[first + lane] : first + lane;
+    const int begin = live ? A.seg_tile_begin[layer] * A.max_per_tile : 0;
+    const int end = live ? A.seg_tile_begin[layer + 1] * A.max_per_tile : 0;
+    const int t0 = __shfl(begin, wave, 64), t1 = __shfl(end, wave, 64), l = __shfl(layer, wave, 64);
+    if (first + wave < A.num_layers && t1 - t0 <= kListMaxima) {
         const uint32_t m = wave_max_u32(fold_maxima<64>(part, t0, t1, lane));
-        if (lane == 0) write_scale(A, w, first + wave, m);
+        if (lane == 0) write_scale(A, w, l, m);
     }
 #pragma unroll 1
     for (int k = 0; k < kListLayers; ++k) {
-        const int a = __builtin_amdgcn_readlane(begin, k), b = __builtin_amdgcn_readlane(begin, k + 1);
+        const int a = __builtin_amdgcn_readlane(begin, k), b = __builtin_amdgcn_readlane(end, k);
         if (b - a <= kListMaxima) continue;         // the same in every wavefront of the workgroup
         const uint32_t bm = block_max<kReduceThreads>(fold_maxima<kReduceThreads>(part, a, b, (int)threadIdx.x));
-        if (threadIdx.x == 0) write_scale(A, w, first + k, bm);
+        if (threadIdx.x == 0) write_scale(A, w, __builtin_amdgcn_readlane(layer, k), bm);
         __syncthreads();                            // block_max's parts are read before the next round writes them
     }
 }
@@ -836,7 +840,7 @@ __global__ void __launch_bounds__(kReduceThreads) k_reduce_scales_list(ScaleArgs
 // where |g_j| >= thr = (LB - B) minus a safety margin that covers the rounding of g + e.
 __global__ void __launch_bounds__(kBlockThreads) k_reduce_lower_bounds(ScaleArgs A)
 {
-    const int l = blockIdx.x, w = A.first_worker + blockIdx.y;
+    const int l = A.layers ? A.layers[blockIdx.x] : (int)blockIdx.x, w = A.first_worker + blockIdx.y;
     const int t0 = A.seg_tile_begin[l], t1 = A.seg_tile_begin[l + 1];
     const uint32_t* part = A.tile_max + (size_t)w * A.row;
     uint32_t local = 0;
@@ -1413,6 +1417,35 @@ __global__ void __launch_bounds__(THREADS) k_weight_dequantize(DequantArgs A)
     }
 }
 
+// Server arithmetic of one lane's elements, from the sum of the workers' messages to the weight codes, and its stores.
+// W: the server only subtracts the mean message, m and v are not used.
+template <int ROUNDING, int V, bool W, bool SH>
+__device__ __forceinline__ void server_lane(const StepScalars& S, const ServerPtrs& sp, const float (&acc)[V], float (&xv)[V],
+                                            float (&mv)[V], float (&vv)[V], const float (&wi)[V], int64_t gi, int nvalid,
+                                            const Shift& sf)
+{
+    if constexpr (W) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) xv[j] = xv[j] - mean_over_workers(S, acc[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const float u = adam_step(S, mean_over_workers(S, acc[j]), mv[j], vv[j]);
+            xv[j] = xv[j] - u;
+        }
+        st<V, SH>(sp.m, gi, nvalid, sf, mv);
+        st<V, SH>(sp.v, gi, nvalid, sf, vv);
+    }
+    st<V, SH>(sp.x, gi, nvalid, sf, xv);
+    if (S.k_x >= 0) {                                    // else Q_x is the identity
+        float wo[V];
+        int jc[V];
+        weight_lane<V, ROUNDING, SH>(S, xv, wi, gi, sf, wo, jc);
+        if (sp.werr) st<V, SH>(sp.werr, gi, nvalid, sf, wo);
+        stw<V, SH>(sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
+    }
+}
+
 // ---- the whole step in one pass (qadam_step_fused) -----------------------------------------------
 // One wavefront's share: `part_len` elements of a tile from `part_begin`, 64 V at a time, the workers' g and e
 // loaded U workers at a time.  FULL: the share is whole, so that no access needs a guard.
@@ -1434,8 +1467,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
         const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
         const int64_t gi = t.start + off;
         // server state first: its latency hides behind the workers' arithmetic
-        float xv[V], mv[V], vv[V], wi[V], wo[V];
-        int jc[V];
+        float xv[V], mv[V], vv[V], wi[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) wi[j] = 0.0f;
         ld<V, SH>(A.sp.x, gi, nvalid, sf, xv);
@@ -1443,8 +1475,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
             ld<V, SH>(A.sp.m, gi, nvalid, sf, mv);
             ld<V, SH>(A.sp.v, gi, nvalid, sf, vv);
         }
-        const bool quantize_x = S.k_x >= 0;              // false: Q_x is the identity
-        if (S.weight_ef && quantize_x) ld<V, SH>(A.sp.werr, gi, nvalid, sf, wi);
+        if (S.weight_ef && S.k_x >= 0) ld<V, SH>(A.sp.werr, gi, nvalid, sf, wi);
         float acc[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) acc[j] = 0.0f;
@@ -1488,27 +1519,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
                 for (int j = 0; j < V; ++j) acc[j] = acc[j] + q[j];
             }
         }
-        // server: mean, (moments, step,) weight quantizer
-        if constexpr (W) {
-#pragma unroll
-            for (int j = 0; j < V; ++j) xv[j] = xv[j] - mean_over_workers(S, acc[j]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const float u = adam_step(S, mean_over_workers(S, acc[j]), mv[j], vv[j]);
-                xv[j] = xv[j] - u;
-            }
-        }
-        if constexpr (!W) {
-            st<V, SH>(A.sp.m, gi, nvalid, sf, mv);
-            st<V, SH>(A.sp.v, gi, nvalid, sf, vv);
-        }
-        st<V, SH>(A.sp.x, gi, nvalid, sf, xv);
-        if (quantize_x) {
-            weight_lane<V, ROUNDING, SH>(S, xv, wi, gi, sf, wo, jc);
-            if (A.sp.werr) st<V, SH>(A.sp.werr, gi, nvalid, sf, wo);
-            stw<V, SH>(A.sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
-        }
+        server_lane<ROUNDING, V, W, SH>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
     }
     if (part_begin + part_len >= t.len)
         for (int i = 0; i < N; ++i) write_pad_words(A.codes[i], t, S.code_bits);
@@ -1535,6 +1546,153 @@ __global__ void __launch_bounds__(64) k_fused(FusedArgs A)
         if (full) fused_part<ROUNDING, 4, W, false, FOLD, U, true>(A, t, ti, part_begin, part_len);
         else fused_part<ROUNDING, 4, W, false, FOLD, 1, false>(A, t, ti, part_begin, part_len);
     }
+}
+
+// ---- short layers: scale and quantization in one go ----------------------------------------------
+struct LayerArgs {
+    const Tile* tiles;              // a tile for each layer
+    Items items;
+    uint32_t* status;
+    StepScalars S;
+    ServerPtrs sp;                  // SERVER only
+    const float* grad[QADAM_MAX_WORKERS];
+    float* mw[QADAM_MAX_WORKERS];   // variant W only
+    float* vw[QADAM_MAX_WORKERS];
+    float* err[QADAM_MAX_WORKERS];
+    uint32_t* codes[QADAM_MAX_WORKERS];
+    float* scales[QADAM_MAX_WORKERS];
+    float* err_bound;               // [N][L]
+    float bound_factor;
+    int first_worker, num_segments;
+};
+
+// A layer of THREADS * C * 4 elements or fewer: p of one worker stays in registers between the scale and the quantizer, the
+// sum of the messages until the server's part, so everything is read once.  SERVER: the whole step of all workers, else one
+// worker's call.  Bound by memory where there are thousands of layers (20000 of 1000 elements, 4 workers: 1.65 GB in 298
+// us), by one worker's chain after the other's where there are few.  One quad per lane wherever the layer fits: with one
+// wavefront and four quads 20000 layers of 997 took 362 us for 335, and 300 of 1000 22.9 for 12.6.
+template <int ROUNDING, int THREADS, int C, bool SERVER, bool W, bool SH>
+__device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
+{
+    const StepScalars& S = A.S;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const QgConst c = make_qg(S.k_g);
+    const Shift sf = make_shift(t);
+    const int num = SERVER ? S.num_workers : 1;
+    // The next worker's loads are under way while this one's maximum is found, where that leaves enough wavefronts per SIMD
+    // (us per step of 4 workers, without / with: 20000 layers of 997 elements 362 / 335, 10000 of 2000 296 / 346).
+    constexpr bool AHEAD = C == 1;
+    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int base[C], nvalid[C];
+    int64_t gi[C];
+    float acc[C][4];
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        base[k] = (k * (THREADS / 64) + wave) * 256;
+        const int off = base[k] + lane * 4;
+        nvalid[k] = min(max(t.len - off, 0), 4);
+        gi[k] = t.start + off;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[k][j] = 0.0f;
+    }
+    // what worker i brings; W: the local moments too
+    float g[C][4], e[C][4], lm[C][4], lv[C][4];
+    auto load_worker = [&](int i) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            ld<4, SH>(A.grad[i], gi[k], nvalid[k], sf, g[k]);
+            ld<4, SH>(A.err[i], gi[k], nvalid[k], sf, e[k]);
+            if constexpr (W) {
+                ld<4, SH>(A.mw[i], gi[k], nvalid[k], sf, lm[k]);
+                ld<4, SH>(A.vw[i], gi[k], nvalid[k], sf, lv[k]);
+            }
+        }
+    };
+    if constexpr (AHEAD) load_worker(A.first_worker);
+    for (int i = A.first_worker; i < A.first_worker + num; ++i) {
+        if constexpr (!AHEAD) load_worker(i);
+        float p[C][4];
+        uint32_t local = 0;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (W) p[k][j] = adam_step(S, g[k][j], lm[k][j], lv[k][j]) + e[k][j];
+                else p[k][j] = g[k][j] + e[k][j];
+                // beyond the end the step alpha m / sqrt(v + eps) is 0 / 0 where eps is 0; codes there are zero bits
+                if (W && j >= nvalid[k]) p[k][j] = 0.0f;
+                const uint32_t ab = f2u(p[k][j]) & 0x7fffffffu;
+                local = ab > local ? ab : local;
+            }
+            if constexpr (W) {
+                st<4, SH>(A.mw[i], gi[k], nvalid[k], sf, lm[k]);
+                st<4, SH>(A.vw[i], gi[k], nvalid[k], sf, lv[k]);
+            }
+        }
+        if (SERVER && AHEAD && i + 1 < num) load_worker(i + 1);
+        uint32_t bits = wave_max_u32(local);
+        if constexpr (THREADS > 64) {
+            // two sets of parts in turn: whoever writes a set for worker i + 2 has passed the barrier of worker i + 1, behind
+            // which nobody reads worker i's
+            __shared__ uint32_t wave_part[2][THREADS / 64];
+            if (lane == 0) wave_part[i & 1][wave] = bits;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < THREADS / 64; ++w) bits = wave_part[i & 1][w] > bits ? wave_part[i & 1][w] : bits;
+        }
+        const Scale sc = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)bits));
+        if (threadIdx.x == 0) {
+            A.scales[i][t.seg] = sc.s;
+            A.err_bound[(size_t)i * A.num_segments + t.seg] = residual_bound(sc.s, A.bound_factor);
+        }
+        check_scale(sc.s, A.status);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            if (base[k] >= t.len) break;
+            float q[4], en[4], U[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) U[j] = 0.0f;
+            if constexpr (ROUNDING == 1) unif<4, SH>(S, gi[k], (uint32_t)i, 0u, sf, U);
+            uint32_t codes;
+            worker_lane<4, ROUNDING>(p[k], zero, sc.s, sc.inv, c, S.mu_bits, U, q, en, codes);      // p + 0 reproduces p
+            st<4, SH>(A.err[i], gi[k], nvalid[k], sf, en);
+            int slot; bool writes;
+            const uint32_t word = pack_planes<4>(codes, S.code_bits, lane, slot, writes);
+            store_chunk_words(A.codes[i], t, base[k], S.code_bits, word, slot, writes);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[k][j] = acc[k][j] + q[j];
+        }
+        write_pad_words(A.codes[i], t, S.code_bits);
+    }
+    if constexpr (SERVER) {
+        float x[C][4], m[C][4], v[C][4], wi[C][4];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wi[k][j] = 0.0f;
+            ld<4, SH>(A.sp.x, gi[k], nvalid[k], sf, x[k]);
+            if constexpr (!W) {
+                ld<4, SH>(A.sp.m, gi[k], nvalid[k], sf, m[k]);
+                ld<4, SH>(A.sp.v, gi[k], nvalid[k], sf, v[k]);
+            }
+            if (S.weight_ef && S.k_x >= 0) ld<4, SH>(A.sp.werr, gi[k], nvalid[k], sf, wi[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            if (base[k] >= t.len) break;
+            server_lane<ROUNDING, 4, W, SH>(S, A.sp, acc[k], x[k], m[k], v[k], wi[k], gi[k], nvalid[k], sf);
+        }
+    }
+}
+
+template <int ROUNDING, int THREADS, int C, bool SERVER, bool W>
+__global__ void __launch_bounds__(THREADS) k_layers(LayerArgs A)
+{
+    const uint32_t item = wave_item(A.items);
+    if (item >= A.items.count) return;
+    const Tile t = A.tiles[item];
+    if (t.flags & kTileUnaligned) layer_step<ROUNDING, THREADS, C, SERVER, W, true>(A, t);
+    else layer_step<ROUNDING, THREADS, C, SERVER, W, false>(A, t);
 }
 
 // ---- Q_g = identity: the messages are fp32 values ------------------------------------------------
@@ -1612,13 +1770,13 @@ __global__ void __launch_bounds__(kBlockThreads) k_plain_messages(FusedArgs A)
 // ---- variant W, first pass: local moments, park p = u + e in the error buffer, scale ------------
 struct MomentsWArgs {
     const Tile* tiles;
-    int num_tiles;
+    int row;                // maxima from one worker's to the next's
     StepScalars S;
     const float* grad[QADAM_MAX_WORKERS];
     float* mw[QADAM_MAX_WORKERS];
     float* vw[QADAM_MAX_WORKERS];
     float* err[QADAM_MAX_WORKERS];
-    uint32_t* tile_max;     // [N][num_tiles * cut.parts]
+    uint32_t* tile_max;     // rows of `row` maxima, cut.parts to a tile
     Cut cut;
     int first_worker;
 };
@@ -1686,7 +1844,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_moments_w(MomentsWArgs A)
     else
         local = moments_w_part<4, false, KEEP>(A.S, A.grad[w], A.mw[w], A.vw[w], A.err[w], t, part_begin, part_len);
     const uint32_t bm = block_max(local);
-    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.num_tiles * A.cut.parts + blockIdx.x] = bm;
+    if (threadIdx.x == 0) A.tile_max[(size_t)w * A.row + blockIdx.x] = bm;
 }
 
 // ---- diagnostic: per-layer sum of squares in fp64, fixed order ---------------------------------
@@ -1779,13 +1937,14 @@ static float residual_bound_factor(const StepScalars& S)
 
 // Every pass gives worker w the same row of the maxima, whether it leaves one per tile or `moment_parts`: calls for
 // different workers may run on different streams.
-static int max_row(const Launch& L) { return L.num_tiles * moment_parts(L); }
+static int max_row(const Launch& L) { return L.scaled.shape.num_tiles * moment_parts(L); }
 
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) A.scales[i] = W.scales[i];
-    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.row = max_row(L); A.seg_tile_begin = L.seg_tile_begin;
-    A.first_worker = first_worker; A.num_segments = L.num_segments; A.num_tiles = L.num_tiles;
+    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.row = max_row(L); A.seg_tile_begin = L.scaled.seg_tile_begin;
+    A.first_worker = first_worker; A.num_segments = L.num_segments; A.num_tiles = L.scaled.shape.num_tiles;
+    A.layers = L.scaled.layers; A.num_layers = L.scaled.num_layers;
     A.err_bound = L.err_bound; A.thr = L.thr;
     A.bound_factor = residual_bound_factor(S);
     A.sample_stride = kSampleStride;
@@ -1793,7 +1952,7 @@ static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S,
 
 static bool fold_in_quantizer(const Launch& L, int num, int max_per_tile)
 {
-    return !L.empty_layers && fold_in_quantizer(L.num_tiles, L.longest_layer * max_per_tile, num);
+    return !L.empty_layers && !L.short_layers && fold_in_quantizer(L.num_tiles, L.longest_layer * max_per_tile, num);
 }
 
 static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
@@ -1801,7 +1960,7 @@ static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num
     Fold F;
     F.row = max_row(L); F.per_tile = max_per_tile;
     F.tile_max = fold_in_quantizer(L, num, max_per_tile) ? L.tile_max + (size_t)worker * F.row : nullptr;
-    F.seg_tile_begin = L.seg_tile_begin;
+    F.seg_tile_begin = L.scaled.seg_tile_begin;
     F.num_segments = L.num_segments;
     F.inv_scales = L.inv_scales + (size_t)worker * L.num_segments;
     F.err_bound = L.err_bound + (size_t)worker * L.num_segments;
@@ -1829,19 +1988,19 @@ static bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)512
 hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
                                 int max_per_tile)
 {
-    if (L.num_segments == 0 || num == 0 || fold_in_quantizer(L, num, max_per_tile)) return hipSuccess;
+    if (L.scaled.num_layers == 0 || num == 0 || fold_in_quantizer(L, num, max_per_tile)) return hipSuccess;
     ScaleArgs A;
     fill_scale_args(A, L, S, W, first_worker);
     A.max_per_tile = max_per_tile;
-    const dim3 grid(reduce_blocks(L.num_segments, num), num), block(kReduceThreads);
-    if (reduce_by_list(L.num_segments, num)) hipLaunchKernelGGL(k_reduce_scales_list, grid, block, 0, L.stream, A);
+    const dim3 grid(reduce_blocks(A.num_layers, num), num), block(kReduceThreads);
+    if (reduce_by_list(A.num_layers, num)) hipLaunchKernelGGL(k_reduce_scales_list, grid, block, 0, L.stream, A);
     else hipLaunchKernelGGL(k_reduce_scales, grid, block, 0, L.stream, A);
     return hipGetLastError();
 }
 
 static void fill_amax_args(AmaxArgs& A, const Launch& L, const WorkerPtrs& W, int first_worker)
 {
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles;
+    A.tiles = L.scaled.tiles; A.num_tiles = L.scaled.shape.num_tiles;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; }
     A.tile_max = L.tile_max; A.row = max_row(L);
     A.first_worker = first_worker;
@@ -1855,6 +2014,7 @@ hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int f
     if (L.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
+    A.tiles = L.tiles;      // every layer's
     hipLaunchKernelGGL(k_check_error_bounds, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
     return hipGetLastError();
 }
@@ -1872,10 +2032,10 @@ static void launch_scan(AmaxArgs& A, const ListShape& shape, int64_t n, int num,
 hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
     (void)S;
-    if (L.num_tiles == 0 || num == 0) return hipSuccess;
+    if (L.scaled.shape.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
-    launch_scan(A, L.shape, L.num_params, num, L.stream);
+    launch_scan(A, L.scaled.shape, L.scaled.num_elems, num, L.stream);
     return hipGetLastError();
 }
 
@@ -1884,30 +2044,30 @@ hipError_t launch_amax(const Launch& L, const StepScalars& S, const WorkerPtrs& 
 // where |g| reaches the threshold.  launch_reduce_scales follows as usual.
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
-    if (L.num_tiles == 0 || num == 0) return hipSuccess;
+    if (L.scaled.shape.num_tiles == 0 || num == 0) return hipSuccess;
     AmaxArgs A;
     fill_amax_args(A, L, W, first_worker);
     A.tile_list = L.sample_tiles;
     hipLaunchKernelGGL(k_amax<false>, dim3(L.num_sample_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
     ScaleArgs R;
     fill_scale_args(R, L, S, W, first_worker);
-    hipLaunchKernelGGL(k_reduce_lower_bounds, dim3(L.num_segments, num), dim3(kBlockThreads), 0, L.stream, R);
+    hipLaunchKernelGGL(k_reduce_lower_bounds, dim3(L.scaled.num_layers, num), dim3(kBlockThreads), 0, L.stream, R);
     A.tile_list = nullptr;
-    hipLaunchKernelGGL(k_amax_filtered, dim3(L.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
+    hipLaunchKernelGGL(k_amax_filtered, dim3(L.scaled.shape.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
     return hipGetLastError();
 }
 
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker)
 {
-    if (L.num_tiles == 0) return hipSuccess;
+    if (L.scaled.shape.num_tiles == 0) return hipSuccess;
     WorkerArgs A;
-    A.tiles = L.tiles;
+    A.tiles = L.scaled.tiles;
     A.status = L.status; A.S = S;
     A.grad = W.grad[worker]; A.err = W.err[worker]; A.codes = W.codes[worker]; A.scales = W.scales[worker];
     A.fold = make_fold(L, S, worker, 1, A.grad ? 1 : moment_parts(L));
     A.worker = worker;
     A.seg_len = 0;
-    A.items = wave_items(L.shape, kQuantizeElems);
+    A.items = wave_items(L.scaled.shape, kQuantizeElems);
     launch_quantizer(A, L.stream);
     return hipGetLastError();
 }
@@ -2018,15 +2178,15 @@ constexpr unsigned kMainPassLds = 10240;
 static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
                                    bool variant_w)
 {
-    if (L.num_tiles == 0) return hipSuccess;
+    if (L.scaled.shape.num_tiles == 0) return hipSuccess;
     FusedArgs A;
-    A.tiles = L.tiles;
+    A.tiles = L.scaled.tiles;
     A.status = L.status; A.S = S; A.sp = sp;
     A.fold = make_fold(L, S, 0, S.num_workers, variant_w ? moment_parts(L) : 1);
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    A.items = wave_items(L.shape, 256);
+    A.items = wave_items(L.scaled.shape, 256);
     const dim3 grid = wave_grid(A.items), block(64);
     // U = 4, or the variant that folds the scales, one worker at a time
 #define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
@@ -2041,6 +2201,53 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     }
 #undef QADAM_LAUNCH_FUSED
     return hipGetLastError();
+}
+
+template <int ROUNDING, bool SERVER, bool W>
+static void launch_layers(LayerArgs& A, const ShortLayers& layers, hipStream_t stream)
+{
+    for (int k = 0; k < kShortSizes; A.tiles += layers.num[k], ++k) {
+        if (layers.num[k] == 0) continue;
+        A.items = layer_items(layers.num[k]);
+        const dim3 grid = wave_grid(A.items);
+        if (k == 0) hipLaunchKernelGGL((k_layers<ROUNDING, 64, 1, SERVER, W>), grid, dim3(64), 0, stream, A);
+        else if (k == 1) hipLaunchKernelGGL((k_layers<ROUNDING, 256, 1, SERVER, W>), grid, dim3(256), 0, stream, A);
+        else hipLaunchKernelGGL((k_layers<ROUNDING, 256, 4, SERVER, W>), grid, dim3(256), 0, stream, A);
+    }
+}
+
+template <bool SERVER>
+static hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
+                                      int worker, bool variant_w)
+{
+    if (!L.short_layers) return hipSuccess;
+    LayerArgs A;
+    A.tiles = L.short_layers;
+    A.status = L.status; A.S = S; A.sp = sp;
+    for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
+        A.grad[i] = W.grad[i]; A.mw[i] = W.mw[i]; A.vw[i] = W.vw[i];
+        A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
+    }
+    A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
+    A.first_worker = worker; A.num_segments = L.num_segments;
+    if (S.rounding == 0) {
+        if (variant_w) launch_layers<0, SERVER, true>(A, L.apart, L.stream);
+        else launch_layers<0, SERVER, false>(A, L.apart, L.stream);
+    } else {
+        if (variant_w) launch_layers<1, SERVER, true>(A, L.apart, L.stream);
+        else launch_layers<1, SERVER, false>(A, L.apart, L.stream);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker, bool variant_w)
+{
+    return launch_short_layers<false>(L, S, W, ServerPtrs{}, worker, variant_w);
+}
+
+hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
+{
+    return launch_short_layers<true>(L, S, W, sp, 0, variant_w);
 }
 
 hipError_t launch_fused(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp)
@@ -2092,17 +2299,17 @@ hipError_t launch_layer_sumsq(const Launch& L, const float* a, const float* b, d
 
 hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
-    if (L.num_tiles == 0 || num == 0) return hipSuccess;
+    if (L.scaled.shape.num_tiles == 0 || num == 0) return hipSuccess;
     MomentsWArgs A;
-    A.tiles = L.tiles; A.num_tiles = L.num_tiles; A.S = S;
+    A.tiles = L.scaled.tiles; A.row = max_row(L); A.S = S;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.mw[i] = W.mw[i]; A.vw[i] = W.vw[i]; A.err[i] = W.err[i];
     }
     A.tile_max = L.tile_max;
     A.first_worker = first_worker;
-    A.cut = moment_cut(L.shape);
-    const dim3 grid((unsigned)L.num_tiles * A.cut.parts, num), block(kBlockThreads);
-    if (keep_parked(L.num_params, num)) hipLaunchKernelGGL(k_moments_w<true>, grid, block, 0, L.stream, A);
+    A.cut = moment_cut(L.scaled.shape);
+    const dim3 grid((unsigned)L.scaled.shape.num_tiles * A.cut.parts, num), block(kBlockThreads);
+    if (keep_parked(L.scaled.num_elems, num)) hipLaunchKernelGGL(k_moments_w<true>, grid, block, 0, L.stream, A);
     else hipLaunchKernelGGL(k_moments_w<false>, grid, block, 0, L.stream, A);
     return hipGetLastError();
 }

@@ -121,6 +121,56 @@ constexpr Items scan_items(const ListShape& s)
 // one dimension of a launch holds fewer than 2^32 work-items
 constexpr bool scan_fits(const Items& I) { return (uint64_t)wave_blocks(I) * 256 < ((uint64_t)1 << 32); }
 
+// ---- layers of one tile, done from the gradient to the codes by one workgroup each (k_layers) -----------------------
+// Sizes of its workgroups: one wavefront for up to 256 elements, four for up to 1024 and for up to a tile.
+constexpr int kShortSizes = 3;
+constexpr int short_size(int len) { return len <= 256 ? 0 : len <= 1024 ? 1 : 2; }
+
+struct ShortLayers {
+    int32_t num[kShortSizes];   // layers of each size
+    int32_t as[kShortSizes];    // [k]: the size whose workgroups do the layers of size k
+
+    constexpr bool any() const { return num[0] + num[1] + num[2] > 0; }
+    constexpr int size_of(int len) const { return as[short_size(len)]; }
+};
+
+// Which of a list's layers of one tile are done that way: all or none.  The general path reads g and e twice and launches
+// its passes mostly for workgroups of a few hundred elements; a workgroup that does its layer alone is a chain of one load,
+// one maximum and one store per worker, and beside longer layers a launch more.  us per step, general path / this way.
+// Only layers of one tile: 20000 of 1000 elements, 4 workers 430 / 298; 100000 of 100 716 / 217; 64 of 100 14.4 / 12.2, one
+// worker's call 7.1 / 4.4; 256 of 4096 26.1 / 27.4, 400 of 4096 42.4 / 34.2; variant W, 8 workers, 64 of 100 23.3 / 24.2, 16
+// workers 34 / 43 and with 256 of them 40 / 42.  Beside longer ones: one of 20 M and 300 of 1000, 4 workers 387 / 397, and
+// 20000 of 1000 1055 / 691; 500 times 10000 and 100 112 / 119, 3000 times 654 / 639 (one worker 307 / 309).
+// Sizes with fewer layers than there are CUs go along with the next one, which saves a launch.
+constexpr ShortLayers short_layers_apart(const ShortLayers& have, int64_t num_tiles, int num_workers)
+{
+    ShortLayers s = have;
+    for (int k = 0; k < kShortSizes; ++k) s.as[k] = k;
+    const int64_t n = (int64_t)have.num[0] + have.num[1] + have.num[2];
+    const bool alone = n == num_tiles;
+    const bool apart = alone ? n >= 320 || (have.num[2] == 0 && num_workers <= 8) : n >= 2048;
+    if (!apart || n > kMaxTiles - 4096) return ShortLayers{};       // a launch in whole rounds (wave_blocks) must fit
+    for (int k = 0; k + 1 < kShortSizes; ++k) {
+        int next = k + 1;
+        while (next < kShortSizes && s.num[next] == 0) ++next;
+        if (s.num[k] == 0 || s.num[k] >= 256 || next == kShortSizes) continue;
+        s.num[next] += s.num[k];
+        s.num[k] = 0;
+        for (int j = 0; j <= k; ++j) if (s.as[j] == k) s.as[j] = next;
+    }
+    return s;
+}
+
+// their workgroups, in the runs of wave_items
+constexpr Items layer_items(int32_t num)
+{
+    Items I{};
+    I.cut = Cut{1, kTileElems};
+    I.count = (uint32_t)num;
+    while (I.run_shift < 8 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
+    return I;
+}
+
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
 // Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
 struct FlatGrid {

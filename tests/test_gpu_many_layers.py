@@ -15,19 +15,22 @@ def _same(dev, host):
     return np.array_equal(dev.cpu().numpy().view(np.uint8), np.ascontiguousarray(host).view(np.uint8))
 
 
-def _step(sizes, N, call, seed):
-    """One step from a state that is nowhere zero; every output compared with the oracle's."""
-    gcfg, ocfg = configs()
+def _step(sizes, N, call, seed, status=0, bad=(), **cfgkw):
+    """One step from a state that is nowhere zero; every output compared with the oracle's.  bad: elements of the first
+    worker's gradient that are infinite."""
+    gcfg, ocfg = configs(**cfgkw)
     seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     P, L, rng = int(seg[-1]), len(sizes), np.random.default_rng(seed)
     f32 = lambda s: rng.standard_normal(P, dtype=np.float32) * np.float32(s)  # noqa: E731
     dev = lambda a: torch.from_numpy(a.copy()).cuda()  # noqa: E731
     hg, he = [f32(1e-2) for _ in range(N)], [f32(1e-3) for _ in range(N)]
+    hg[0][list(bad)] = np.inf
     hx, hw = f32(0.02), f32(1e-3)
     nm = N if call[0] == "w" else 1
     hm, hv = [f32(1e-3) for _ in range(nm)], [f32(1e-3) ** 2 for _ in range(nm)]
     g, e, m, v = ([dev(a) for a in b] for b in (hg, he, hm, hv))
-    x, werr, wcodes = dev(hx), dev(hw), torch.full((P,), 77, dtype=torch.int8, device="cuda")
+    x, werr = dev(hx), dev(hw)
+    wcodes = torch.full((P,), 77, dtype=torch.int8 if gcfg.k_x <= 6 else torch.int16, device="cuda")
     q = QAdam(gcfg, seg.tolist(), N)
     codes = [torch.full((q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(N)]
     scales = [torch.full((L,), -1.0, device="cuda") for _ in range(N)]
@@ -49,7 +52,7 @@ def _step(sizes, N, call, seed):
         out = oracle.step_w(ocfg, seg, 1, 1e-3, 0.999, hg, he, hm, hv, hx, hw, want_tie=False)
     else:
         out = oracle.step_s(ocfg, seg, 1, 1e-3, 0.999, hg, he, hx, hm[0], hv[0], hw, want_tie=False)
-    assert q.get_status() == 0
+    assert q.get_status() == status
     for i in range(N):
         assert _same(scales[i], out["scales"][i]) and _same(codes[i], out["words"][i]) and _same(e[i], he[i]), (call, i)
     assert all(_same(a, b) for a, b in zip(m + v + [x, werr, wcodes], hm + hv + [hx, hw, out["wcodes"]])), call

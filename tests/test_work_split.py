@@ -136,6 +136,33 @@ def test_scale_pass_has_a_workgroup_for_every_tile(tmp_path):
     CHECK(!scan_fits(scan_items(shape(kMaxTiles - 1, 1, false))), "the largest list");""")
 
 
+def test_short_layers_have_a_workgroup_that_holds_them(tmp_path):
+    _run(tmp_path, """
+    const int counts[] = {0, 1, 255, 256, 319, 320, 2047, 2048, 1 << 20, (1 << 24) - 4097, (1 << 24) - 1};
+    const int holds[kShortSizes] = {256, 1024, 4096}, threads[kShortSizes] = {64, 256, 256};
+    int taken = 0;
+    for (int a : counts) for (int b : counts) for (int c : counts) for (int longer : {0, 5}) for (int N : {1, 8, 9, 32}) {
+        const long long n = (long long)a + b + c;
+        if (n + longer >= kMaxTiles) continue;
+        ShortLayers have{};
+        have.num[0] = a; have.num[1] = b; have.num[2] = c;
+        const ShortLayers s = short_layers_apart(have, n + longer, N);
+        CHECK((long long)s.num[0] + s.num[1] + s.num[2] == (s.any() ? n : 0), "%d %d %d", a, b, c);
+        if (!s.any()) continue;
+        ++taken;
+        int left[kShortSizes] = {s.num[0], s.num[1], s.num[2]};
+        for (int k = 0; k < kShortSizes; ++k) {
+            CHECK(s.as[k] >= k && holds[s.as[k]] >= holds[k], "%d %d %d", a, b, c);
+            left[s.as[k]] -= have.num[k];
+            const Items I = layer_items(s.num[k]);
+            CHECK((unsigned long long)wave_blocks(I) * threads[k] < (1ull << 32) && wave_blocks(I) >= (unsigned)s.num[k], "%d", s.num[k]);
+        }
+        CHECK(!left[0] && !left[1] && !left[2], "%d %d %d", a, b, c);
+    }
+    CHECK(taken > 100, "%d", taken);
+    for (int len = 1; len <= kTileElems; ++len) CHECK(len <= holds[short_size(len)], "%d", len);""")
+
+
 def test_flat_launches_cover_the_longest_vector(tmp_path):
     """Vectors have up to 2^36 elements (tiles of 4096 below 2^24); x counts work-items below 2^32, y stays below 2^16."""
     _run(tmp_path, """
