@@ -28,6 +28,7 @@ struct qadam_ctx {
     int32_t*  d_scaled;         // with short layers apart: scaled.seg_tile_begin and scaled.layers, one behind the other
     const Tile* short_layers;
     ShortLayers apart;
+    ListShape short_shape[kShortSizes];
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
     uint32_t* d_tile_max;       // [num_workers][num_tiles * pieces of a tile in variant W's first pass]
@@ -121,7 +122,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
-    L.scaled = h->scaled; L.short_layers = h->short_layers; L.apart = h->apart;
+    L.scaled = h->scaled; L.short_layers = h->short_layers; L.apart = h->apart; L.short_shape = h->short_shape;
     L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
@@ -315,8 +316,13 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
                 sample_tiles.push_back(h->scaled.shape.num_tiles);
             }
             tiles.push_back(t);
-            if (apart) short_layers[h->apart.size_of((int)n)].push_back(t);
-            else if (split) scaled_tiles.push_back(t);
+            if (apart) {
+                const int size = h->apart.size_of((int)n);
+                short_layers[size].push_back(t);
+                add_tiles(h->short_shape[size], 1, t.len);
+            } else if (split) {
+                scaled_tiles.push_back(t);
+            }
             if (!apart) add_tiles(h->scaled.shape, 1, t.len);
             add_tiles(h->shape, 1, t.len);
         }

@@ -87,6 +87,7 @@ struct Launch {
     int32_t     longest_layer;  // tiles of the longest layer
     const Tile* short_layers;   // device: the layers that k_layers does, one tile each, by size; null: none
     ShortLayers apart;          // how many of each size
+    const ListShape* short_shape;   // host, [kShortSizes]: their tiles
     int32_t     num_segments;
     int64_t     num_params;
     double*     tile_sum;   // device, [num_tiles]: per-tile partial sums of the norm diagnostic

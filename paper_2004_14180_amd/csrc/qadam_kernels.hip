@@ -2072,21 +2072,23 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
     return hipGetLastError();
 }
 
-static void fill_server_args(ServerArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W)
+static void fill_server_args(ServerArgs& A, const StepScalars& S, const WorkerPtrs& W)
 {
-    A.tiles = L.tiles; A.S = S;
-    A.items = wave_items(L.shape, 256);
+    A.S = S;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
-static void launch_server_kernel(const Launch& L, const ServerArgs& A)
+static void launch_server_tiles(ServerArgs& A, const Tile* tiles, const ListShape& shape, hipStream_t stream)
 {
+    if (shape.num_tiles == 0) return;
+    A.tiles = tiles;
+    A.items = wave_items(shape, 256);
     const dim3 grid = wave_grid(A.items), block(64);
     const bool four = A.S.num_workers % 4 == 0;
 #define QADAM_LAUNCH_SERVER(MB)                                                                       \
     do {                                                                                              \
-        if (four) hipLaunchKernelGGL((k_server_step<4, MB>), grid, block, 0, L.stream, A);            \
-        else hipLaunchKernelGGL((k_server_step<1, MB>), grid, block, 0, L.stream, A);                 \
+        if (four) hipLaunchKernelGGL((k_server_step<4, MB>), grid, block, 0, stream, A);              \
+        else hipLaunchKernelGGL((k_server_step<1, MB>), grid, block, 0, stream, A);                   \
     } while (0)
     if (A.S.mu_bits == 1) QADAM_LAUNCH_SERVER(1);
     else if (A.S.mu_bits == 2) QADAM_LAUNCH_SERVER(2);
@@ -2094,11 +2096,22 @@ static void launch_server_kernel(const Launch& L, const ServerArgs& A)
 #undef QADAM_LAUNCH_SERVER
 }
 
+static void launch_server_kernel(const Launch& L, ServerArgs& A)
+{
+    if (!server_by_section(L.shape, L.short_layers != nullptr)) {
+        launch_server_tiles(A, L.tiles, L.shape, L.stream);
+        return;
+    }
+    launch_server_tiles(A, L.scaled.tiles, L.scaled.shape, L.stream);
+    const Tile* tiles = L.short_layers;
+    for (int k = 0; k < kShortSizes; tiles += L.apart.num[k], ++k) launch_server_tiles(A, tiles, L.short_shape[k], L.stream);
+}
+
 hipError_t launch_server_step(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp)
 {
     if (L.num_tiles == 0) return hipSuccess;
     ServerArgs A;
-    fill_server_args(A, L, S, W);
+    fill_server_args(A, S, W);
     A.x = sp.x; A.m = sp.m; A.v = sp.v; A.apply_only = 0;
     launch_server_kernel(L, A);
     return hipGetLastError();
@@ -2108,7 +2121,7 @@ hipError_t launch_server_apply_w(const Launch& L, const StepScalars& S, const Wo
 {
     if (L.num_tiles == 0) return hipSuccess;
     ServerArgs A;
-    fill_server_args(A, L, S, W);
+    fill_server_args(A, S, W);
     A.x = x; A.m = nullptr; A.v = nullptr; A.apply_only = 1;
     launch_server_kernel(L, A);
     return hipGetLastError();

@@ -171,6 +171,15 @@ constexpr Items layer_items(int32_t num)
     return I;
 }
 
+// Whether the server takes the section of longer layers and each size of short ones in launches of their own: where one
+// launch would be cut into longer pieces because short tiles among whole ones leave most of them empty.  us, one launch /
+// by section: one layer of 20 M and 20000 of 1000, 4 workers 230 / 165, one worker 215 / 168; 3000 times 4096 and eight of
+// 64, 4 workers 82 / 71; 400 times 9000 and twenty of 64 37.4 / 26.7; 500 times 4096 and sixteen of 64 31.8 / 19.3.
+constexpr bool server_by_section(const ListShape& all, bool split)
+{
+    return split && cut_tiles(all, 256, ((int64_t)1 << 26) - 4096, 1).part_len > 256;
+}
+
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
 // Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
 struct FlatGrid {

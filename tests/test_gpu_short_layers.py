@@ -38,6 +38,13 @@ def test_each_side_of_the_rule(call, sizes, N):
     _step(sizes, N, call, seed=len(sizes) + N)
 
 
+@pytest.mark.parametrize("call", ["calls", "w_calls"])
+@pytest.mark.parametrize("sizes,N", [(([4096] + [64] * 16) * 500, 3), (([9001] + [64] * 20 + [0, 700]) * 400, 4)])
+def test_server_by_section(call, sizes, N):
+    """Lists whose server takes each size of short layers, and the longer ones, in launches of their own."""
+    _step(sizes, N, call, seed=N)
+
+
 @pytest.mark.parametrize("call", ["fused", "calls"])
 def test_infinite_gradients(call):
     """In a layer of each size: its scale is infinite, its codes are zero, the status word says so."""

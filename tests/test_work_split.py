@@ -173,3 +173,13 @@ def test_flat_launches_cover_the_longest_vector(tmp_path):
             CHECK(g.x >= 1 && (unsigned long long)g.x * threads < (1ull << 32) && g.y < (1u << 16), "%lld", n);
             CHECK(blocks * per >= (unsigned long long)n && blocks * per < n + (unsigned long long)g.x * per, "%lld", n);
         }""")
+
+
+def test_server_by_section_where_one_launch_would_be_sparse(tmp_path):
+    _run(tmp_path, """
+    const auto list = [](int whole, int rest, int tiny, int len) {
+        ListShape s{}; add_tiles(s, whole, kTileElems); if (rest) add_tiles(s, whole / 2, rest); add_tiles(s, tiny, len); return s; };
+    CHECK(server_by_section(list(500, 0, 8000, 64), true) && !server_by_section(list(500, 0, 8000, 64), false), "tiles alone");
+    CHECK(server_by_section(list(800, 809, 8400, 64), true), "beside longer layers");
+    CHECK(!server_by_section(list(20000, 0, 0, 1), true) && !server_by_section(list(0, 0, 20000, 1000), true), "uniform");
+    CHECK(!server_by_section(list(30, 0, 330, 64), true), "too few to fill the chip");""")
