@@ -1313,24 +1313,37 @@ struct WeightArgs {
     int64_t n;
 };
 
-// A single wavefront per 256 consecutive elements, one quad per lane, in memory order.  Bound by HBM (x, e^x in; e^x,
-// codes out).  Wavefronts that start and end on their own keep reads and writes mixed: 124 M parameters, 4 workers
+// THREADS * PIECES quads per workgroup, PIECES per lane, in memory order.  Bound by HBM (x, e^x in; e^x, codes out) on long
+// vectors, where wavefronts that start and end on their own keep reads and writes mixed: 124 M parameters, 4 workers
 // through the separate calls, whole step 2302 us with 256 threads and four quads per lane, 2280 with 64 threads and
-// two, 2267 with 64 and one.
-template <int ROUNDING>
-__global__ void __launch_bounds__(64) k_weight_quantize(WeightArgs A)
+// two, 2267 with 64 and one.  Where its data is in the cache the rate at which workgroups start bounds it
+// (quantize_in_cache).
+template <int ROUNDING, int THREADS, int PIECES>
+__global__ void __launch_bounds__(THREADS) k_weight_quantize(WeightArgs A)
 {
     const StepScalars& S = A.S;
-    const int64_t gi = 4 * (flat_index() * 64 + threadIdx.x);
-    if (gi >= A.n) return;
-    const int nvalid = (int)min((int64_t)4, A.n - gi);
-    float xv[4], wi[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wo[4];
-    int j[4];
-    load_v<4>(A.x + gi, nvalid, xv);
-    if (S.weight_ef) load_v<4>(A.werr + gi, nvalid, wi);
-    weight_lane<4, ROUNDING>(S, xv, wi, gi, Shift{}, wo, j);
-    if (A.werr) store_v<4>(A.werr + gi, nvalid, wo);
-    store_wcodes<4>(A.wcodes, S.wcode_bytes, gi, nvalid, j);
+    const int64_t first = 4 * (flat_index() * (THREADS * PIECES) + threadIdx.x);
+    float xv[PIECES][4], wi[PIECES][4];
+    int nvalid[PIECES];
+#pragma unroll
+    for (int k = 0; k < PIECES; ++k) {
+        const int64_t gi = first + k * THREADS * 4;
+        nvalid[k] = (int)max((int64_t)0, min((int64_t)4, A.n - gi));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wi[k][t] = 0.0f;
+        load_v<4>(A.x + gi, nvalid[k], xv[k]);
+        if (S.weight_ef) load_v<4>(A.werr + gi, nvalid[k], wi[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < PIECES; ++k) {
+        if (nvalid[k] == 0) continue;
+        const int64_t gi = first + k * THREADS * 4;
+        float wo[4];
+        int j[4];
+        weight_lane<4, ROUNDING>(S, xv[k], wi[k], gi, Shift{}, wo, j);
+        if (A.werr) store_v<4>(A.werr + gi, nvalid[k], wo);
+        store_wcodes<4>(A.wcodes, S.wcode_bytes, gi, nvalid[k], j);
+    }
 }
 
 struct DequantArgs {
@@ -2133,14 +2146,31 @@ static dim3 flat_grid(int64_t n, int threads, int per_block)
     return dim3(g.x, g.y);
 }
 
+template <int THREADS, int PIECES>
+static void launch_weight_quantizer(const WeightArgs& A, hipStream_t stream)
+{
+    const dim3 grid = flat_grid(A.n, THREADS, THREADS * PIECES * 4), block(THREADS);
+    if (A.S.rounding == 0) hipLaunchKernelGGL((k_weight_quantize<0, THREADS, PIECES>), grid, block, 0, stream, A);
+    else hipLaunchKernelGGL((k_weight_quantize<1, THREADS, PIECES>), grid, block, 0, stream, A);
+}
+
+// Workgroups of 256 threads with four quads per lane where weights, residual and codes stay in the cache and fill the chip
+// with them, else of one wavefront with one.  us, 64 x 1 / 256 x 4: int8 codes, 9 bytes per element, 1 M (2^20) elements
+// 3.6 / 4.3, 2 M 5.9 / 4.8, 3 M 7.3 / 5.5, 4 M 9.4 / 8.3, 6 M 12.7 / 12.1, 8 M 17.4 / 16.8, 11.7 M 23.8 / 25.1; int16 without
+// error feedback, 10 bytes, 2 M 5.5 / 4.1, 4 M 8.3 / 6.6, 8 M 14.6 / 12.5.
+static bool quantize_in_cache(int64_t n, int code_bytes, bool residual)
+{
+    const int64_t bytes = n * (4 + (residual ? 4 : 0) + code_bytes);
+    return bytes >= (int64_t)16 << 20 && bytes <= (int64_t)96 << 20;
+}
+
 hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const float* x, float* werr, void* wcodes)
 {
     if (L.num_params == 0) return hipSuccess;
     WeightArgs A;
     A.S = S; A.x = x; A.werr = werr; A.wcodes = wcodes; A.n = L.num_params;
-    const dim3 grid = flat_grid(L.num_params, 64, 256), block(64);
-    if (S.rounding == 0) hipLaunchKernelGGL(k_weight_quantize<0>, grid, block, 0, L.stream, A);
-    else hipLaunchKernelGGL(k_weight_quantize<1>, grid, block, 0, L.stream, A);
+    if (quantize_in_cache(A.n, S.wcode_bytes, werr != nullptr)) launch_weight_quantizer<256, 4>(A, L.stream);
+    else launch_weight_quantizer<64, 1>(A, L.stream);
     return hipGetLastError();
 }
 

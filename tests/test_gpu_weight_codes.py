@@ -52,3 +52,24 @@ def test_decoder_each_side_of_its_rule(k_x, half):
             want = (wc.to(torch.float32) * 2.0 ** -(k_x + 1)).to(out.dtype)      # exact, then one rounding
             assert torch.equal(out[:n], want) and (out[n:] == 7).all(), n
             q.close()
+
+
+@pytest.mark.parametrize("k_x,weight_ef,rounding", [(6, 1, 0), (14, 1, 1), (14, 0, 0)])
+def test_quantizer_each_side_of_its_rule(k_x, weight_ef, rounding):
+    """The vector lengths on both sides of the two lines between the weight quantizer's launch shapes (16 and 96 MiB of
+    weights, residual and codes), each with a ragged end."""
+    size = 8 + (1 if k_x <= 6 else 2)
+    gcfg, ocfg = configs(k_x=k_x, weight_ef=weight_ef, rounding=rounding)
+    for line in (16 << 20, 96 << 20):
+        for n in (line // size - 1, line // size + 1, line // size + 4099):
+            rng = np.random.default_rng(n)
+            x = rng.uniform(-0.55, 0.55, n).astype(np.float32)
+            werr = (rng.standard_normal(n, dtype=np.float32) * np.float32(1e-3))
+            q = QAdam(gcfg, [0, n], 1)
+            err = torch.from_numpy(np.concatenate([werr, np.full(16, 7, np.float32)])).cuda()
+            wc = torch.full((n + 16,), 77, dtype=torch.int8 if k_x <= 6 else torch.int16, device="cuda")
+            q.weight_quantize(3, torch.from_numpy(x).cuda(), err[:n], wc[:n])
+            want = oracle.weight_quantize(ocfg, 3, x, werr)
+            assert np.array_equal(wc[:n].cpu().numpy(), want["wcodes"]) and np.array_equal(err[:n].cpu().numpy(), werr), n
+            assert (wc[n:] == 77).all() and (err[n:] == 7).all(), n
+            q.close()
