@@ -2186,11 +2186,11 @@ static void launch_decoder(const Launch& L, const DequantArgs& A)
 // 9.9 / 10.7, 24 M 20.4 / 19.4, 124 M 115 / 94, 400 M 372 / 302; the others (64 x 1) int8 to binary16 2 M 3.7 / 2.8, 4 M
 // 3.7 / 3.9, 11.7 M 6.2 / 8.0, 40 M 20.2 / 21.2, 124 M 60.3 / 59.0, 400 M 197 / 181; int16 to fp32 1 M 2.8 / 2.7, 4 M
 // 4.0 / 6.0, 11.7 M 11.7 / 13.5, 40 M 38.8 / 38.6, 400 M 406 / 354; int16 to binary16 4 M 3.8 / 4.0, 8 M 5.1 / 6.1, 11.7 M
-// 8.7 / 8.2, 400 M 252 / 237.
+// 8.7 / 8.2, 400 M 252 / 237.  Outputs written in turn from one stream, int8 to binary16, 2^21 codes (6 MB): 2.9 / 3.6.
 static bool decode_in_cache(int64_t n, int code_bytes, bool half)
 {
     const int64_t bytes = n * (code_bytes + (half ? 2 : 4));
-    return bytes >= (int64_t)8 << 20 && bytes <= (int64_t)(half && code_bytes == 2 ? 40 : 160) << 20;
+    return bytes >= (int64_t)6 << 20 && bytes <= (int64_t)(half && code_bytes == 2 ? 40 : 160) << 20;
 }
 
 hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const void* wcodes, void* xhat, bool half)

@@ -39,10 +39,10 @@ def test_lengths(n, k_x, weight_ef, rounding):
 
 @pytest.mark.parametrize("k_x,half", [(6, False), (6, True), (14, False), (14, True)])
 def test_decoder_each_side_of_its_rule(k_x, half):
-    """The vector lengths on both sides of the two lines between the decoder's launch shapes (8 MiB, and 160 or 40 MiB of
+    """The vector lengths on both sides of the two lines between the decoder's launch shapes (6 MiB, and 160 or 40 MiB of
     codes and output), each with a ragged end."""
     size = (1 if k_x <= 6 else 2) + (2 if half else 4)
-    for line in (8 << 20, (40 if half and k_x > 6 else 160) << 20):
+    for line in (6 << 20, (40 if half and k_x > 6 else 160) << 20):
         for n in (line // size, line // size + 1, line // size + 4099):
             q = QAdam(configs(k_x=k_x)[0], [0, n], 1)
             wt, top = (torch.int8, 64) if k_x <= 6 else (torch.int16, 1 << 14)
