@@ -1592,8 +1592,10 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
     const QgConst c = make_qg(S.k_g);
     const Shift sf = make_shift(t);
     const int num = SERVER ? S.num_workers : 1;
-    // The next worker's loads are under way while this one's maximum is found, where that leaves enough wavefronts per SIMD
-    // (us per step of 4 workers, without / with: 20000 layers of 997 elements 362 / 335, 10000 of 2000 296 / 346).
+    // The next worker's loads, behind the last one's the server's, are under way while this one's maximum is found, where that
+    // leaves enough wavefronts per SIMD (us per step of 4 workers, without / with the next worker's: 20000 layers of 997
+    // elements 362 / 335, 10000 of 2000 296 / 346; with the next worker's / the server's too, 20000 of 1000: 299 / 289, one
+    // worker 160 / 158).
     constexpr bool AHEAD = C == 1;
     const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     int base[C], nvalid[C];
@@ -1621,6 +1623,20 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
             }
         }
     };
+    float x[C][4], m[C][4], v[C][4], wi[C][4];
+    auto load_server = [&]() {
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wi[k][j] = 0.0f;
+            ld<4, SH>(A.sp.x, gi[k], nvalid[k], sf, x[k]);
+            if constexpr (!W) {
+                ld<4, SH>(A.sp.m, gi[k], nvalid[k], sf, m[k]);
+                ld<4, SH>(A.sp.v, gi[k], nvalid[k], sf, v[k]);
+            }
+            if (S.weight_ef && S.k_x >= 0) ld<4, SH>(A.sp.werr, gi[k], nvalid[k], sf, wi[k]);
+        }
+    };
     if constexpr (AHEAD) load_worker(A.first_worker);
     for (int i = A.first_worker; i < A.first_worker + num; ++i) {
         if constexpr (!AHEAD) load_worker(i);
@@ -1642,7 +1658,10 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
                 st<4, SH>(A.vw[i], gi[k], nvalid[k], sf, lv[k]);
             }
         }
-        if (SERVER && AHEAD && i + 1 < num) load_worker(i + 1);
+        if (SERVER && AHEAD) {
+            if (i + 1 < num) load_worker(i + 1);
+            else load_server();
+        }
         uint32_t bits = wave_max_u32(local);
         if constexpr (THREADS > 64) {
             // two sets of parts in turn: whoever writes a set for worker i + 2 has passed the barrier of worker i + 1, behind
@@ -1678,18 +1697,7 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
         write_pad_words(A.codes[i], t, S.code_bits);
     }
     if constexpr (SERVER) {
-        float x[C][4], m[C][4], v[C][4], wi[C][4];
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wi[k][j] = 0.0f;
-            ld<4, SH>(A.sp.x, gi[k], nvalid[k], sf, x[k]);
-            if constexpr (!W) {
-                ld<4, SH>(A.sp.m, gi[k], nvalid[k], sf, m[k]);
-                ld<4, SH>(A.sp.v, gi[k], nvalid[k], sf, v[k]);
-            }
-            if (S.weight_ef && S.k_x >= 0) ld<4, SH>(A.sp.werr, gi[k], nvalid[k], sf, wi[k]);
-        }
+        if constexpr (!AHEAD) load_server();
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             if (base[k] >= t.len) break;

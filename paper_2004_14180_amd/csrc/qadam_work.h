@@ -161,13 +161,16 @@ constexpr ShortLayers short_layers_apart(const ShortLayers& have, int64_t num_ti
     return s;
 }
 
-// their workgroups, in the runs of wave_items
+// Their workgroups, in runs of up to 32 per XCD: long enough for the scales of neighbours to meet in a line of one L2, and no
+// longer, since every layer of a run is as many bytes of every stream that the XCDs drift apart by.  us per step, runs of 1 /
+// 8 / 32 / 256: 20000 layers of 1000 elements, 4 workers 300 / 288 / 290 / 303, one worker 164 / 158 / 158 / 166; 100000 of
+// 100, one worker 139 / 127 / 127 / 126.
 constexpr Items layer_items(int32_t num)
 {
     Items I{};
     I.cut = Cut{1, kTileElems};
     I.count = (uint32_t)num;
-    while (I.run_shift < 8 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
+    while (I.run_shift < 5 && (I.count >> I.run_shift) >= 128) ++I.run_shift;
     return I;
 }
 
