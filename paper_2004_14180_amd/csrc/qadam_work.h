@@ -222,9 +222,12 @@ constexpr unsigned reduce_blocks(int num_segments, int num)
 // 256 26.4 / 27.9; sixteen: 16 24.1 / 29.2.  Eight layers, one worker: 1024 tiles (128 each) 46.1 / 41.6; 64 layers of 4
 // tiles, four workers 26.6 / 25.9.  Four maxima per tile (variant W), one layer, one worker: 128 tiles (512) 12.7 / 12.2,
 // 192 (768) 14.0 / 14.7, 512 26.1 / 33.2, 1024 46.0 / 69.0.  One worker's call: 512 tiles 14.4 / 14.3, 1024 20.8 / 24.9.
+// One worker, layers with a maximum or none for each lane: 1500 tiles in layers of 15, its call 24.6 / 23.9, its step 60.0 /
+// 56.8; 1488 in layers of 62, 24.6 / 23.5 and 62.3 / 59.0; 4000 in layers of 25, call 53.2 / 57.5.
 constexpr bool fold_in_quantizer(int num_tiles, int longest, int num_workers)
 {
-    return num_workers <= 10 && longest <= (1536 >> num_workers) && (int64_t)num_tiles * num_workers <= 1024;
+    const int most = num_workers == 1 && longest <= 64 ? 2048 : 1024;
+    return num_workers <= 10 && longest <= (1536 >> num_workers) && (int64_t)num_tiles * num_workers <= most;
 }
 
 }  // namespace qadam

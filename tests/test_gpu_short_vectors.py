@@ -24,6 +24,14 @@ def test_each_side_of_the_fold(N, tiles, fused):
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
+@pytest.mark.parametrize("layers,tiles", [(32, 64), (33, 64), (31, 65), (1024, 2), (1025, 2)])
+@pytest.mark.parametrize("fused", [True, False])
+def test_one_worker_each_side_of_the_fold_of_short_layers(layers, tiles, fused):
+    """Twice the tiles for one worker where no layer has more than 64 of them."""
+    rep, st = _custom([tiles * T - 6] * layers, 1, 1, seed=layers + tiles, fused=fused)
+    assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+
+
 @pytest.mark.parametrize("N,longest,others", [(1, 768, 0), (1, 769, 0), (1, 700, 324), (1, 700, 325), (2, 384, 0), (2, 385, 0),
                                               (4, 96, 160), (4, 97, 0), (10, 1, 101), (10, 1, 102), (11, 1, 50)])
 @pytest.mark.parametrize("fused", [True, False])
