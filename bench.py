@@ -33,8 +33,14 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0      # MI355X published HBM3E bandwidth
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2004_14180_amd", "csrc", "qadam_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2004_14180_amd", "csrc")
+KERNEL_SOURCES = [os.path.join(CSRC, name) for name in ("qadam_kernels.hip", "qadam_work.h")]
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "fused_step_gpt1p3b_pmc_traffic.txt")
+
+
+def kernel_source_sha256():
+    """SHA-256 of the kernels and of the header that divides their work, one behind the other."""
+    return hashlib.sha256(b"".join(open(p, "rb").read() for p in KERNEL_SOURCES)).hexdigest()
 
 
 def measured_traffic_bytes(key="k_fused_traffic_bytes_per_launch"):
@@ -47,7 +53,7 @@ def measured_traffic_bytes(key="k_fused_traffic_bytes_per_launch"):
         m_val = re.search(r"^%s:\s*([0-9.eE+]+)" % re.escape(key), text, re.M)
         if not m_sha or not m_val:
             return None
-        if hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest() != m_sha.group(1):
+        if kernel_source_sha256() != m_sha.group(1):
             return None
         return float(m_val.group(1))
     except OSError:
