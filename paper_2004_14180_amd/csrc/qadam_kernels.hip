@@ -1973,7 +1973,8 @@ static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S,
 
 static bool fold_in_quantizer(const Launch& L, int num, int max_per_tile)
 {
-    return !L.empty_layers && !L.short_layers && fold_in_quantizer(L.num_tiles, L.longest_layer * max_per_tile, num);
+    return !L.empty_layers && !L.short_layers
+        && fold_in_quantizer(L.num_tiles, L.num_params, L.longest_layer * max_per_tile, num, max_per_tile);
 }
 
 static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
@@ -2442,7 +2443,7 @@ hipError_t noalloc_quantize_segment(const StepScalars& S, int64_t n, const float
     std::memset(&F, 0, sizeof F);
     F.row = num_tiles; F.per_tile = 1; F.num_segments = 1;
     F.inv_scales = inv_scale; F.err_bound = err_bound; F.bound_factor = residual_bound_factor(S);
-    if (num_tiles > 0 && fold_in_quantizer(num_tiles, num_tiles, 1)) {
+    if (num_tiles > 0 && fold_in_quantizer(num_tiles, n, num_tiles, 1, 1)) {
         F.tile_max = tile_max;
     } else {
         ScaleArgs R;

@@ -216,18 +216,23 @@ constexpr unsigned reduce_blocks(int num_segments, int num)
 }
 
 // Whether the quantizing kernel folds the maxima itself: every wavefront those of its layer (`longest`: most maxima of one
-// layer) for each of its workers, one after the other, which saves the launch of k_reduce_scales, about 2.5 us with its gap.
-// GPU time of a step, us, with the launch / folded.  One layer, one worker: 512 tiles 26.1 / 24.5, 768 36.5 / 35.6, 1024
-// 47.0 / 50.3; two workers: 192 tiles 15.7 / 15.1, 384 27.2 / 24.2, 512 33.7 / 34.4; four: 64 13.3 / 12.8, 128 16.2 / 17.6,
-// 256 26.4 / 27.9; sixteen: 16 24.1 / 29.2.  Eight layers, one worker: 1024 tiles (128 each) 46.1 / 41.6; 64 layers of 4
-// tiles, four workers 26.6 / 25.9.  Four maxima per tile (variant W), one layer, one worker: 128 tiles (512) 12.7 / 12.2,
-// 192 (768) 14.0 / 14.7, 512 26.1 / 33.2, 1024 46.0 / 69.0.  One worker's call: 512 tiles 14.4 / 14.3, 1024 20.8 / 24.9.
-// One worker, layers with a maximum or none for each lane: 1500 tiles in layers of 15, its call 24.6 / 23.9, its step 60.0 /
-// 56.8; 1488 in layers of 62, 24.6 / 23.5 and 62.3 / 59.0; 4000 in layers of 25, call 53.2 / 57.5.
-constexpr bool fold_in_quantizer(int num_tiles, int longest, int num_workers)
+// layer, `per_tile` to a tile) for each of its workers, one after the other, which saves the launch of k_reduce_scales.  A
+// step this short is bound by what the host enqueues, and the launch is 2.7 us of it; on the GPU alone (a captured graph) the
+// fold is level up to about four workers and the slower way beyond (sixteen of 16 tiles 24.1 / 29.2), so it goes as far as
+// the host's time covers that.  us per step in a loop of calls, with the launch / folded, one layer.  One maximum per tile:
+// one worker, 512 tiles 22.3 / 21.3; two, 256 20.1 / 17.4, 512 29.5 / 28.3; four, 128 22.6 / 20.1, 256 22.6 / 22.7; eight, 64
+// 27.9 / 25.2, 128 27.7 / 25.1; sixteen, 64 37.8 / 35.1, 128 42.7 / 46.0.  Four maxima per tile (variant W): one worker, 256
+// tiles 19.9 / 17.2, 512 25.4 / 26.8, 1024 46.5 / 52.7; two, 256 22.6 / 22.7, 512 40.6 / 44.4; four, 128 24.8 / 23.1, 256
+// 36.7 / 38.6; eight, 64 32.7 / 30.2, 128 38.5 / 41.7; sixteen, 32 48.6 / 46.0, 64 49.6 / 51.1.  Lists: eight workers, 45
+// tiles of 16 layers 27.9 / 25.1; variant W, 78 of 77 33.7 / 30.9.
+// GPU time of one worker's call, one layer: 512 tiles 14.4 / 14.3, 1024 20.8 / 24.9.  One worker, layers with a maximum or none
+// for each lane: 1500 tiles in layers of 15, its call 24.6 / 23.9, its step 60.0 / 56.8; 1488 in layers of 62, 24.6 / 23.5
+// and 62.3 / 59.0; 4000 in layers of 25, call 53.2 / 57.5.
+constexpr bool fold_in_quantizer(int num_tiles, int64_t num_elems, int longest, int num_workers, int per_tile)
 {
-    const int most = num_workers == 1 && longest <= 64 ? 2048 : 1024;
-    return num_workers <= 10 && longest <= (1536 >> num_workers) && (int64_t)num_tiles * num_workers <= most;
+    if (num_workers == 1 && longest <= 64) return num_tiles <= 2048;
+    return (num_tiles <= 128 || (int64_t)num_tiles * num_workers <= 1024) && longest <= (per_tile == 1 ? 768 : 1024)
+        && num_elems * num_workers <= (int64_t)1 << (per_tile == 1 ? 22 : 21);
 }
 
 }  // namespace qadam

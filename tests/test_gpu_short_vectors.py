@@ -33,10 +33,11 @@ def test_one_worker_each_side_of_the_fold_of_short_layers(layers, tiles, fused):
 
 
 @pytest.mark.parametrize("N,longest,others", [(1, 768, 0), (1, 769, 0), (1, 700, 324), (1, 700, 325), (2, 384, 0), (2, 385, 0),
-                                              (4, 96, 160), (4, 97, 0), (10, 1, 101), (10, 1, 102), (11, 1, 50)])
+                                              (2, 512, 0), (2, 513, 0), (4, 96, 160), (4, 97, 0), (10, 1, 101), (10, 1, 102),
+                                              (11, 1, 50), (16, 64, 0), (16, 65, 0), (16, 1, 126)])
 @pytest.mark.parametrize("fused", [True, False])
 def test_each_side_of_the_longest_folded_layer(N, longest, others, fused):
-    """The limits on the longest layer's tiles (halved with every worker more) and on tiles times workers."""
+    """The limits on the longest layer's tiles, on tiles times workers and on elements times workers."""
     sizes = [3] + [T - 1] * (others - 1) + [longest * T - 6] if others else [longest * T - 6]
     rep, st = _custom(sizes, N, 2, seed=longest + N, fused=fused, trust=2)
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
@@ -48,7 +49,8 @@ def test_worker_moments_each_side_of_the_fold(N, tiles):
     _worker_moments(N, tiles, [(tiles - 5) * T, 1000, T + 1025, 3, 2049])
 
 
-@pytest.mark.parametrize("N,tiles", [(1, 192), (1, 193), (2, 96), (2, 97), (4, 24), (4, 25)])
+@pytest.mark.parametrize("N,tiles", [(1, 192), (1, 193), (2, 96), (2, 97), (4, 24), (4, 25), (1, 256), (1, 257), (2, 250), (2, 256),
+                                     (8, 58), (8, 64)])
 def test_worker_moments_each_side_of_the_longest_folded_layer(N, tiles):
     _worker_moments(N, tiles, [tiles * T, 1000, T + 1025, 3, 2049])
 
