@@ -2224,7 +2224,9 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
 // LDS that a workgroup of the main pass reserves and does not use: it holds the pass to 16 wavefronts per CU, each
 // with the loads of four workers in flight.  More of them only spread the accesses over more DRAM pages, fewer
 // leave the memory idle (1.3 G parameters, 4 workers, whole step: 20 per CU 22.0 ms, 16 21.7, 12 21.6, 8 22.5;
-// 124 M, 8 workers: 3.95 / 3.89 / 3.87 / 4.09; 11.7 M, 4 workers: 229 / 227 / 236 / 250 us).
+// 124 M, 8 workers: 3.95 / 3.89 / 3.87 / 4.09; 11.7 M, 4 workers: 229 / 227 / 236 / 250 us).  Variant W, which has one load
+// per worker in flight where the other has two, reserves none (16 wavefronts / as many as fit, 28: 1.3 G, 8 workers, the pass
+// 18.99 / 17.41 ms; whole step of 4 workers, 11.7 M 327 / 316 us, 24 M 702 / 681, 64 M 1821 / 1768).
 constexpr unsigned kMainPassLds = 10240;
 
 static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
@@ -2240,11 +2242,12 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     }
     A.items = wave_items(L.scaled.shape, 256);
     const dim3 grid = wave_grid(A.items), block(64);
+    const unsigned lds = variant_w ? 0u : kMainPassLds;
     // U = 4, or the variant that folds the scales, one worker at a time
 #define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
     do {                                                                                                           \
         if (A.fold.tile_max) hipLaunchKernelGGL((k_fused<R, 1, WV>), grid, block, 0, L.stream, A);                 \
-        else hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, kMainPassLds, L.stream, A);                      \
+        else hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, lds, L.stream, A);                              \
     } while (0)
     if (S.rounding == 0) {
         if (variant_w) QADAM_LAUNCH_FUSED(0, true); else QADAM_LAUNCH_FUSED(0, false);
