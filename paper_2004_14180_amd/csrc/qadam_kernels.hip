@@ -38,6 +38,7 @@
 
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "qadam_internal.h"
 
@@ -204,6 +205,47 @@ __device__ __forceinline__ float qg_decode_planes(const uint32_t (&w)[4], uint32
     qa = mu > 0u ? qa : 0.0f;
     return u2f(f2u(qa) | sign);
 }
+
+// Four consecutive elements of a lane at once, added to acc: q_j = s * L_j with L_j = +-2^(mu-1-k_g) or 0, which binary16
+// holds in its upper byte.  The plane bits of the four elements are spread to the four bytes of a word, one byte permute
+// looks the four levels up, and since s * L_j is exact for the scales this is used with (fast_scale), the sum with one
+// rounding, acc + s * L_j, is what a multiplication and an addition give.  18 vector instructions for four elements of 3-bit
+// codes where bit by bit it is 40.
+struct Levels {
+    uint32_t lo, hi;       // byte mu: upper byte of binary16 2^(mu-1-k_g), mu = 0..3 and 4..7
+};
+
+__device__ __forceinline__ Levels make_levels(int k_g)
+{
+    uint64_t b = 0;
+#pragma unroll
+    for (int mu = 1; mu < 8; ++mu) b |= (uint64_t)((14 + mu - k_g) << 2) << (8 * mu);
+    return {(uint32_t)b, (uint32_t)(b >> 32)};
+}
+
+__device__ __forceinline__ uint32_t spread4(uint32_t word, uint32_t pos)
+{
+    return __umul24(__builtin_amdgcn_ubfe(word, pos, 4u), 0x204081u) & 0x01010101u;
+}
+
+template <int MU_BITS>
+__device__ __forceinline__ void add_decoded(const uint32_t (&w)[4], uint32_t pos, float s, const Levels& T, float (&acc)[4])
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    uint32_t mu = spread4(w[0], pos);
+#pragma unroll
+    for (int k = 1; k < MU_BITS; ++k) mu |= spread4(w[k], pos) << k;
+    const uint32_t l = __builtin_amdgcn_perm(T.hi, T.lo, mu) | (spread4(w[MU_BITS], pos) << 7);
+    const h2 a = __builtin_bit_cast(h2, __builtin_amdgcn_perm(0u, l, 0x010c000cu));
+    const h2 b = __builtin_bit_cast(h2, __builtin_amdgcn_perm(0u, l, 0x030c020cu));
+    acc[0] = __builtin_fmaf((float)a.x, s, acc[0]);
+    acc[1] = __builtin_fmaf((float)a.y, s, acc[1]);
+    acc[2] = __builtin_fmaf((float)b.x, s, acc[2]);
+    acc[3] = __builtin_fmaf((float)b.y, s, acc[3]);
+}
+
+// scales from 2^-100 to 2^100: s * 2^-6 .. s * 2^6 are normal numbers
+__device__ __forceinline__ bool fast_scale(float s) { return f2u(s) - (27u << 23) <= (200u << 23); }
 
 // ------------------------------------------------------------------------------------------------
 // Bit-plane packing.  A lane holds the codes of elements 4*lane..4*lane+3 of a 256-element
@@ -1220,84 +1262,187 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
     if ((int)threadIdx.x < ((used + 3) & ~3) - used) A.codes[used + threadIdx.x] = 0u;
 }
 
-// ---- server side alone (qadam_server_step) -------------------------------------------------------
+// ---- server side alone (qadam_server_step, qadam_server_apply_w) ---------------------------------
 struct ServerArgs {
     const Tile* tiles;
     Items items;
-    StepScalars S;
-    float* x; float* m; float* v;
+    StepScalars S;          // k_x < 0: no weight codes
+    ServerPtrs sp;
     const uint32_t* codes[QADAM_MAX_WORKERS];
     const float* scales[QADAM_MAX_WORKERS];
-    int apply_only;         // variant W: x <- x - mean_i q_i, no moments
 };
 
-// U = number of workers whose code words are loaded together (N must be a multiple of U);
-// MU_BITS = bits of the level index (code bits minus the sign)
-template <int V, int U, int MU_BITS, bool SH = false>
-__device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, int part_begin, int part_len)
+// Server arithmetic of one lane's elements, from the sum of the workers' messages to the weight codes, and its stores.
+// W: the server only subtracts the mean message, m and v are not used.
+template <int ROUNDING, int V, bool W, bool SH>
+__device__ __forceinline__ void server_lane(const StepScalars& S, const ServerPtrs& sp, const float (&acc)[V], float (&xv)[V],
+                                            float (&mv)[V], float (&vv)[V], const float (&wi)[V], int64_t gi, int nvalid,
+                                            const Shift& sf)
 {
-    constexpr int WAVE_ELEMS = 64 * V;
-    const StepScalars& S = A.S;
-    const int lane = threadIdx.x;
-    const int part_end = min(t.len, part_begin + part_len);
-    const QgConst c = make_qg(S.k_g);
-    const Shift sf = make_shift(t);
-    for (int base = part_begin; base < part_end; base += WAVE_ELEMS) {
-        const int off = base + lane * V;
-        const int nvalid = min(max(t.len - off, 0), V);
-        if (nvalid == 0) continue;
-        const int64_t gi = t.start + off;
-        const int64_t cw = t.code_word + (int64_t)(base >> 5) * S.code_bits;
-        // server state first: its latency hides behind the decoding
-        float xv[V], mv[V], vv[V];
-        ld<V, SH>(A.x, gi, nvalid, sf, xv);
-        if (!A.apply_only) {
-            ld<V, SH>(A.m, gi, nvalid, sf, mv);
-            ld<V, SH>(A.v, gi, nvalid, sf, vv);
+    if constexpr (W) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) xv[j] = xv[j] - mean_over_workers(S, acc[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const float u = adam_step(S, mean_over_workers(S, acc[j]), mv[j], vv[j]);
+            xv[j] = xv[j] - u;
         }
-        float acc[V];
-#pragma unroll
-        for (int j = 0; j < V; ++j) acc[j] = 0.0f;
-        for (int i0 = 0; i0 < S.num_workers; i0 += U) {
-            uint32_t w[U][4];
-            uint32_t pos = 0;
-#pragma unroll
-            for (int u = 0; u < U; ++u) pos = load_planes<V, MU_BITS>(A.codes[i0 + u] + cw, lane, w[u]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float s = A.scales[i0 + u][t.seg];
-#pragma unroll
-                for (int j = 0; j < V; ++j)
-                    acc[j] = acc[j] + qg_decode_planes<MU_BITS>(w[u], pos + (uint32_t)j, s, c);
-            }
-        }
-        if (A.apply_only) {
-#pragma unroll
-            for (int j = 0; j < V; ++j) xv[j] = xv[j] - mean_over_workers(S, acc[j]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const float u = adam_step(S, mean_over_workers(S, acc[j]), mv[j], vv[j]);
-                xv[j] = xv[j] - u;
-            }
-            st<V, SH>(A.m, gi, nvalid, sf, mv);
-            st<V, SH>(A.v, gi, nvalid, sf, vv);
-        }
-        st<V, SH>(A.x, gi, nvalid, sf, xv);
+        st<V, SH>(sp.m, gi, nvalid, sf, mv);
+        st<V, SH>(sp.v, gi, nvalid, sf, vv);
+    }
+    st<V, SH>(sp.x, gi, nvalid, sf, xv);
+    if (S.k_x >= 0) {                                    // else Q_x is the identity
+        float wo[V];
+        int jc[V];
+        weight_lane<V, ROUNDING, SH>(S, xv, wi, gi, sf, wo, jc);
+        if (sp.werr) st<V, SH>(sp.werr, gi, nvalid, sf, wo);
+        stw<V, SH>(sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
     }
 }
 
-template <int U, int MU_BITS>
+constexpr int kServerElems = 256;
+
+// LDS that a workgroup of the server reserves at least, which holds the pass to 26 wavefronts per CU, or to 20 where the code
+// words take no LDS: as in the main pass, more of them only spread the accesses over more DRAM pages.  us, as many as fit / 26
+// or 20 / 16 wavefronts: 2^26 elements, one worker 300 / 266 / 264, two 304 / 269 / 265, four 306 / 274 / 272, eight 304 / 286
+// / 299, sixteen 373 / 377 / 385; 2^24, eight workers 81.0 / 78.3 / 83.7; 2^22, four 23.0 / 23.0 / 23.4.
+constexpr unsigned server_lds(int held) { return held ? 8192 : 6144; }
+
+// One word per lane from memory to LDS, lane n's to dst[n], without a register in between.  wait_for_loads before it is read.
+__device__ __forceinline__ void load_to_lds(const uint32_t* src, uint32_t* dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)src,
+                                     (__attribute__((address_space(3))) uint32_t*)dst, 4, 0, 0);
+}
+
+__device__ __forceinline__ void wait_for_loads()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ void wait_for_lds()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);         // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
+// One worker's message.  The decoded value of a code has two forms, with the same bits (add_decoded).
+template <int MU_BITS, bool FAST>
+__device__ __forceinline__ void add_message(const uint32_t (&w)[4], float s, int k_g, float (&acc)[4])
+{
+    const uint32_t pos = (threadIdx.x & 7) * 4u;
+    if constexpr (FAST) {
+        add_decoded<MU_BITS>(w, pos, s, make_levels(k_g), acc);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = acc[j] + qg_decode_planes<MU_BITS>(w, pos + (uint32_t)j, s, make_qg(k_g));
+    }
+}
+
+// One turn of a wavefront: 256 elements of a tile from `base`.  MU_BITS: bits of the level index (code bits minus the sign).
+// FULL: the turn is whole, so that no access needs a guard.  U: the number of workers, whose code words and scales are held
+// in registers; 0: any number of workers, whose words go through LDS, so that one narrow load per worker brings what the lanes
+// of a group share and all workers' loads are under way at once.  Bound by memory.  Loads of every lane's own, four workers (or
+// one) at a time, and values decoded bit by bit / this way, us: 2^24 elements, three workers 82.1 / 73.1, five 89.2 / 79.5, eight
+// 91.7 / 81.5, sixteen 133 / 92; 2^26, sixteen 452 / 372; 2^28, sixteen 1640 / 1440.  Four workers, whose loads were issued
+// together before: 274 / 274 at 2^26.  Through LDS / held: 51 k elements, four workers 3.9 / 3.7; 2^22, three 24.5 / 22.9.
+template <int MU_BITS, int U, bool W, bool SH, bool FULL>
+__device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, int base)
+{
+    constexpr int CODE_BITS = MU_BITS + 1, WORDS = 8 * CODE_BITS;
+    const StepScalars& S = A.S;
+    const int lane = threadIdx.x;
+    const int N = S.num_workers;
+    const Shift sf = make_shift(t);
+    const int off = base + lane * 4;
+    const int nvalid = FULL ? 4 : min(max(t.len - off, 0), 4);
+    const int64_t gi = t.start + off, cw = t.code_word + (int64_t)(base >> 5) * CODE_BITS;
+    float xv[4], mv[4], vv[4], wi[4], acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { wi[j] = 0.0f; acc[j] = 0.0f; }
+    // Everything this turn reads is under way before the first of it is used.
+    const float* scales = nullptr;
+    if constexpr (U == 0) {
+        wait_for_lds();                         // what the turn before read
+        scales = A.scales[min(lane, N - 1)];
+    }
+    ld<4, SH>(A.sp.x, gi, nvalid, sf, xv);
+    if constexpr (!W) {
+        ld<4, SH>(A.sp.m, gi, nvalid, sf, mv);
+        ld<4, SH>(A.sp.v, gi, nvalid, sf, vv);
+    }
+    if constexpr (U == 0) {
+        // the scales, worker n's in lane n, and the code words, which go straight to LDS
+        extern __shared__ uint32_t words[];     // [N][WORDS]
+        const float scale = scales[t.seg];
+        // the words behind a tile's last group may lie behind the end of the buffer
+        if (lane < WORDS && (FULL || base + lane / CODE_BITS * 32 < t.len)) {
+#pragma unroll 4
+            for (int i = 0; i < N; ++i) load_to_lds(A.codes[i] + cw + lane, words + i * WORDS);
+        }
+        wait_for_loads();
+        const bool fast = __builtin_amdgcn_ballot_w64(!fast_scale(scale)) == 0;
+        auto add_all = [&](auto is_fast) {
+            const uint32_t* group = words + (lane >> 3) * CODE_BITS;
+            for (int i = 0; i < N; ++i, group += WORDS) {
+                uint32_t w[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) w[b] = b < CODE_BITS ? group[b] : 0u;
+                const float s = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(scale), i));
+                add_message<MU_BITS, decltype(is_fast)::value>(w, s, S.k_g, acc);
+            }
+        };
+        if (fast) add_all(std::true_type{});
+        else add_all(std::false_type{});
+    } else {
+        uint32_t w[U][4];
+        float s[U];
+        bool fast = true;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) w[u][b] = 0u;
+            if (FULL || nvalid > 0) load_planes<4, MU_BITS>(A.codes[u] + cw, lane, w[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            s[u] = A.scales[u][t.seg];
+            fast = fast && fast_scale(s[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (fast) add_message<MU_BITS, true>(w[u], s[u], S.k_g, acc);
+            else add_message<MU_BITS, false>(w[u], s[u], S.k_g, acc);
+        }
+    }
+    if (!FULL && nvalid == 0) return;
+    server_lane<0, 4, W, SH>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
+}
+
+// LONG: pieces of more than one turn.
+template <int MU_BITS, int U, bool W, bool LONG>
 __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 {
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
     const Tile t = A.tiles[item / A.items.cut.parts];
-    const int part_len = A.items.cut.part_len;
-    const int part_begin = (int)(item % A.items.cut.parts) * part_len;
-    if (part_begin >= t.len) return;
-    if (t.flags & kTileUnaligned) server_part<4, U, MU_BITS, true>(A, t, part_begin, part_len);
-    else server_part<4, U, MU_BITS, false>(A, t, part_begin, part_len);
+    const int part_begin = (int)(item % A.items.cut.parts) * A.items.cut.part_len;
+    const int part_end = LONG ? min(t.len, part_begin + A.items.cut.part_len) : t.len;
+    int base = part_begin;
+    do {
+        if (base >= part_end) return;
+        const bool full = base + kServerElems <= t.len;
+        if (t.flags & kTileUnaligned) {
+            if (full) server_part<MU_BITS, U, W, true, true>(A, t, base);
+            else server_part<MU_BITS, U, W, true, false>(A, t, base);
+        } else {
+            if (full) server_part<MU_BITS, U, W, false, true>(A, t, base);
+            else server_part<MU_BITS, U, W, false, false>(A, t, base);
+        }
+        base += kServerElems;
+    } while (LONG);
 }
 
 // ---- weight quantizer alone (qadam_weight_quantize) ----------------------------------------------
@@ -1427,35 +1572,6 @@ __global__ void __launch_bounds__(THREADS) k_weight_dequantize(DequantArgs A)
                 for (int t = 0; t < E; ++t) if (i + t < A.n) out[t] = xh[t];
             }
         }
-    }
-}
-
-// Server arithmetic of one lane's elements, from the sum of the workers' messages to the weight codes, and its stores.
-// W: the server only subtracts the mean message, m and v are not used.
-template <int ROUNDING, int V, bool W, bool SH>
-__device__ __forceinline__ void server_lane(const StepScalars& S, const ServerPtrs& sp, const float (&acc)[V], float (&xv)[V],
-                                            float (&mv)[V], float (&vv)[V], const float (&wi)[V], int64_t gi, int nvalid,
-                                            const Shift& sf)
-{
-    if constexpr (W) {
-#pragma unroll
-        for (int j = 0; j < V; ++j) xv[j] = xv[j] - mean_over_workers(S, acc[j]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const float u = adam_step(S, mean_over_workers(S, acc[j]), mv[j], vv[j]);
-            xv[j] = xv[j] - u;
-        }
-        st<V, SH>(sp.m, gi, nvalid, sf, mv);
-        st<V, SH>(sp.v, gi, nvalid, sf, vv);
-    }
-    st<V, SH>(sp.x, gi, nvalid, sf, xv);
-    if (S.k_x >= 0) {                                    // else Q_x is the identity
-        float wo[V];
-        int jc[V];
-        weight_lane<V, ROUNDING, SH>(S, xv, wi, gi, sf, wo, jc);
-        if (sp.werr) st<V, SH>(sp.werr, gi, nvalid, sf, wo);
-        stw<V, SH>(sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
     }
 }
 
@@ -2094,59 +2210,64 @@ hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const W
     return hipGetLastError();
 }
 
-static void fill_server_args(ServerArgs& A, const StepScalars& S, const WorkerPtrs& W)
+static void fill_server_args(ServerArgs& A, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp)
 {
-    A.S = S;
+    A.S = S; A.sp = sp;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
+template <int U, bool W, bool LONG>
+static void launch_server_pieces(const ServerArgs& A, hipStream_t stream)
+{
+    const dim3 grid = wave_grid(A.items), block(64);
+    const unsigned need = U ? 0u : (unsigned)(A.S.num_workers * kServerElems / 32 * A.S.code_bits * 4);
+    const unsigned lds = need > server_lds(U) ? need : server_lds(U);
+    if (A.S.mu_bits == 1) hipLaunchKernelGGL((k_server_step<1, U, W, LONG>), grid, block, lds, stream, A);
+    else if (A.S.mu_bits == 2) hipLaunchKernelGGL((k_server_step<2, U, W, LONG>), grid, block, lds, stream, A);
+    else hipLaunchKernelGGL((k_server_step<3, U, W, LONG>), grid, block, lds, stream, A);
+}
+
+template <bool W>
 static void launch_server_tiles(ServerArgs& A, const Tile* tiles, const ListShape& shape, hipStream_t stream)
 {
     if (shape.num_tiles == 0) return;
     A.tiles = tiles;
-    A.items = wave_items(shape, 256);
-    const dim3 grid = wave_grid(A.items), block(64);
-    const bool four = A.S.num_workers % 4 == 0;
-#define QADAM_LAUNCH_SERVER(MB)                                                                       \
-    do {                                                                                              \
-        if (four) hipLaunchKernelGGL((k_server_step<4, MB>), grid, block, 0, stream, A);              \
-        else hipLaunchKernelGGL((k_server_step<1, MB>), grid, block, 0, stream, A);                   \
-    } while (0)
-    if (A.S.mu_bits == 1) QADAM_LAUNCH_SERVER(1);
-    else if (A.S.mu_bits == 2) QADAM_LAUNCH_SERVER(2);
-    else QADAM_LAUNCH_SERVER(3);
-#undef QADAM_LAUNCH_SERVER
+    A.items = wave_items(shape, kServerElems);
+    if (A.items.cut.part_len > kServerElems) launch_server_pieces<0, W, true>(A, stream);
+    else if (A.S.num_workers == 1) launch_server_pieces<1, W, false>(A, stream);
+    else if (A.S.num_workers == 2) launch_server_pieces<2, W, false>(A, stream);
+    else if (A.S.num_workers == 3) launch_server_pieces<3, W, false>(A, stream);
+    else if (A.S.num_workers == 4) launch_server_pieces<4, W, false>(A, stream);
+    else launch_server_pieces<0, W, false>(A, stream);
 }
 
-static void launch_server_kernel(const Launch& L, ServerArgs& A)
+// the server's part alone, of every layer: no weight codes
+template <bool W>
+static hipError_t launch_server_alone(const Launch& L, const StepScalars& S, const WorkerPtrs& W_, const ServerPtrs& sp)
 {
+    if (L.num_tiles == 0) return hipSuccess;
+    ServerArgs A;
+    fill_server_args(A, S, W_, sp);
+    A.S.k_x = -1;
     if (!server_by_section(L.shape, L.short_layers != nullptr)) {
-        launch_server_tiles(A, L.tiles, L.shape, L.stream);
-        return;
+        launch_server_tiles<W>(A, L.tiles, L.shape, L.stream);
+        return hipGetLastError();
     }
-    launch_server_tiles(A, L.scaled.tiles, L.scaled.shape, L.stream);
+    launch_server_tiles<W>(A, L.scaled.tiles, L.scaled.shape, L.stream);
     const Tile* tiles = L.short_layers;
-    for (int k = 0; k < kShortSizes; tiles += L.apart.num[k], ++k) launch_server_tiles(A, tiles, L.short_shape[k], L.stream);
+    for (int k = 0; k < kShortSizes; tiles += L.apart.num[k], ++k)
+        launch_server_tiles<W>(A, tiles, L.short_shape[k], L.stream);
+    return hipGetLastError();
 }
 
 hipError_t launch_server_step(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp)
 {
-    if (L.num_tiles == 0) return hipSuccess;
-    ServerArgs A;
-    fill_server_args(A, S, W);
-    A.x = sp.x; A.m = sp.m; A.v = sp.v; A.apply_only = 0;
-    launch_server_kernel(L, A);
-    return hipGetLastError();
+    return launch_server_alone<false>(L, S, W, sp);
 }
 
 hipError_t launch_server_apply_w(const Launch& L, const StepScalars& S, const WorkerPtrs& W, float* x)
 {
-    if (L.num_tiles == 0) return hipSuccess;
-    ServerArgs A;
-    fill_server_args(A, S, W);
-    A.x = x; A.m = nullptr; A.v = nullptr; A.apply_only = 1;
-    launch_server_kernel(L, A);
-    return hipGetLastError();
+    return launch_server_alone<true>(L, S, W, ServerPtrs{x, nullptr, nullptr, nullptr, nullptr});
 }
 
 static dim3 flat_grid(int64_t n, int threads, int per_block)
