@@ -125,7 +125,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.scaled = h->scaled; L.short_layers = h->short_layers; L.apart = h->apart; L.short_shape = h->short_shape;
     L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
-    L.num_params = h->num_params; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
+    L.num_params = h->num_params; L.code_words = h->code_words; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
     return L;
 }
 

@@ -90,6 +90,7 @@ struct Launch {
     const ListShape* short_shape;   // host, [kShortSizes]: their tiles
     int32_t     num_segments;
     int64_t     num_params;
+    int64_t     code_words;     // of one worker
     double*     tile_sum;   // device, [num_tiles]: per-tile partial sums of the norm diagnostic
     float*      err_bound;  // device, [num_workers][num_segments]: bound on |e| left by the last step
     uint32_t*   thr;        // device, [num_workers][num_segments]: thresholds of the filtered scale pass

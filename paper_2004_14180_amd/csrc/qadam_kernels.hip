@@ -1262,7 +1262,7 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
     if ((int)threadIdx.x < ((used + 3) & ~3) - used) A.codes[used + threadIdx.x] = 0u;
 }
 
-// ---- server side alone (qadam_server_step, qadam_server_apply_w) ---------------------------------
+// ---- server side (qadam_server_step, qadam_server_apply_w, the last launch of a step by worker) ---
 struct ServerArgs {
     const Tile* tiles;
     Items items;
@@ -1307,7 +1307,12 @@ constexpr int kServerElems = 256;
 // words take no LDS: as in the main pass, more of them only spread the accesses over more DRAM pages.  us, as many as fit / 26
 // or 20 / 16 wavefronts: 2^26 elements, one worker 300 / 266 / 264, two 304 / 269 / 265, four 306 / 274 / 272, eight 304 / 286
 // / 299, sixteen 373 / 377 / 385; 2^24, eight workers 81.0 / 78.3 / 83.7; 2^22, four 23.0 / 23.0 / 23.4.
-constexpr unsigned server_lds(int held) { return held ? 8192 : 6144; }
+// With the weights' residual to read as well 20 or 16 are enough (whole step by worker, 26 or 20 / 20 or 16: 2^26 elements,
+// two workers 839 / 824, eight 2103 / 2084; 1.3 G, four 20.15 / 20.04 ms).
+constexpr unsigned server_lds(bool held, bool residual)
+{
+    return held ? (residual ? 10240 : 8192) : (residual ? 8192 : 6144);
+}
 
 // One word per lane from memory to LDS, lane n's to dst[n], without a register in between.  wait_for_loads before it is read.
 __device__ __forceinline__ void load_to_lds(const uint32_t* src, uint32_t* dst)
@@ -1348,7 +1353,7 @@ __device__ __forceinline__ void add_message(const uint32_t (&w)[4], float s, int
 // one) at a time, and values decoded bit by bit / this way, us: 2^24 elements, three workers 82.1 / 73.1, five 89.2 / 79.5, eight
 // 91.7 / 81.5, sixteen 133 / 92; 2^26, sixteen 452 / 372; 2^28, sixteen 1640 / 1440.  Four workers, whose loads were issued
 // together before: 274 / 274 at 2^26.  Through LDS / held: 51 k elements, four workers 3.9 / 3.7; 2^22, three 24.5 / 22.9.
-template <int MU_BITS, int U, bool W, bool SH, bool FULL>
+template <int MU_BITS, int U, int ROUNDING, bool W, bool SH, bool FULL>
 __device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, int base)
 {
     constexpr int CODE_BITS = MU_BITS + 1, WORDS = 8 * CODE_BITS;
@@ -1373,6 +1378,7 @@ __device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, 
         ld<4, SH>(A.sp.m, gi, nvalid, sf, mv);
         ld<4, SH>(A.sp.v, gi, nvalid, sf, vv);
     }
+    if (S.weight_ef && S.k_x >= 0) ld<4, SH>(A.sp.werr, gi, nvalid, sf, wi);
     if constexpr (U == 0) {
         // the scales, worker n's in lane n, and the code words, which go straight to LDS
         extern __shared__ uint32_t words[];     // [N][WORDS]
@@ -1418,11 +1424,11 @@ __device__ __forceinline__ void server_part(const ServerArgs& A, const Tile& t, 
         }
     }
     if (!FULL && nvalid == 0) return;
-    server_lane<0, 4, W, SH>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
+    server_lane<ROUNDING, 4, W, SH>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
 }
 
 // LONG: pieces of more than one turn.
-template <int MU_BITS, int U, bool W, bool LONG>
+template <int MU_BITS, int U, int ROUNDING, bool W, bool LONG>
 __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
 {
     const uint32_t item = wave_item(A.items);
@@ -1435,11 +1441,11 @@ __global__ void __launch_bounds__(64) k_server_step(ServerArgs A)
         if (base >= part_end) return;
         const bool full = base + kServerElems <= t.len;
         if (t.flags & kTileUnaligned) {
-            if (full) server_part<MU_BITS, U, W, true, true>(A, t, base);
-            else server_part<MU_BITS, U, W, true, false>(A, t, base);
+            if (full) server_part<MU_BITS, U, ROUNDING, W, true, true>(A, t, base);
+            else server_part<MU_BITS, U, ROUNDING, W, true, false>(A, t, base);
         } else {
-            if (full) server_part<MU_BITS, U, W, false, true>(A, t, base);
-            else server_part<MU_BITS, U, W, false, false>(A, t, base);
+            if (full) server_part<MU_BITS, U, ROUNDING, W, false, true>(A, t, base);
+            else server_part<MU_BITS, U, ROUNDING, W, false, false>(A, t, base);
         }
         base += kServerElems;
     } while (LONG);
@@ -2195,18 +2201,25 @@ hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const Wor
     return hipGetLastError();
 }
 
-hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker)
+// `num`: workers whose maxima one pass left.  parked: variant W, p lies in the error buffer.
+static void launch_quantizer(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker, int num, bool parked)
 {
-    if (L.scaled.shape.num_tiles == 0) return hipSuccess;
     WorkerArgs A;
     A.tiles = L.scaled.tiles;
     A.status = L.status; A.S = S;
-    A.grad = W.grad[worker]; A.err = W.err[worker]; A.codes = W.codes[worker]; A.scales = W.scales[worker];
-    A.fold = make_fold(L, S, worker, 1, A.grad ? 1 : moment_parts(L));
+    A.grad = parked ? nullptr : W.grad[worker];
+    A.err = W.err[worker]; A.codes = W.codes[worker]; A.scales = W.scales[worker];
+    A.fold = make_fold(L, S, worker, num, parked ? moment_parts(L) : 1);
     A.worker = worker;
     A.seg_len = 0;
     A.items = wave_items(L.scaled.shape, kQuantizeElems);
     launch_quantizer(A, L.stream);
+}
+
+hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker)
+{
+    if (L.scaled.shape.num_tiles == 0) return hipSuccess;
+    launch_quantizer(L, S, W, worker, 1, W.grad[worker] == nullptr);
     return hipGetLastError();
 }
 
@@ -2216,29 +2229,29 @@ static void fill_server_args(ServerArgs& A, const StepScalars& S, const WorkerPt
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i]; }
 }
 
-template <int U, bool W, bool LONG>
+template <int U, int ROUNDING, bool W, bool LONG>
 static void launch_server_pieces(const ServerArgs& A, hipStream_t stream)
 {
     const dim3 grid = wave_grid(A.items), block(64);
     const unsigned need = U ? 0u : (unsigned)(A.S.num_workers * kServerElems / 32 * A.S.code_bits * 4);
-    const unsigned lds = need > server_lds(U) ? need : server_lds(U);
-    if (A.S.mu_bits == 1) hipLaunchKernelGGL((k_server_step<1, U, W, LONG>), grid, block, lds, stream, A);
-    else if (A.S.mu_bits == 2) hipLaunchKernelGGL((k_server_step<2, U, W, LONG>), grid, block, lds, stream, A);
-    else hipLaunchKernelGGL((k_server_step<3, U, W, LONG>), grid, block, lds, stream, A);
+    const unsigned least = server_lds(U != 0, A.S.weight_ef && A.S.k_x >= 0), lds = need > least ? need : least;
+    if (A.S.mu_bits == 1) hipLaunchKernelGGL((k_server_step<1, U, ROUNDING, W, LONG>), grid, block, lds, stream, A);
+    else if (A.S.mu_bits == 2) hipLaunchKernelGGL((k_server_step<2, U, ROUNDING, W, LONG>), grid, block, lds, stream, A);
+    else hipLaunchKernelGGL((k_server_step<3, U, ROUNDING, W, LONG>), grid, block, lds, stream, A);
 }
 
-template <bool W>
+template <int ROUNDING, bool W>
 static void launch_server_tiles(ServerArgs& A, const Tile* tiles, const ListShape& shape, hipStream_t stream)
 {
     if (shape.num_tiles == 0) return;
     A.tiles = tiles;
     A.items = wave_items(shape, kServerElems);
-    if (A.items.cut.part_len > kServerElems) launch_server_pieces<0, W, true>(A, stream);
-    else if (A.S.num_workers == 1) launch_server_pieces<1, W, false>(A, stream);
-    else if (A.S.num_workers == 2) launch_server_pieces<2, W, false>(A, stream);
-    else if (A.S.num_workers == 3) launch_server_pieces<3, W, false>(A, stream);
-    else if (A.S.num_workers == 4) launch_server_pieces<4, W, false>(A, stream);
-    else launch_server_pieces<0, W, false>(A, stream);
+    if (A.items.cut.part_len > kServerElems) launch_server_pieces<0, ROUNDING, W, true>(A, stream);
+    else if (A.S.num_workers == 1) launch_server_pieces<1, ROUNDING, W, false>(A, stream);
+    else if (A.S.num_workers == 2) launch_server_pieces<2, ROUNDING, W, false>(A, stream);
+    else if (A.S.num_workers == 3) launch_server_pieces<3, ROUNDING, W, false>(A, stream);
+    else if (A.S.num_workers == 4) launch_server_pieces<4, ROUNDING, W, false>(A, stream);
+    else launch_server_pieces<0, ROUNDING, W, false>(A, stream);
 }
 
 // the server's part alone, of every layer: no weight codes
@@ -2250,13 +2263,13 @@ static hipError_t launch_server_alone(const Launch& L, const StepScalars& S, con
     fill_server_args(A, S, W_, sp);
     A.S.k_x = -1;
     if (!server_by_section(L.shape, L.short_layers != nullptr)) {
-        launch_server_tiles<W>(A, L.tiles, L.shape, L.stream);
+        launch_server_tiles<0, W>(A, L.tiles, L.shape, L.stream);
         return hipGetLastError();
     }
-    launch_server_tiles<W>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+    launch_server_tiles<0, W>(A, L.scaled.tiles, L.scaled.shape, L.stream);
     const Tile* tiles = L.short_layers;
     for (int k = 0; k < kShortSizes; tiles += L.apart.num[k], ++k)
-        launch_server_tiles<W>(A, tiles, L.short_shape[k], L.stream);
+        launch_server_tiles<0, W>(A, tiles, L.short_shape[k], L.stream);
     return hipGetLastError();
 }
 
@@ -2342,6 +2355,38 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
     return hipGetLastError();
 }
 
+// Whether the whole step runs as one launch per worker and one for the server instead of as one main pass.  The main pass
+// writes no code word that it has to read again, but it has 2N + 4 read and N + 5 written streams open at once; three or four
+// at a time lie in fewer DRAM pages, and the memory gives 6.3 to 6.6 TB/s for 5.2 to 6.3 wherever the buffers lie.  Where the
+// scale pass (variant W: the moments) leaves its data in the cache the streams cost less and the launches more.  us per
+// step, main pass / by worker: one worker of 24 M (2^20) elements 241 / 241, 64 M 656 / 641; 4 of 16 M 323 / 338, 24 M 497 / 498,
+// 32 M 673 / 638, 96 M 2035 / 1901; 8 of 12 M 436 / 444, 16 M 581 / 547, 96 M 3566 / 3238; 16 of 4 M 255 / 301, 8 M 550 / 543,
+// 96 M 6798 / 6002; variant W, 4 of 24 M 726 / 723, 64 M 1964 / 1929, 8 of 12 M 705 / 708, 96 M 5769 / 5588.
+// Two code buffers that overlap would not survive until the server reads them; the main pass reads none.
+static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, bool variant_w)
+{
+    const int64_t n = L.scaled.num_elems;
+    if (variant_w ? keep_parked(n, S.num_workers) : keep_scanned(n, S.num_workers)) return false;
+    for (int i = 1; i < S.num_workers; ++i)
+        for (int k = 0; k < i; ++k)
+            if (W.codes[i] < W.codes[k] + L.code_words && W.codes[k] < W.codes[i] + L.code_words) return false;
+    return true;
+}
+
+static void launch_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
+{
+    for (int i = 0; i < S.num_workers; ++i) launch_quantizer(L, S, W, i, S.num_workers, variant_w);
+    ServerArgs A;
+    fill_server_args(A, S, W, sp);
+    if (S.rounding == 0) {
+        if (variant_w) launch_server_tiles<0, true>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+        else launch_server_tiles<0, false>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+    } else {
+        if (variant_w) launch_server_tiles<1, true>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+        else launch_server_tiles<1, false>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+    }
+}
+
 // LDS that a workgroup of the main pass reserves and does not use: it holds the pass to 16 wavefronts per CU, each
 // with the loads of four workers in flight.  More of them only spread the accesses over more DRAM pages, fewer
 // leave the memory idle (1.3 G parameters, 4 workers, whole step: 20 per CU 22.0 ms, 16 21.7, 12 21.6, 8 22.5;
@@ -2354,6 +2399,10 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
                                    bool variant_w)
 {
     if (L.scaled.shape.num_tiles == 0) return hipSuccess;
+    if (step_by_worker(L, S, W, variant_w)) {
+        launch_by_worker(L, S, W, sp, variant_w);
+        return hipGetLastError();
+    }
     FusedArgs A;
     A.tiles = L.scaled.tiles;
     A.status = L.status; A.S = S; A.sp = sp;

@@ -1,0 +1,91 @@
+"""GPU parity of the whole-step calls where a large vector makes them one launch per worker and one for the server: on both
+sides of the size from which they are, the outputs are those of the separate calls, bit for bit, and on the far side those of
+the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2004_14180_amd import QAdam
+from parity_util import configs
+from test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+N = 16
+LIMIT = (768 << 20) // (8 * N)          # elements up to which the scale pass leaves its data in the cache
+LIMIT_W = (512 << 20) // (4 * N)        # ... and variant W its sums
+
+
+def _bits(t):
+    return t.view(torch.int32) if t.dtype == torch.float32 else t
+
+
+class _State:
+    def __init__(self, sizes, w, one_buffer=False, **cfgkw):
+        self.cfg, _ = configs(**cfgkw)
+        seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        P = int(seg[-1])
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(P)
+        f = lambda s: torch.empty(P, device="cuda").normal_(0.0, s, generator=gen)  # noqa: E731
+        self.q = QAdam(self.cfg, seg.tolist(), N)
+        self.g, self.e = [f(1e-2) for _ in range(N)], [f(1e-3) for _ in range(N)]
+        self.m, self.v = ([f(1e-3) for _ in range(N if w else 1)] for _ in range(2))
+        self.v = [t * t for t in self.v]
+        self.x, self.werr = f(0.02), f(1e-3)
+        self.wcodes = torch.zeros(P, dtype=torch.int8 if self.cfg.k_x <= 6 else torch.int16, device="cuda")
+        words = lambda: torch.full((self.q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda")  # noqa: E731
+        self.codes = [words()] * N if one_buffer else [words() for _ in range(N)]
+        self.scales = [torch.zeros(len(sizes), device="cuda") for _ in range(N)]
+
+    def step(self, t, w, whole):
+        q = self.q
+        if whole and w:
+            q.step_fused_w(t, 1e-3, 0.999, self.g, self.m, self.v, self.e, self.codes, self.scales, self.x, self.werr, self.wcodes)
+        elif whole:
+            q.step_fused(t, 1e-3, 0.999, self.g, self.e, self.codes, self.scales, self.x, self.m[0], self.v[0], self.werr, self.wcodes)
+        elif w:
+            for i in range(N):
+                q.worker_step_w(i, t, 1e-3, 0.999, self.g[i], self.m[i], self.v[i], self.e[i], self.codes[i], self.scales[i])
+            q.server_apply_w(t, self.codes, self.scales, self.x)
+            q.weight_quantize(t, self.x, self.werr, self.wcodes)
+        else:
+            for i in range(N):
+                q.worker_quantize(i, t, self.g[i], self.e[i], self.codes[i], self.scales[i])
+            q.server_step(t, 1e-3, 0.999, self.codes, self.scales, self.x, self.m[0], self.v[0])
+            q.weight_quantize(t, self.x, self.werr, self.wcodes)
+
+    def state(self):
+        return self.e + self.scales + self.m + self.v + [self.x, self.werr, self.wcodes]
+
+
+@pytest.mark.parametrize("w", [False, True])
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=0, k_x=14, weight_ef=0), dict(k_g=4, k_x=6, rounding=1, seed=3)])
+def test_whole_step_gives_the_bits_of_the_separate_calls(w, more, cfgkw):
+    # long and short layers, on and off the 16-byte grid
+    sizes = [4096 * 700, 1001, 70000, 3, 40001]
+    sizes.append((LIMIT_W if w else LIMIT) + more - sum(sizes))
+    a, b = _State(sizes, w, **cfgkw), _State(sizes, w, **cfgkw)
+    for t in (1, 2):
+        a.step(t, w, True)
+        b.step(t, w, False)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+    assert a.q.get_status() == 0
+
+
+def test_a_layer_list_by_worker_against_the_oracle():
+    sizes = [1001, 4096 * 900 + 5, 255, LIMIT - 4096 * 900, 77777, 1]
+    rep, st = _custom(sizes, N, 2, seed=41, trust=2)
+    assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+
+
+@pytest.mark.parametrize("w", [False, True])
+def test_overlapping_code_buffers_do_not_change_the_step(w):
+    """A caller without use for the codes may pass one buffer for all workers."""
+    sizes = [1001, (LIMIT_W if w else LIMIT) + 50000]
+    a, b = _State(sizes, w), _State(sizes, w, one_buffer=True)
+    for t in (1, 2):
+        a.step(t, w, True)
+        b.step(t, w, True)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state(), b.state())), t
