@@ -45,8 +45,8 @@
  *   - Return value: QADAM_OK or a negative error code.  QADAM_EINVAL, QADAM_EALIGN and QADAM_ERANGE come from
  *     checks made before anything is enqueued: the buffers are untouched.  QADAM_EHIP means a kernel launch
  *     was refused by the runtime part way through the call: launches accepted before it still run, so the
- *     buffers of the call are then in an intermediate state (variant S: scales written, state not yet
- *     advanced; variant W: m_i, v_i already advanced and the error buffers holding the parked
+ *     buffers of the call are then in an intermediate state (variant S: scales written, server state not yet
+ *     advanced, the error buffers of some layers and workers perhaps; variant W: m_i, v_i already advanced and the error buffers holding the parked
  *     alpha_t m_i / sqrt(v_i + eps) + e_i instead of e_i) and the step cannot be repeated on them.
  *     Non-finite scales (NaN/Inf in g + e) are data errors: they set a bit in the status word that
  *     qadam_get_status reads; the outputs of that layer are then unspecified (codes stay in range).
@@ -254,6 +254,11 @@ int qadam_weight_dequantize_f16(qadam_handle_t h, const void* wcodes_dev, void* 
  * checked against the bound recorded by the previous step; a violation sets QADAM_STATUS_ERR_BOUND_VIOLATED
  * in the status word.  An integration that runs clean with 3 honours the contract of 1 and 2. */
 int qadam_trust_error_buffers(qadam_handle_t h, int32_t on);
+
+/* Bring-up aid: the workgroups of a layer that fits the chip's registers meet over its scale, and each polls `polls` times for
+ * it before it finds the scale by itself from the whole layer (as happens where other work keeps most of the GPU busy).
+ * 0: always by itself; -1: the default.  No result depends on it, only the time. */
+int qadam_set_scale_polls(qadam_handle_t h, int32_t polls);
 
 /* Placement of a handle's buffers inside ONE caller-allocated block (host arithmetic only; nothing is
  * allocated, no HIP call is made).  Why: the main pass of qadam_step_fused reads 2N+4 and writes N+5 streams at

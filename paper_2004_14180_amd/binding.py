@@ -26,7 +26,7 @@ EXPORTS = [
     "qadam_step_fused", "qadam_worker_step_w", "qadam_server_apply_w", "qadam_step_fused_w", "qadam_weight_dequantize",
     "qadam_weight_dequantize_f16", "qadam_layer_sumsq", "qadam_trust_error_buffers",
     "qadam_get_status", "qadam_last_error", "qadam_profile_enable", "qadam_profile_read",
-    "qadam_quantize_segment_noalloc", "qadam_arena_layout",
+    "qadam_quantize_segment_noalloc", "qadam_arena_layout", "qadam_set_scale_polls",
 ]
 
 
@@ -115,6 +115,7 @@ def load_library():
     lib.qadam_get_status.argtypes = [vp, C.POINTER(_Status), i32, vp]
     lib.qadam_last_error.restype = C.c_char_p
     lib.qadam_profile_enable.argtypes = [vp, i32]
+    lib.qadam_set_scale_polls.argtypes = [vp, i32]
     lib.qadam_profile_read.argtypes = [vp, C.POINTER(_Profile)]
     lib.qadam_quantize_segment_noalloc.argtypes = [i32, i64, vp, vp, vp, vp, vp]
     lib.qadam_arena_layout.argtypes = [vp, C.c_size_t, i32, C.POINTER(_Arena)]
@@ -367,6 +368,10 @@ class QAdam:
         """Opt in to the filtered scale pass (see include/qadam.h for the contract):
         0 off, 1 where it pays, 2 always, 3 full pass plus a check of the contract (status bit 2)."""
         self._check(self._lib.qadam_trust_error_buffers(self._h, int(on)))
+
+    def set_scale_polls(self, polls=-1):
+        """Polls for a layer's scale before a workgroup finds it by itself (results never depend on it); -1: the default."""
+        self._check(self._lib.qadam_set_scale_polls(self._h, int(polls)))
 
     def profile_enable(self, on=True):
         self._check(self._lib.qadam_profile_enable(self._h, int(on)))

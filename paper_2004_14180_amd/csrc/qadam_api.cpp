@@ -29,6 +29,11 @@ struct qadam_ctx {
     const Tile* short_layers;
     ShortLayers apart;
     ListShape short_shape[kShortSizes];
+    Section   rest;             // see Launch
+    Parked    parked;
+    int32_t*  d_rest;           // rest.seg_tile_begin and rest.layers, one behind the other
+    void*     d_parked;         // parked.layers and parked.units
+    int32_t   num_rest_sample_tiles;
     uint32_t* d_status;
     float*    d_inv_scales;     // [num_workers][num_segments]
     uint32_t* d_tile_max;       // [num_workers][num_tiles * pieces of a tile in variant W's first pass]
@@ -122,7 +127,11 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
-    L.scaled = h->scaled; L.short_layers = h->short_layers; L.apart = h->apart; L.short_shape = h->short_shape;
+    L.scaled = h->scaled; L.max_row = h->scaled.shape.num_tiles * moment_parts(L);
+    L.parked = h->parked; L.rest = h->rest; L.parked_done = false;
+    L.rest_sample_tiles = h->d_sample_tiles + h->num_sample_tiles; L.num_rest_sample_tiles = h->num_rest_sample_tiles;
+    L.served_tiles = h->scaled.tiles; L.served = h->scaled.shape;
+    L.short_layers = h->short_layers; L.apart = h->apart; L.short_shape = h->short_shape;
     L.num_segments = h->num_segments;
     L.empty_layers = h->empty_layers;
     L.num_params = h->num_params; L.code_words = h->code_words; L.status = h->d_status; L.stream = static_cast<hipStream_t>(stream);
@@ -194,6 +203,16 @@ int check_capture(const qadam_ctx* h, void* stream, bool* capturing)
         return fail(QADAM_EINVAL, "stream is capturing a graph: a replay would reuse this step's random stream "
                                   "(rounding = 1) or bias correction (adam_flavor = 1)");
     return QADAM_OK;
+}
+
+// Polls of about a microsecond each: ten times the longest wait of workgroups that run beside each other (25 us).
+constexpr int kParkedPolls = 250;
+
+void free_parked(qadam_ctx* h)
+{
+    if (h->d_rest) (void)hipFree(h->d_rest);
+    if (h->d_parked) (void)hipFree(h->d_parked);
+    if (h->parked.meeting) (void)hipFree(h->parked.meeting);
 }
 
 bool identity_g(const qadam_ctx* h) { return h->cfg.k_g == QADAM_IDENTITY; }
@@ -285,8 +304,22 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     }
     if (h->code_bits > 0) h->apart = short_layers_apart(shorts, tile_count, num_workers);
     const bool split = h->apart.any();
+    // layers for k_parked, if any call can use it
+    int64_t park_elems = 0, park_units = 0, scaled_elems = 0;
+    auto parkable = [&](int64_t n) { return n > (split ? kTileElems : 0) && n <= kParkedLongest; };
+    for (int l = 0; l < num_segments; ++l) {
+        const int64_t n = seg_offsets[l + 1] - seg_offsets[l];
+        if (!split || n > kTileElems) scaled_elems += n;
+        if (parkable(n)) { park_elems += n; park_units += parked_units(n); }
+    }
+    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1) ||
+                                                worth_parking(park_elems, park_units, scaled_elems, num_workers));
     std::vector<Tile> scaled_tiles, short_layers[kShortSizes];
     std::vector<int32_t> sample_tiles, scaled_begin, scaled_layers;
+    std::vector<Tile> rest_tiles;
+    std::vector<int32_t> rest_samples, rest_begin, rest_layers;
+    std::vector<ParkedLayer> parked_layers;
+    std::vector<ParkedUnit> parked_units_of;
     std::vector<int32_t> seg_tile_begin(num_segments + 1, 0);
     int64_t word_off = 0;
     for (int l = 0; l < num_segments; ++l) {
@@ -296,6 +329,25 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         const int64_t used_words = (n + 31) / 32 * h->code_bits;
         if (n == 0) h->empty_layers = true;
         const bool apart = split && n > 0 && n <= kTileElems;
+        const bool parks = parks_any && parkable(n);
+        if (parks_any) rest_begin.push_back((int32_t)rest_tiles.size());
+        if (parks) {
+            ParkedLayer p;
+            p.t = Tile{a, word_off, (int32_t)n, l, (a % 4 != 0 ? kTileUnaligned : 0) | (int32_t)(seg_words - used_words) << 8, 0};
+            p.num_units = parked_units(n);
+            p.first_unit = (int32_t)parked_units_of.size();
+            if (parked_layers.empty()) h->parked.meeting_words = kMeetingLine;     // the units drawn
+            p.meeting = h->parked.meeting_words;
+            p.copies = meeting_copies(p.num_units);
+            h->parked.meeting_words += meeting_words(p.num_units);
+            h->parked.num_elems += n;
+            for (int u = 0; u < p.num_units; ++u) parked_units_of.push_back({(int32_t)parked_layers.size(), u});
+            parked_layers.push_back(p);
+        } else if (parks_any && !apart) {
+            rest_layers.push_back(l);
+            ++h->rest.num_layers;
+            h->rest.num_elems += n;
+        }
         if (split) scaled_begin.push_back((int32_t)scaled_tiles.size());
         if (!apart) {
             if (split) scaled_layers.push_back(l);
@@ -314,6 +366,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             if (!apart && (o / h->tile_elems) % kSampleStride == 0) {
                 t.flags |= kTileSampled;
                 sample_tiles.push_back(h->scaled.shape.num_tiles);
+                if (parks_any && !parks) rest_samples.push_back(h->rest.shape.num_tiles);
             }
             tiles.push_back(t);
             if (apart) {
@@ -324,6 +377,10 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
                 scaled_tiles.push_back(t);
             }
             if (!apart) add_tiles(h->scaled.shape, 1, t.len);
+            if (parks_any && !apart && !parks) {
+                rest_tiles.push_back(t);
+                add_tiles(h->rest.shape, 1, t.len);
+            }
             add_tiles(h->shape, 1, t.len);
         }
         const int32_t layer_tiles = (int32_t)tiles.size() - seg_tile_begin[l];
@@ -335,6 +392,8 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     seg_tile_begin[num_segments] = (int32_t)tiles.size();
     h->num_tiles = (int32_t)tiles.size();
     h->num_sample_tiles = (int32_t)sample_tiles.size();
+    h->num_rest_sample_tiles = (int32_t)rest_samples.size();
+    h->parked.num_units = (int32_t)parked_units_of.size();
 
     hipError_t e = hipGetDevice(&h->device);
     // set-up of the allocation-free entry point for this device (address of its static array), so that
@@ -355,6 +414,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         e = hipMalloc(reinterpret_cast<void**>(&h->d_err_bound), sizeof(float) * (size_t)num_segments * num_workers);
     if (e == hipSuccess && num_segments > 0)
         e = hipMalloc(reinterpret_cast<void**>(&h->d_thr), sizeof(uint32_t) * (size_t)num_segments * num_workers);
+    if (parks_any) sample_tiles.insert(sample_tiles.end(), rest_samples.begin(), rest_samples.end());
     if (e == hipSuccess && h->num_sample_tiles > 0) {
         e = hipMalloc(reinterpret_cast<void**>(&h->d_sample_tiles), sizeof(int32_t) * sample_tiles.size());
         if (e == hipSuccess)
@@ -369,6 +429,28 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             e = hipMemcpy(h->d_scaled, scaled_begin.data(), sizeof(int32_t) * scaled_begin.size(), hipMemcpyHostToDevice);
         tiles.insert(tiles.end(), scaled_tiles.begin(), scaled_tiles.end());
         for (const std::vector<Tile>& s : short_layers) tiles.insert(tiles.end(), s.begin(), s.end());
+    }
+    const size_t rest_at = tiles.size();
+    if (e == hipSuccess && parks_any) {
+        tiles.insert(tiles.end(), rest_tiles.begin(), rest_tiles.end());
+        rest_begin.push_back((int32_t)rest_tiles.size());
+        rest_begin.insert(rest_begin.end(), rest_layers.begin(), rest_layers.end());
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_rest), sizeof(int32_t) * rest_begin.size());
+        if (e == hipSuccess)
+            e = hipMemcpy(h->d_rest, rest_begin.data(), sizeof(int32_t) * rest_begin.size(), hipMemcpyHostToDevice);
+        const size_t layer_bytes = sizeof(ParkedLayer) * parked_layers.size();
+        const size_t unit_bytes = sizeof(ParkedUnit) * parked_units_of.size();
+        if (e == hipSuccess) e = hipMalloc(&h->d_parked, layer_bytes + unit_bytes);
+        if (e == hipSuccess) e = hipMemcpy(h->d_parked, parked_layers.data(), layer_bytes, hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(static_cast<char*>(h->d_parked) + layer_bytes, parked_units_of.data(), unit_bytes, hipMemcpyHostToDevice);
+        h->parked.layers = static_cast<ParkedLayer*>(h->d_parked);
+        h->parked.units = reinterpret_cast<ParkedUnit*>(static_cast<char*>(h->d_parked) + layer_bytes);
+        const size_t meeting_bytes = sizeof(uint32_t) * (size_t)h->parked.meeting_words * num_workers;
+        if (e == hipSuccess && meeting_bytes > 0) {
+            e = hipMalloc(reinterpret_cast<void**>(&h->parked.meeting), meeting_bytes);
+            if (e == hipSuccess) e = hipMemset(h->parked.meeting, 0, meeting_bytes);
+        }
     }
     if (e == hipSuccess && h->num_tiles > 0) {
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tiles), sizeof(Tile) * tiles.size());
@@ -386,6 +468,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         if (h->d_thr) (void)hipFree(h->d_thr);
         if (h->d_sample_tiles) (void)hipFree(h->d_sample_tiles);
         if (h->d_scaled) (void)hipFree(h->d_scaled);
+        free_parked(h);
         delete h;
         return hip_fail(e, "qadam_init device tables");
     }
@@ -393,6 +476,12 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     h->scaled.seg_tile_begin = split ? h->d_scaled : h->d_seg_tile_begin;
     h->scaled.layers = split ? h->d_scaled + num_segments + 1 : nullptr;
     h->short_layers = split ? h->scaled.tiles + h->scaled.shape.num_tiles : nullptr;
+    if (parks_any) {
+        h->rest.tiles = h->d_tiles + rest_at;
+        h->rest.seg_tile_begin = h->d_rest;
+        h->rest.layers = h->d_rest + num_segments + 1;
+    }
+    h->parked.polls = kParkedPolls;
     *out = h;
     return QADAM_OK;
 }
@@ -412,6 +501,7 @@ int qadam_destroy(qadam_handle_t h)
     if (h->d_thr) (void)hipFree(h->d_thr);
     if (h->d_sample_tiles) (void)hipFree(h->d_sample_tiles);
     if (h->d_scaled) (void)hipFree(h->d_scaled);
+    free_parked(h);
     delete h;
     return QADAM_OK;
 }
@@ -437,14 +527,17 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step, const 
     W.grad[worker] = grad_dev; W.err[worker] = err_dev;
     W.codes[worker] = static_cast<uint32_t*>(codes_dev); W.scales[worker] = scales_dev;
     const StepScalars S = make_scalars(h, step, 0.0f, 0.0f);
-    const Launch L = make_launch(h, stream);
+    Launch L = make_launch(h, stream);
+    const bool parked = use_parked(L, W, worker, 1);
+    if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
     // a recorded call always takes the full scale pass: a replay must not depend on what ran before it
     const bool recorded = !capturing && bound_usable(h, worker, err_dev);
-    const bool filtered = recorded && (h->trust_errs == 2 || (h->trust_errs == 1 && h->scaled.shape.num_tiles >= kFilterMinTiles));
+    const bool filtered = recorded && (h->trust_errs == 2 || (h->trust_errs == 1 && L.scaled.shape.num_tiles >= kFilterMinTiles));
     if (h->trust_errs == 3 && recorded) QADAM_HIP(launch_check_error_bounds(L, W, worker, 1));
     BoundRecord record(h, worker, 1, W);
+    if (parked) QADAM_HIP(launch_parked(L, S, W, worker, 1));
     if (filtered) QADAM_HIP(launch_amax_filtered(L, S, W, worker, 1));
     else QADAM_HIP(launch_amax(L, S, W, worker, 1));
     QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1));
@@ -558,7 +651,9 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     sp.x = x_dev; sp.m = m_dev; sp.v = v_dev;
     sp.werr = idx ? nullptr : werr_dev; sp.wcodes = idx ? nullptr : wcodes_dev;
     const StepScalars S = make_scalars(h, step, lr, beta2);
-    const Launch L = make_launch(h, stream);
+    Launch L = make_launch(h, stream);
+    const bool parked = !idg && use_parked(L, W, 0, h->num_workers);
+    if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[0], L.stream));
@@ -569,7 +664,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     } else {
         // the filtered pass costs two more (small) launches: only worth it from about 10^8 worker-elements on
         bool filtered = h->trust_errs == 2 ||
-                        (h->trust_errs == 1 && (int64_t)h->scaled.shape.num_tiles * h->num_workers >= kFilterMinTiles);
+                        (h->trust_errs == 1 && (int64_t)L.scaled.shape.num_tiles * h->num_workers >= kFilterMinTiles);
         bool all_recorded = true;
         for (int i = 0; i < h->num_workers; ++i) all_recorded = all_recorded && bound_usable(h, i, W.err[i]);
         all_recorded = all_recorded && !capturing;     // a recorded call always takes the full scale pass
@@ -581,6 +676,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
         QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers));
         if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
         QADAM_HIP(launch_short_layers(L, S, W, sp, false));
+        if (parked) QADAM_HIP(launch_parked(L, S, W, 0, h->num_workers));
         QADAM_HIP(launch_fused(L, S, W, sp));
         record.complete = !capturing;
     }
@@ -744,6 +840,14 @@ int qadam_trust_error_buffers(qadam_handle_t h, int32_t on)
     if (on < 0 || on > 3) return fail(QADAM_EINVAL, "on must be 0, 1, 2 or 3");
     h->trust_errs = on;
     for (bool& b : h->bound_valid) b = false;     // the next step reads everything and starts the record
+    return QADAM_OK;
+}
+
+int qadam_set_scale_polls(qadam_handle_t h, int32_t polls)
+{
+    QADAM_CHECK(check_handle(h));
+    if (polls < -1) return fail(QADAM_EINVAL, "polls must be -1 or more");
+    h->parked.polls = polls < 0 ? kParkedPolls : polls;
     return QADAM_OK;
 }
 

@@ -75,6 +75,26 @@ struct Section {
     ListShape   shape;
 };
 
+// A layer of k_parked, and a workgroup of it.
+struct ParkedLayer {
+    Tile    t;              // the whole layer
+    int32_t num_units, first_unit;
+    int32_t meeting, copies;    // first word of its meeting place, polled copies of the scale
+};
+
+struct ParkedUnit {
+    int32_t layer, unit;
+};
+
+struct Parked {
+    const ParkedUnit*  units;   // device
+    const ParkedLayer* layers;  // device
+    uint32_t* meeting;      // device, [num_workers][meeting_words], zero between launches
+    int32_t   num_units, meeting_words;
+    int64_t   num_elems;
+    int32_t   polls;        // before a workgroup finds the scale by itself
+};
+
 struct Launch {
     const Tile* tiles;      // device
     float*      inv_scales; // device, [num_workers][num_segments]: 1/s where the fast quotient is safe, else 0
@@ -84,6 +104,14 @@ struct Launch {
     int32_t     num_tiles;
     ListShape   shape;
     Section     scaled;
+    int32_t     max_row;    // maxima from one worker's row to the next's
+    Parked      parked;     // layers of `scaled` that k_parked can do; num_units == 0: none
+    Section     rest;       // `scaled` without them
+    const int32_t* rest_sample_tiles;
+    int32_t     num_rest_sample_tiles;
+    bool        parked_done;    // `scaled` is `rest`, k_parked does the others
+    const Tile* served_tiles;   // the tiles of both
+    ListShape   served;
     int32_t     longest_layer;  // tiles of the longest layer
     const Tile* short_layers;   // device: the layers that k_layers does, one tile each, by size; null: none
     ShortLayers apart;          // how many of each size
@@ -104,6 +132,16 @@ struct Launch {
 // maxima per tile that the first pass of variant W leaves
 inline int moment_parts(const Launch& L) { return (int)moment_cut(L.scaled.shape).parts; }
 
+// the launch of what k_parked leaves
+inline Launch without_parked(const Launch& L)
+{
+    Launch R = L;
+    R.scaled = L.rest;
+    R.sample_tiles = L.rest_sample_tiles; R.num_sample_tiles = L.num_rest_sample_tiles;
+    R.parked_done = true;
+    return R;
+}
+
 // Launchers (defined in qadam_kernels.hip).  `first_worker`/`num` select the workers a launch covers.
 // scales in two stages without atomics: per-tile maxima, then one workgroup per (worker, layer)
 // (of long lists: per 16 layers) reduces its tiles and also writes the reciprocal used by the fast quotient
@@ -112,6 +150,8 @@ hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const Wor
                                 int max_per_tile = 1);
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
+bool use_parked(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
+hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker);
 // the short layers of the list, from the gradient (variant_w: through the local moments) to the codes, for one worker; or
 // the whole step of all workers

@@ -404,6 +404,18 @@ __device__ __forceinline__ void load_shifted(const float* __restrict__ p, int nv
     }
 }
 
+// wherever it lies
+__device__ __forceinline__ void load_any(const float* __restrict__ p, int nvalid, float (&out)[4])
+{
+    if (nvalid == 4) {
+        const f4 t = __builtin_nontemporal_load(reinterpret_cast<const f4_a4*>(p));
+        out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] = j < nvalid ? p[j] : 0.0f;
+    }
+}
+
 __device__ __forceinline__ void store_shifted(float* __restrict__ p, int nvalid, const float (&in)[4])
 {
     if (nvalid == 4) {
@@ -699,7 +711,7 @@ __device__ __forceinline__ void load_scan(const float* __restrict__ p, int nvali
 // maximum does not care which lane sees which element, so the range is walked as the aligned quads of
 // memory it contains plus at most three single elements at either end.  thr != 0: e is read only for
 // quads (elements) whose |g| reaches thr (filtered scale pass).
-template <bool KEEP>
+template <bool KEEP, int THREADS = kBlockThreads>
 __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, const float* __restrict__ e,
                                                int64_t start, int len, uint32_t thr)
 {
@@ -719,12 +731,12 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
         }
     }
     // four quads per lane per trip, their loads issued together (a tile holds at most 1024 quads)
-    for (int64_t q0 = a0 + (int64_t)threadIdx.x * 4; q0 < a1; q0 += kBlockThreads * 16) {
+    for (int64_t q0 = a0 + (int64_t)threadIdx.x * 4; q0 < a1; q0 += THREADS * 16) {
         float gv[4][4], ev[4][4];
         bool live[4], cand[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t q = q0 + (int64_t)k * kBlockThreads * 4;
+            const int64_t q = q0 + (int64_t)k * THREADS * 4;
             live[k] = q < a1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { gv[k][j] = 0.0f; ev[k][j] = 0.0f; }
@@ -741,7 +753,7 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
                     top = ab > top ? ab : top;
                 }
                 cand[k] = live[k] && top >= thr;
-                if (cand[k]) load_scan<4, KEEP>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
+                if (cand[k]) load_scan<4, KEEP>(e + q0 + (int64_t)k * THREADS * 4, 4, ev[k]);
             }
         }
 #pragma unroll
@@ -1203,6 +1215,15 @@ static void launch_quantizer(const WorkerArgs& A, hipStream_t stream)
     else launch_quantizer<false>(A, stream);
 }
 
+__device__ __forceinline__ void wait_for_loads()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ void wait_for_stores() { wait_for_loads(); }    // one counter for both
+
 // ---- a short segment in one workgroup (qadam_quantize_segment_noalloc) ---------------------------
 // Scale and quantization in one launch: g and e are read once and p stays in registers across the reduction.
 // Bound by latency: one load, two barriers, one store.  10 k elements 13.4 -> 9.5 us per call against the two
@@ -1262,6 +1283,301 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
     if ((int)threadIdx.x < ((used + 3) & ~3) - used) A.codes[used + threadIdx.x] = 0u;
 }
 
+// ---- layers that the chip's registers hold: scale and quantization in one launch -----------------
+// The workgroups of a layer keep p = g + e on the chip, meet over the layer's scale and then quantize what they hold, so that
+// g and e are read once: 12.4 bytes per element for 20.4 of the two passes.  A workgroup holds two units, the younger one in
+// registers, the older one in LDS.  Each turn it quantizes the older one chunk by chunk while the next unit is loaded in
+// its place, so that loads and stores mix and a layer's units have a turn's time to meet.  Bound by memory: 85 M elements, one
+// worker 257 -> 206 us, 340 M 738 us; beyond the first and last turn 6.0 TB/s.  Layers of one unit each, which do not meet,
+// take the same time.  Chunks whose loads are in flight together, 2 / 4 / 8: 209 / 206 / 220 us (8 spills); workgroups of 256 /
+// 512 / 1024 threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded, waited for and stored in
+// turn 229.  Units are drawn from a counter in the order of the layers; dealt out beforehand they end 10 us later.
+//
+// No workgroup depends on another one being resident: each waits a bounded number of polls for the scale, and then finds
+// it by itself by reading the whole layer, publishes it and goes on.  What the others have not published yet they cannot
+// have overwritten, so a maximum that was complete before any scale of the layer could be seen is the layer's.
+struct ParkedArgs {
+    const ParkedUnit* units;
+    const ParkedLayer* layers;
+    StepScalars S;
+    const float* grad[QADAM_MAX_WORKERS];
+    float* err[QADAM_MAX_WORKERS];
+    uint32_t* codes[QADAM_MAX_WORKERS];
+    float* scales[QADAM_MAX_WORKERS];
+    uint32_t* maxima;       // rows of `row` maxima, one row per worker, one maximum per unit
+    uint32_t* meeting;      // [N][meeting_words], zero between launches
+    float* inv_scales;      // [N][L]
+    float* err_bound;       // [N][L]
+    float bound_factor;
+    int row, meeting_words, num_segments, first_worker, polls;
+    uint32_t num_units, total;      // of one worker, of all
+    uint32_t* status;
+};
+
+constexpr int kParkedLoads = 4;                 // chunks whose loads are in flight together
+constexpr uint32_t kNoUnit = 0xffffffffu;
+constexpr uint32_t kPublished = 0x80000000u;    // marks a published scale, whose own sign bit is 0
+
+// f(0), f(1), .. f(N - 1) with constants, however long f is (an unrolled loop has a limit)
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+__device__ __forceinline__ uint32_t load_agent(const uint32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void store_agent(uint32_t* p, uint32_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A unit and its layer, the same in all lanes.
+struct Place {
+    ParkedLayer P;
+    int unit, w;
+    uint32_t* meeting;
+};
+
+__device__ __forceinline__ Place place_of(const ParkedArgs& A, uint32_t item)
+{
+    const ParkedUnit u = A.units[item % A.num_units];
+    Place q;
+    q.P = A.layers[u.layer];
+    q.unit = u.unit;
+    q.w = A.first_worker + (int)(item / A.num_units);
+    q.meeting = A.meeting + (size_t)q.w * A.meeting_words + q.P.meeting;
+    return q;
+}
+
+// by one wavefront
+__device__ __forceinline__ void publish_scale(const ParkedArgs& A, const Place& q, uint32_t max_bits)
+{
+    const int lane = threadIdx.x & 63;
+    if (q.P.num_units > 1 && lane < q.P.copies) store_agent(q.meeting + (1 + lane) * kMeetingLine, max_bits | kPublished);
+    if (lane == 0) {
+        const Scale r = make_scale(max_bits);
+        A.scales[q.w][q.P.t.seg] = r.s;
+        A.inv_scales[(size_t)q.w * A.num_segments + q.P.t.seg] = r.inv;
+        A.err_bound[(size_t)q.w * A.num_segments + q.P.t.seg] = residual_bound(r.s, A.bound_factor);
+    }
+    wait_for_stores();                          // before this workgroup leaves the meeting
+}
+
+// Hands in a unit's maximum; whoever comes last publishes the scale.  By one wavefront.
+__device__ __forceinline__ void arrive(const ParkedArgs& A, const Place& q, uint32_t bm)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t* maxima = A.maxima + (size_t)q.w * A.row + q.P.first_unit;
+    uint32_t arrived = 0;
+    if (lane == 0) {
+        store_agent(maxima + q.unit, bm);
+        wait_for_stores();                      // the maximum is in memory before the arrival is
+        arrived = __hip_atomic_fetch_add(q.meeting, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
+    if ((arrived & kArrivals) != (uint32_t)q.P.num_units - 1u) return;
+    uint32_t local = 0;
+    for (int i = lane; i < q.P.num_units; i += 64) {
+        const uint32_t v = load_agent(maxima + i);
+        local = v > local ? v : local;
+    }
+    publish_scale(A, q, (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(local)));
+}
+
+__device__ __forceinline__ uint32_t poll_scale(const Place& q)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)load_agent(q.meeting + (1 + q.unit % q.P.copies) * kMeetingLine));
+}
+
+// What the turn begins with, to every thread: the published scale, where the workgroup holds a unit of a layer of several
+// (`met`), and the next unit to load, unless they have run out (`draw`).
+__device__ __forceinline__ uint32_t begin_turn(const ParkedArgs& A, const Place& q, bool met, bool draw, uint32_t& next)
+{
+    __shared__ uint32_t shared_word, shared_next;
+    const bool one = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) == 0;
+    if (one) {
+        uint32_t* drawn = A.meeting + (size_t)A.first_worker * A.meeting_words;
+        uint32_t ticket = 0, word = 0;
+        for (int i = 0; met && i < A.polls; ++i) {
+            word = poll_scale(q);
+            if (word) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        if (threadIdx.x == 0) {
+            // Drawn behind the wait: a unit that is drawn is loaded without another wait, so the layer waited for can be complete.
+            if (draw) ticket = __hip_atomic_fetch_add(drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            shared_word = word;
+            shared_next = draw && gridDim.x + ticket < A.total ? gridDim.x + ticket : kNoUnit;
+            // every workgroup draws until it draws in vain, which makes A.total draws
+            if (draw && ticket == A.total - 1) store_agent(drawn, 0u);
+        }
+    }
+    __syncthreads();
+    uint32_t word = shared_word;
+    if (draw) next = (uint32_t)__builtin_amdgcn_readfirstlane((int)shared_next);
+    if (met && word == 0) {
+        const Tile& t = q.P.t;
+        uint32_t local = 0;
+        for (int o = 0; o < t.len; o += kTileElems) {
+            const uint32_t m = amax_range<false, kParkedThreads>(A.grad[q.w], A.err[q.w], t.start + o, min(t.len - o, kTileElems), 0u);
+            local = m > local ? m : local;
+        }
+        const uint32_t all = block_max<kParkedThreads>(local);      // every thread's reads are done
+        if (one) {
+            word = poll_scale(q);
+            if (word == 0) {
+                word = all | kPublished;
+                publish_scale(A, q, all);
+            }
+            if (threadIdx.x == 0) shared_word = word;
+        }
+        __syncthreads();
+        word = shared_word;
+    }
+    return word;
+}
+
+template <int ROUNDING>
+__global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
+{
+    const StepScalars& S = A.S;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mine = (int)threadIdx.x * 4;
+    const QgConst c = make_qg(S.k_g);
+    extern __shared__ float4 held[];                    // [kParkedChunks][kParkedThreads]
+    float p[kParkedChunks][4];                          // the younger unit; the older one is in LDS
+    uint32_t item = kNoUnit, other_item = kNoUnit;      // the older one, the younger one
+    uint32_t word = 0, other_word = 0;                  // their scales where they are known at once
+#pragma unroll
+    for (int k = 0; k < kParkedChunks; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[k][j] = 0.0f;
+    uint32_t next = blockIdx.x;
+    bool first = true;
+#pragma unroll 1
+    for (;;) {
+        const Place q = place_of(A, item != kNoUnit ? item : 0u);
+        const bool met = item != kNoUnit && q.P.num_units > 1, draw = !first && next != kNoUnit;
+        if (met || draw) {
+            const uint32_t seen = begin_turn(A, q, met, draw, next);
+            if (met) word = seen;
+        }
+        first = false;
+        if (item == kNoUnit && next == kNoUnit && other_item == kNoUnit) break;
+        uint32_t departed = 0;
+        if (met && threadIdx.x == 0)
+            departed = __hip_atomic_fetch_add(q.meeting, kDeparture, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const Place n = place_of(A, next != kNoUnit ? next : 0u);
+        const Scale sc = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)(word & ~kPublished)));
+        const int q_stride = q.P.num_units * kParkedChunk, q_begin = q.unit * kParkedChunk;
+        const int n_stride = n.P.num_units * kParkedChunk, n_begin = n.unit * kParkedChunk;
+        const bool q_whole = q_begin + (kParkedChunks - 1) * q_stride + kParkedChunk <= q.P.t.len;
+        const bool n_whole = n_begin + (kParkedChunks - 1) * n_stride + kParkedChunk <= n.P.t.len;
+        const float* n_grad = A.grad[n.w] + n.P.t.start;
+        const float* n_err = A.err[n.w] + n.P.t.start;
+        static_for<kParkedChunks / kParkedLoads>([&](auto turn) {
+            constexpr int k0 = decltype(turn)::value * kParkedLoads;
+            float g[kParkedLoads][4], e[kParkedLoads][4];
+            if (next != kNoUnit) {
+                if (n_whole) {
+#pragma unroll
+                    for (int k = 0; k < kParkedLoads; ++k) {
+                        const int base = n_begin + (k0 + k) * n_stride;
+                        load_any(n_grad + base + mine, 4, g[k]);
+                        load_any(n_err + base + mine, 4, e[k]);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kParkedLoads; ++k) {
+                        const int base = n_begin + (k0 + k) * n_stride;
+                        const int nvalid = min(max(n.P.t.len - base - mine, 0), 4);
+                        load_any(n_grad + base + mine, nvalid, g[k]);
+                        load_any(n_err + base + mine, nvalid, e[k]);
+                    }
+                }
+            }
+            asm volatile("" : : : "memory");    // the loads are on their way before the arithmetic
+#pragma unroll
+            for (int k = k0; k < k0 + kParkedLoads; ++k) {
+                float4& spot = held[k * kParkedThreads + threadIdx.x];
+                const int base = q_begin + k * q_stride + wave * 256;
+                if (item != kNoUnit && (q_whole || base < q.P.t.len)) {
+                    const int nvalid = q_whole ? 4 : min(max(q.P.t.len - base - lane * 4, 0), 4);
+                    const float4 v = spot;
+                    const float old[4] = {v.x, v.y, v.z, v.w};
+                    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    float unused[4], en[4], U[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) U[j] = 0.0f;
+                    if constexpr (ROUNDING == 1) {
+                        const int64_t gi = q.P.t.start + base + lane * 4;
+                        const Shift sf = make_shift(q.P.t);
+                        if (sf.r) uniforms_shifted(S, gi, (uint32_t)q.w, 0u, sf.r, U);
+                        else uniforms<4>(S, gi, (uint32_t)q.w, 0u, U);
+                    }
+                    uint32_t codes;
+                    worker_lane<4, ROUNDING>(old, zero, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);     // p + 0 reproduces p
+                    store_shifted(A.err[q.w] + q.P.t.start + base + lane * 4, nvalid, en);
+                    int slot; bool writes;
+                    const uint32_t planes = pack_planes<4>(codes, S.code_bits, lane, slot, writes);
+                    store_chunk_words(A.codes[q.w], q.P.t, base, S.code_bits, planes, slot, writes);
+                }
+                spot = make_float4(p[k][0], p[k][1], p[k][2], p[k][3]);
+                asm volatile("" : : : "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (next != kNoUnit) {
+#pragma unroll
+                for (int k = 0; k < kParkedLoads; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        p[k0 + k][j] = g[k][j] + e[k][j];
+                        asm volatile("" : "+v"(p[k0 + k][j]) : : "memory");
+                    }
+            }
+        });
+        if (item != kNoUnit && q.unit == 0) {
+            write_pad_words(A.codes[q.w], q.P.t, S.code_bits);
+            check_scale(sc.s, A.status);
+        }
+        __syncthreads();                        // the words in LDS are read
+        // The last one to leave makes the meeting place ready for the next launch.
+        if (met && threadIdx.x == 0 && departed / kDeparture == (uint32_t)q.P.num_units - 1u) {
+            store_agent(q.meeting, 0u);
+            for (int i = 1; i <= q.P.copies; ++i) store_agent(q.meeting + i * kMeetingLine, 0u);
+        }
+        if (next != kNoUnit) {
+            uint32_t local = 0;
+#pragma unroll
+            for (int k = 0; k < kParkedChunks; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t ab = f2u(p[k][j]) & 0x7fffffffu;
+                    local = ab > local ? ab : local;
+                }
+            const uint32_t bm = block_max<kParkedThreads>(local);
+            // not by the wavefront that begins the next turn, whose wait goes on beside this one
+            if (wave == kParkedThreads / 64 - 1) {
+                if (n.P.num_units == 1) publish_scale(A, n, bm);
+                else arrive(A, n, bm);
+            }
+            word = bm;                          // of a layer of one unit
+        }
+        item = other_item;
+        other_item = next;
+        const uint32_t youngest = word;
+        word = other_word;
+        other_word = youngest;
+    }
+}
+
 // ---- server side (qadam_server_step, qadam_server_apply_w, the last launch of a step by worker) ---
 struct ServerArgs {
     const Tile* tiles;
@@ -1319,12 +1635,6 @@ __device__ __forceinline__ void load_to_lds(const uint32_t* src, uint32_t* dst)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)src,
                                      (__attribute__((address_space(3))) uint32_t*)dst, 4, 0, 0);
-}
-
-__device__ __forceinline__ void wait_for_loads()
-{
-    __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0)
-    asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ void wait_for_lds()
@@ -2080,7 +2390,7 @@ static float residual_bound_factor(const StepScalars& S)
 
 // Every pass gives worker w the same row of the maxima, whether it leaves one per tile or `moment_parts`: calls for
 // different workers may run on different streams.
-static int max_row(const Launch& L) { return L.scaled.shape.num_tiles * moment_parts(L); }
+static int max_row(const Launch& L) { return L.max_row; }
 
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
@@ -2095,7 +2405,7 @@ static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S,
 
 static bool fold_in_quantizer(const Launch& L, int num, int max_per_tile)
 {
-    return !L.empty_layers && !L.short_layers
+    return !L.parked_done && !L.empty_layers && !L.short_layers
         && fold_in_quantizer(L.num_tiles, L.num_params, L.longest_layer * max_per_tile, num, max_per_tile);
 }
 
@@ -2198,6 +2508,42 @@ hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const Wor
     hipLaunchKernelGGL(k_reduce_lower_bounds, dim3(L.scaled.num_layers, num), dim3(kBlockThreads), 0, L.stream, R);
     A.tile_list = nullptr;
     hipLaunchKernelGGL(k_amax_filtered, dim3(L.scaled.shape.num_tiles, num), dim3(kBlockThreads), 0, L.stream, A);
+    return hipGetLastError();
+}
+
+static bool codes_overlap(const Launch& L, const WorkerPtrs& W, int first_worker, int num)
+{
+    for (int i = first_worker + 1; i < first_worker + num; ++i)
+        for (int k = first_worker; k < i; ++k)
+            if (W.codes[i] < W.codes[k] + L.code_words && W.codes[k] < W.codes[i] + L.code_words) return true;
+    return false;
+}
+
+// Two code buffers that overlap are left to the main pass, which gives them an order.
+bool use_parked(const Launch& L, const WorkerPtrs& W, int first_worker, int num)
+{
+    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num)
+        && !codes_overlap(L, W, first_worker, num);
+}
+
+hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
+{
+    if (L.parked.num_units == 0) return hipSuccess;
+    ParkedArgs A;
+    A.units = L.parked.units; A.layers = L.parked.layers; A.S = S;
+    for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
+        A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
+    }
+    A.row = max_row(L); A.maxima = L.tile_max + L.rest.shape.num_tiles;
+    A.meeting = L.parked.meeting; A.meeting_words = L.parked.meeting_words;
+    A.inv_scales = L.inv_scales; A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
+    A.num_segments = L.num_segments; A.first_worker = first_worker; A.polls = L.parked.polls;
+    A.status = L.status;
+    A.num_units = (uint32_t)L.parked.num_units; A.total = A.num_units * (uint32_t)num;
+    const unsigned lds = kParkedThreads * kParkedChunks * sizeof(float4);
+    const dim3 grid(A.total < (uint32_t)kParkedGroups ? A.total : (uint32_t)kParkedGroups), block(kParkedThreads);
+    if (S.rounding == 0) hipLaunchKernelGGL(k_parked<0>, grid, block, lds, L.stream, A);
+    else hipLaunchKernelGGL(k_parked<1>, grid, block, lds, L.stream, A);
     return hipGetLastError();
 }
 
@@ -2367,23 +2713,21 @@ static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPt
 {
     const int64_t n = L.scaled.num_elems;
     if (variant_w ? keep_parked(n, S.num_workers) : keep_scanned(n, S.num_workers)) return false;
-    for (int i = 1; i < S.num_workers; ++i)
-        for (int k = 0; k < i; ++k)
-            if (W.codes[i] < W.codes[k] + L.code_words && W.codes[k] < W.codes[i] + L.code_words) return false;
-    return true;
+    return !codes_overlap(L, W, 0, S.num_workers);
 }
 
 static void launch_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
 {
-    for (int i = 0; i < S.num_workers; ++i) launch_quantizer(L, S, W, i, S.num_workers, variant_w);
+    if (L.scaled.shape.num_tiles > 0)
+        for (int i = 0; i < S.num_workers; ++i) launch_quantizer(L, S, W, i, S.num_workers, variant_w);
     ServerArgs A;
     fill_server_args(A, S, W, sp);
     if (S.rounding == 0) {
-        if (variant_w) launch_server_tiles<0, true>(A, L.scaled.tiles, L.scaled.shape, L.stream);
-        else launch_server_tiles<0, false>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+        if (variant_w) launch_server_tiles<0, true>(A, L.served_tiles, L.served, L.stream);
+        else launch_server_tiles<0, false>(A, L.served_tiles, L.served, L.stream);
     } else {
-        if (variant_w) launch_server_tiles<1, true>(A, L.scaled.tiles, L.scaled.shape, L.stream);
-        else launch_server_tiles<1, false>(A, L.scaled.tiles, L.scaled.shape, L.stream);
+        if (variant_w) launch_server_tiles<1, true>(A, L.served_tiles, L.served, L.stream);
+        else launch_server_tiles<1, false>(A, L.served_tiles, L.served, L.stream);
     }
 }
 
@@ -2398,8 +2742,8 @@ constexpr unsigned kMainPassLds = 10240;
 static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp,
                                    bool variant_w)
 {
-    if (L.scaled.shape.num_tiles == 0) return hipSuccess;
-    if (step_by_worker(L, S, W, variant_w)) {
+    if (L.served.num_tiles == 0) return hipSuccess;
+    if (L.parked_done || step_by_worker(L, S, W, variant_w)) {
         launch_by_worker(L, S, W, sp, variant_w);
         return hipGetLastError();
     }

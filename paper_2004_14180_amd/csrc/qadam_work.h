@@ -183,6 +183,47 @@ constexpr bool server_by_section(const ListShape& all, bool split)
     return split && cut_tiles(all, 256, ((int64_t)1 << 26) - 4096, 1).part_len > 256;
 }
 
+// ---- layers that the chip's registers hold (k_parked) -----------------------------------------------------------------
+// Unit u of a layer's n is its chunks u, u + n, ..., kParkedChunks at most, so that the workgroups of a layer walk it side
+// by side.  A workgroup holds two units.
+constexpr int kParkedThreads = 512;
+constexpr int kParkedChunk = kParkedThreads * 4, kParkedChunks = 8;
+
+constexpr int parked_units(int64_t len)
+{
+    const int64_t chunks = (len + kParkedChunk - 1) / kParkedChunk;
+    return (int)((chunks + kParkedChunks - 1) / kParkedChunks);
+}
+
+// Layers of up to 384 units (6.3 M elements).  The 512 workgroups of a launch (kParkedGroups, two per CU) hold two units each,
+// and a layer of nearly as many units as there are workgroups leaves none of them for its neighbours.  One worker's call of 85 M
+// elements, us, two passes / this way: layers of 36 units 260 / 210, 144 260 / 206, 256 259 / 206, 384 272 / 222, 512 257 / 284.
+constexpr int kParkedGroups = 512;
+constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
+
+// Whether a call for num workers does the layers of up to kParkedLongest elements this way: `elems` in `units`, of the `all`
+// elements whose scales have a pass of their own.  The launch starts by loading only and ends by storing only, which costs it
+// about 29 us (85 M elements in 206 us, 340 M in 738).  us, without / with, layers of 2^18 to 2^21 elements: step of one worker
+// of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 / 82.6, 8 M 155 / 141, 32 M
+// 599 / 482; 8 of 2 M 71.0 / 71.9, 4 M 137 / 121, 32 M 1020 / 755; one worker's call of 4 M 13.5 / 20.9, 8 M 31.2 / 29.6, 64 M
+// 207 / 165.  A unit costs about the same however few elements it has: 4000 layers of 5000, one worker's call 69.4 / 78.8, step
+// of 4 workers 404 / 395; 500 of 10000 and 100, 4 workers 107 / 123, 3000 times 609 / 513; 1000 of 20000 375 / 338.  Beside a
+// long layer the step goes worker by worker for its sake: one of 20 M and 300 of 1000, 4 workers 371 / 412; 1.3 G with 0.1 G of
+// them 20.96 / 20.95 ms.
+constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num)
+{
+    const int64_t work = elems * num, M = 1 << 20;
+    const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
+    return work >= (num == 1 ? 8 : 24) * M && (filled || work >= 72 * M) && 4 * elems >= all;
+}
+
+// The meeting place of a layer's workgroups: a word that counts arrivals and departures, and copies of the published scale
+// for up to eight of them each to poll, every one in a line of its own.  Words.
+constexpr int kMeetingLine = 32;
+constexpr uint32_t kArrivals = 0xffffu, kDeparture = 0x10000u;
+constexpr int meeting_copies(int units) { return units <= 8 ? 1 : units >= 512 ? 64 : (units + 7) / 8; }
+constexpr int meeting_words(int units) { return units > 1 ? (1 + meeting_copies(units)) * kMeetingLine : 0; }
+
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
 // Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
 struct FlatGrid {

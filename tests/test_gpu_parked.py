@@ -1,0 +1,108 @@
+"""GPU parity of layers whose scale and quantization are one launch (k_parked): units of every filling, on and off the 16-byte
+grid, the longest layer, both ways a workgroup comes by the scale, calls on two streams, captured calls, non-finite scales."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2004_14180_amd import QAdam, QAdamConfig
+from test_gpu_by_worker import N, _State, _bits
+from test_gpu_parity import _custom
+
+pytestmark = pytest.mark.gpu
+
+M = 1 << 20
+UNIT, LONGEST = 16384, 384 * 16384
+LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers; one worker's call: 8 M
+
+
+def _sizes(total):
+    s = [1, 2047, 2048, 2049, 5, UNIT - 1, UNIT, UNIT + 1, 9 * UNIT - 3, 3, 40 * UNIT + 2050]
+    return s + [total - sum(s)]
+
+
+@pytest.mark.parametrize("polls", [-1, 0])
+@pytest.mark.parametrize("less", [0, 1])
+@pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=0, k_x=14, weight_ef=0), dict(k_g=4, k_x=6, rounding=1, seed=3)])
+def test_whole_step_gives_the_bits_of_the_separate_calls(polls, less, cfgkw):
+    sizes = _sizes(LEAST - less)
+    a, b = _State(sizes, False, **cfgkw), _State(sizes, False, **cfgkw)
+    a.q.set_scale_polls(polls)
+    for t in (1, 2):
+        a.step(t, False, True)
+        b.step(t, False, False)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+    assert a.q.get_status() == 0
+
+
+@pytest.mark.parametrize("sizes,workers,trust", [([LONGEST, 2 * M, 1001, 0, 70001], 1, 0),      # all parked, an empty layer
+                                                 ([LONGEST + 1, 2 * M - 1, 7], 1, 0),           # not enough of them
+                                                 ([LONGEST + 1, 3, LONGEST - 1, 2 * M], 3, 2)])  # beside a longer one, filtered
+def test_against_the_oracle(sizes, workers, trust):
+    rep, st = _custom(sizes, workers, 2, seed=43, trust=trust)
+    assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+
+
+def _calls(streams, polls):
+    sizes = [2 * M] * 3 + [1003, 2 * M]
+    seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    q = QAdam(QAdamConfig(), seg, 2)
+    q.set_scale_polls(polls)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    P = int(seg[-1])
+    f = lambda s: torch.empty(P, device="cuda").normal_(0.0, s, generator=gen)  # noqa: E731
+    g, e = [f(1e-2) for _ in range(2)], [f(1e-3) for _ in range(2)]
+    codes = [torch.full((q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+    scales = [torch.zeros(len(sizes), device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    for t in (1, 2, 3):
+        for i in range(2):
+            q.worker_quantize(i, t, g[i], e[i], codes[i], scales[i], stream=streams[i])
+    torch.cuda.synchronize()
+    assert q.get_status() == 0
+    return e + codes + scales
+
+
+def test_workers_on_two_streams():
+    one = _calls([torch.cuda.current_stream()] * 2, -1)
+    two = _calls([torch.cuda.Stream() for _ in range(2)], -1)
+    assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(one, two))
+
+
+def test_captured_step_is_the_eager_one():
+    sizes = _sizes(LEAST)
+    a, b = _State(sizes, False), _State(sizes, False)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        a.step(1, False, True)
+    for t in (1, 2, 3):
+        graph.replay()
+        b.step(1, False, True)
+        torch.cuda.synchronize()
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+
+
+@pytest.mark.parametrize("polls", [-1, 0])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_scale_that_is_not_finite_stays_in_its_layer(polls, bad):
+    sizes = _sizes(LEAST)
+    a, b = _State(sizes, False), _State(sizes, False)
+    a.q.set_scale_polls(polls)
+    at = sum(sizes[:8]) + 5 * UNIT                       # in the layer of nine units
+    for s in (a, b):
+        s.g[3][at] = bad
+    a.step(1, False, True)
+    b.step(1, False, False)
+    assert a.q.get_status() == b.q.get_status() == 1
+    for p, r in zip(a.codes + a.scales, b.codes + b.scales):
+        assert torch.equal(_bits(p), _bits(r))
+    lo, hi = sum(sizes[:8]), sum(sizes[:9])
+    for p, r in zip(a.e, b.e):
+        assert torch.equal(_bits(p[:lo]), _bits(r[:lo])) and torch.equal(_bits(p[hi:]), _bits(r[hi:]))
+
+
+def test_polls_are_checked():
+    q = QAdam(QAdamConfig(), [0, 10], 1)
+    with pytest.raises(Exception):
+        q.set_scale_polls(-2)

@@ -183,3 +183,24 @@ def test_server_by_section_where_one_launch_would_be_sparse(tmp_path):
     CHECK(server_by_section(list(800, 809, 8400, 64), true), "beside longer layers");
     CHECK(!server_by_section(list(20000, 0, 0, 1), true) && !server_by_section(list(0, 0, 20000, 1000), true), "uniform");
     CHECK(!server_by_section(list(30, 0, 330, 64), true), "too few to fill the chip");""")
+
+
+def test_units_cover_a_parked_layer(tmp_path):
+    """Chunk c of a layer is in unit c mod n, and no unit has more chunks than a workgroup holds; the workgroups that are
+    there can hold the longest layer, its units fit the counts of arrivals and departures, and it has no more polled copies
+    of the scale than one wavefront writes."""
+    _run(tmp_path, """
+    const int unit = kParkedChunk * kParkedChunks;
+    for (int64_t len : {(int64_t)1, (int64_t)kParkedChunk, (int64_t)kParkedChunk + 1, (int64_t)unit, (int64_t)unit + 1, (int64_t)9 * unit - 1,
+                        kParkedLongest - 1, kParkedLongest}) {
+        const int n = parked_units(len);
+        const int64_t chunks = (len + kParkedChunk - 1) / kParkedChunk;
+        for (int u = 0; u < n; ++u) CHECK((chunks - u + n - 1) / n >= 1 && (chunks - u + n - 1) / n <= kParkedChunks, "%lld", (long long)len);
+        CHECK(n < kParkedGroups && (unsigned)n <= kArrivals && (uint64_t)n * kDeparture < (1ull << 32), "%lld", (long long)len);
+        CHECK(meeting_copies(n) >= 1 && meeting_copies(n) <= 64, "%lld", (long long)len);
+        CHECK(meeting_words(n) == (n > 1 ? (1 + meeting_copies(n)) * kMeetingLine : 0), "%lld", (long long)len);
+    }
+    const int64_t M = 1 << 20;
+    CHECK(worth_parking(8 * M, 512, 8 * M, 1) && !worth_parking(8 * M - 1, 512, 8 * M, 1), "one worker");
+    CHECK(worth_parking(6 * M, 384, 24 * M, 4) && !worth_parking(6 * M - 1, 384, 6 * M, 4), "four workers");
+    CHECK(!worth_parking(6 * M, 384, 24 * M + 1, 4) && !worth_parking(20 * M, 4000, 20 * M, 1), "beside a long layer, mostly empty units");""")
