@@ -1379,8 +1379,9 @@ __device__ __forceinline__ void arrive(const ParkedArgs& A, const Place& q, uint
     uint32_t* maxima = A.maxima + (size_t)q.w * A.row + q.P.first_unit;
     uint32_t arrived = 0;
     if (lane == 0) {
-        store_agent(maxima + q.unit, bm);
-        wait_for_stores();                      // the maximum is in memory before the arrival is
+        // An exchange, whose answer says that the maximum is where the others find it, before the arrival is counted.
+        const uint32_t before = __hip_atomic_exchange(maxima + q.unit, bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" : : "v"(before) : "memory");
         arrived = __hip_atomic_fetch_add(q.meeting, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
