@@ -21,6 +21,8 @@
 //     of workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole pass;
 //   * a segment that starts off the 16-byte grid keeps the same lane-to-element mapping (the codes are
 //     anchored at the segment start) and moves its data with dword-aligned 128-bit accesses;
+//   * layers of up to 6.3 M elements in long lists stay on the chip between the scale and the quantizer: the workgroups of a
+//     layer meet over its scale while they load and store units of other layers (k_parked);
 //   * when the error buffers are what the previous step wrote, |e| <= s/4 (half the widest gap of
 //     the grid), so an element whose |g| lies that far below a known lower bound of the scale
 //     cannot be the maximum: the filtered scale pass takes the exact maxima of every 64th tile as
@@ -2523,9 +2525,9 @@ static bool codes_overlap(const Launch& L, const WorkerPtrs& W, int first_worker
 }
 
 // Two code buffers that overlap are left to the main pass, which gives them an order.
-bool use_parked(const Launch& L, const WorkerPtrs& W, int first_worker, int num)
+bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
 {
-    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num)
+    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1)
         && !codes_overlap(L, W, first_worker, num);
 }
 

@@ -210,11 +210,15 @@ constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
 // of 4 workers 404 / 395; 500 of 10000 and 100, 4 workers 107 / 123, 3000 times 609 / 513; 1000 of 20000 375 / 338.  Beside a
 // long layer the step goes worker by worker for its sake: one of 20 M and 300 of 1000, 4 workers 371 / 412; 1.3 G with 0.1 G of
 // them 20.96 / 20.95 ms.
-constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num)
+// Stochastic rounding, whose random numbers keep the vector units busy: one worker's call of 16 M 58 / 65, 32 M 109 / 109, 64 M
+// 209 / 191; step of 4 workers of 8 M 159 / 162, off the grid 168 / 178, of 16 M 306 / 286 and 380 / 317.  A list most of which is a
+// longer layer: 5 M beside 12 M, 8 workers 558 / 568; 12 M beside 30 M, 4 workers 777 / 763.
+constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic)
 {
     const int64_t work = elems * num, M = 1 << 20;
     const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
-    return work >= (num == 1 ? 8 : 24) * M && (filled || work >= 72 * M) && 4 * elems >= all;
+    const int64_t least = !filled ? 72 : stochastic || 2 * elems < all ? 48 : num == 1 ? 8 : 24;
+    return work >= least * M && 4 * elems >= all;
 }
 
 // The meeting place of a layer's workgroups: a word that counts arrivals and departures, and copies of the published scale

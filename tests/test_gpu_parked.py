@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 M = 1 << 20
 UNIT, LONGEST = 16384, 384 * 16384
-LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers; one worker's call: 8 M
+LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers, twice that for stochastic
+                                        # rounding; one worker's call: 8 M, 48 M
 
 
 def _sizes(total):
@@ -24,7 +25,7 @@ def _sizes(total):
 @pytest.mark.parametrize("less", [0, 1])
 @pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=0, k_x=14, weight_ef=0), dict(k_g=4, k_x=6, rounding=1, seed=3)])
 def test_whole_step_gives_the_bits_of_the_separate_calls(polls, less, cfgkw):
-    sizes = _sizes(LEAST - less)
+    sizes = _sizes((2 if cfgkw.get("rounding") else 1) * LEAST - less)
     a, b = _State(sizes, False, **cfgkw), _State(sizes, False, **cfgkw)
     a.q.set_scale_polls(polls)
     for t in (1, 2):

@@ -201,6 +201,9 @@ def test_units_cover_a_parked_layer(tmp_path):
         CHECK(meeting_words(n) == (n > 1 ? (1 + meeting_copies(n)) * kMeetingLine : 0), "%lld", (long long)len);
     }
     const int64_t M = 1 << 20;
-    CHECK(worth_parking(8 * M, 512, 8 * M, 1) && !worth_parking(8 * M - 1, 512, 8 * M, 1), "one worker");
-    CHECK(worth_parking(6 * M, 384, 24 * M, 4) && !worth_parking(6 * M - 1, 384, 6 * M, 4), "four workers");
-    CHECK(!worth_parking(6 * M, 384, 24 * M + 1, 4) && !worth_parking(20 * M, 4000, 20 * M, 1), "beside a long layer, mostly empty units");""")
+    CHECK(worth_parking(8 * M, 512, 8 * M, 1, false) && !worth_parking(8 * M - 1, 512, 8 * M, 1, false), "one worker");
+    CHECK(worth_parking(6 * M, 384, 12 * M, 4, false) && !worth_parking(6 * M - 1, 384, 6 * M, 4, false), "four workers");
+    CHECK(worth_parking(12 * M, 768, 48 * M, 4, false) && !worth_parking(12 * M - 1, 768, 24 * M, 4, false), "beside a longer layer");
+    CHECK(!worth_parking(12 * M, 768, 48 * M + 1, 4, false), "beside a much longer layer");
+    CHECK(worth_parking(12 * M, 768, 12 * M, 4, true) && !worth_parking(12 * M - 1, 768, 12 * M, 4, true), "stochastic");
+    CHECK(worth_parking(18 * M, 4000, 18 * M, 4, false) && !worth_parking(18 * M - 1, 4000, 18 * M, 4, false), "mostly empty units");""")
