@@ -24,6 +24,7 @@ struct qadam_ctx {
     int32_t   num_tiles;
     ListShape shape;
     int32_t   longest_layer;    // tiles of the longest layer
+    int32_t   max_row;          // see Launch
     Section   scaled;           // see Launch
     int32_t*  d_scaled;         // with short layers apart: scaled.seg_tile_begin and scaled.layers, one behind the other
     const Tile* short_layers;
@@ -127,7 +128,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
-    L.scaled = h->scaled; L.max_row = h->scaled.shape.num_tiles * moment_parts(L);
+    L.scaled = h->scaled; L.max_row = h->max_row;
     L.parked = h->parked; L.rest = h->rest; L.parked_done = false;
     L.rest_sample_tiles = h->d_sample_tiles + h->num_sample_tiles; L.num_rest_sample_tiles = h->num_rest_sample_tiles;
     L.served_tiles = h->scaled.tiles; L.served = h->scaled.shape;
@@ -388,6 +389,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         word_off += seg_words;
     }
     h->code_words = word_off;
+    h->max_row = h->scaled.shape.num_tiles * (int32_t)moment_cut(h->scaled.shape).parts;
 
     seg_tile_begin[num_segments] = (int32_t)tiles.size();
     h->num_tiles = (int32_t)tiles.size();
@@ -407,7 +409,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     if (e == hipSuccess)
         e = hipMemcpy(h->d_seg_tile_begin, seg_tile_begin.data(), sizeof(int32_t) * (num_segments + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess && h->scaled.shape.num_tiles > 0)
-        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->scaled.shape.num_tiles * num_workers * moment_cut(h->scaled.shape).parts);
+        e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_max), sizeof(uint32_t) * (size_t)h->max_row * num_workers);
     if (e == hipSuccess && h->num_tiles > 0)
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tile_sum), sizeof(double) * (size_t)h->num_tiles);
     if (e == hipSuccess && num_segments > 0)

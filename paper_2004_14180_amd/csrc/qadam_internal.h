@@ -104,7 +104,8 @@ struct Launch {
     int32_t     num_tiles;
     ListShape   shape;
     Section     scaled;
-    int32_t     max_row;    // maxima from one worker's row to the next's
+    int32_t     max_row;    // maxima from one worker's row to the next's, the same in every call and pass: calls for
+                            // different workers may run on different streams
     Parked      parked;     // layers of `scaled` that k_parked can do; num_units == 0: none
     Section     rest;       // `scaled` without them
     const int32_t* rest_sample_tiles;

@@ -2393,14 +2393,10 @@ static float residual_bound_factor(const StepScalars& S)
     return (S.rounding == 0 ? half_gap : 2.0f * half_gap) * (1.0f + 0x1p-20f);
 }
 
-// Every pass gives worker w the same row of the maxima, whether it leaves one per tile or `moment_parts`: calls for
-// different workers may run on different streams.
-static int max_row(const Launch& L) { return L.max_row; }
-
 static void fill_scale_args(ScaleArgs& A, const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker)
 {
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) A.scales[i] = W.scales[i];
-    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.row = max_row(L); A.seg_tile_begin = L.scaled.seg_tile_begin;
+    A.inv_scales = L.inv_scales; A.tile_max = L.tile_max; A.row = L.max_row; A.seg_tile_begin = L.scaled.seg_tile_begin;
     A.first_worker = first_worker; A.num_segments = L.num_segments; A.num_tiles = L.scaled.shape.num_tiles;
     A.layers = L.scaled.layers; A.num_layers = L.scaled.num_layers;
     A.err_bound = L.err_bound; A.thr = L.thr;
@@ -2417,7 +2413,7 @@ static bool fold_in_quantizer(const Launch& L, int num, int max_per_tile)
 static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num, int max_per_tile)
 {
     Fold F;
-    F.row = max_row(L); F.per_tile = max_per_tile;
+    F.row = L.max_row; F.per_tile = max_per_tile;
     F.tile_max = fold_in_quantizer(L, num, max_per_tile) ? L.tile_max + (size_t)worker * F.row : nullptr;
     F.seg_tile_begin = L.scaled.seg_tile_begin;
     F.num_segments = L.num_segments;
@@ -2461,7 +2457,7 @@ static void fill_amax_args(AmaxArgs& A, const Launch& L, const WorkerPtrs& W, in
 {
     A.tiles = L.scaled.tiles; A.num_tiles = L.scaled.shape.num_tiles;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) { A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; }
-    A.tile_max = L.tile_max; A.row = max_row(L);
+    A.tile_max = L.tile_max; A.row = L.max_row;
     A.first_worker = first_worker;
     A.tile_list = nullptr; A.thr = L.thr; A.num_segments = L.num_segments;
     A.err_bound = L.err_bound; A.status = L.status;
@@ -2539,7 +2535,7 @@ hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
-    A.row = max_row(L); A.maxima = L.tile_max + L.rest.shape.num_tiles;
+    A.row = L.max_row; A.maxima = L.tile_max + L.rest.shape.num_tiles;
     A.meeting = L.parked.meeting; A.meeting_words = L.parked.meeting_words;
     A.inv_scales = L.inv_scales; A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
     A.num_segments = L.num_segments; A.first_worker = first_worker; A.polls = L.parked.polls;
@@ -2875,7 +2871,7 @@ hipError_t launch_worker_moments_w(const Launch& L, const StepScalars& S, const 
 {
     if (L.scaled.shape.num_tiles == 0 || num == 0) return hipSuccess;
     MomentsWArgs A;
-    A.tiles = L.scaled.tiles; A.row = max_row(L); A.S = S;
+    A.tiles = L.scaled.tiles; A.row = L.max_row; A.S = S;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.mw[i] = W.mw[i]; A.vw[i] = W.vw[i]; A.err[i] = W.err[i];
     }
