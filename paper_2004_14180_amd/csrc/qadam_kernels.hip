@@ -1226,8 +1226,6 @@ __device__ __forceinline__ void wait_for_loads()
     asm volatile("" ::: "memory");
 }
 
-__device__ __forceinline__ void wait_for_stores() { wait_for_loads(); }    // one counter for both
-
 // ---- a short segment in one workgroup (qadam_quantize_segment_noalloc) ---------------------------
 // Scale and quantization in one launch: g and e are read once and p stays in registers across the reduction.
 // Bound by latency: one load, two barriers, one store.  10 k elements 13.4 -> 9.5 us per call against the two
@@ -1298,8 +1296,9 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
 // turn 229.  Units are drawn from a counter in the order of the layers; dealt out beforehand they end 10 us later.
 //
 // No workgroup depends on another one being resident: each waits a bounded number of polls for the scale, and then finds
-// it by itself by reading the whole layer, publishes it and goes on.  What the others have not published yet they cannot
-// have overwritten, so a maximum that was complete before any scale of the layer could be seen is the layer's.
+// it by itself by reading the whole layer, publishes it and goes on.  Whoever overwrote a part of the layer had seen one of
+// the copies of its scale.  The copies come to be seen in any order, so behind its reads the workgroup looks at every copy:
+// if none is there, nothing of what it read was overwritten and its maximum is the layer's; else it takes the scale it finds.
 struct ParkedArgs {
     const ParkedUnit* units;
     const ParkedLayer* layers;
@@ -1364,14 +1363,19 @@ __device__ __forceinline__ Place place_of(const ParkedArgs& A, uint32_t item)
 __device__ __forceinline__ void publish_scale(const ParkedArgs& A, const Place& q, uint32_t max_bits)
 {
     const int lane = threadIdx.x & 63;
-    if (q.P.num_units > 1 && lane < q.P.copies) store_agent(q.meeting + (1 + lane) * kMeetingLine, max_bits | kPublished);
+    if (q.P.num_units > 1 && lane < q.P.copies) {
+        // Exchanges, whose answers say that the copies are where the others find them and the last to leave clears them,
+        // before this workgroup leaves the meeting.
+        const uint32_t before = __hip_atomic_exchange(q.meeting + (1 + lane) * kMeetingLine, max_bits | kPublished,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" : : "v"(before) : "memory");
+    }
     if (lane == 0) {
         const Scale r = make_scale(max_bits);
         A.scales[q.w][q.P.t.seg] = r.s;
         A.inv_scales[(size_t)q.w * A.num_segments + q.P.t.seg] = r.inv;
         A.err_bound[(size_t)q.w * A.num_segments + q.P.t.seg] = residual_bound(r.s, A.bound_factor);
     }
-    wait_for_stores();                          // before this workgroup leaves the meeting
 }
 
 // Hands in a unit's maximum; whoever comes last publishes the scale.  By one wavefront.
@@ -1399,6 +1403,14 @@ __device__ __forceinline__ void arrive(const ParkedArgs& A, const Place& q, uint
 __device__ __forceinline__ uint32_t poll_scale(const Place& q)
 {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)load_agent(q.meeting + (1 + q.unit % q.P.copies) * kMeetingLine));
+}
+
+// The scale where any copy shows it, else 0.  By one wavefront, behind its workgroup's reads of the layer.
+__device__ __forceinline__ uint32_t scale_behind_reads(const Place& q)
+{
+    const int copy = copy_behind_reads(threadIdx.x & 63, q.P.copies);
+    const uint32_t word = copy < 0 ? 0u : load_agent(q.meeting + (1 + copy) * kMeetingLine);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(word));
 }
 
 // What the turn begins with, to every thread: the published scale, where the workgroup holds a unit of a layer of several
@@ -1436,7 +1448,7 @@ __device__ __forceinline__ uint32_t begin_turn(const ParkedArgs& A, const Place&
         }
         const uint32_t all = block_max<kParkedThreads>(local);      // every thread's reads are done
         if (one) {
-            word = poll_scale(q);
+            word = scale_behind_reads(q);
             if (word == 0) {
                 word = all | kPublished;
                 publish_scale(A, q, all);

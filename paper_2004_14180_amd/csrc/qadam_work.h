@@ -226,6 +226,8 @@ constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num,
 constexpr int kMeetingLine = 32;
 constexpr uint32_t kArrivals = 0xffffu, kDeparture = 0x10000u;
 constexpr int meeting_copies(int units) { return units <= 8 ? 1 : units >= 512 ? 64 : (units + 7) / 8; }
+// The copy that a lane looks at behind its workgroup's reads of a layer, -1: none.  Every copy is some lane's.
+constexpr int copy_behind_reads(int lane, int copies) { return lane < copies ? lane : -1; }
 constexpr int meeting_words(int units) { return units > 1 ? (1 + meeting_copies(units)) * kMeetingLine : 0; }
 
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------

@@ -35,6 +35,20 @@ def test_whole_step_gives_the_bits_of_the_separate_calls(polls, less, cfgkw):
     assert a.q.get_status() == 0
 
 
+@pytest.mark.parametrize("polls", [1, 2, 4])
+def test_scales_found_in_both_ways_within_a_layer(polls):
+    """Few polls: some workgroups of a layer read it while others have its scale already and overwrite what they hold.  The layers
+    have more than eight units, whose workgroups poll several copies of the scale."""
+    sizes = [LEAST // 8, 40 * UNIT + 77, 20 * UNIT + 1, 9 * UNIT]
+    sizes.append(LEAST - sum(sizes))
+    a, b = _State(sizes, False), _State(sizes, False)
+    a.q.set_scale_polls(polls)
+    for t in (1, 2, 3):
+        a.step(t, False, True)
+        b.step(t, False, False)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+
+
 @pytest.mark.parametrize("sizes,workers,trust", [([LONGEST, 2 * M, 1001, 0, 70001], 1, 0),      # all parked, an empty layer
                                                  ([LONGEST + 1, 2 * M - 1, 7], 1, 0),           # not enough of them
                                                  ([LONGEST + 1, 3, LONGEST - 1, 2 * M], 3, 2)])  # beside a longer one, filtered

@@ -207,3 +207,24 @@ def test_units_cover_a_parked_layer(tmp_path):
     CHECK(!worth_parking(12 * M, 768, 48 * M + 1, 4, false), "beside a much longer layer");
     CHECK(worth_parking(12 * M, 768, 12 * M, 4, true) && !worth_parking(12 * M - 1, 768, 12 * M, 4, true), "stochastic");
     CHECK(worth_parking(18 * M, 4000, 18 * M, 4, false) && !worth_parking(18 * M - 1, 4000, 18 * M, 4, false), "mostly empty units");""")
+
+
+def test_a_scale_published_in_part_is_seen_behind_the_reads_of_a_layer(tmp_path):
+    """The copies of a layer's scale appear one by one.  A workgroup that polls one of them may overwrite its unit as soon as
+    that one is there, so a workgroup that has read the layer meanwhile has to see the scale whichever copy it is."""
+    _run(tmp_path, """
+    for (int units = 2; units <= kParkedGroups; ++units) {
+        const int copies = meeting_copies(units);
+        for (int first = 0; first < copies; ++first) {
+            bool landed[64] = {}, seen = false;
+            landed[first] = true;
+            bool polled = false;
+            for (int u = 0; u < units; ++u) polled |= u % copies == first;
+            for (int lane = 0; lane < 64; ++lane) {
+                const int c = copy_behind_reads(lane, copies);
+                CHECK(c >= -1 && c < copies, "%d units, lane %d", units, lane);
+                seen |= c >= 0 && landed[c];
+            }
+            CHECK(seen || !polled, "%d units, copy %d", units, first);
+        }
+    }""")
