@@ -255,9 +255,9 @@ int qadam_weight_dequantize_f16(qadam_handle_t h, const void* wcodes_dev, void* 
  * in the status word.  An integration that runs clean with 3 honours the contract of 1 and 2. */
 int qadam_trust_error_buffers(qadam_handle_t h, int32_t on);
 
-/* Bring-up aid: the workgroups of a layer that fits the chip's registers meet over its scale, and each polls `polls` times for
- * it before it finds the scale by itself from the whole layer (as happens where other work keeps most of the GPU busy).
- * 0: always by itself; -1: the default.  No result depends on it, only the time. */
+/* Bring-up aid: the workgroups of a layer that the chip holds meet over its scale, and each polls `polls` times for it before it
+ * puts its part of the layer aside, to be read again later in the same call (as happens where other work keeps most of the GPU
+ * busy).  0: always; -1: the default.  No result depends on it, only the time. */
 int qadam_set_scale_polls(qadam_handle_t h, int32_t polls);
 
 /* Placement of a handle's buffers inside ONE caller-allocated block (host arithmetic only; nothing is

@@ -370,7 +370,7 @@ class QAdam:
         self._check(self._lib.qadam_trust_error_buffers(self._h, int(on)))
 
     def set_scale_polls(self, polls=-1):
-        """Polls for a layer's scale before a workgroup finds it by itself (results never depend on it); -1: the default."""
+        """Polls for a layer's scale before a workgroup puts its part aside (results never depend on it); -1: the default."""
         self._check(self._lib.qadam_set_scale_polls(self._h, int(polls)))
 
     def profile_enable(self, on=True):

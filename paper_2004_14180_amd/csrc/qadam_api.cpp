@@ -206,14 +206,12 @@ int check_capture(const qadam_ctx* h, void* stream, bool* capturing)
     return QADAM_OK;
 }
 
-// Polls of about a microsecond each: ten times the longest wait of workgroups that run beside each other (25 us).
-constexpr int kParkedPolls = 250;
-
 void free_parked(qadam_ctx* h)
 {
     if (h->d_rest) (void)hipFree(h->d_rest);
     if (h->d_parked) (void)hipFree(h->d_parked);
     if (h->parked.meeting) (void)hipFree(h->parked.meeting);
+    if (h->parked.aside) (void)hipFree(h->parked.aside);
 }
 
 bool identity_g(const qadam_ctx* h) { return h->cfg.k_g == QADAM_IDENTITY; }
@@ -337,7 +335,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             p.t = Tile{a, word_off, (int32_t)n, l, (a % 4 != 0 ? kTileUnaligned : 0) | (int32_t)(seg_words - used_words) << 8, 0};
             p.num_units = parked_units(n);
             p.first_unit = (int32_t)parked_units_of.size();
-            if (parked_layers.empty()) h->parked.meeting_words = kMeetingLine;     // the units drawn
+            if (parked_layers.empty()) h->parked.meeting_words = kMeetingCounts;
             p.meeting = h->parked.meeting_words;
             p.copies = meeting_copies(p.num_units);
             h->parked.meeting_words += meeting_words(p.num_units);
@@ -453,6 +451,8 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             e = hipMalloc(reinterpret_cast<void**>(&h->parked.meeting), meeting_bytes);
             if (e == hipSuccess) e = hipMemset(h->parked.meeting, 0, meeting_bytes);
         }
+        if (e == hipSuccess && h->parked.num_units > 0)
+            e = hipMalloc(reinterpret_cast<void**>(&h->parked.aside), sizeof(uint32_t) * (size_t)h->parked.num_units * num_workers);
     }
     if (e == hipSuccess && h->num_tiles > 0) {
         e = hipMalloc(reinterpret_cast<void**>(&h->d_tiles), sizeof(Tile) * tiles.size());

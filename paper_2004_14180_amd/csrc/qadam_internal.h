@@ -89,10 +89,11 @@ struct ParkedUnit {
 struct Parked {
     const ParkedUnit*  units;   // device
     const ParkedLayer* layers;  // device
-    uint32_t* meeting;      // device, [num_workers][meeting_words], zero between launches
+    uint32_t* meeting;      // device, [num_workers][meeting_words], zero between launches but for the launches counted
+    uint32_t* aside;        // device, [num_workers][num_units]
     int32_t   num_units, meeting_words;
     int64_t   num_elems;
-    int32_t   polls;        // before a workgroup finds the scale by itself
+    int32_t   polls;        // for a scale before a workgroup puts its unit aside
 };
 
 struct Launch {

@@ -715,7 +715,7 @@ __device__ __forceinline__ void load_scan(const float* __restrict__ p, int nvali
 // maximum does not care which lane sees which element, so the range is walked as the aligned quads of
 // memory it contains plus at most three single elements at either end.  thr != 0: e is read only for
 // quads (elements) whose |g| reaches thr (filtered scale pass).
-template <bool KEEP, int THREADS = kBlockThreads>
+template <bool KEEP>
 __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, const float* __restrict__ e,
                                                int64_t start, int len, uint32_t thr)
 {
@@ -735,12 +735,12 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
         }
     }
     // four quads per lane per trip, their loads issued together (a tile holds at most 1024 quads)
-    for (int64_t q0 = a0 + (int64_t)threadIdx.x * 4; q0 < a1; q0 += THREADS * 16) {
+    for (int64_t q0 = a0 + (int64_t)threadIdx.x * 4; q0 < a1; q0 += kBlockThreads * 16) {
         float gv[4][4], ev[4][4];
         bool live[4], cand[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t q = q0 + (int64_t)k * THREADS * 4;
+            const int64_t q = q0 + (int64_t)k * kBlockThreads * 4;
             live[k] = q < a1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { gv[k][j] = 0.0f; ev[k][j] = 0.0f; }
@@ -757,7 +757,7 @@ __device__ __forceinline__ uint32_t amax_range(const float* __restrict__ g, cons
                     top = ab > top ? ab : top;
                 }
                 cand[k] = live[k] && top >= thr;
-                if (cand[k]) load_scan<4, KEEP>(e + q0 + (int64_t)k * THREADS * 4, 4, ev[k]);
+                if (cand[k]) load_scan<4, KEEP>(e + q0 + (int64_t)k * kBlockThreads * 4, 4, ev[k]);
             }
         }
 #pragma unroll
@@ -1293,12 +1293,14 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
 // worker 257 -> 206 us, 340 M 738 us; beyond the first and last turn 6.0 TB/s.  Layers of one unit each, which do not meet,
 // take the same time.  Chunks whose loads are in flight together, 2 / 4 / 8: 209 / 206 / 220 us (8 spills); workgroups of 256 /
 // 512 / 1024 threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded, waited for and stored in
-// turn 229.  Units are drawn from a counter in the order of the layers; dealt out beforehand they end 10 us later.
+// turn 229.  A workgroup's first unit is the one of its own number, the others are drawn from a counter in the order of the layers:
+// all dealt out beforehand they end 10 us later, all drawn they begin 4 us later, as 512 draws at once take that long.
 //
-// No workgroup depends on another one being resident: each waits a bounded number of polls for the scale, and then finds
-// it by itself by reading the whole layer, publishes it and goes on.  Whoever overwrote a part of the layer had seen one of
-// the copies of its scale.  The copies come to be seen in any order, so behind its reads the workgroup looks at every copy:
-// if none is there, nothing of what it read was overwritten and its maximum is the layer's; else it takes the scale it finds.
+// No workgroup depends on another one being resident.  A workgroup claims its first unit when it starts, and a unit that is claimed
+// or drawn is held by a running workgroup, which loads it and hands in its maximum without waiting in between.  A workgroup whose
+// polls run out, or whose layer has units that are not held yet, puts its unit aside: it leaves it as it is in memory, goes on,
+// and loads it once more when the units have run out.  If a first unit is missing, it claims that one and loads it instead.  So
+// every unit of a layer that is waited for comes to be held, and the scale comes.
 struct ParkedArgs {
     const ParkedUnit* units;
     const ParkedLayer* layers;
@@ -1308,7 +1310,8 @@ struct ParkedArgs {
     uint32_t* codes[QADAM_MAX_WORKERS];
     float* scales[QADAM_MAX_WORKERS];
     uint32_t* maxima;       // rows of `row` maxima, one row per worker, one maximum per unit
-    uint32_t* meeting;      // [N][meeting_words], zero between launches
+    uint32_t* meeting;      // [N][meeting_words], zero between launches but for the launches counted
+    uint32_t* aside;        // [N][num_units]: of a unit put aside, the one its workgroup put aside before it
     float* inv_scales;      // [N][L]
     float* err_bound;       // [N][L]
     float bound_factor;
@@ -1320,6 +1323,10 @@ struct ParkedArgs {
 constexpr int kParkedLoads = 4;                 // chunks whose loads are in flight together
 constexpr uint32_t kNoUnit = 0xffffffffu;
 constexpr uint32_t kPublished = 0x80000000u;    // marks a published scale, whose own sign bit is 0
+// Every wait ends, also where two calls for one worker overlap, which the boundary forbids, and their counts are wrong: this
+// many polls (about a second) for a scale that has to come, then a NaN in its place, which the status word reports.
+constexpr int kLastPolls = 1 << 20;
+constexpr uint32_t kNoScale = kPublished | 0x7fc00000u;
 
 // f(0), f(1), .. f(N - 1) with constants, however long f is (an unrolled loop has a limit)
 template <int N, typename F>
@@ -1405,60 +1412,98 @@ __device__ __forceinline__ uint32_t poll_scale(const Place& q)
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)load_agent(q.meeting + (1 + q.unit % q.P.copies) * kMeetingLine));
 }
 
-// The scale where any copy shows it, else 0.  By one wavefront, behind its workgroup's reads of the layer.
-__device__ __forceinline__ uint32_t scale_behind_reads(const Place& q)
+// The counts of a launch, in the first worker's row: the numbers drawn, the launches before this one and, from kClaims on, for
+// every first unit the launch that claimed it last.
+__device__ __forceinline__ uint32_t* counts_of(const ParkedArgs& A) { return A.meeting + (size_t)A.first_worker * A.meeting_words; }
+
+// By one thread.
+__device__ __forceinline__ bool claim(uint32_t* counts, uint32_t unit, uint32_t launch)
 {
-    const int copy = copy_behind_reads(threadIdx.x & 63, q.P.copies);
-    const uint32_t word = copy < 0 ? 0u : load_agent(q.meeting + (1 + copy) * kMeetingLine);
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(word));
+    return __hip_atomic_exchange(counts + kClaims + unit, launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != launch;
 }
 
-// What the turn begins with, to every thread: the published scale, where the workgroup holds a unit of a layer of several
-// (`met`), and the next unit to load, unless they have run out (`draw`).
-__device__ __forceinline__ uint32_t begin_turn(const ParkedArgs& A, const Place& q, bool met, bool draw, uint32_t& next)
+// A first unit from `first` to `last` that nobody holds, or kNoUnit.  By one wavefront.
+__device__ __forceinline__ uint32_t unclaimed(const uint32_t* counts, uint32_t first, uint32_t last, uint32_t launch)
 {
-    __shared__ uint32_t shared_word, shared_next;
-    const bool one = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) == 0;
-    if (one) {
-        uint32_t* drawn = A.meeting + (size_t)A.first_worker * A.meeting_words;
-        uint32_t ticket = 0, word = 0;
-        for (int i = 0; met && i < A.polls; ++i) {
-            word = poll_scale(q);
-            if (word) break;
-            __builtin_amdgcn_s_sleep(8);
+    for (; first <= last && first < (uint32_t)kParkedGroups; first += 64) {
+        const uint32_t u = first + (threadIdx.x & 63);
+        const bool free = u <= last && u < (uint32_t)kParkedGroups && load_agent(counts + kClaims + u) != launch;
+        const uint64_t any = __builtin_amdgcn_ballot_w64(free);
+        if (any) return first + (uint32_t)__builtin_ctzll(any);
+    }
+    return kNoUnit;
+}
+
+// By one thread.  kNoUnit: they have run out.
+__device__ __forceinline__ uint32_t draw_unit(const ParkedArgs& A, uint32_t* counts, uint32_t launch)
+{
+    const uint32_t unit = kParkedGroups + __hip_atomic_fetch_add(counts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Every workgroup draws until it draws in vain, once, and has claimed or lost its first unit before: nothing more is drawn or
+    // claimed in this launch.
+    if (unit == A.total + kParkedGroups - 1u) {
+        store_agent(counts, 0u);
+        store_agent(counts + 1, launch);
+    }
+    return unit < A.total ? unit : kNoUnit;
+}
+
+// What a turn begins with, and what the first wavefront keeps for it.
+struct Turn {
+    uint32_t word;          // the scale of the unit to quantize, 0: the unit was put aside
+    uint32_t next;          // the unit to load, kNoUnit: none is left
+    uint32_t again;         // it was put aside before
+    uint32_t launch;        // the number of the launch
+    uint32_t kept;          // before the first turn the workgroup's own first unit, kNoUnit: another one has it
+    uint32_t out;           // the counter has run out
+    uint32_t aside;         // the unit that the workgroup put aside last
+};
+
+// To every thread: the scale of `item`, a unit of a layer of several (`met`), and the next unit.
+__device__ __forceinline__ void begin_turn(const ParkedArgs& A, const Place& q, uint32_t item, bool met, Turn& turn)
+{
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) == 0) {
+        uint32_t* counts = counts_of(A);
+        uint32_t* links = A.aside + (size_t)A.first_worker * A.num_units;
+        const uint32_t launch = (uint32_t)__builtin_amdgcn_readfirstlane((int)turn.launch);
+        const bool out = __builtin_amdgcn_readfirstlane((int)turn.out) != 0;
+        uint32_t word = 0, missing = kNoUnit;
+        if (met) {
+            const uint32_t first = item - (uint32_t)q.unit, last = first + (uint32_t)q.P.num_units - 1u;     // of the layer's units
+            for (int i = 0; i < (out ? kLastPolls : A.polls); ++i) {
+                word = poll_scale(q);
+                if (word) break;
+                if (i % kPollsUnheld == kPollsUnheld - 1) {
+                    missing = unclaimed(counts, first, last, launch);
+                    if (missing != kNoUnit || (!out && kParkedGroups + load_agent(counts) <= last)) break;
+                }
+                __builtin_amdgcn_s_sleep(8);
+            }
         }
         if (threadIdx.x == 0) {
-            // Drawn behind the wait: a unit that is drawn is loaded without another wait, so the layer waited for can be complete.
-            if (draw) ticket = __hip_atomic_fetch_add(drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            shared_word = word;
-            shared_next = draw && gridDim.x + ticket < A.total ? gridDim.x + ticket : kNoUnit;
-            // every workgroup draws until it draws in vain, which makes A.total draws
-            if (draw && ticket == A.total - 1) store_agent(drawn, 0u);
+            if (met && word == 0) {
+                if (out && missing == kNoUnit) {
+                    word = kNoScale;
+                } else {
+                    store_agent(links + item, turn.aside);
+                    turn.aside = item;
+                }
+            }
+            // Behind the wait: a unit that is held is loaded without another one, so that its layer can be complete.
+            uint32_t next = turn.kept, again = 0;
+            if (missing != kNoUnit && claim(counts, missing, launch)) next = missing;
+            if (next == kNoUnit && !out) {
+                next = draw_unit(A, counts, launch);
+                turn.out = next == kNoUnit;
+            }
+            if (next == kNoUnit && turn.aside != kNoUnit) {
+                next = turn.aside;
+                turn.aside = load_agent(links + next);
+                again = 1;
+            }
+            turn.word = word; turn.next = next; turn.again = again; turn.kept = kNoUnit;
         }
     }
     __syncthreads();
-    uint32_t word = shared_word;
-    if (draw) next = (uint32_t)__builtin_amdgcn_readfirstlane((int)shared_next);
-    if (met && word == 0) {
-        const Tile& t = q.P.t;
-        uint32_t local = 0;
-        for (int o = 0; o < t.len; o += kTileElems) {
-            const uint32_t m = amax_range<false, kParkedThreads>(A.grad[q.w], A.err[q.w], t.start + o, min(t.len - o, kTileElems), 0u);
-            local = m > local ? m : local;
-        }
-        const uint32_t all = block_max<kParkedThreads>(local);      // every thread's reads are done
-        if (one) {
-            word = scale_behind_reads(q);
-            if (word == 0) {
-                word = all | kPublished;
-                publish_scale(A, q, all);
-            }
-            if (threadIdx.x == 0) shared_word = word;
-        }
-        __syncthreads();
-        word = shared_word;
-    }
-    return word;
 }
 
 template <int ROUNDING>
@@ -1476,17 +1521,29 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
     for (int k = 0; k < kParkedChunks; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) p[k][j] = 0.0f;
-    uint32_t next = blockIdx.x;
-    bool first = true;
+    uint32_t next = kNoUnit;
+    __shared__ Turn turn;
+    if (threadIdx.x == 0) {
+        uint32_t* counts = counts_of(A);
+        turn.launch = counts[1] + 1u;
+        turn.kept = claim(counts, blockIdx.x, turn.launch) ? blockIdx.x : kNoUnit;
+        turn.out = 0;
+        turn.aside = kNoUnit;
+    }
 #pragma unroll 1
     for (;;) {
-        const Place q = place_of(A, item != kNoUnit ? item : 0u);
-        const bool met = item != kNoUnit && q.P.num_units > 1, draw = !first && next != kNoUnit;
-        if (met || draw) {
-            const uint32_t seen = begin_turn(A, q, met, draw, next);
-            if (met) word = seen;
+        const Place q = place_of(A, item != kNoUnit ? item : next != kNoUnit ? next : 0u);
+        bool met = item != kNoUnit && q.P.num_units > 1;
+        begin_turn(A, q, item, met, turn);
+        next = (uint32_t)__builtin_amdgcn_readfirstlane((int)turn.next);
+        const bool again = __builtin_amdgcn_readfirstlane((int)turn.again) != 0;
+        if (met) {
+            word = turn.word;
+            if (__builtin_amdgcn_readfirstlane((int)word) == 0) {
+                item = kNoUnit;
+                met = false;
+            }
         }
-        first = false;
         if (item == kNoUnit && next == kNoUnit && other_item == kNoUnit) break;
         uint32_t departed = 0;
         if (met && threadIdx.x == 0)
@@ -1499,8 +1556,8 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
         const bool n_whole = n_begin + (kParkedChunks - 1) * n_stride + kParkedChunk <= n.P.t.len;
         const float* n_grad = A.grad[n.w] + n.P.t.start;
         const float* n_err = A.err[n.w] + n.P.t.start;
-        static_for<kParkedChunks / kParkedLoads>([&](auto turn) {
-            constexpr int k0 = decltype(turn)::value * kParkedLoads;
+        static_for<kParkedChunks / kParkedLoads>([&](auto part) {
+            constexpr int k0 = decltype(part)::value * kParkedLoads;
             float g[kParkedLoads][4], e[kParkedLoads][4];
             if (next != kNoUnit) {
                 if (n_whole) {
@@ -1536,8 +1593,11 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                     if constexpr (ROUNDING == 1) {
                         const int64_t gi = q.P.t.start + base + lane * 4;
                         const Shift sf = make_shift(q.P.t);
-                        if (sf.r) uniforms_shifted(S, gi, (uint32_t)q.w, 0u, sf.r, U);
-                        else uniforms<4>(S, gi, (uint32_t)q.w, 0u, U);
+                        StepScalars R = S;
+                        // the keys of the ten rounds are worked out here and not held in registers over the turns
+                        asm volatile("" : "+s"(R.key0), "+s"(R.key1));
+                        if (sf.r) uniforms_shifted(R, gi, (uint32_t)q.w, 0u, sf.r, U);
+                        else uniforms<4>(R, gi, (uint32_t)q.w, 0u, U);
                     }
                     uint32_t codes;
                     worker_lane<4, ROUNDING>(old, zero, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);     // p + 0 reproduces p
@@ -1560,8 +1620,8 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                     }
             }
         });
-        if (item != kNoUnit && q.unit == 0) {
-            write_pad_words(A.codes[q.w], q.P.t, S.code_bits);
+        if (item != kNoUnit) {
+            if (q.unit == 0) write_pad_words(A.codes[q.w], q.P.t, S.code_bits);
             check_scale(sc.s, A.status);
         }
         __syncthreads();                        // the words in LDS are read
@@ -1583,7 +1643,7 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
             // not by the wavefront that begins the next turn, whose wait goes on beside this one
             if (wave == kParkedThreads / 64 - 1) {
                 if (n.P.num_units == 1) publish_scale(A, n, bm);
-                else arrive(A, n, bm);
+                else if (!again) arrive(A, n, bm);
             }
             word = bm;                          // of a layer of one unit
         }
@@ -2548,13 +2608,13 @@ hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
     }
     A.row = L.max_row; A.maxima = L.tile_max + L.rest.shape.num_tiles;
-    A.meeting = L.parked.meeting; A.meeting_words = L.parked.meeting_words;
+    A.meeting = L.parked.meeting; A.aside = L.parked.aside; A.meeting_words = L.parked.meeting_words;
     A.inv_scales = L.inv_scales; A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
     A.num_segments = L.num_segments; A.first_worker = first_worker; A.polls = L.parked.polls;
     A.status = L.status;
     A.num_units = (uint32_t)L.parked.num_units; A.total = A.num_units * (uint32_t)num;
     const unsigned lds = kParkedThreads * kParkedChunks * sizeof(float4);
-    const dim3 grid(A.total < (uint32_t)kParkedGroups ? A.total : (uint32_t)kParkedGroups), block(kParkedThreads);
+    const dim3 grid(kParkedGroups), block(kParkedThreads);
     if (S.rounding == 0) hipLaunchKernelGGL(k_parked<0>, grid, block, lds, L.stream, A);
     else hipLaunchKernelGGL(k_parked<1>, grid, block, lds, L.stream, A);
     return hipGetLastError();

@@ -199,6 +199,9 @@ constexpr int parked_units(int64_t len)
 // and a layer of nearly as many units as there are workgroups leaves none of them for its neighbours.  One worker's call of 85 M
 // elements, us, two passes / this way: layers of 36 units 260 / 210, 144 260 / 206, 256 259 / 206, 384 272 / 222, 512 257 / 284.
 constexpr int kParkedGroups = 512;
+// Polls for a scale, of about 0.7 us each, before a workgroup puts its unit aside: where the layer's units are all held, and
+// between two looks whether they are.
+constexpr int kParkedPolls = 250, kPollsUnheld = 8;
 constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
 
 // Whether a call for num workers does the layers of up to kParkedLongest elements this way: `elems` in `units`, of the `all`
@@ -225,9 +228,9 @@ constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num,
 // for up to eight of them each to poll, every one in a line of its own.  Words.
 constexpr int kMeetingLine = 32;
 constexpr uint32_t kArrivals = 0xffffu, kDeparture = 0x10000u;
+// In front of a worker's meeting places: the counts of a launch, and the claims of the workgroups' first units.
+constexpr int kClaims = kMeetingLine, kMeetingCounts = kClaims + kParkedGroups;
 constexpr int meeting_copies(int units) { return units <= 8 ? 1 : units >= 512 ? 64 : (units + 7) / 8; }
-// The copy that a lane looks at behind its workgroup's reads of a layer, -1: none.  Every copy is some lane's.
-constexpr int copy_behind_reads(int lane, int copies) { return lane < copies ? lane : -1; }
 constexpr int meeting_words(int units) { return units > 1 ? (1 + meeting_copies(units)) * kMeetingLine : 0; }
 
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------

@@ -1,5 +1,8 @@
 """GPU parity of layers whose scale and quantization are one launch (k_parked): units of every filling, on and off the 16-byte
-grid, the longest layer, both ways a workgroup comes by the scale, calls on two streams, captured calls, non-finite scales."""
+grid, the longest layer, units that wait for their scale and units put aside, calls on two streams and beside other work,
+captured calls, non-finite scales."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -36,9 +39,9 @@ def test_whole_step_gives_the_bits_of_the_separate_calls(polls, less, cfgkw):
 
 
 @pytest.mark.parametrize("polls", [1, 2, 4])
-def test_scales_found_in_both_ways_within_a_layer(polls):
-    """Few polls: some workgroups of a layer read it while others have its scale already and overwrite what they hold.  The layers
-    have more than eight units, whose workgroups poll several copies of the scale."""
+def test_some_units_of_a_layer_are_put_aside(polls):
+    """Few polls: some workgroups of a layer quantize the units they hold while others put theirs aside and load them again.  The
+    layers have more than eight units, whose workgroups poll several copies of the scale."""
     sizes = [LEAST // 8, 40 * UNIT + 77, 20 * UNIT + 1, 9 * UNIT]
     sizes.append(LEAST - sum(sizes))
     a, b = _State(sizes, False), _State(sizes, False)
@@ -57,31 +60,69 @@ def test_against_the_oracle(sizes, workers, trust):
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
-def _calls(streams, polls):
-    sizes = [2 * M] * 3 + [1003, 2 * M]
-    seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
-    q = QAdam(QAdamConfig(), seg, 2)
-    q.set_scale_polls(polls)
-    gen = torch.Generator(device="cuda")
-    gen.manual_seed(5)
-    P = int(seg[-1])
-    f = lambda s: torch.empty(P, device="cuda").normal_(0.0, s, generator=gen)  # noqa: E731
-    g, e = [f(1e-2) for _ in range(2)], [f(1e-3) for _ in range(2)]
-    codes = [torch.full((q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
-    scales = [torch.zeros(len(sizes), device="cuda") for _ in range(2)]
+class _Calls:
+    """worker_quantize for two workers, whose layers one worker's call parks."""
+
+    def __init__(self, sizes):
+        seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        self.q = q = QAdam(QAdamConfig(), seg, 2)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(5)
+        P = int(seg[-1])
+        f = lambda s: torch.empty(P, device="cuda").normal_(0.0, s, generator=gen)  # noqa: E731
+        self.g, self.e = [f(1e-2) for _ in range(2)], [f(1e-3) for _ in range(2)]
+        self.codes = [torch.full((q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+        self.scales = [torch.zeros(len(sizes), device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+
+    def run(self, streams, steps=3, beside=None):
+        """Seconds; beside: enqueues work on another stream before every step."""
+        t0 = time.perf_counter()
+        for t in range(1, steps + 1):
+            if beside:
+                beside()
+            for i in range(2):
+                self.q.worker_quantize(i, t, self.g[i], self.e[i], self.codes[i], self.scales[i], stream=streams[i])
+        torch.cuda.synchronize()
+        assert self.q.get_status() == 0
+        return time.perf_counter() - t0
+
+    def state(self):
+        return self.e + self.codes + self.scales
+
+
+SIZES = [2 * M] * 3 + [1003, 2 * M]
+
+
+def _matmuls():
+    a, stream = torch.randn(4096, 4096, device="cuda", dtype=torch.bfloat16), torch.cuda.Stream()
+
+    def run():
+        with torch.cuda.stream(stream):
+            for _ in range(8):
+                torch.matmul(a, a)
     torch.cuda.synchronize()
-    for t in (1, 2, 3):
-        for i in range(2):
-            q.worker_quantize(i, t, g[i], e[i], codes[i], scales[i], stream=streams[i])
-    torch.cuda.synchronize()
-    assert q.get_status() == 0
-    return e + codes + scales
+    return run
 
 
 def test_workers_on_two_streams():
-    one = _calls([torch.cuda.current_stream()] * 2, -1)
-    two = _calls([torch.cuda.Stream() for _ in range(2)], -1)
-    assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(one, two))
+    one, two, beside = _Calls(SIZES), _Calls(SIZES), _Calls(SIZES)
+    one.run([torch.cuda.current_stream()] * 2)
+    two.run([torch.cuda.Stream() for _ in range(2)])
+    beside.run([torch.cuda.Stream() for _ in range(2)], beside=_matmuls())
+    assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(one.state(), two.state()))
+    assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(one.state(), beside.state()))
+
+
+def test_calls_on_two_streams_do_not_wait_for_workgroups_without_a_place():
+    """The workgroups of two calls share the chip, so that half of each call's have no place yet.  Where the others waited for
+    them, and then read whole layers to find the scale, a call took twelve times as long as alone; it takes about as long, and
+    twice as long is more than any run of one side differs."""
+    c = _Calls([768 * 768, 3 * 768 * 768, 768, 4 * 768 * 768, 4 * 768 * 768, 768] * 12)
+    one, two = [torch.cuda.current_stream()] * 2, [torch.cuda.Stream() for _ in range(2)]
+    c.run(one), c.run(two)
+    alone, beside = (min(c.run(streams, 10) for _ in range(3)) for streams in (one, two))
+    assert beside < 2.0 * alone, (alone, beside)
 
 
 def test_captured_step_is_the_eager_one():

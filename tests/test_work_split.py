@@ -209,22 +209,10 @@ def test_units_cover_a_parked_layer(tmp_path):
     CHECK(worth_parking(18 * M, 4000, 18 * M, 4, false) && !worth_parking(18 * M - 1, 4000, 18 * M, 4, false), "mostly empty units");""")
 
 
-def test_a_scale_published_in_part_is_seen_behind_the_reads_of_a_layer(tmp_path):
-    """The copies of a layer's scale appear one by one.  A workgroup that polls one of them may overwrite its unit as soon as
-    that one is there, so a workgroup that has read the layer meanwhile has to see the scale whichever copy it is."""
+def test_a_parked_launch_has_a_unit_for_every_workgroup(tmp_path):
+    """A workgroup's first unit is the one of its own number."""
     _run(tmp_path, """
-    for (int units = 2; units <= kParkedGroups; ++units) {
-        const int copies = meeting_copies(units);
-        for (int first = 0; first < copies; ++first) {
-            bool landed[64] = {}, seen = false;
-            landed[first] = true;
-            bool polled = false;
-            for (int u = 0; u < units; ++u) polled |= u % copies == first;
-            for (int lane = 0; lane < 64; ++lane) {
-                const int c = copy_behind_reads(lane, copies);
-                CHECK(c >= -1 && c < copies, "%d units, lane %d", units, lane);
-                seen |= c >= 0 && landed[c];
-            }
-            CHECK(seen || !polled, "%d units, copy %d", units, first);
-        }
-    }""")
+    const int64_t unit = kParkedChunk * kParkedChunks;
+    for (int num = 1; num <= 32; ++num) for (int stochastic = 0; stochastic < 2; ++stochastic)
+        for (int64_t units = 1; units <= 2 * kParkedGroups; ++units) for (int64_t elems : {units, units * unit / 2, units * unit})
+            CHECK(!worth_parking(elems, units, elems, num, stochastic) || units * num >= kParkedGroups, "%lld", (long long)units);""")
