@@ -261,10 +261,12 @@ int qadam_trust_error_buffers(qadam_handle_t h, int32_t on);
 int qadam_set_scale_polls(qadam_handle_t h, int32_t polls);
 
 /* Placement of a handle's buffers inside ONE caller-allocated block (host arithmetic only; nothing is
- * allocated, no HIP call is made).  Why: the main pass of qadam_step_fused reads 2N+4 and writes N+5 streams at
- * once, and on MI355X its speed depends on where those streams lie in physical memory: with the buffers
- * packed closely one after the other (what a process gets when it allocates them in turn on a freshly booted
- * GPU) the pass runs 8-14 % slower than with the streams spread widely over the device's memory.  A block
+ * allocated, no HIP call is made).  Why: a step keeps many streams open at once (the whole step in one main pass 2N+4 read
+ * and N+5 written ones), and on MI355X its speed depends on where those streams lie in physical memory: with the
+ * buffers packed closely one after the other (what a process gets when it allocates them in turn on a freshly
+ * booted GPU) the main pass runs 8-14 % slower than with the streams spread widely over the device's memory.  Large
+ * vectors are then done in one launch per worker and one for the server, with fewer streams each; where the
+ * buffers lie as this layout deals them and the block is 192 GiB or more, in the main pass.  A block
  * obtained with one hipMalloc on an otherwise empty device is physically contiguous, so offsets inside it
  * decide the placement: the layout deals the buffers of each kind alternately to the first half of the block
  * and to its second half.  The block should therefore be much larger than the buffers (ideally most of the

@@ -800,39 +800,44 @@ int qadam_arena_layout(qadam_handle_t h, size_t arena_bytes, int32_t with_worker
     if (!h) return fail(QADAM_EINVAL, "null handle");
     if (!out) return fail(QADAM_EINVAL, "null layout");
     std::memset(out, 0xff, sizeof *out);            // every entry SIZE_MAX until placed
-    const int N = h->num_workers;
-    constexpr size_t align = 2u << 20;              // buffers start on 2 MiB boundaries (the driver's large pages)
-    auto rup = [](size_t n) { return (n + align - 1) / align * align; };
-    const size_t big = rup((size_t)h->num_params * 4u);
-    const size_t code = rup(qadam_grad_code_bytes(h));
-    const size_t wcode = rup(qadam_weight_code_bytes(h));
-    const size_t scale = rup((size_t)h->num_segments * 4u);
-    // the buffers in the order they are dealt to the two groups: the read+write streams first, then the
-    // read-only gradients, then the small write-only ones
-    struct Item { size_t* where; size_t bytes; };
-    std::vector<Item> items;
-    items.push_back({&out->x, big}); items.push_back({&out->m, big});
-    items.push_back({&out->v, big}); items.push_back({&out->werr, big});
-    for (int i = 0; i < N; ++i) items.push_back({&out->errs[i], big});
-    if (with_worker_moments)
-        for (int i = 0; i < N; ++i) { items.push_back({&out->mw[i], big}); items.push_back({&out->vw[i], big}); }
-    for (int i = 0; i < N; ++i) items.push_back({&out->grads[i], big});
-    for (int i = 0; i < N; ++i) items.push_back({&out->codes[i], code});
-    items.push_back({&out->wcodes, wcode});
-    for (int i = 0; i < N; ++i) items.push_back({&out->scales[i], scale});
+    const bool moments = with_worker_moments != 0;
+    constexpr size_t align = kArenaAlign;
+    const size_t big = arena_round((size_t)h->num_params * 4u);
+    const size_t code = arena_round(qadam_grad_code_bytes(h));
+    const size_t wcode = arena_round(qadam_weight_code_bytes(h));
+    const size_t scale = arena_round((size_t)h->num_segments * 4u);
+    auto bytes = [&](Buffer b) {
+        return b == Buffer::codes ? code : b == Buffer::wcodes ? wcode : b == Buffer::scales ? scale : big;
+    };
+    auto where = [&](Buffer b, int i) -> size_t& {
+        switch (b) {
+        case Buffer::x: return out->x;
+        case Buffer::m: return out->m;
+        case Buffer::v: return out->v;
+        case Buffer::werr: return out->werr;
+        case Buffer::err: return out->errs[i];
+        case Buffer::mw: return out->mw[i];
+        case Buffer::vw: return out->vw[i];
+        case Buffer::grad: return out->grads[i];
+        case Buffer::codes: return out->codes[i];
+        case Buffer::wcodes: return out->wcodes;
+        default: return out->scales[i];
+        }
+    };
     size_t fill[2] = {0, 0};
-    for (size_t k = 0; k < items.size(); ++k) {
-        const int grp = (int)(k & 1);
-        *items[k].where = fill[grp];                // offset inside the group for now
-        fill[grp] += items[k].bytes;
-    }
+    deal_buffers(h->num_workers, moments, [&](Buffer b, int i, int group) {
+        where(b, i) = fill[group];                  // offset inside the group for now
+        fill[group] += bytes(b);
+    });
     out->bytes_needed = fill[0] + fill[1];
     if (arena_bytes < out->bytes_needed) return fail(QADAM_ERANGE, "the block is smaller than the buffers");
     // group 1 starts in the middle of the block, or right behind group 0 when the block is that tight
     size_t second = (arena_bytes / 2) / align * align;
     if (second < fill[0]) second = fill[0];
     if (second + fill[1] > arena_bytes) second = fill[0];
-    for (size_t k = 1; k < items.size(); k += 2) *items[k].where += second;
+    deal_buffers(h->num_workers, moments, [&](Buffer b, int i, int group) {
+        if (group == 1) where(b, i) += second;
+    });
     return QADAM_OK;
 }
 

@@ -2782,10 +2782,43 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
 // 32 M 673 / 638, 96 M 2035 / 1901; 8 of 12 M 436 / 444, 16 M 581 / 547, 96 M 3566 / 3238; 16 of 4 M 255 / 301, 8 M 550 / 543,
 // 96 M 6798 / 6002; variant W, 4 of 24 M 726 / 723, 64 M 1964 / 1929, 8 of 12 M 705 / 708, 96 M 5769 / 5588.
 // Two code buffers that overlap would not survive until the server reads them; the main pass reads none.
-static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, bool variant_w)
+// Where the buffers lie as qadam_arena_layout deals them and its groups are a third of the device's memory apart or more, the
+// streams of the main pass are spread as well as they can be, and from three workers on (variant W: always) it is as fast or
+// faster.  ms per step, main pass / by worker, groups 132 GiB apart: 1.3 G parameters, one worker 11.12 / 11.03, two 15.06 / 15.09,
+// four 20.13 / 20.44, eight 33.66 / 34.28, variant W 11.00 / 11.20, 18.52 / 18.79, 33.46 / 34.05, 64.08 / 65.19; 24 M, eight 0.657 /
+// 0.667; 96 M, three 1.268 / 1.284, eight 2.565 / 2.544; 64 M, four 1.014 / 1.013; 256 M, one 2.15 / 2.07, sixteen 12.48 / 12.53.
+// 50 GiB apart: 96 M, eight 2.802 / 2.570; 256 M, sixteen 13.68 / 12.76; 70 GiB: 1.3 G, four 22.24 / 21.01.  Allocated one by one:
+// 1.3 G, four 23.05 / 21.49, eight 34.73 / 34.84.
+constexpr int64_t kGroupsApart = (int64_t)96 << 30;
+
+static bool dealt_apart(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
+{
+    const uint64_t big = arena_round((uint64_t)L.num_params * 4u), code = arena_round((uint64_t)L.code_words * 4u);
+    auto bytes = [&](Buffer b) {
+        return b == Buffer::codes ? code : b == Buffer::wcodes ? arena_round((uint64_t)L.num_params * S.wcode_bytes)
+             : b == Buffer::scales ? arena_round((uint64_t)L.num_segments * 4u) : big;
+    };
+    auto at = [&](Buffer b, int i) -> uint64_t {
+        switch (b) {
+        case Buffer::x: return (uint64_t)sp.x;
+        case Buffer::m: return (uint64_t)sp.m;
+        case Buffer::v: return (uint64_t)sp.v;
+        case Buffer::werr: return (uint64_t)sp.werr;
+        case Buffer::err: return (uint64_t)W.err[i];
+        case Buffer::mw: return (uint64_t)W.mw[i];
+        case Buffer::vw: return (uint64_t)W.vw[i];
+        case Buffer::grad: return (uint64_t)W.grad[i];
+        default: return 0;                          // the small ones may lie anywhere
+        }
+    };
+    return groups_apart(S.num_workers, variant_w, bytes, at) >= kGroupsApart;
+}
+
+static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
 {
     const int64_t n = L.scaled.num_elems;
     if (variant_w ? keep_parked(n, S.num_workers) : keep_scanned(n, S.num_workers)) return false;
+    if ((variant_w || S.num_workers > 2) && dealt_apart(L, S, W, sp, variant_w)) return false;
     return !codes_overlap(L, W, 0, S.num_workers);
 }
 
@@ -2816,7 +2849,7 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
                                    bool variant_w)
 {
     if (L.served.num_tiles == 0) return hipSuccess;
-    if (L.parked_done || step_by_worker(L, S, W, variant_w)) {
+    if (L.parked_done || step_by_worker(L, S, W, sp, variant_w)) {
         launch_by_worker(L, S, W, sp, variant_w);
         return hipGetLastError();
     }

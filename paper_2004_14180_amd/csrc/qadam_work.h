@@ -233,6 +233,47 @@ constexpr int kClaims = kMeetingLine, kMeetingCounts = kClaims + kParkedGroups;
 constexpr int meeting_copies(int units) { return units <= 8 ? 1 : units >= 512 ? 64 : (units + 7) / 8; }
 constexpr int meeting_words(int units) { return units > 1 ? (1 + meeting_copies(units)) * kMeetingLine : 0; }
 
+// ---- buffers in one block (qadam_arena_layout) -------------------------------------------------------------------------
+enum class Buffer { x, m, v, werr, err, mw, vw, grad, codes, wcodes, scales };
+
+// f(buffer, worker, group) in the order in which the layout deals them to its two groups: the read+write streams first, then the
+// read-only gradients, then the small write-only ones.
+template <typename F>
+void deal_buffers(int workers, bool worker_moments, F&& f)
+{
+    int dealt = 0;
+    auto deal = [&](Buffer b, int i) { f(b, i, dealt++ & 1); };
+    for (Buffer b : {Buffer::x, Buffer::m, Buffer::v, Buffer::werr}) deal(b, 0);
+    for (int i = 0; i < workers; ++i) deal(Buffer::err, i);
+    if (worker_moments)
+        for (int i = 0; i < workers; ++i) { deal(Buffer::mw, i); deal(Buffer::vw, i); }
+    for (int i = 0; i < workers; ++i) deal(Buffer::grad, i);
+    for (int i = 0; i < workers; ++i) deal(Buffer::codes, i);
+    deal(Buffer::wcodes, 0);
+    for (int i = 0; i < workers; ++i) deal(Buffer::scales, i);
+}
+
+// What a buffer of `elems` parameters takes in the block: buffers start on 2 MiB boundaries (the driver's large pages).
+constexpr uint64_t kArenaAlign = 2u << 20;
+constexpr uint64_t arena_round(uint64_t n) { return (n + kArenaAlign - 1) / kArenaAlign * kArenaAlign; }
+
+// Bytes from the first group to the second where the buffers lie as the layout deals them, 0 where they do not.  bytes(b): of
+// one buffer, rounded up; at(b, i): its address, 0: not in use.
+template <typename Bytes, typename At>
+int64_t groups_apart(int workers, bool worker_moments, Bytes&& bytes, At&& at)
+{
+    uint64_t begin[2] = {0, 0}, fill[2] = {0, 0};
+    bool dealt = true;
+    deal_buffers(workers, worker_moments, [&](Buffer b, int i, int group) {
+        if (const uint64_t p = at(b, i)) {
+            if (begin[group] == 0) begin[group] = p - fill[group];
+            dealt = dealt && begin[group] == p - fill[group];
+        }
+        fill[group] += bytes(b);
+    });
+    return dealt && begin[0] != 0 && begin[1] > begin[0] ? (int64_t)(begin[1] - begin[0]) : 0;
+}
+
 // ---- flat launches (weight quantizer, decoder) -----------------------------------------------------------------------
 // Workgroups of `per_block` consecutive elements each, in rows of 2^31 work-items.
 struct FlatGrid {

@@ -21,7 +21,7 @@ def _bits(t):
 
 
 class _State:
-    def __init__(self, sizes, w, one_buffer=False, **cfgkw):
+    def __init__(self, sizes, w, one_buffer=False, block=0, **cfgkw):
         self.cfg, _ = configs(**cfgkw)
         seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
         P = int(seg[-1])
@@ -37,6 +37,21 @@ class _State:
         words = lambda: torch.full((self.q.grad_code_bytes() // 4,), -1, dtype=torch.int32, device="cuda")  # noqa: E731
         self.codes = [words()] * N if one_buffer else [words() for _ in range(N)]
         self.scales = [torch.zeros(len(sizes), device="cuda") for _ in range(N)]
+        if block:
+            self._move(block, w, P)
+
+    def _move(self, nbytes, w, P):
+        """The buffers as qadam_arena_layout deals them to one block."""
+        self.block = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        lay = self.q.arena_layout(nbytes, w)
+        at = lambda t, o: self.block[o:o + 4 * P].view(torch.float32).copy_(t)  # noqa: E731
+        all_at = lambda ts, name: [at(t, o) for t, o in zip(ts, lay[name])]  # noqa: E731
+        self.g, self.e = all_at(self.g, "grads"), all_at(self.e, "errs")
+        if w:
+            self.m, self.v = all_at(self.m, "mw"), all_at(self.v, "vw")
+        else:
+            self.m, self.v = [at(self.m[0], lay["m"])], [at(self.v[0], lay["v"])]
+        self.x, self.werr = at(self.x, lay["x"]), at(self.werr, lay["werr"])
 
     def step(self, t, w, whole):
         q = self.q
@@ -89,3 +104,18 @@ def test_overlapping_code_buffers_do_not_change_the_step(w):
         a.step(t, w, True)
         b.step(t, w, True)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state(), b.state())), t
+
+
+@pytest.mark.parametrize("w", [False, True])
+def test_buffers_dealt_apart_do_not_change_the_step(w):
+    """One block as qadam_arena_layout deals it, its groups more than 96 GiB apart, where the call is one main pass."""
+    torch.cuda.empty_cache()
+    nbytes = 200 << 30
+    if torch.cuda.mem_get_info()[0] < nbytes + (16 << 30):
+        pytest.skip("the device's memory is not free")
+    sizes = [384 * 16384 + 4097, 1001, 70000, 3, (LIMIT_W if w else 0) + 5]
+    a, b = _State(sizes, w), _State(sizes, w, block=nbytes)
+    for t in (1, 2):
+        a.step(t, w, True)
+        b.step(t, w, True)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t

@@ -216,3 +216,30 @@ def test_a_parked_launch_has_a_unit_for_every_workgroup(tmp_path):
     for (int num = 1; num <= 32; ++num) for (int stochastic = 0; stochastic < 2; ++stochastic)
         for (int64_t units = 1; units <= 2 * kParkedGroups; ++units) for (int64_t elems : {units, units * unit / 2, units * unit})
             CHECK(!worth_parking(elems, units, elems, num, stochastic) || units * num >= kParkedGroups, "%lld", (long long)units);""")
+
+
+def test_buffers_dealt_to_two_groups_are_recognized(tmp_path):
+    """The distance of the groups is found from the addresses of the buffers that a call has; a buffer that lies elsewhere is
+    noticed, whichever it is."""
+    _run(tmp_path, """
+    auto bytes = [](Buffer b) { return arena_round(b == Buffer::codes ? 300 << 20 : b == Buffer::wcodes ? 700 << 20 : b == Buffer::scales ? 100 : (uint64_t)3 << 30); };
+    for (int N : {1, 2, 3, 8, 32}) for (int w = 0; w < 2; ++w) for (uint64_t apart : {(uint64_t)200 << 30, (uint64_t)500 << 30}) {
+        uint64_t place[11][32] = {}, fill[2] = {0, 0};
+        int dealt = 0;
+        deal_buffers(N, w, [&](Buffer b, int i, int group) {
+            place[(int)b][i] = (1ull << 44) + group * apart + fill[group];
+            fill[group] += bytes(b);
+            ++dealt;
+        });
+        CHECK(dealt == 5 + (w ? 6 : 4) * N, "%d of %d", dealt, N);
+        for (int moved = -1; moved < 8; ++moved) {
+            const bool used = moved < 0 || w || (moved != (int)Buffer::mw && moved != (int)Buffer::vw);
+            if (!used) continue;
+            auto at = [&](Buffer b, int i) -> uint64_t {
+                if (b >= Buffer::codes || (w && (b == Buffer::m || b == Buffer::v))) return 0;
+                return place[(int)b][i] + ((int)b == moved && i == (b >= Buffer::err ? N - 1 : 0) ? kArenaAlign : 0);
+            };
+            const bool counts = moved >= 0 && !(w && (moved == (int)Buffer::m || moved == (int)Buffer::v));
+            CHECK(groups_apart(N, w, bytes, at) == (counts ? 0 : (int64_t)apart), "%d workers, moved %d", N, moved);
+        }
+    }""")
