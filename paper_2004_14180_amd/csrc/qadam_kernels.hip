@@ -56,18 +56,27 @@ __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
 
 // ------------------------------------------------------------------------------------------------
-// Philox4x32-10 (Salmon et al., SC'11): counter (c0..c3), key (k0,k1) -> four 32-bit words.
+// Philox4x32-10 (Salmon et al., SC'11): counter (c0..c3), key (k0,k1) -> four 32-bit words.  HALVES: the products' halves by a
+// multiplication each, else both by one.  us, halves / one: the main pass, whose registers the 64-bit products crowd, one worker
+// of 20 M (2^20) elements 177 / 199, 4.7 M 51.1 / 52.8, four of 20 M 375 / 378; k_parked, GPT-2 small, 8 workers 3419 / 3382 per
+// step, off the grid 4088 / 3925; worker quantizer off the grid, 80 M 303 / 287; weight quantizer, 5 M 13.1 / 12.7.
 // ------------------------------------------------------------------------------------------------
+template <bool HALVES>
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t (&out)[4])
 {
     constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        // one instruction for both halves of a product
-        const uint64_t m0 = (uint64_t)M0 * c0, m1 = (uint64_t)M1 * c2;
-        const uint32_t hi0 = (uint32_t)(m0 >> 32), lo0 = (uint32_t)m0;
-        const uint32_t hi1 = (uint32_t)(m1 >> 32), lo1 = (uint32_t)m1;
+        uint32_t hi0, lo0, hi1, lo1;
+        if constexpr (HALVES) {
+            hi0 = __umulhi(M0, c0); lo0 = M0 * c0;
+            hi1 = __umulhi(M1, c2); lo1 = M1 * c2;
+        } else {
+            const uint64_t m0 = (uint64_t)M0 * c0, m1 = (uint64_t)M1 * c2;
+            hi0 = (uint32_t)(m0 >> 32); lo0 = (uint32_t)m0;
+            hi1 = (uint32_t)(m1 >> 32); lo1 = (uint32_t)m1;
+        }
         c0 = hi1 ^ c1 ^ k0;
         c1 = lo1;
         c2 = hi0 ^ c3 ^ k1;
@@ -80,13 +89,13 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 
 // Uniforms in [0,1) with 24 bits for the V consecutive elements starting at global index gi.
 // Counter = (gi/4 low, gi/4 high, step, worker + (stream << 16)); element j takes word j mod 4.
-template <int V>
+template <int V, bool HALVES>
 __device__ __forceinline__ void uniforms(const StepScalars& S, int64_t gi, uint32_t worker, uint32_t stream,
                                          float (&U)[V])
 {
     const uint64_t blk = (uint64_t)gi >> 2;
     uint32_t out[4];
-    philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), S.step, worker + (stream << 16), S.key0, S.key1, out);
+    philox4x32_10<HALVES>((uint32_t)blk, (uint32_t)(blk >> 32), S.step, worker + (stream << 16), S.key0, S.key1, out);
     if constexpr (V == 4) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) U[j] = (float)(out[j] >> 8) * 0x1p-24f;
@@ -461,12 +470,13 @@ __device__ __forceinline__ void store_wcodes_shifted(void* __restrict__ base, in
 
 // uniforms of four consecutive elements that start r into a Philox block: words r..3 of the block
 // of gi and words 0..r-1 of the next one
+template <bool HALVES>
 __device__ __forceinline__ void uniforms_shifted(const StepScalars& S, int64_t gi, uint32_t worker, uint32_t stream,
                                                  int r, float (&U)[4])
 {
     float lo[4], hi[4];
-    uniforms<4>(S, gi - r, worker, stream, lo);
-    uniforms<4>(S, gi - r + 4, worker, stream, hi);
+    uniforms<4, HALVES>(S, gi - r, worker, stream, lo);
+    uniforms<4, HALVES>(S, gi - r + 4, worker, stream, hi);
     const bool r1 = r == 1, r2 = r == 2;
     U[0] = r1 ? lo[1] : (r2 ? lo[2] : lo[3]);
     U[1] = r1 ? lo[2] : (r2 ? lo[3] : hi[0]);
@@ -497,12 +507,12 @@ __device__ __forceinline__ void stw(void* __restrict__ base, int wcode_bytes, in
     else store_wcodes<V>(base, wcode_bytes, gi, nvalid, j);
 }
 
-template <int V, bool SH>
+template <int V, bool SH, bool HALVES = false>
 __device__ __forceinline__ void unif(const StepScalars& S, int64_t gi, uint32_t worker, uint32_t stream, const Shift& sf,
                                      float (&U)[V])
 {
-    if constexpr (SH) uniforms_shifted(S, gi, worker, stream, sf.r, U);
-    else uniforms<V>(S, gi, worker, stream, U);
+    if constexpr (SH) uniforms_shifted<HALVES>(S, gi, worker, stream, sf.r, U);
+    else uniforms<V, HALVES>(S, gi, worker, stream, U);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -550,7 +560,7 @@ __device__ __forceinline__ void qx_value(float y, float two_kx1, float inv_two_k
     xhat = jf * inv_two_kx1;
 }
 
-template <int V, int ROUNDING, bool SH = false>
+template <int V, int ROUNDING, bool SH = false, bool HALVES = false>
 __device__ __forceinline__ void weight_lane(const StepScalars& S, const float (&x)[V], const float (&werr_in)[V],
                                             int64_t gi, const Shift& sf, float (&werr_out)[V], int (&j)[V])
 {
@@ -560,7 +570,7 @@ __device__ __forceinline__ void weight_lane(const StepScalars& S, const float (&
     float U[V];
 #pragma unroll
     for (int t = 0; t < V; ++t) U[t] = 0.0f;
-    if constexpr (ROUNDING == 1) unif<V, SH>(S, gi, 0u, 1u, sf, U);
+    if constexpr (ROUNDING == 1) unif<V, SH, HALVES>(S, gi, 0u, 1u, sf, U);
 #pragma unroll
     for (int t = 0; t < V; ++t) {
         const float y = S.weight_ef ? x[t] + werr_in[t] : x[t];
@@ -1596,8 +1606,8 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                         StepScalars R = S;
                         // the keys of the ten rounds are worked out here and not held in registers over the turns
                         asm volatile("" : "+s"(R.key0), "+s"(R.key1));
-                        if (sf.r) uniforms_shifted(R, gi, (uint32_t)q.w, 0u, sf.r, U);
-                        else uniforms<4>(R, gi, (uint32_t)q.w, 0u, U);
+                        if (sf.r) uniforms_shifted<false>(R, gi, (uint32_t)q.w, 0u, sf.r, U);
+                        else uniforms<4, false>(R, gi, (uint32_t)q.w, 0u, U);
                     }
                     uint32_t codes;
                     worker_lane<4, ROUNDING>(old, zero, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);     // p + 0 reproduces p
@@ -1667,7 +1677,7 @@ struct ServerArgs {
 
 // Server arithmetic of one lane's elements, from the sum of the workers' messages to the weight codes, and its stores.
 // W: the server only subtracts the mean message, m and v are not used.
-template <int ROUNDING, int V, bool W, bool SH>
+template <int ROUNDING, int V, bool W, bool SH, bool HALVES = false>
 __device__ __forceinline__ void server_lane(const StepScalars& S, const ServerPtrs& sp, const float (&acc)[V], float (&xv)[V],
                                             float (&mv)[V], float (&vv)[V], const float (&wi)[V], int64_t gi, int nvalid,
                                             const Shift& sf)
@@ -1688,7 +1698,7 @@ __device__ __forceinline__ void server_lane(const StepScalars& S, const ServerPt
     if (S.k_x >= 0) {                                    // else Q_x is the identity
         float wo[V];
         int jc[V];
-        weight_lane<V, ROUNDING, SH>(S, xv, wi, gi, sf, wo, jc);
+        weight_lane<V, ROUNDING, SH, HALVES>(S, xv, wi, gi, sf, wo, jc);
         if (sp.werr) st<V, SH>(sp.werr, gi, nvalid, sf, wo);
         stw<V, SH>(sp.wcodes, S.wcode_bytes, gi, nvalid, sf, jc);
     }
@@ -2030,7 +2040,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
                 float q[V], en[V], Ur[V];
 #pragma unroll
                 for (int j = 0; j < V; ++j) Ur[j] = 0.0f;
-                if constexpr (ROUNDING == 1) unif<V, SH>(S, gi, (uint32_t)i, 0u, sf, Ur);
+                if constexpr (ROUNDING == 1) unif<V, SH, true>(S, gi, (uint32_t)i, 0u, sf, Ur);
                 uint32_t codes;
                 worker_lane<V, ROUNDING>(g[u], e[u], s, inv_s, c, S.mu_bits, Ur, q, en, codes);
                 st<V, SH>(A.err[i], gi, nvalid, sf, en);
@@ -2041,7 +2051,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
                 for (int j = 0; j < V; ++j) acc[j] = acc[j] + q[j];
             }
         }
-        server_lane<ROUNDING, V, W, SH>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
+        server_lane<ROUNDING, V, W, SH, true>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
     }
     if (part_begin + part_len >= t.len)
         for (int i = 0; i < N; ++i) write_pad_words(A.codes[i], t, S.code_bits);
