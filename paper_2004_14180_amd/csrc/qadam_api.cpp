@@ -26,6 +26,7 @@ struct qadam_ctx {
     int32_t   longest_layer;    // tiles of the longest layer
     int32_t   max_row;          // see Launch
     Section   scaled;           // see Launch
+    int64_t   off_grid_elems;
     int32_t*  d_scaled;         // with short layers apart: scaled.seg_tile_begin and scaled.layers, one behind the other
     const Tile* short_layers;
     ShortLayers apart;
@@ -128,7 +129,7 @@ Launch make_launch(const qadam_ctx* h, void* stream)
     L.err_bound = h->d_err_bound; L.thr = h->d_thr;
     L.sample_tiles = h->d_sample_tiles; L.num_sample_tiles = h->num_sample_tiles;
     L.num_tiles = h->num_tiles; L.shape = h->shape; L.longest_layer = h->longest_layer;
-    L.scaled = h->scaled; L.max_row = h->max_row;
+    L.scaled = h->scaled; L.off_grid_elems = h->off_grid_elems; L.max_row = h->max_row;
     L.parked = h->parked; L.rest = h->rest; L.parked_done = false;
     L.rest_sample_tiles = h->d_sample_tiles + h->num_sample_tiles; L.num_rest_sample_tiles = h->num_rest_sample_tiles;
     L.served_tiles = h->scaled.tiles; L.served = h->scaled.shape;
@@ -352,6 +353,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             if (split) scaled_layers.push_back(l);
             ++h->scaled.num_layers;
             h->scaled.num_elems += n;
+            if (a % 4 != 0) h->off_grid_elems += n;
         }
         for (int64_t o = 0; o < n; o += h->tile_elems) {
             Tile t;

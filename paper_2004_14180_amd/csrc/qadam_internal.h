@@ -105,6 +105,7 @@ struct Launch {
     int32_t     num_tiles;
     ListShape   shape;
     Section     scaled;
+    int64_t     off_grid_elems; // of `scaled`: of layers that start off the 16-byte grid
     int32_t     max_row;    // maxima from one worker's row to the next's, the same in every call and pass: calls for
                             // different workers may run on different streams
     Parked      parked;     // layers of `scaled` that k_parked can do; num_units == 0: none

@@ -2505,23 +2505,6 @@ static Fold make_fold(const Launch& L, const StepScalars& S, int worker, int num
     return F;
 }
 
-// Whether the scale pass over n elements of num workers leaves g and e in the cache for the quantizing pass.  A hit
-// costs the memory nothing, a line kept in vain pushes out another's.  us per step, non-temporal / ordinary loads:
-// 4 workers of 2 M (2^20) elements 48.9 / 47.4, 8 M 165.3 / 158.3, 16 M 317.6 / 304.4, 24 M 470.5 / 457.4, 32 M 618 / 611;
-// 8 workers of 12 M 407 / 401; the handle-free call on 24 M 83.4 / 82.4.  One worker's separate call has little else
-// to push out, and gains less: four calls of 8 M in a row 188.4 / 185.5, one of 16 M 159.8 / 159.3, of 24 M 232.0 /
-// 233.2, of 40 M 375.6 / 379.7; four of 119 M 2299 / 2342.
-static bool keep_scanned(int64_t n, int num)
-{
-    const int64_t bytes = 8 * n * num;
-    return bytes <= (num > 1 ? (int64_t)768 << 20 : (int64_t)192 << 20);
-}
-
-// Whether the first pass of variant W leaves the parked p of num workers in the cache for the pass that quantizes it.
-// us per step, non-temporal / ordinary stores: 4 workers of 4 M (2^20) elements 125.7 / 123.4, 16 M 480 / 458, 24 M
-// 709 / 685, 30 M 874 / 866, 48 M 1374 / 1407; one worker of 64 M 601 / 577.
-static bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)512 << 20; }
-
 hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num,
                                 int max_per_tile)
 {
@@ -2784,13 +2767,6 @@ hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const
     return hipGetLastError();
 }
 
-// Whether the whole step runs as one launch per worker and one for the server instead of as one main pass.  The main pass
-// writes no code word that it has to read again, but it has 2N + 4 read and N + 5 written streams open at once; three or four
-// at a time lie in fewer DRAM pages, and the memory gives 6.3 to 6.6 TB/s for 5.2 to 6.3 wherever the buffers lie.  Where the
-// scale pass (variant W: the moments) leaves its data in the cache the streams cost less and the launches more.  us per
-// step, main pass / by worker: one worker of 24 M (2^20) elements 241 / 241, 64 M 656 / 641; 4 of 16 M 323 / 338, 24 M 497 / 498,
-// 32 M 673 / 638, 96 M 2035 / 1901; 8 of 12 M 436 / 444, 16 M 581 / 547, 96 M 3566 / 3238; 16 of 4 M 255 / 301, 8 M 550 / 543,
-// 96 M 6798 / 6002; variant W, 4 of 24 M 726 / 723, 64 M 1964 / 1929, 8 of 12 M 705 / 708, 96 M 5769 / 5588.
 // Two code buffers that overlap would not survive until the server reads them; the main pass reads none.
 // Where the buffers lie as qadam_arena_layout deals them and its groups are a third of the device's memory apart or more, the
 // streams of the main pass are spread as well as they can be, and from three workers on (variant W: always) it is as fast or
@@ -2826,8 +2802,7 @@ static bool dealt_apart(const Launch& L, const StepScalars& S, const WorkerPtrs&
 
 static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
 {
-    const int64_t n = L.scaled.num_elems;
-    if (variant_w ? keep_parked(n, S.num_workers) : keep_scanned(n, S.num_workers)) return false;
+    if (!worth_by_worker(L.scaled.num_elems, L.off_grid_elems, S.num_workers, variant_w, S.rounding == 1)) return false;
     if ((variant_w || S.num_workers > 2) && dealt_apart(L, S, W, sp, variant_w)) return false;
     return !codes_overlap(L, W, 0, S.num_workers);
 }

@@ -183,6 +183,46 @@ constexpr bool server_by_section(const ListShape& all, bool split)
     return split && cut_tiles(all, 256, ((int64_t)1 << 26) - 4096, 1).part_len > 256;
 }
 
+// ---- which data a first pass leaves in the cache, and which vectors are large --------------------------------------------
+// Whether the scale pass over n elements of num workers leaves g and e in the cache for the quantizing pass.  A hit
+// costs the memory nothing, a line kept in vain pushes out another's.  us per step, non-temporal / ordinary loads:
+// 4 workers of 2 M (2^20) elements 48.9 / 47.4, 8 M 165.3 / 158.3, 16 M 317.6 / 304.4, 24 M 470.5 / 457.4, 32 M 618 / 611;
+// 8 workers of 12 M 407 / 401; the handle-free call on 24 M 83.4 / 82.4.  One worker's separate call has little else
+// to push out, and gains less: four calls of 8 M in a row 188.4 / 185.5, one of 16 M 159.8 / 159.3, of 24 M 232.0 /
+// 233.2, of 40 M 375.6 / 379.7; four of 119 M 2299 / 2342.
+constexpr bool keep_scanned(int64_t n, int num)
+{
+    const int64_t bytes = 8 * n * num;
+    return bytes <= (num > 1 ? (int64_t)768 << 20 : (int64_t)192 << 20);
+}
+
+// Whether the first pass of variant W leaves the parked p of num workers in the cache for the pass that quantizes it.
+// us per step, non-temporal / ordinary stores: 4 workers of 4 M (2^20) elements 125.7 / 123.4, 16 M 480 / 458, 24 M
+// 709 / 685, 30 M 874 / 866, 48 M 1374 / 1407; one worker of 64 M 601 / 577.
+constexpr bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)512 << 20; }
+
+// Whether the whole step runs as one launch per worker and one for the server instead of as one main pass.  The main pass
+// writes no code word that it has to read again, but it has 2N + 4 read and N + 5 written streams open at once; three or four
+// at a time lie in fewer DRAM pages, and the memory gives 6.3 to 6.6 TB/s for 5.2 to 6.3 wherever the buffers lie.  Where the
+// scale pass (variant W: the moments) leaves its data in the cache the streams cost less and the launches more.  us per
+// step, main pass / by worker: one worker of 24 M (2^20) elements 241 / 241, 64 M 656 / 641; 4 of 16 M 323 / 338, 24 M 497 / 498,
+// 32 M 673 / 638, 96 M 2035 / 1901; 8 of 12 M 436 / 444, 16 M 581 / 547, 96 M 3566 / 3238; 16 of 4 M 255 / 301, 8 M 550 / 543,
+// 96 M 6798 / 6002; variant W, 4 of 24 M 726 / 723, 64 M 1964 / 1929, 8 of 12 M 705 / 708, 96 M 5769 / 5588.
+// Near the lines it took longer in some forms, which begin later.  us per step, main pass / by worker, nearest rounding: 12 workers of
+// 8 M 409 / 425, 12 M 594 / 604; 16 of 6 M 390 / 410, 8 M 523 / 518, 12 M 734 / 736, 16 M 999 / 963.  Layers off the 16-byte grid: one
+// worker of 28 M 285 / 290, 32 M 329 / 327; 3 of 32 M 590 / 586; 4 of 24 M 525 / 536, 28 M 606 / 607, 32 M 708 / 701; 8 of 12 M 444 /
+// 473, 20 M 740 / 747, 24 M 895 / 890; 16 of 6 M 411 / 461, 12 M 832 / 843, 16 M 1138 / 1101.  Variant W: 8 workers of 18 M 978 / 992,
+// 37 M 1994 / 1997, 50 M 2650 / 2639; 16 of 9 M 950 / 982, 25 M 2641 / 2648, 37 M 3987 / 3969; with stochastic rounding 1 of 129 M
+// 1184 / 1232, 4 of 56 M 1595 / 1640, 8 of 16 M 925 / 959, 16 of 14 M 1535 / 1616.
+constexpr bool worth_by_worker(int64_t n, int64_t off_grid, int num, bool variant_w, bool stochastic)
+{
+    const int64_t work = n * num, M = 1 << 20;
+    if (variant_w) return !stochastic && !keep_parked(n, num) && (num <= 4 || work >= 400 * M);
+    if (keep_scanned(n, num)) return false;
+    if (2 * off_grid > n) return num == 1 ? n >= 32 * M : num <= 3 || work >= (96 + 8 * num) * M;
+    return num <= 8 || n >= 14 * M;
+}
+
 // ---- layers that the chip's registers hold (k_parked) -----------------------------------------------------------------
 // Unit u of a layer's n is its chunks u, u + n, ..., kParkedChunks at most, so that the workgroups of a layer walk it side
 // by side.  A workgroup holds two units.
