@@ -312,7 +312,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         if (!split || n > kTileElems) scaled_elems += n;
         if (parkable(n)) { park_elems += n; park_units += parked_units(n); }
     }
-    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1, cfg->rounding == 1) ||
+    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1, cfg->rounding == 1, true) ||
                                                 worth_parking(park_elems, park_units, scaled_elems, num_workers, cfg->rounding == 1));
     std::vector<Tile> scaled_tiles, short_layers[kShortSizes];
     std::vector<int32_t> sample_tiles, scaled_begin, scaled_layers;
@@ -532,7 +532,7 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step, const 
     W.codes[worker] = static_cast<uint32_t*>(codes_dev); W.scales[worker] = scales_dev;
     const StepScalars S = make_scalars(h, step, 0.0f, 0.0f);
     Launch L = make_launch(h, stream);
-    const bool parked = use_parked(L, S, W, worker, 1);
+    const bool parked = use_parked(L, S, W, worker, 1, true);
     if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
@@ -656,7 +656,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     sp.werr = idx ? nullptr : werr_dev; sp.wcodes = idx ? nullptr : wcodes_dev;
     const StepScalars S = make_scalars(h, step, lr, beta2);
     Launch L = make_launch(h, stream);
-    const bool parked = !idg && use_parked(L, S, W, 0, h->num_workers);
+    const bool parked = !idg && use_parked(L, S, W, 0, h->num_workers, false);
     if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));

@@ -153,7 +153,7 @@ hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const Wor
                                 int max_per_tile = 1);
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
-bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
+bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call);
 hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker);
 // the short layers of the list, from the gradient (variant_w: through the local moments) to the codes, for one worker; or

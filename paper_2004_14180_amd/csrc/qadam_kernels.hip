@@ -2586,9 +2586,9 @@ static bool codes_overlap(const Launch& L, const WorkerPtrs& W, int first_worker
 }
 
 // Two code buffers that overlap are left to the main pass, which gives them an order.
-bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
+bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call)
 {
-    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1)
+    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1, call)
         && !codes_overlap(L, W, first_worker, num);
 }
 

@@ -244,23 +244,29 @@ constexpr int kParkedGroups = 512;
 constexpr int kParkedPolls = 250, kPollsUnheld = 8;
 constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
 
-// Whether a call for num workers does the layers of up to kParkedLongest elements this way: `elems` in `units`, of the `all`
-// elements whose scales have a pass of their own.  The launch starts by loading only and ends by storing only, which costs it
-// about 29 us (85 M elements in 206 us, 340 M in 738).  us, without / with, layers of 2^18 to 2^21 elements: step of one worker
-// of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 / 82.6, 8 M 155 / 141, 32 M
-// 599 / 482; 8 of 2 M 71.0 / 71.9, 4 M 137 / 121, 32 M 1020 / 755; one worker's call of 4 M 13.5 / 20.9, 8 M 31.2 / 29.6, 64 M
-// 207 / 165.  A unit costs about the same however few elements it has: 4000 layers of 5000, one worker's call 69.4 / 78.8, step
-// of 4 workers 404 / 395; 500 of 10000 and 100, 4 workers 107 / 123, 3000 times 609 / 513; 1000 of 20000 375 / 338.  Beside a
-// long layer the step goes worker by worker for its sake: one of 20 M and 300 of 1000, 4 workers 371 / 412; 1.3 G with 0.1 G of
-// them 20.96 / 20.95 ms.
-// Stochastic rounding, whose random numbers keep the vector units busy: one worker's call of 16 M 58 / 65, 32 M 109 / 109, 64 M
-// 209 / 191; step of 4 workers of 8 M 159 / 162, off the grid 168 / 178, of 16 M 306 / 286 and 380 / 317.  A list most of which is a
-// longer layer: 5 M beside 12 M, 8 workers 558 / 568; 12 M beside 30 M, 4 workers 777 / 763.
-constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic)
+// Whether a step of num workers, or one worker's separate call (`call`), does the layers of up to kParkedLongest elements this way:
+// `elems` in `units`, of the `all` elements whose scales have a pass of their own.  The launch starts by loading only and ends by
+// storing only, which costs it about 29 us (85 M elements in 206 us, 340 M in 738).  us, without / with, layers of 2^18 to 2^21
+// elements: step of one worker of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 /
+// 82.6, 8 M 155 / 141, 32 M 599 / 482; 8 of 2 M 71.0 / 71.9, 4 M 137 / 121, 32 M 1020 / 755.  A unit costs about the same however few
+// elements it has: 4000 layers of 5000, one worker's call 69.4 / 78.8, step of 4 workers 404 / 395; 500 of 10000 and 100, 4 workers
+// 107 / 123, 3000 times 609 / 513; 1000 of 20000 375 / 338.  Beside a long layer the step goes worker by worker for its sake: one of
+// 20 M and 300 of 1000, 4 workers 371 / 412; 1.3 G with 0.1 G of them 20.96 / 20.95 ms.  A list most of which is a longer layer: 5 M
+// beside 12 M, 8 workers 558 / 568; 12 M beside 30 M, 4 workers 777 / 763.
+// One worker's call has little to gain while its data is in the cache, and a last turn of few workgroups takes it as long as a full
+// one: layers of 1 M, 8 M in all 29.8 / 30.7, 9 M 35.0 / 36.1 to 38.9, 12 M 43.6 / 45.5, 16 M 54.3 / 51.9, 24 M 79.9 / 73.1, 64 M 207 /
+// 165; of 5 M, 10 M 37.7 / 40.5, 15 M 51.3 / 51.1, 20 M 67.5 / 71.5, 25 M 86 / 76.
+// Stochastic rounding, whose random numbers keep the vector units busy: one worker's call of 16 M 58 / 65, 32 M 109 / 109, 50 M in
+// layers of 5 M 165 / 166 and off the grid 191 / 196, 64 M 211 / 196; step of 2 workers of 24 M 286 / 293, 30 M 358 / 362, 4 of 8 M 159 /
+// 162, off the grid 168 / 178, of 16 M 306 / 286 and 380 / 317.  Beside longer layers, 8 workers, 6 M beside 12 M 612 / 627, off the
+// grid 684 / 737, 12 M beside 12 M 812 / 783 and 916 / 918, 4 workers 465 / 476 and 522 / 567.
+constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic, bool call = false)
 {
-    const int64_t work = elems * num, M = 1 << 20;
+    const int64_t work = elems * num, M = 1 << 20, turns = (units + kParkedGroups - 1) / kParkedGroups;
     const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
-    const int64_t least = !filled ? 72 : stochastic || 2 * elems < all ? 48 : num == 1 ? 8 : 24;
+    const bool full_turns = 16 * units >= 15 * turns * kParkedGroups;
+    const int64_t least = stochastic && elems < all ? 96 : !filled ? 72 : stochastic ? (call || num == 2 ? 64 : 48)
+                        : 2 * elems < all ? 48 : num > 1 ? 24 : !call ? 8 : full_turns ? 15 : 24;
     return work >= least * M && 4 * elems >= all;
 }
 

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 M = 1 << 20
 UNIT, LONGEST = 16384, 384 * 16384
 LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers, twice that for stochastic
-                                        # rounding; one worker's call: 8 M, 48 M
+                                        # rounding; one worker's separate call: 24 M, 64 M
 
 
 def _sizes(total):
@@ -91,7 +91,7 @@ class _Calls:
         return self.e + self.codes + self.scales
 
 
-SIZES = [2 * M] * 3 + [1003, 2 * M]
+SIZES = [2 * M] * 11 + [1003, 2 * M]     # a separate call parks from 24 M on
 
 
 def _matmuls():

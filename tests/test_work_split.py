@@ -215,7 +215,7 @@ def test_a_parked_launch_has_a_unit_for_every_workgroup(tmp_path):
     const int64_t unit = kParkedChunk * kParkedChunks;
     for (int num = 1; num <= 32; ++num) for (int stochastic = 0; stochastic < 2; ++stochastic)
         for (int64_t units = 1; units <= 2 * kParkedGroups; ++units) for (int64_t elems : {units, units * unit / 2, units * unit})
-            CHECK(!worth_parking(elems, units, elems, num, stochastic) || units * num >= kParkedGroups, "%lld", (long long)units);""")
+            CHECK(!(worth_parking(elems, units, elems, num, stochastic) || worth_parking(elems, units, elems, num, stochastic, true)) || units * num >= kParkedGroups, "%lld", (long long)units);""")
 
 
 def test_buffers_dealt_to_two_groups_are_recognized(tmp_path):
@@ -261,3 +261,14 @@ def test_where_the_whole_step_goes_by_worker(tmp_path):
     CHECK(w(128 * M + 1, 1) && !w(128 * M, 1) && w(32 * M + 1, 4) && !w(32 * M, 4), "variant W");
     CHECK(w(50 * M, 8) && !w(50 * M - 1, 8) && w(25 * M, 16) && !w(25 * M - 1, 16), "variant W, many workers");
     CHECK(!worth_by_worker(400 * M, 0, 4, true, true), "variant W, stochastic rounding");""")
+
+
+def test_lines_of_parking_for_a_separate_call_and_stochastic_rounding(tmp_path):
+    _run(tmp_path, """
+    const int64_t M = 1 << 20, unit = kParkedChunk * kParkedChunks;
+    auto call = [&](int64_t elems, bool stochastic) { return worth_parking(elems, (elems + unit - 1) / unit, elems, 1, stochastic, true); };
+    CHECK(!call(8 * M, false) && !call(12 * M, false) && !call(20 * M, false) && !call(22 * M, false), "turns partly empty, or one");
+    CHECK(call(15 * M, false) && call(16 * M, false) && !call(16 * M + 1, false) && call(24 * M, false) && call(25 * M, false), "full turns, many");
+    CHECK(call(64 * M, true) && !call(64 * M - 1, true), "stochastic");
+    CHECK(worth_parking(32 * M, 2048, 32 * M, 2, true) && !worth_parking(32 * M - 1, 2048, 32 * M, 2, true), "two workers");
+    CHECK(worth_parking(12 * M, 768, 24 * M, 8, true) && !worth_parking(12 * M - 1, 768, 24 * M, 8, true), "beside longer layers");""")
