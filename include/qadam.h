@@ -257,7 +257,8 @@ int qadam_trust_error_buffers(qadam_handle_t h, int32_t on);
 
 /* Bring-up aid: the workgroups of a layer that the chip holds meet over its scale, and each polls `polls` times for it before it
  * puts its part of the layer aside, to be read again later in the same call (as happens where other work keeps most of the GPU
- * busy).  0: always; -1: the default.  No result depends on it, only the time. */
+ * busy).  0: always; -1: the default; more than 2^20 count as 2^20, about a second.  No result depends on it, only the
+ * time. */
 int qadam_set_scale_polls(qadam_handle_t h, int32_t polls);
 
 /* Placement of a handle's buffers inside ONE caller-allocated block (host arithmetic only; nothing is

@@ -856,7 +856,7 @@ int qadam_set_scale_polls(qadam_handle_t h, int32_t polls)
 {
     QADAM_CHECK(check_handle(h));
     if (polls < -1) return fail(QADAM_EINVAL, "polls must be -1 or more");
-    h->parked.polls = polls < 0 ? kParkedPolls : polls;
+    h->parked.polls = polls < 0 ? kParkedPolls : polls < kLastPolls ? polls : kLastPolls;
     return QADAM_OK;
 }
 

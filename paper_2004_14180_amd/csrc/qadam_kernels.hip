@@ -1333,9 +1333,7 @@ struct ParkedArgs {
 constexpr int kParkedLoads = 4;                 // chunks whose loads are in flight together
 constexpr uint32_t kNoUnit = 0xffffffffu;
 constexpr uint32_t kPublished = 0x80000000u;    // marks a published scale, whose own sign bit is 0
-// Every wait ends, also where two calls for one worker overlap, which the boundary forbids, and their counts are wrong: this
-// many polls (about a second) for a scale that has to come, then a NaN in its place, which the status word reports.
-constexpr int kLastPolls = 1 << 20;
+// in place of a scale that did not come (kLastPolls); the status word reports it
 constexpr uint32_t kNoScale = kPublished | 0x7fc00000u;
 
 // f(0), f(1), .. f(N - 1) with constants, however long f is (an unrolled loop has a limit)

@@ -242,6 +242,9 @@ constexpr int kParkedGroups = 512;
 // Polls for a scale, of about 0.7 us each, before a workgroup puts its unit aside: where the layer's units are all held, and
 // between two looks whether they are.
 constexpr int kParkedPolls = 250, kPollsUnheld = 8;
+// Every wait ends, also where two calls for one worker overlap, which the boundary forbids, and their counts are wrong: this
+// many polls (about a second) at most, and for a scale that has to come a NaN in its place then.
+constexpr int kLastPolls = 1 << 20;
 constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
 
 // Whether a step of num workers, or one worker's separate call (`call`), does the layers of up to kParkedLongest elements this way:

@@ -162,3 +162,4 @@ def test_polls_are_checked():
     q = QAdam(QAdamConfig(), [0, 10], 1)
     with pytest.raises(Exception):
         q.set_scale_polls(-2)
+    q.set_scale_polls(2**31 - 1)            # accepted, as many as end in a bounded time are used
