@@ -1,6 +1,7 @@
 """GPU parity of the whole-step calls where a large vector makes them one launch per worker and one for the server: on both
 sides of the size from which they are, the outputs are those of the separate calls, bit for bit, and on the far side those of
-the oracle."""
+the oracle.  Most of every list is one layer that the chip does not hold, else the step would take a third way (k_parked); the
+rules that choose are applied to these lists on the CPU in test_work_split.py."""
 import numpy as np
 import pytest
 import torch
@@ -11,9 +12,16 @@ from test_gpu_parity import _custom
 
 pytestmark = pytest.mark.gpu
 
-N = 16
-LIMIT = (768 << 20) // (8 * N)          # elements up to which the scale pass leaves its data in the cache
-LIMIT_W = (512 << 20) // (4 * N)        # ... and variant W its sums
+N = 4
+M = 1 << 20
+LAST = {"s": 24 * M, "s off": 32 * M - 1, "w": 32 * M}      # elements up to which the step is one main pass
+
+
+def sizes_of(kind, more):
+    """A long layer and short ones, LAST + more elements; the long one starts on the 16-byte grid or off it."""
+    short = [4096 * 700, 1001, 70000, 3, 40001]
+    long_one = LAST[kind] + more - sum(short)
+    return [short[1], long_one] + short[:1] + short[2:] if kind == "s off" else [long_one] + short
 
 
 def _bits(t):
@@ -21,8 +29,9 @@ def _bits(t):
 
 
 class _State:
-    def __init__(self, sizes, w, one_buffer=False, block=0, **cfgkw):
+    def __init__(self, sizes, w, one_buffer=False, block=0, workers=N, **cfgkw):
         self.cfg, _ = configs(**cfgkw)
+        self.workers = N = workers
         seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
         P = int(seg[-1])
         gen = torch.Generator(device="cuda")
@@ -54,7 +63,7 @@ class _State:
         self.x, self.werr = at(self.x, lay["x"]), at(self.werr, lay["werr"])
 
     def step(self, t, w, whole):
-        q = self.q
+        q, N = self.q, self.workers
         if whole and w:
             q.step_fused_w(t, 1e-3, 0.999, self.g, self.m, self.v, self.e, self.codes, self.scales, self.x, self.werr, self.wcodes)
         elif whole:
@@ -74,13 +83,11 @@ class _State:
         return self.e + self.scales + self.m + self.v + [self.x, self.werr, self.wcodes]
 
 
-@pytest.mark.parametrize("w", [False, True])
+@pytest.mark.parametrize("kind", sorted(LAST))
 @pytest.mark.parametrize("more", [0, 1])
 @pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=0, k_x=14, weight_ef=0), dict(k_g=4, k_x=6, rounding=1, seed=3)])
-def test_whole_step_gives_the_bits_of_the_separate_calls(w, more, cfgkw):
-    # long and short layers, on and off the 16-byte grid
-    sizes = [4096 * 700, 1001, 70000, 3, 40001]
-    sizes.append((LIMIT_W if w else LIMIT) + more - sum(sizes))
+def test_whole_step_gives_the_bits_of_the_separate_calls(kind, more, cfgkw):
+    sizes, w = sizes_of(kind, more), kind == "w"
     a, b = _State(sizes, w, **cfgkw), _State(sizes, w, **cfgkw)
     for t in (1, 2):
         a.step(t, w, True)
@@ -90,15 +97,15 @@ def test_whole_step_gives_the_bits_of_the_separate_calls(w, more, cfgkw):
 
 
 def test_a_layer_list_by_worker_against_the_oracle():
-    sizes = [1001, 4096 * 900 + 5, 255, LIMIT - 4096 * 900, 77777, 1]
-    rep, st = _custom(sizes, N, 2, seed=41, trust=2)
+    """From the second step on with the filtered scale pass."""
+    rep, st = _custom(sizes_of("s", 1), N, 2, seed=41, trust=2)
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
-@pytest.mark.parametrize("w", [False, True])
-def test_overlapping_code_buffers_do_not_change_the_step(w):
+@pytest.mark.parametrize("kind", ["s", "w"])
+def test_overlapping_code_buffers_do_not_change_the_step(kind):
     """A caller without use for the codes may pass one buffer for all workers."""
-    sizes = [1001, (LIMIT_W if w else LIMIT) + 50000]
+    sizes, w = sizes_of(kind, 1), kind == "w"
     a, b = _State(sizes, w), _State(sizes, w, one_buffer=True)
     for t in (1, 2):
         a.step(t, w, True)
@@ -106,14 +113,14 @@ def test_overlapping_code_buffers_do_not_change_the_step(w):
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state(), b.state())), t
 
 
-@pytest.mark.parametrize("w", [False, True])
-def test_buffers_dealt_apart_do_not_change_the_step(w):
+@pytest.mark.parametrize("kind", ["s", "w"])
+def test_buffers_dealt_apart_do_not_change_the_step(kind):
     """One block as qadam_arena_layout deals it, its groups more than 96 GiB apart, where the call is one main pass."""
     torch.cuda.empty_cache()
     nbytes = 200 << 30
     if torch.cuda.mem_get_info()[0] < nbytes + (16 << 30):
         pytest.skip("the device's memory is not free")
-    sizes = [384 * 16384 + 4097, 1001, 70000, 3, (LIMIT_W if w else 0) + 5]
+    sizes, w = sizes_of(kind, 1), kind == "w"
     a, b = _State(sizes, w), _State(sizes, w, block=nbytes)
     for t in (1, 2):
         a.step(t, w, True)

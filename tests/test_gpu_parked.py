@@ -8,15 +8,19 @@ import pytest
 import torch
 
 from paper_2004_14180_amd import QAdam, QAdamConfig
-from test_gpu_by_worker import N, _State, _bits
+from test_gpu_by_worker import _State as _AnyState, _bits
 from test_gpu_parity import _custom
 
 pytestmark = pytest.mark.gpu
 
-M = 1 << 20
+M, N = 1 << 20, 16
 UNIT, LONGEST = 16384, 384 * 16384
 LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers, twice that for stochastic
                                         # rounding; one worker's separate call: 24 M, 64 M
+
+
+def _State(sizes, w, **kw):
+    return _AnyState(sizes, w, workers=N, **kw)
 
 
 def _sizes(total):
@@ -123,6 +127,16 @@ def test_calls_on_two_streams_do_not_wait_for_workgroups_without_a_place():
     c.run(one), c.run(two)
     alone, beside = (min(c.run(streams, 10) for _ in range(3)) for streams in (one, two))
     assert beside < 2.0 * alone, (alone, beside)
+
+
+def test_overlapping_code_buffers_do_not_change_the_step():
+    """A caller without use for the codes may pass one buffer for all workers, whose layers are then not parked."""
+    sizes = _sizes(LEAST)
+    a, b = _State(sizes, False), _State(sizes, False, one_buffer=True)
+    for t in (1, 2):
+        a.step(t, False, True)
+        b.step(t, False, True)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state(), b.state())), t
 
 
 def test_captured_step_is_the_eager_one():

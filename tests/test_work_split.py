@@ -272,3 +272,42 @@ def test_lines_of_parking_for_a_separate_call_and_stochastic_rounding(tmp_path):
     CHECK(call(64 * M, true) && !call(64 * M - 1, true), "stochastic");
     CHECK(worth_parking(32 * M, 2048, 32 * M, 2, true) && !worth_parking(32 * M - 1, 2048, 32 * M, 2, true), "two workers");
     CHECK(worth_parking(12 * M, 768, 24 * M, 8, true) && !worth_parking(12 * M - 1, 768, 24 * M, 8, true), "beside longer layers");""")
+
+
+def _c_list(sizes):
+    return "{" + ", ".join("%d" % n for n in sizes) + "}"
+
+
+def test_the_lists_of_the_gpu_tests_lie_on_both_sides_of_the_rules(tmp_path):
+    """The lists with which the GPU tests of the step by worker and of parked layers compare the ways that a step can take."""
+    import test_gpu_by_worker as by
+    import test_gpu_parked as parked
+    body = """
+    struct Counts { int64_t all, elems, units, off; };
+    auto count = [](std::initializer_list<int64_t> sizes) {
+        Counts c{};
+        for (int64_t n : sizes) {
+            if (c.all % 4 != 0) c.off += n;
+            if (n <= kParkedLongest) { c.elems += n; c.units += parked_units(n); }
+            c.all += n;
+        }
+        return c;
+    };
+    auto parks = [](const Counts& c, int num, bool stochastic) { return worth_parking(c.elems, c.units, c.all, num, stochastic); };"""
+    for kind in by.LAST:
+        for more in (0, 1):
+            body += """
+    for (int stochastic = 0; stochastic < 2; ++stochastic) {
+        const Counts c = count(%s);
+        CHECK(%d || !parks(c, %d, stochastic), "%s");
+        CHECK(worth_by_worker(c.all, c.off, %d, %d, stochastic) == (%d && !(%d && stochastic)), "%s %d");
+    }""" % (_c_list(by.sizes_of(kind, more)), kind == "w", by.N, kind, by.N, kind == "w", more, kind == "w", kind, more)
+    for stochastic in (0, 1):
+        for less in (0, 1):
+            body += """
+    CHECK(parks(count(%s), %d, %d) == %d, "parked, %d");""" % (
+                _c_list(parked._sizes((1 + stochastic) * parked.LEAST - less)), parked.N, stochastic, 1 - less, less)
+    body += """
+    CHECK(worth_parking(%d, %d, %d, 1, false, true), "separate calls");""" % (
+        sum(parked.SIZES), sum((n + parked.UNIT - 1) // parked.UNIT for n in parked.SIZES), sum(parked.SIZES))
+    _run(tmp_path, body)
