@@ -416,7 +416,9 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
     q = QAdam(QAdamConfig(k_g=wl.k_g, k_x=wl.k_x, rounding=rounding, weight_ef=weight_ef, beta1=wl.beta1,
                           eps=wl.eps), wl.seg_offsets, N)
     use_graph = headline and args.graph
-    q.profile_enable(not use_graph)
+    q.profile_enable(True)
+    if use_graph:
+        warmup = max(warmup, 1)
     if args.scale_pass == "filtered":
         q.trust_error_buffers(True)
     code_bits = q.grad_code_bytes() * 8.0 / P
@@ -473,12 +475,11 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
                 out.append((dt, a, b))
         return out
 
-    # the library applies the filter from 32768 (tile, worker) pairs on (about 1.3e8 worker-elements);
-    # a recorded graph always takes the full pass
-    tiles = sum((n + 4095) // 4096 for n in wl.sizes)
-    filtered = (args.scale_pass == "filtered" and not variant_w and wl.k_g >= 0 and tiles * N >= 32768
-                and not use_graph)
     res = timed_steps(1, warmup, steps)
+    # what the last step did, from the library: the shares of the elements; of a recorded step, which always takes the full
+    # scale pass, what the eager one before it did
+    scanned, filtered, codes_read = (n / P for n in q.profile_work())
+    filtered = filtered > 0 and not use_graph
     step_ms, scale_ms, main_ms = ([r[k] for r in res] for k in range(3))
     full_pass = None
     if filtered and not args.no_full_comparison:
@@ -502,7 +503,7 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
         # first pass (dominant): per worker read g, m_i, v_i, e_i and write m_i, v_i, p = 28 B;
         # second pass: per worker read p, write e and the code; server read/write x and e^x, weight code
         a_first = 28.0 * N
-        a_second = N * (8.0 + code_bits / 8.0) + 8.0 + (8.0 if weight_ef else 4.0) + wcode_bytes
+        a_second = N * (8.0 + (1.0 + codes_read) * code_bits / 8.0) + 8.0 + (8.0 if weight_ef else 4.0) + wcode_bytes
         roofline = {"bound": "hbm", "kernel": "k_moments_w (first pass of qadam_step_fused_w)",
                     "scope": "this kernel's launches only",
                     "achieved": gbs(a_first, scale_avg), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -514,20 +515,23 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
                                    "frac": round(gbs(a_first + a_second, ms_per_step) / HBM_PEAK_GBS, 4)}}
     else:
         a_main = algorithmic_bytes_per_param(N, code_bits, wcode_bytes, weight_ef)
-        # scale pass: g and e of every worker; filtered: g, plus e of the few elements that can be the maximum
-        a_scale = (4.0 if filtered else 8.0) * N if code_bits else 0.0
+        # scale pass: g and e of every worker; filtered: g, plus e of the few elements that can be the maximum.  Layers
+        # that stay on the chip between scale and quantizer have none, they are read once, within the main part.
+        a_scale = (4.0 if filtered else 8.0) * N * scanned
         is_headline_cfg = (headline and args.shrink == 1 and args.k_g is None and args.k_x is None
                            and args.rounding == 0 and config == 5)
         traffic = measured_traffic_bytes() if is_headline_cfg else None
         scale_traffic = measured_traffic_bytes("filtered_scale_pass_traffic_bytes_per_step" if filtered else
                                                "full_scale_pass_traffic_bytes_per_step") if is_headline_cfg else None
-        # A scale pass above the peak read less than that: layers that stay on the chip between scale and quantizer
-        # (k_parked) are read once, within the main part, and the step's bytes are the method's minimum or little more.
-        apart = gbs(a_scale, scale_avg) <= HBM_PEAK_GBS
-        a_step = a_main + (a_scale if apart else 0.0)
+        # where the server is a launch of its own it reads the codes back
+        a_codes = codes_read * N * code_bits / 8.0
+        a_step = a_main + a_scale + a_codes
         roofline = {"bound": "hbm",
-                    "kernel": "main part of qadam_step_fused, from the scales on (large vectors: k_worker_quantize per worker "
-                              "and k_server_step; short ones: k_fused; layers read once: k_parked)",
+                    "kernel": "main part of qadam_step_fused, from the scales on: %s%s" % (
+                        "k_worker_quantize per worker and k_server_step" if codes_read else "k_fused" if code_bits else
+                        "k_plain_messages",
+                        "; layers that are read once (%.1f %%): k_parked, k_layers" % (100 * (1 - scanned))
+                        if code_bits and scanned < 1 else ""),
                     "scope": "these launches only; whole_step below covers the scale pass as well",
                     "achieved": gbs(a_main, main_avg), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs(a_main, main_avg) / HBM_PEAK_GBS, 4),
@@ -537,11 +541,13 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
                     "algorithmic_bytes_per_param": a_main, "avg_launch_ms": round(main_avg, 4),
                     "scale_pass": {"mode": "filtered" if filtered else "full",
                                    "algorithmic_bytes_per_param": a_scale, "avg_launch_ms": round(scale_avg, 4),
-                                   "achieved": gbs(a_scale, scale_avg) if apart else None,
+                                   "achieved": gbs(a_scale, scale_avg) if scanned else None,
+                                   "share_of_elements": round(scanned, 4),
                                    # HBM bytes of the pass per step by the same counters (filtered: g of every
                                    # element, the sampled tiles and the few e that can matter)
                                    "traffic": scale_traffic},
-                    # bytes the step moves by design (main pass + scale pass) over the step's wall time
+                    "codes_read_back_bytes_per_param": round(a_codes, 4),
+                    # bytes the step moves by design (main part, scale pass, codes read back) over the step's wall time
                     "whole_step": {"bytes_per_param": a_step, "GBs": gbs(a_step, ms_per_step),
                                    "frac": round(gbs(a_step, ms_per_step) / HBM_PEAK_GBS, 4)},
                     # the method's own minimum (every buffer once, no read for the scales) over the step time

@@ -301,16 +301,27 @@ int qadam_layer_sumsq(qadam_handle_t h, const float* a_dev, const float* b_dev, 
  * the clear. */
 int qadam_get_status(qadam_handle_t h, qadam_status_t* out, int32_t clear, void* stream);
 
-/* Kernel timing for measurements.  When enabled, qadam_step_fused (and qadam_step_fused_w) bracket their two passes with HIP
+/* Kernel timing for measurements.  When enabled, qadam_step_fused (and qadam_step_fused_w) bracket their two parts with HIP
  * events on the caller's stream; qadam_profile_read waits for the last bracketed call and returns
- * the durations in milliseconds: scale_pass_ms (the read of g and e that produces the per-layer
- * scales) and main_pass_ms (the fused worker + server + weight-quantize kernel). */
+ * the durations in milliseconds: scale_pass_ms (the read of g and e that produces the per-layer scales, of the layers that
+ * have such a pass of their own; variant W: the moments) and main_pass_ms (everything behind it, in one kernel or in several;
+ * layers whose scale and codes come from one launch are done here as a whole). */
 typedef struct {
     float scale_pass_ms;
     float main_pass_ms;
 } qadam_profile_t;
 int qadam_profile_enable(qadam_handle_t h, int32_t on);
 int qadam_profile_read(qadam_handle_t h, qadam_profile_t* out);
+
+/* What the call that qadam_profile_read reports on did, in elements of the parameter vector (each stands for one element of
+ * every worker): scanned, of layers whose scales took a pass of their own; filtered, those of them whose e that pass read only
+ * where it can matter (all or none); codes_read, those whose codes the server read back from memory. */
+typedef struct {
+    int64_t scanned;
+    int64_t filtered;
+    int64_t codes_read;
+} qadam_profile_work_t;
+int qadam_profile_work(qadam_handle_t h, qadam_profile_work_t* out);
 
 /* Text of the last HIP error seen by this thread's calls (static storage). */
 const char* qadam_last_error(void);

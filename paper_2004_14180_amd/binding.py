@@ -25,7 +25,7 @@ EXPORTS = [
     "qadam_num_params", "qadam_worker_quantize", "qadam_server_step", "qadam_weight_quantize",
     "qadam_step_fused", "qadam_worker_step_w", "qadam_server_apply_w", "qadam_step_fused_w", "qadam_weight_dequantize",
     "qadam_weight_dequantize_f16", "qadam_layer_sumsq", "qadam_trust_error_buffers",
-    "qadam_get_status", "qadam_last_error", "qadam_profile_enable", "qadam_profile_read",
+    "qadam_get_status", "qadam_last_error", "qadam_profile_enable", "qadam_profile_read", "qadam_profile_work",
     "qadam_quantize_segment_noalloc", "qadam_arena_layout", "qadam_set_scale_polls",
 ]
 
@@ -44,6 +44,10 @@ class _Config(C.Structure):
 
 class _Profile(C.Structure):
     _fields_ = [("scale_pass_ms", C.c_float), ("main_pass_ms", C.c_float)]
+
+
+class _ProfileWork(C.Structure):
+    _fields_ = [("scanned", C.c_int64), ("filtered", C.c_int64), ("codes_read", C.c_int64)]
 
 
 class _Arena(C.Structure):
@@ -117,6 +121,7 @@ def load_library():
     lib.qadam_profile_enable.argtypes = [vp, i32]
     lib.qadam_set_scale_polls.argtypes = [vp, i32]
     lib.qadam_profile_read.argtypes = [vp, C.POINTER(_Profile)]
+    lib.qadam_profile_work.argtypes = [vp, C.POINTER(_ProfileWork)]
     lib.qadam_quantize_segment_noalloc.argtypes = [i32, i64, vp, vp, vp, vp, vp]
     lib.qadam_arena_layout.argtypes = [vp, C.c_size_t, i32, C.POINTER(_Arena)]
     _lib, _torch = lib, torch
@@ -381,6 +386,12 @@ class QAdam:
         pr = _Profile()
         self._check(self._lib.qadam_profile_read(self._h, C.byref(pr)))
         return float(pr.scale_pass_ms), float(pr.main_pass_ms)
+
+    def profile_work(self):
+        """(scanned, filtered, codes_read) of the call that profile_read reports on, see qadam_profile_work_t."""
+        w = _ProfileWork()
+        self._check(self._lib.qadam_profile_work(self._h, C.byref(w)))
+        return int(w.scanned), int(w.filtered), int(w.codes_read)
 
     def get_status(self, clear=False, stream=None) -> int:
         st = _Status()

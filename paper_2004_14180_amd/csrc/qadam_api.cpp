@@ -51,6 +51,7 @@ struct qadam_ctx {
     const float* bound_err[QADAM_MAX_WORKERS];  // the error buffer that row was recorded for
     bool       profile;
     bool       profile_valid;
+    qadam_profile_work_t profile_work;
     hipEvent_t ev[3];
 };
 
@@ -660,6 +661,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
+    qadam_profile_work_t work = {0, 0, 0};
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[0], L.stream));
     if (idg) {
         // the error buffers are not touched: whatever is recorded about them stays true
@@ -683,9 +685,13 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
         if (parked) QADAM_HIP(launch_parked(L, S, W, 0, h->num_workers));
         QADAM_HIP(launch_fused(L, S, W, sp));
         record.complete = !capturing;
+        if (h->profile)
+            work = {L.scaled.num_elems, filtered ? L.scaled.num_elems : 0,
+                    step_by_worker(L, S, W, sp, false) ? h->scaled.num_elems : 0};
     }
     if (h->profile && !capturing) {
         QADAM_HIP(hipEventRecord(h->ev[2], L.stream));
+        h->profile_work = work;
         h->profile_valid = true;
     }
     return QADAM_OK;
@@ -767,6 +773,8 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     record.complete = !idg && !capturing;   // with the identity quantizer no scale, hence no bound, was produced
     if (h->profile && !capturing) {
         QADAM_HIP(hipEventRecord(h->ev[2], L.stream));
+        const int64_t scanned = idg ? 0 : L.scaled.num_elems;
+        h->profile_work = {scanned, 0, scanned > 0 && step_by_worker(L, S, W, sp, true) ? scanned : 0};
         h->profile_valid = true;
     }
     return QADAM_OK;
@@ -880,6 +888,15 @@ int qadam_profile_read(qadam_handle_t h, qadam_profile_t* out)
     QADAM_HIP(hipEventSynchronize(h->ev[2]));
     QADAM_HIP(hipEventElapsedTime(&out->scale_pass_ms, h->ev[0], h->ev[1]));
     QADAM_HIP(hipEventElapsedTime(&out->main_pass_ms, h->ev[1], h->ev[2]));
+    return QADAM_OK;
+}
+
+int qadam_profile_work(qadam_handle_t h, qadam_profile_work_t* out)
+{
+    QADAM_CHECK(check_handle(h));
+    if (!out) return fail(QADAM_EINVAL, "null profile");
+    if (!h->profile || !h->profile_valid) return fail(QADAM_EINVAL, "no profiled call to read");
+    *out = h->profile_work;
     return QADAM_OK;
 }
 

@@ -163,6 +163,8 @@ hipError_t launch_short_layers(const Launch& L, const StepScalars& S, const Work
 hipError_t launch_server_step(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp);
 hipError_t launch_weight_quantize(const Launch& L, const StepScalars& S, const float* x, float* werr, void* wcodes);
 hipError_t launch_weight_dequantize(const Launch& L, const StepScalars& S, const void* wcodes, void* xhat, bool half);
+// whether the two below are one launch per worker and one for the server, which reads the codes
+bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w);
 hipError_t launch_fused(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp);
 // Q_g = identity: the messages are fp32 values (variant S: the gradients; variant W: the parked
 // update + error, whose buffers are then cleared)

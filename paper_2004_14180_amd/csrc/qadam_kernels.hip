@@ -17,8 +17,9 @@
 //     (non-negative floats order like integers; NaN/Inf sort above every finite value and so
 //     surface in the scale), wavefront reduction by cross-lane shuffles, LDS across the four
 //     wavefronts, one plain store of the tile's maximum; the tile maxima of a layer are folded by a
-//     second small kernel, or where they are few by the quantizing wavefronts themselves.  No atomics: thousands
-//     of workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole pass;
+//     second small kernel, or where they are few by the quantizing wavefronts themselves.  No atomics in these
+//     passes: thousands of workgroups hitting one freshly zeroed word at the start of every layer cost more than the whole
+//     pass (the workgroups of k_parked, which are few per layer, count themselves with one each);
 //   * a segment that starts off the 16-byte grid keeps the same lane-to-element mapping (the codes are
 //     anchored at the segment start) and moves its data with dword-aligned 128-bit accesses;
 //   * layers of up to 6.3 M elements in long lists stay on the chip between the scale and the quantizer: the workgroups of a
@@ -2798,8 +2799,9 @@ static bool dealt_apart(const Launch& L, const StepScalars& S, const WorkerPtrs&
     return groups_apart(S.num_workers, variant_w, bytes, at) >= kGroupsApart;
 }
 
-static bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
+bool step_by_worker(const Launch& L, const StepScalars& S, const WorkerPtrs& W, const ServerPtrs& sp, bool variant_w)
 {
+    if (L.parked_done) return true;
     if (!worth_by_worker(L.scaled.num_elems, L.off_grid_elems, S.num_workers, variant_w, S.rounding == 1)) return false;
     if ((variant_w || S.num_workers > 2) && dealt_apart(L, S, W, sp, variant_w)) return false;
     return !codes_overlap(L, W, 0, S.num_workers);
@@ -2832,7 +2834,7 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
                                    bool variant_w)
 {
     if (L.served.num_tiles == 0) return hipSuccess;
-    if (L.parked_done || step_by_worker(L, S, W, sp, variant_w)) {
+    if (step_by_worker(L, S, W, sp, variant_w)) {
         launch_by_worker(L, S, W, sp, variant_w);
         return hipGetLastError();
     }

@@ -89,11 +89,14 @@ class _State:
 def test_whole_step_gives_the_bits_of_the_separate_calls(kind, more, cfgkw):
     sizes, w = sizes_of(kind, more), kind == "w"
     a, b = _State(sizes, w, **cfgkw), _State(sizes, w, **cfgkw)
+    a.q.profile_enable()
     for t in (1, 2):
         a.step(t, w, True)
         b.step(t, w, False)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
     assert a.q.get_status() == 0
+    by_worker = more == 1 and not (w and cfgkw.get("rounding"))
+    assert a.q.profile_work() == (sum(sizes), 0, sum(sizes) if by_worker else 0)
 
 
 def test_a_layer_list_by_worker_against_the_oracle():
@@ -107,10 +110,12 @@ def test_overlapping_code_buffers_do_not_change_the_step(kind):
     """A caller without use for the codes may pass one buffer for all workers."""
     sizes, w = sizes_of(kind, 1), kind == "w"
     a, b = _State(sizes, w), _State(sizes, w, one_buffer=True)
+    a.q.profile_enable(), b.q.profile_enable()
     for t in (1, 2):
         a.step(t, w, True)
         b.step(t, w, True)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state(), b.state())), t
+    assert a.q.profile_work()[2] == sum(sizes) and b.q.profile_work()[2] == 0
 
 
 @pytest.mark.parametrize("kind", ["s", "w"])
@@ -122,7 +127,9 @@ def test_buffers_dealt_apart_do_not_change_the_step(kind):
         pytest.skip("the device's memory is not free")
     sizes, w = sizes_of(kind, 1), kind == "w"
     a, b = _State(sizes, w), _State(sizes, w, block=nbytes)
+    a.q.profile_enable(), b.q.profile_enable()
     for t in (1, 2):
         a.step(t, w, True)
         b.step(t, w, True)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+    assert a.q.profile_work()[2] == sum(sizes) and b.q.profile_work()[2] == 0

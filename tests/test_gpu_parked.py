@@ -35,11 +35,13 @@ def test_whole_step_gives_the_bits_of_the_separate_calls(polls, less, cfgkw):
     sizes = _sizes((2 if cfgkw.get("rounding") else 1) * LEAST - less)
     a, b = _State(sizes, False, **cfgkw), _State(sizes, False, **cfgkw)
     a.q.set_scale_polls(polls)
+    a.q.profile_enable()
     for t in (1, 2):
         a.step(t, False, True)
         b.step(t, False, False)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
     assert a.q.get_status() == 0
+    assert a.q.profile_work()[0] == (sum(sizes) if less else 0)
 
 
 @pytest.mark.parametrize("polls", [1, 2, 4])
