@@ -43,9 +43,9 @@ def kernel_source_sha256():
     return hashlib.sha256(b"".join(open(p, "rb").read() for p in KERNEL_SOURCES)).hexdigest()
 
 
-def measured_traffic_bytes(key="k_fused_traffic_bytes_per_launch"):
+def measured_traffic_bytes(key):
     """HBM bytes of the headline workload's kernels as the rocprofv3 counter summary under profiles/ records
-    them (per launch of the fused main pass; per step for the scale pass) -- only if that summary was taken
+    them (per launch of the fused main pass; per step for the others) -- only if that summary was taken
     from the kernel source that is being timed now (it stores the source's SHA-256); otherwise None."""
     try:
         text = open(TRAFFIC_PROFILE).read()
@@ -518,9 +518,10 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
         # scale pass: g and e of every worker; filtered: g, plus e of the few elements that can be the maximum.  Layers
         # that stay on the chip between scale and quantizer have none, they are read once, within the main part.
         a_scale = (4.0 if filtered else 8.0) * N * scanned
-        is_headline_cfg = (headline and args.shrink == 1 and args.k_g is None and args.k_x is None
+        is_headline_cfg = (headline and args.shrink == 1 and not args.misalign and args.k_g is None and args.k_x is None
                            and args.rounding == 0 and config == 5)
-        traffic = measured_traffic_bytes() if is_headline_cfg else None
+        traffic = measured_traffic_bytes("by_worker_traffic_bytes_per_step" if codes_read else
+                                         "k_fused_traffic_bytes_per_launch") if is_headline_cfg else None
         scale_traffic = measured_traffic_bytes("filtered_scale_pass_traffic_bytes_per_step" if filtered else
                                                "full_scale_pass_traffic_bytes_per_step") if is_headline_cfg else None
         # where the server is a launch of its own it reads the codes back
