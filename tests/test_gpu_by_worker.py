@@ -133,3 +133,5 @@ def test_buffers_dealt_apart_do_not_change_the_step(kind):
         b.step(t, w, True)
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
     assert a.q.profile_work()[2] == sum(sizes) and b.q.profile_work()[2] == 0
+    del b                                   # the next tests' handles allocate beside torch
+    torch.cuda.empty_cache()
