@@ -209,17 +209,23 @@ constexpr bool keep_parked(int64_t n, int num) { return 4 * n * num <= (int64_t)
 // 32 M 673 / 638, 96 M 2035 / 1901; 8 of 12 M 436 / 444, 16 M 581 / 547, 96 M 3566 / 3238; 16 of 4 M 255 / 301, 8 M 550 / 543,
 // 96 M 6798 / 6002; variant W, 4 of 24 M 726 / 723, 64 M 1964 / 1929, 8 of 12 M 705 / 708, 96 M 5769 / 5588.
 // Near the lines it took longer in some forms, which begin later.  us per step, main pass / by worker, nearest rounding: 12 workers of
-// 8 M 409 / 425, 12 M 594 / 604; 16 of 6 M 390 / 410, 8 M 523 / 518, 12 M 734 / 736, 16 M 999 / 963.  Layers off the 16-byte grid: one
-// worker of 28 M 285 / 290, 32 M 329 / 327; 3 of 32 M 590 / 586; 4 of 24 M 525 / 536, 28 M 606 / 607, 32 M 708 / 701; 8 of 12 M 444 /
-// 473, 20 M 740 / 747, 24 M 895 / 890; 16 of 6 M 411 / 461, 12 M 832 / 843, 16 M 1138 / 1101.  Variant W: 8 workers of 18 M 978 / 992,
-// 37 M 1994 / 1997, 50 M 2650 / 2639; 16 of 9 M 950 / 982, 25 M 2641 / 2648, 37 M 3987 / 3969; with stochastic rounding 1 of 129 M
-// 1184 / 1232, 4 of 56 M 1595 / 1640, 8 of 16 M 925 / 959, 16 of 14 M 1535 / 1616.
+// 8 M 409 / 425, 12 M 594 / 604; 16 of 6 M 390 / 410, 8 M 523 / 518, 12 M 734 / 736, 16 M 999 / 963.  Variant W: 5 workers of 85 M
+// 2781 / 2841, 200 M 6593 / 6691; 8 of 18 M 978 / 992, 37 M 1994 / 1997, 50 M 2650 / 2639; 16 of 28 M 2790 / 2877, 50 M 5379 / 5300; with
+// stochastic rounding 1 of 129 M 1184 / 1232, 4 of 56 M 1595 / 1640, 8 of 16 M 925 / 959, 16 of 14 M 1535 / 1616.
+// Layers off the 16-byte grid, where the main pass depends more on where the buffers lie; the least and the largest ratio main pass / by
+// worker of two to three allocations each, one layer and GPT lists: one worker of 34 M 0.96 0.98, 100 M 0.98 1.00, 185 M 1.00 1.00, 500 M
+// 1.01 1.02; 2 of 50 M 1.02 1.03, 72 M 1.03 1.06, 276 M 1.05 1.07; 3 of 34 M 0.95 1.01, 67 M 1.04 1.07, 257 M 1.06 1.08; 4 of 34 M 0.93
+// 0.97, 50 M 1.02 1.04, 120 M 1.02 1.04, 351 M 1.05 1.08; 5 of 30 M 0.94 0.97, 50 M 0.99 1.02, 276 M 1.02 1.02; 8 of 21 M 0.91 0.91, 40 M
+// 0.97 1.03, 120 M 1.04 1.07; 16 of 30 M 0.94 1.03, 80 M 0.99 1.05, 120 M 0.96 0.98, 130 M 0.96 0.96.  Variant W: one of 130 M 1.02
+// 1.03, 1 G 1.03 1.04; 2 of 65 M 1.01 1.01, 600 M 1.01 1.01; 3 of 45 M 0.98 0.98, 120 M 0.97 1.02; 4 of 33 M 0.99 1.03, 330 M 1.05 1.05,
+// 351 M 0.97 0.98; 5 of 82 M 0.97 1.03, 200 M 0.98 0.99; 8 of 51 M 0.99 0.99, 170 M 0.97 0.97.
 constexpr bool worth_by_worker(int64_t n, int64_t off_grid, int num, bool variant_w, bool stochastic)
 {
     const int64_t work = n * num, M = 1 << 20;
-    if (variant_w) return !stochastic && !keep_parked(n, num) && (num <= 4 || work >= 400 * M);
+    const bool off = 2 * off_grid > n;
+    if (variant_w) return !stochastic && !keep_parked(n, num) && (off ? num <= 2 : num <= 4 || (num >= 8 && n >= 50 * M));
     if (keep_scanned(n, num)) return false;
-    if (2 * off_grid > n) return num == 1 ? n >= 32 * M : num <= 3 || work >= (96 + 8 * num) * M;
+    if (off) return num == 1 ? n >= 128 * M : num == 2 || (num <= 8 && work >= (64 + 32 * num) * M);
     return num <= 8 || n >= 14 * M;
 }
 

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 N = 4
 M = 1 << 20
-LAST = {"s": 24 * M, "s off": 32 * M - 1, "w": 32 * M}      # elements up to which the step is one main pass
+LAST = {"s": 24 * M, "s off": 48 * M - 1, "w": 32 * M}      # elements up to which the step is one main pass
 
 
 def sizes_of(kind, more):

@@ -251,15 +251,17 @@ def test_where_the_whole_step_goes_by_worker(tmp_path):
     const int64_t M = 1 << 20;
     auto grid = [&](int64_t n, int num) { return worth_by_worker(n, 0, num, false, false); };
     auto off = [&](int64_t n, int num) { return worth_by_worker(n, n, num, false, true); };
-    auto w = [&](int64_t n, int num) { return worth_by_worker(n, n, num, true, false); };
+    auto w = [&](int64_t n, int num) { return worth_by_worker(n, 0, num, true, false); };
+    auto w_off = [&](int64_t n, int num) { return worth_by_worker(n, n, num, true, false); };
     CHECK(grid(24 * M + 1, 1) && !grid(24 * M, 1) && grid(24 * M + 1, 4) && !grid(24 * M, 4), "one worker, four");
     CHECK(grid(12 * M + 1, 8) && !grid(12 * M, 8) && grid(14 * M, 16) && !grid(14 * M - 1, 16), "eight, sixteen");
-    CHECK(off(32 * M, 1) && !off(32 * M - 1, 1), "one worker off the grid");
-    CHECK(off(32 * M + 1, 3) && !off(32 * M, 3) && off(32 * M, 4) && !off(32 * M - 1, 4), "off the grid");
-    CHECK(off(20 * M, 8) && !off(20 * M - 1, 8) && off(14 * M, 16) && !off(14 * M - 1, 16), "off the grid, many workers");
-    CHECK(!worth_by_worker(24 * M, 12 * M + 1, 4, false, false) && worth_by_worker(25 * M, 12 * M, 4, false, false), "half of it off the grid");
+    CHECK(off(128 * M, 1) && !off(128 * M - 1, 1) && off(48 * M + 1, 2) && !off(48 * M, 2), "one worker off the grid, two");
+    CHECK(off(54 * M, 3) && !off(53 * M, 3) && off(48 * M, 4) && !off(48 * M - 1, 4), "off the grid");
+    CHECK(off(40 * M, 8) && !off(40 * M - 1, 8) && !off(400 * M, 9) && !off(400 * M, 16), "off the grid, many workers");
+    CHECK(!worth_by_worker(25 * M, 13 * M, 4, false, false) && worth_by_worker(25 * M, 12 * M, 4, false, false), "half of it off the grid");
     CHECK(w(128 * M + 1, 1) && !w(128 * M, 1) && w(32 * M + 1, 4) && !w(32 * M, 4), "variant W");
-    CHECK(w(50 * M, 8) && !w(50 * M - 1, 8) && w(25 * M, 16) && !w(25 * M - 1, 16), "variant W, many workers");
+    CHECK(w(50 * M, 8) && !w(50 * M - 1, 8) && w(50 * M, 16) && !w(50 * M - 1, 16) && !w(400 * M, 5), "variant W, many workers");
+    CHECK(w_off(128 * M + 1, 1) && w_off(64 * M + 1, 2) && !w_off(64 * M, 2) && !w_off(400 * M, 3), "variant W off the grid");
     CHECK(!worth_by_worker(400 * M, 0, 4, true, true), "variant W, stochastic rounding");""")
 
 
