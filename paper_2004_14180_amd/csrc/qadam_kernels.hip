@@ -118,6 +118,7 @@ struct QgConst {
     int ebias;             // 126 - k_g: exponent field of level mu is mu + ebias
     uint32_t half_l1_bits; // bit pattern of 2^(-k_g-1)
     uint32_t l1_bits;      // bit pattern of 2^-k_g
+    float up, down;        // 2^(k_g+2) and its reciprocal: a level times `up` is 2^(mu+1)
 };
 
 __device__ __forceinline__ QgConst make_qg(int k_g)
@@ -126,6 +127,8 @@ __device__ __forceinline__ QgConst make_qg(int k_g)
     c.ebias = 126 - k_g;
     c.half_l1_bits = (uint32_t)(126 - k_g) << 23;
     c.l1_bits = (uint32_t)(127 - k_g) << 23;
+    c.up = u2f((uint32_t)(129 + k_g) << 23);
+    c.down = u2f((uint32_t)(125 - k_g) << 23);
     return c;
 }
 
@@ -153,54 +156,79 @@ __device__ __forceinline__ uint32_t qg_stochastic_bits(uint32_t ab, const QgCons
     return valid ? lvl : 0u;
 }
 
-// One worker's share of one lane: p = g + e, level, dequantized value q, residual p - q, and the
-// V codes (4 bits each) of the lane.  s is the layer scale, inv_s its reciprocal or 0 when the
-// fast quotient must not be used (tiny, huge, zero or non-finite scale).
-template <int V, int ROUNDING>
-__device__ __forceinline__ void worker_lane(const float (&g)[V], const float (&e)[V], float s, float inv_s,
-                                            const QgConst& c, int mu_bits, const float (&U)[V],
-                                            float (&q)[V], float (&enew)[V], uint32_t& codes)
+// The four codes of a lane from its levels times 2^(k_g+2), with the sign of p: +-2^(mu+1), whose exponent field is 128 + mu, or
+// +-0.  Element j's code is the four bits from bit 0, 16, 4 and 20 on (spread so that pack_planes gathers a plane's four bits
+// with one multiplication).
+__device__ __forceinline__ uint32_t pack_codes(const uint32_t (&L)[4], int mu_bits)
 {
-    float p[V], r[V];
+    uint32_t half[2];
 #pragma unroll
-    for (int j = 0; j < V; ++j) p[j] = g[j] + e[j];
-    const bool valid = s > 0.0f && s < __builtin_inff();
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t h = __builtin_amdgcn_perm(L[2 * k + 1], L[2 * k], 0x07060302u);     // the upper halves of two of them
+        const uint32_t sign = h & (h << 1) & 0x80008000u;                                   // no sign for the level 0
+        half[k] = (h & 0x03800380u) | (sign >> (8 - mu_bits));
+    }
+    return half[0] >> 7 | half[1] >> 3;
+}
+
+// One worker's share of one lane, p = g + e: level, dequantized value q, which is added to acc, residual p - q, and the
+// lane's codes (pack_codes).  s is the layer scale, inv_s its reciprocal or 0 when the fast quotient must not be used (tiny,
+// huge, zero or non-finite scale).
+// The fast form works on p / s times 2^(k_g+2), where the levels are 4, 8, .. and what is below 2 goes to 0, whatever k_g.
+// Products with these powers of two and with the levels are exact for the scales it is used with, so that the sums with one
+// rounding, p - s L and acc + s L, are what a multiplication and an addition give; the level 0 takes the sign -0, whose product
+// leaves both of them as they are and makes a residual of +0 of p = -0, as p - q does.
+// Bound by the vector ALUs where few wavefronts share a SIMD.  97 vector instructions for four
+// elements and their three planes, 138 with the levels' own exponents, a multiplication and an addition each and codes put
+// together one by one.  us per step, that way / this way: 10 k elements in one workgroup 5.89 / 5.21; 11.7 M
+// parameters, 4 workers 195.4 / 190.5; GPT-2 small, 4 workers by separate calls 2078 / 2059.
+template <int ROUNDING>
+__device__ __forceinline__ void worker_lane(const float (&p)[4], float s, float inv_s, const QgConst& c, int mu_bits,
+                                            const float (&U)[4], float (&acc)[4], float (&enew)[4], uint32_t& codes)
+{
+    float r[4];
+    uint32_t L[4];
     if (ROUNDING == 0 && inv_s != 0.0f) {
-        uint32_t near = 0;
+        const float inv_up = inv_s * c.up, s_down = s * c.down;
+        uint32_t near = 0xffffffffu;
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            r[j] = p[j] * inv_s;
+        for (int j = 0; j < 4; ++j) {
+            r[j] = p[j] * inv_up;
             // within 8 ulp of a power of two or of 0.75 times one?
-            const uint32_t t = (f2u(r[j]) & 0x7fffffffu) + 0x00400000u;
-            near |= (((t + 8u) & 0x003fffffu) < 16u) ? 1u : 0u;
+            near = min(near, (f2u(r[j]) + 8u) << 10);
         }
-        if (near) {
+        if (near < 16u << 10) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) r[j] = p[j] / s;
+            for (int j = 0; j < 4; ++j) r[j] = (p[j] / s) * c.up;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            // as qg_nearest_bits, 2^(k_g+2) times as large
+            const float lvl = __builtin_amdgcn_fmed3f(u2f((f2u(r[j]) + 0x00400000u) & 0x7f800000u), 4.0f, c.up);
+            L[j] = fabsf(r[j]) >= 2.0f ? f2u(copysignf(lvl, r[j])) : 0x80000000u;
+            acc[j] = __builtin_fmaf(s_down, u2f(L[j]), acc[j]);
+            enew[j] = __builtin_fmaf(-s_down, u2f(L[j]), p[j]);
         }
     } else {
+        const bool valid = s > 0.0f && s < __builtin_inff();
+        const uint32_t zero_below = valid ? c.half_l1_bits : 0xffffffffu;
+        const float s_mul = valid ? s : 0.0f;               // an invalid scale quantizes everything to 0
 #pragma unroll
-        for (int j = 0; j < V; ++j) r[j] = p[j] / s;
-    }
-    const uint32_t zero_below = valid ? c.half_l1_bits : 0xffffffffu;
-    const float s_mul = valid ? s : 0.0f;               // an invalid scale quantizes everything to 0
-    const int sign_shift = 31 - mu_bits;
-    codes = 0;
+        for (int j = 0; j < 4; ++j) r[j] = p[j] / s;
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const uint32_t ab = f2u(r[j]) & 0x7fffffffu;
-        uint32_t lvl;
-        if constexpr (ROUNDING == 0) lvl = qg_nearest_bits(ab, c, zero_below);
-        else lvl = qg_stochastic_bits(ab, c, U[j], valid);
-        const float qa = s_mul * u2f(lvl);                // s * 2^(mu-1-k_g); 0 when lvl == 0
-        const uint32_t sign = f2u(p[j]) & 0x80000000u;
-        const float qv = u2f(f2u(qa) | sign);
-        q[j] = qv;
-        enew[j] = p[j] - qv;
-        const int mu = max((int)(lvl >> 23) - c.ebias, 0);
-        const uint32_t code = mu > 0 ? ((uint32_t)mu | (sign >> sign_shift)) : 0u;
-        codes |= code << (4 * j);
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t ab = f2u(r[j]) & 0x7fffffffu, sign = f2u(p[j]) & 0x80000000u;
+            uint32_t lvl;
+            if constexpr (ROUNDING == 0) lvl = qg_nearest_bits(ab, c, zero_below);
+            else lvl = qg_stochastic_bits(ab, c, U[j], valid);
+            const float qa = s_mul * u2f(lvl);                // s * 2^(mu-1-k_g); 0 when lvl == 0
+            const float qv = u2f(f2u(qa) | sign);
+            acc[j] = acc[j] + qv;
+            enew[j] = p[j] - qv;
+            L[j] = f2u(u2f(lvl) * c.up) | sign;
+        }
     }
+    codes = pack_codes(L, mu_bits);
 }
 
 // Value of the code stored at bit `pos` of a 32-element group's plane words w[0..MU_BITS]
@@ -263,8 +291,8 @@ __device__ __forceinline__ bool fast_scale(float s) { return f2u(s) - (27u << 23
 
 // ------------------------------------------------------------------------------------------------
 // Bit-plane packing.  A lane holds the codes of elements 4*lane..4*lane+3 of a 256-element
-// wave chunk as four nibbles of `codes`; the 8 lanes 8G..8G+7 form 32-element group G.  For plane k
-// every lane gathers its 4 plane bits (a multiply moves bits 0,4,8,12 to bits 9..12), shifts them
+// wave chunk as pack_codes leaves them; the 8 lanes 8G..8G+7 form 32-element group G.  For plane k
+// every lane gathers its 4 plane bits (a multiply moves bits 0,16,4,20 to bits 17..20), shifts them
 // to position 4*(lane%8) and the group ORs them with three DPP steps (swap within pairs, swap
 // pairs within quads, mirror the two quads of a half row).  Lane 8G+k keeps word k.  Must be
 // called with all 64 lanes active.
@@ -277,26 +305,22 @@ __device__ __forceinline__ uint32_t dpp_or8(uint32_t w)
     return w;
 }
 
-template <int V>
-__device__ __forceinline__ uint32_t pack_planes(uint32_t codes, int code_bits, int lane, int& word_slot,
-                                                bool& writes)
+__device__ __forceinline__ uint32_t pack_planes(uint32_t codes, int code_bits, int lane, int& word_slot, bool& writes)
 {
     uint32_t sel = 0;
-    if constexpr (V == 4) {
-        const int sub = lane & 7;
-        const int sh = sub * 4;
+    const int sub = lane & 7;
+    const int sh = sub * 4;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k < code_bits) {
-                const uint32_t t = codes & (0x1111u << k);
-                const uint32_t nib = ((t * 0x249u) >> (9 + k)) & 0xFu;
-                const uint32_t w = dpp_or8(nib << sh);
-                sel = sub == k ? w : sel;
-            }
+    for (int k = 0; k < 4; ++k) {
+        if (k < code_bits) {
+            const uint32_t t = codes & (0x00110011u << k);
+            const uint32_t nib = (__umul24(t, 0x28005u) >> (17 + k)) & 0xFu;
+            const uint32_t w = dpp_or8(nib << sh);
+            sel = sub == k ? w : sel;
         }
-        word_slot = (lane >> 3) * code_bits + sub;     // word within the wave chunk's 8 groups
-        writes = sub < code_bits;
     }
+    word_slot = (lane >> 3) * code_bits + sub;     // word within the wave chunk's 8 groups
+    writes = sub < code_bits;
     return sel;
 }
 
@@ -1149,10 +1173,8 @@ __device__ __forceinline__ void worker_part(const WorkerArgs& A, const Tile& t, 
         const int off = part_begin + k * WAVE_ELEMS + lane * V;
         const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
         if constexpr (PARKED) {
-            // the first pass left p = u + e in the error buffer; p + 0 reproduces it
+            // the first pass left p = u + e in the error buffer
             ld<V, SH>(A.err, t.start + off, nvalid, sf, g[k]);
-#pragma unroll
-            for (int j = 0; j < V; ++j) e[k][j] = 0.0f;
         } else {
             ld<V, SH>(A.grad, t.start + off, nvalid, sf, g[k]);
             ld<V, SH>(A.err, t.start + off, nvalid, sf, e[k]);
@@ -1167,15 +1189,15 @@ __device__ __forceinline__ void worker_part(const WorkerArgs& A, const Tile& t, 
         const int off = base + lane * V;
         const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
         const int64_t gi = t.start + off;
-        float q[V], en[V], U[V];
+        float p[V], unused[V], en[V], U[V];
 #pragma unroll
-        for (int j = 0; j < V; ++j) U[j] = 0.0f;
+        for (int j = 0; j < V; ++j) { p[j] = PARKED ? g[k][j] : g[k][j] + e[k][j]; unused[j] = 0.0f; U[j] = 0.0f; }
         if constexpr (ROUNDING == 1) unif<V, SH>(S, gi, (uint32_t)A.worker, 0u, sf, U);
         uint32_t codes;
-        worker_lane<V, ROUNDING>(g[k], e[k], sc.s, sc.inv, c, S.mu_bits, U, q, en, codes);
+        worker_lane<ROUNDING>(p, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);
         st<V, SH>(A.err, gi, nvalid, sf, en);
         int slot; bool writes;
-        const uint32_t word = pack_planes<V>(codes, S.code_bits, lane, slot, writes);
+        const uint32_t word = pack_planes(codes, S.code_bits, lane, slot, writes);
         store_chunk_words(A.codes, t, base, S.code_bits, word, slot, writes);
     }
     if (part_begin + C * WAVE_ELEMS >= t.len) write_pad_words(A.codes, t, S.code_bits);
@@ -1277,18 +1299,18 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
     }
     const Scale sc = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)block_max<kSegmentThreads>(local)));
     if (threadIdx.x == 0) A.scale[0] = sc.s;
-    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int k = 0; k < kSegmentRuns; ++k) {
         const int base = (k * (kSegmentThreads / 64) + wave) * 256;
         if (base >= A.n) break;
         const int off = base + lane * 4;
-        float q[4], en[4];
+        const float no_uniforms[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        float unused[4] = {0.0f, 0.0f, 0.0f, 0.0f}, en[4];
         uint32_t codes;
-        worker_lane<4, 0>(p[k], zero, sc.s, sc.inv, c, S.mu_bits, zero, q, en, codes);     // p + 0 reproduces p
+        worker_lane<0>(p[k], sc.s, sc.inv, c, S.mu_bits, no_uniforms, unused, en, codes);
         store_v<4>(A.err + off, min(max(A.n - off, 0), 4), en);
         int slot; bool writes;
-        const uint32_t word = pack_planes<4>(codes, S.code_bits, lane, slot, writes);
+        const uint32_t word = pack_planes(codes, S.code_bits, lane, slot, writes);
         if (writes && base + slot / S.code_bits * 32 < A.n) A.codes[(base >> 5) * S.code_bits + slot] = word;
     }
     // zero words up to a multiple of 16 bytes
@@ -1595,10 +1617,9 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                     const int nvalid = q_whole ? 4 : min(max(q.P.t.len - base - lane * 4, 0), 4);
                     const float4 v = spot;
                     const float old[4] = {v.x, v.y, v.z, v.w};
-                    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                     float unused[4], en[4], U[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) U[j] = 0.0f;
+                    for (int j = 0; j < 4; ++j) { unused[j] = 0.0f; U[j] = 0.0f; }
                     if constexpr (ROUNDING == 1) {
                         const int64_t gi = q.P.t.start + base + lane * 4;
                         const Shift sf = make_shift(q.P.t);
@@ -1609,10 +1630,10 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                         else uniforms<4, false>(R, gi, (uint32_t)q.w, 0u, U);
                     }
                     uint32_t codes;
-                    worker_lane<4, ROUNDING>(old, zero, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);     // p + 0 reproduces p
+                    worker_lane<ROUNDING>(old, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);
                     store_shifted(A.err[q.w] + q.P.t.start + base + lane * 4, nvalid, en);
                     int slot; bool writes;
-                    const uint32_t planes = pack_planes<4>(codes, S.code_bits, lane, slot, writes);
+                    const uint32_t planes = pack_planes(codes, S.code_bits, lane, slot, writes);
                     store_chunk_words(A.codes[q.w], q.P.t, base, S.code_bits, planes, slot, writes);
                 }
                 spot = make_float4(p[k][0], p[k][1], p[k][2], p[k][3]);
@@ -2016,9 +2037,7 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
             for (int u = 0; u < U; ++u) {
                 if (U > 1 && i0 + u >= N) break;
                 if constexpr (W) {
-                    ld<V, SH>(A.err[i0 + u], gi, nvalid, sf, g[u]);       // parked p; p + 0 reproduces it
-#pragma unroll
-                    for (int j = 0; j < V; ++j) e[u][j] = 0.0f;
+                    ld<V, SH>(A.err[i0 + u], gi, nvalid, sf, g[u]);       // parked p
                 } else {
                     ld<V, SH>(A.grad[i0 + u], gi, nvalid, sf, g[u]);
                     ld<V, SH>(A.err[i0 + u], gi, nvalid, sf, e[u]);
@@ -2036,18 +2055,16 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
                     sc = stored_scale(A.fold, i, t, A.scales[i]);
                 }
                 const float s = sc.s, inv_s = sc.inv;
-                float q[V], en[V], Ur[V];
+                float p[V], en[V], Ur[V];
 #pragma unroll
-                for (int j = 0; j < V; ++j) Ur[j] = 0.0f;
+                for (int j = 0; j < V; ++j) { p[j] = W ? g[u][j] : g[u][j] + e[u][j]; Ur[j] = 0.0f; }
                 if constexpr (ROUNDING == 1) unif<V, SH, true>(S, gi, (uint32_t)i, 0u, sf, Ur);
                 uint32_t codes;
-                worker_lane<V, ROUNDING>(g[u], e[u], s, inv_s, c, S.mu_bits, Ur, q, en, codes);
+                worker_lane<ROUNDING>(p, s, inv_s, c, S.mu_bits, Ur, acc, en, codes);
                 st<V, SH>(A.err[i], gi, nvalid, sf, en);
                 int slot; bool writes;
-                const uint32_t word = pack_planes<V>(codes, S.code_bits, lane, slot, writes);
+                const uint32_t word = pack_planes(codes, S.code_bits, lane, slot, writes);
                 store_chunk_words(A.codes[i], t, base, S.code_bits, word, slot, writes);
-#pragma unroll
-                for (int j = 0; j < V; ++j) acc[j] = acc[j] + q[j];
             }
         }
         server_lane<ROUNDING, V, W, SH, true>(S, A.sp, acc, xv, mv, vv, wi, gi, nvalid, sf);
@@ -2115,7 +2132,6 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
     // elements 362 / 335, 10000 of 2000 296 / 346; with the next worker's / the server's too, 20000 of 1000: 299 / 289, one
     // worker 160 / 158).
     constexpr bool AHEAD = C == 1;
-    const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     int base[C], nvalid[C];
     int64_t gi[C];
     float acc[C][4];
@@ -2199,18 +2215,16 @@ __device__ __forceinline__ void layer_step(const LayerArgs& A, const Tile& t)
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             if (base[k] >= t.len) break;
-            float q[4], en[4], U[4];
+            float en[4], U[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) U[j] = 0.0f;
             if constexpr (ROUNDING == 1) unif<4, SH>(S, gi[k], (uint32_t)i, 0u, sf, U);
             uint32_t codes;
-            worker_lane<4, ROUNDING>(p[k], zero, sc.s, sc.inv, c, S.mu_bits, U, q, en, codes);      // p + 0 reproduces p
+            worker_lane<ROUNDING>(p[k], sc.s, sc.inv, c, S.mu_bits, U, acc[k], en, codes);
             st<4, SH>(A.err[i], gi[k], nvalid[k], sf, en);
             int slot; bool writes;
-            const uint32_t word = pack_planes<4>(codes, S.code_bits, lane, slot, writes);
+            const uint32_t word = pack_planes(codes, S.code_bits, lane, slot, writes);
             store_chunk_words(A.codes[i], t, base[k], S.code_bits, word, slot, writes);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[k][j] = acc[k][j] + q[j];
         }
         write_pad_words(A.codes[i], t, S.code_bits);
     }
