@@ -306,15 +306,17 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     if (h->code_bits > 0) h->apart = short_layers_apart(shorts, tile_count, num_workers);
     const bool split = h->apart.any();
     // layers for k_parked, if any call can use it
-    int64_t park_elems = 0, park_units = 0, scaled_elems = 0;
-    auto parkable = [&](int64_t n) { return n > (split ? kTileElems : 0) && n <= kParkedLongest; };
+    int64_t park_elems = 0, park_units = 0, park_longest = 0, scaled_elems = 0;
+    auto parkable = [&](int64_t n) { return n > (split ? kTileElems : 0) && n <= kParkedLongestOfThree; };
     for (int l = 0; l < num_segments; ++l) {
         const int64_t n = seg_offsets[l + 1] - seg_offsets[l];
         if (!split || n > kTileElems) scaled_elems += n;
-        if (parkable(n)) { park_elems += n; park_units += parked_units(n); }
+        if (!parkable(n)) continue;
+        park_elems += n; park_units += parked_units(n);
+        if (n > park_longest) park_longest = n;
     }
-    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1, cfg->rounding == 1, true) ||
-                                                worth_parking(park_elems, park_units, scaled_elems, num_workers, cfg->rounding == 1));
+    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1, cfg->rounding == 1, true, park_longest) ||
+                                                worth_parking(park_elems, park_units, scaled_elems, num_workers, cfg->rounding == 1, false, park_longest));
     std::vector<Tile> scaled_tiles, short_layers[kShortSizes];
     std::vector<int32_t> sample_tiles, scaled_begin, scaled_layers;
     std::vector<Tile> rest_tiles;
@@ -342,6 +344,7 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
             p.copies = meeting_copies(p.num_units);
             h->parked.meeting_words += meeting_words(p.num_units);
             h->parked.num_elems += n;
+            if (n > h->parked.longest) h->parked.longest = n;
             for (int u = 0; u < p.num_units; ++u) parked_units_of.push_back({(int32_t)parked_layers.size(), u});
             parked_layers.push_back(p);
         } else if (parks_any && !apart) {

@@ -92,7 +92,7 @@ struct Parked {
     uint32_t* meeting;      // device, [num_workers][meeting_words], zero between launches but for the launches counted
     uint32_t* aside;        // device, [num_workers][num_units]
     int32_t   num_units, meeting_words;
-    int64_t   num_elems;
+    int64_t   num_elems, longest;   // elements of all of them, of the longest
     int32_t   polls;        // for a scale before a workgroup puts its unit aside
 };
 

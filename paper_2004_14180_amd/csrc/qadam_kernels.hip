@@ -22,7 +22,7 @@
 //     pass (the workgroups of k_parked, which are few per layer, count themselves with one each);
 //   * a segment that starts off the 16-byte grid keeps the same lane-to-element mapping (the codes are
 //     anchored at the segment start) and moves its data with dword-aligned 128-bit accesses;
-//   * layers of up to 6.3 M elements in long lists stay on the chip between the scale and the quantizer: the workgroups of a
+//   * layers of up to 17.8 M elements in long lists stay on the chip between the scale and the quantizer: the workgroups of a
 //     layer meet over its scale while they load and store units of other layers (k_parked);
 //   * when the error buffers are what the previous step wrote, |e| <= s/4 (half the widest gap of
 //     the grid), so an element whose |g| lies that far below a known lower bound of the scale
@@ -1320,14 +1320,22 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
 
 // ---- layers that the chip's registers hold: scale and quantization in one launch -----------------
 // The workgroups of a layer keep p = g + e on the chip, meet over the layer's scale and then quantize what they hold, so that
-// g and e are read once: 12.4 bytes per element for 20.4 of the two passes.  A workgroup holds two units, the younger one in
-// registers, the older one in LDS.  Each turn it quantizes the older one chunk by chunk while the next unit is loaded in
-// its place, so that loads and stores mix and a layer's units have a turn's time to meet.  Bound by memory: 85 M elements, one
-// worker 257 -> 206 us, 340 M 738 us; beyond the first and last turn 6.0 TB/s.  Layers of one unit each, which do not meet,
-// take the same time.  Chunks whose loads are in flight together, 2 / 4 / 8: 209 / 206 / 220 us (8 spills); workgroups of 256 /
-// 512 / 1024 threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded, waited for and stored in
-// turn 229.  A workgroup's first unit is the one of its own number, the others are drawn from a counter in the order of the layers:
-// all dealt out beforehand they end 10 us later, all drawn they begin 4 us later, as 512 draws at once take that long.
+// g and e are read once: 12.4 bytes per element for 20.4 of the two passes.  A workgroup holds two units or three, the oldest one in
+// LDS, the younger ones in registers.  Each turn it quantizes the oldest one chunk by chunk while the next unit is loaded and the
+// others move up, so that loads and stores mix and a layer's units have a turn or two to meet.  Bound by memory: 85 M elements, one
+// worker 257 -> 194 us with two units, layers of 8 to 17 M elements 261 -> 209 with three; beyond the first and last turns 6.0 TB/s.
+// Layers of one unit each, which do not meet, take the same time.  Chunks whose loads are in flight together, two units, 2 / 4 / 8: 209 /
+// 206 / 220 us (8 spills); three units, 2 / 4 (4 spills): 211 / 228, where 1024 units meet 1706 / 1822; workgroups of 256 / 512 / 1024
+// threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded, waited for and stored in turn 229.  A workgroup's
+// first unit is the one of its own number, the others are drawn from a counter in the order of the layers: all dealt out beforehand
+// they end 10 us later, all drawn they begin 4 us later, as 512 draws at once take that long.
+// A turn that quantizes a whole unit and loads a whole one runs straight through, without a guard around a store: where paths with and
+// without stores join, the wait for the loads becomes one for everything (two units, layers of 144 units 200 / 194).  The maxima of a layer
+// are folded with up to 1024 loads under way, 16 to a lane; one after the other they kept its workgroups waiting (three units, step of
+// 4 workers, layers of 1024 units 1706 / 1671, 768 units 1351 / 1258).
+// Measured and not taken: turns without a barrier, whose first wavefront draws, hands in and asks ahead and tells the others through LDS
+// (85 M elements 248); the next unit drawn and the scale asked for at the end of the turn before, the arrival counted during the next
+// (768 units 303, as units are put aside that a unit drawn too early keeps waiting).
 //
 // No workgroup depends on another one being resident.  A workgroup claims its first unit when it starts, and a unit that is claimed
 // or drawn is held by a running workgroup, which loads it and hands in its maximum without waiting in between.  A workgroup whose
@@ -1353,7 +1361,7 @@ struct ParkedArgs {
     uint32_t* status;
 };
 
-constexpr int kParkedLoads = 4;                 // chunks whose loads are in flight together
+constexpr int kParkedFold = 16;                 // maxima of a layer that a lane of its last workgroup loads together
 constexpr uint32_t kNoUnit = 0xffffffffu;
 constexpr uint32_t kPublished = 0x80000000u;    // marks a published scale, whose own sign bit is 0
 // in place of a scale that did not come (kLastPolls); the status word reports it
@@ -1379,6 +1387,21 @@ __device__ __forceinline__ void store_agent(uint32_t* p, uint32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A table that nothing writes while the kernel runs, through the scalar cache: the index is the same in all lanes.
+template <typename T>
+__device__ __forceinline__ T load_constant(const T* p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    typedef const __attribute__((address_space(4))) uint32_t* Words;
+    const Words from = (Words)(uint64_t)p;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = from[i];
+    T t;
+    __builtin_memcpy(&t, w, sizeof(T));
+    return t;
+}
+
 // A unit and its layer, the same in all lanes.
 struct Place {
     ParkedLayer P;
@@ -1388,9 +1411,9 @@ struct Place {
 
 __device__ __forceinline__ Place place_of(const ParkedArgs& A, uint32_t item)
 {
-    const ParkedUnit u = A.units[item % A.num_units];
+    const ParkedUnit u = load_constant(A.units + item % A.num_units);
     Place q;
-    q.P = A.layers[u.layer];
+    q.P = load_constant(A.layers + u.layer);
     q.unit = u.unit;
     q.w = A.first_worker + (int)(item / A.num_units);
     q.meeting = A.meeting + (size_t)q.w * A.meeting_words + q.P.meeting;
@@ -1431,9 +1454,13 @@ __device__ __forceinline__ void arrive(const ParkedArgs& A, const Place& q, uint
     arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
     if ((arrived & kArrivals) != (uint32_t)q.P.num_units - 1u) return;
     uint32_t local = 0;
-    for (int i = lane; i < q.P.num_units; i += 64) {
-        const uint32_t v = load_agent(maxima + i);
-        local = v > local ? v : local;
+    // all of them at once: the layer's workgroups wait for this
+    for (int i = lane; i < q.P.num_units; i += 64 * kParkedFold) {
+        uint32_t v[kParkedFold];
+#pragma unroll
+        for (int k = 0; k < kParkedFold; ++k) v[k] = load_agent(maxima + min(i + k * 64, q.P.num_units - 1));
+#pragma unroll
+        for (int k = 0; k < kParkedFold; ++k) local = v[k] > local ? v[k] : local;
     }
     publish_scale(A, q, (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(local)));
 }
@@ -1537,7 +1564,84 @@ __device__ __forceinline__ void begin_turn(const ParkedArgs& A, const Place& q, 
     __syncthreads();
 }
 
-template <int ROUNDING>
+// A layer's part of a buffer of one worker, for accesses with one register of offset per lane beside scalar ones.  A layer that is parked
+// takes less than 2^31 bytes.  Stores are not buffer stores: with the offset in a scalar register the compiler knows of no wait between
+// one and the next write to its registers, and the first word of lanes 12 to 15 of each row of 16 was stored as that write left it.
+typedef __amdgpu_buffer_rsrc_t Buf;
+typedef __attribute__((address_space(1))) char* Out;
+
+__device__ __forceinline__ uint64_t uniform_address(const void* p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return (uint64_t)hi << 32 | lo;
+}
+
+__device__ __forceinline__ Buf buffer_of(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)uniform_address(p), 0, -1, 0x00020000);
+}
+
+__device__ __forceinline__ Out out_of(void* p) { return (Out)uniform_address(p); }
+
+constexpr int kNonTemporal = 2;
+
+__device__ __forceinline__ void load_buffer(Buf b, uint32_t lane_bytes, int bytes, float (&out)[4])
+{
+    const u4 t = __builtin_amdgcn_raw_buffer_load_b128(b, (int)lane_bytes, bytes, kNonTemporal);
+    out[0] = u2f(t.x); out[1] = u2f(t.y); out[2] = u2f(t.z); out[3] = u2f(t.w);
+}
+
+__device__ __forceinline__ void store_out(Out to, uint32_t lane_bytes, int bytes, const float (&in)[4])
+{
+    const f4 t = {in[0], in[1], in[2], in[3]};
+    __builtin_nontemporal_store(t, (__attribute__((address_space(1))) f4_a4*)(to + (uint32_t)bytes + lane_bytes));
+}
+
+// Quantizes and stores a wavefront's 256 elements from `base`.  WHOLE: all of them are the layer's, so that no store is guarded and
+// the wait for loads issued before is not one for the stores as well.
+template <int ROUNDING, bool WHOLE>
+__device__ __forceinline__ void parked_chunk(const ParkedArgs& A, const QgConst& c, const Place& q, const Scale& sc, int base, float4 v,
+                                             Out err, Out code_words)
+{
+    const StepScalars& S = A.S;
+    const int lane = threadIdx.x & 63;
+    const int nvalid = WHOLE ? 4 : min(max(q.P.t.len - base - lane * 4, 0), 4);
+    const float old[4] = {v.x, v.y, v.z, v.w};
+    float unused[4], en[4], U[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { unused[j] = 0.0f; U[j] = 0.0f; }
+    if constexpr (ROUNDING == 1) {
+        const int64_t gi = q.P.t.start + base + lane * 4;
+        const Shift sf = make_shift(q.P.t);
+        StepScalars R = S;
+        // the keys of the ten rounds are worked out here and not held in registers over the turns
+        asm volatile("" : "+s"(R.key0), "+s"(R.key1));
+        if (sf.r) uniforms_shifted<false>(R, gi, (uint32_t)q.w, 0u, sf.r, U);
+        else uniforms<4, false>(R, gi, (uint32_t)q.w, 0u, U);
+    }
+    uint32_t codes;
+    worker_lane<ROUNDING>(old, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);
+    if constexpr (WHOLE) {
+        store_out(err, (uint32_t)lane * 16u, base * 4, en);
+    } else {
+        store_shifted(A.err[q.w] + q.P.t.start + base + lane * 4, nvalid, en);
+    }
+    int slot; bool writes;
+    const uint32_t planes = pack_planes(codes, S.code_bits, lane, slot, writes);
+    if constexpr (WHOLE) {
+        // lanes with no plane of their own store their group's first word once more
+        const uint32_t first = (uint32_t)__builtin_amdgcn_ds_bpermute((lane & 56) * 4, (int)planes);
+        *(__attribute__((address_space(1))) uint32_t*)(code_words + (uint32_t)((base >> 5) * S.code_bits * 4) + (uint32_t)(writes ? slot : slot - (lane & 7)) * 4u) =
+            writes ? planes : first;
+    } else {
+        store_chunk_words(A.codes[q.w], q.P.t, base, S.code_bits, planes, slot, writes);
+    }
+}
+
+// HELD: units in registers.  LOADS: chunks whose loads are in flight together.
+template <int ROUNDING, int HELD, int LOADS>
 __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
 {
     const StepScalars& S = A.S;
@@ -1545,13 +1649,17 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
     const int mine = (int)threadIdx.x * 4;
     const QgConst c = make_qg(S.k_g);
     extern __shared__ float4 held[];                    // [kParkedChunks][kParkedThreads]
-    float p[kParkedChunks][4];                          // the younger unit; the older one is in LDS
-    uint32_t item = kNoUnit, other_item = kNoUnit;      // the older one, the younger one
-    uint32_t word = 0, other_word = 0;                  // their scales where they are known at once
+    float p[HELD][kParkedChunks][4];                    // the younger units, the youngest last; the oldest one is in LDS
+    uint32_t item = kNoUnit, younger[HELD];             // the oldest one, the younger ones
+    uint32_t word = 0, younger_word[HELD];              // their scales where they are known at once
 #pragma unroll
-    for (int k = 0; k < kParkedChunks; ++k)
+    for (int h = 0; h < HELD; ++h) {
+        younger[h] = kNoUnit; younger_word[h] = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) p[k][j] = 0.0f;
+        for (int k = 0; k < kParkedChunks; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[h][k][j] = 0.0f;
+    }
     uint32_t next = kNoUnit;
     __shared__ Turn turn;
     if (threadIdx.x == 0) {
@@ -1575,7 +1683,10 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
                 met = false;
             }
         }
-        if (item == kNoUnit && next == kNoUnit && other_item == kNoUnit) break;
+        bool any = item != kNoUnit || next != kNoUnit;
+#pragma unroll
+        for (int h = 0; h < HELD; ++h) any = any || younger[h] != kNoUnit;
+        if (!any) break;
         uint32_t departed = 0;
         if (met && threadIdx.x == 0)
             departed = __hip_atomic_fetch_add(q.meeting, kDeparture, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1585,22 +1696,54 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
         const int n_stride = n.P.num_units * kParkedChunk, n_begin = n.unit * kParkedChunk;
         const bool q_whole = q_begin + (kParkedChunks - 1) * q_stride + kParkedChunk <= q.P.t.len;
         const bool n_whole = n_begin + (kParkedChunks - 1) * n_stride + kParkedChunk <= n.P.t.len;
+        const bool straight = item != kNoUnit && next != kNoUnit && q_whole && n_whole;
         const float* n_grad = A.grad[n.w] + n.P.t.start;
         const float* n_err = A.err[n.w] + n.P.t.start;
-        static_for<kParkedChunks / kParkedLoads>([&](auto part) {
-            constexpr int k0 = decltype(part)::value * kParkedLoads;
-            float g[kParkedLoads][4], e[kParkedLoads][4];
+        const Buf n_grad_buf = buffer_of(n_grad), n_err_buf = buffer_of(n_err);
+        const Out q_err = out_of(A.err[q.w] + q.P.t.start), q_codes = out_of(A.codes[q.w] + q.P.t.code_word);
+        static_for<kParkedChunks / LOADS>([&](auto part) {
+            constexpr int k0 = decltype(part)::value * LOADS;
+            float g[LOADS][4], e[LOADS][4];
+            if (straight) {
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k) {
+                    const int base = n_begin + (k0 + k) * n_stride;
+                    load_buffer(n_grad_buf, (uint32_t)threadIdx.x * 16u, base * 4, g[k]);
+                    load_buffer(n_err_buf, (uint32_t)threadIdx.x * 16u, base * 4, e[k]);
+                }
+                asm volatile("" : : : "memory");
+#pragma unroll
+                for (int k = k0; k < k0 + LOADS; ++k) {
+                    float4& spot = held[k * kParkedThreads + threadIdx.x];
+                    parked_chunk<ROUNDING, true>(A, c, q, sc, q_begin + k * q_stride + wave * 256, spot, q_err, q_codes);
+                    spot = make_float4(p[0][k][0], p[0][k][1], p[0][k][2], p[0][k][3]);
+#pragma unroll
+                    for (int h = 0; h + 1 < HELD; ++h)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) p[h][k][j] = p[h + 1][k][j];
+                    asm volatile("" : : : "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        p[HELD - 1][k0 + k][j] = g[k][j] + e[k][j];
+                        asm volatile("" : "+v"(p[HELD - 1][k0 + k][j]) : : "memory");
+                    }
+                return;
+            }
             if (next != kNoUnit) {
                 if (n_whole) {
 #pragma unroll
-                    for (int k = 0; k < kParkedLoads; ++k) {
+                    for (int k = 0; k < LOADS; ++k) {
                         const int base = n_begin + (k0 + k) * n_stride;
                         load_any(n_grad + base + mine, 4, g[k]);
                         load_any(n_err + base + mine, 4, e[k]);
                     }
                 } else {
 #pragma unroll
-                    for (int k = 0; k < kParkedLoads; ++k) {
+                    for (int k = 0; k < LOADS; ++k) {
                         const int base = n_begin + (k0 + k) * n_stride;
                         const int nvalid = min(max(n.P.t.len - base - mine, 0), 4);
                         load_any(n_grad + base + mine, nvalid, g[k]);
@@ -1610,43 +1753,27 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
             }
             asm volatile("" : : : "memory");    // the loads are on their way before the arithmetic
 #pragma unroll
-            for (int k = k0; k < k0 + kParkedLoads; ++k) {
+            for (int k = k0; k < k0 + LOADS; ++k) {
                 float4& spot = held[k * kParkedThreads + threadIdx.x];
                 const int base = q_begin + k * q_stride + wave * 256;
                 if (item != kNoUnit && (q_whole || base < q.P.t.len)) {
-                    const int nvalid = q_whole ? 4 : min(max(q.P.t.len - base - lane * 4, 0), 4);
-                    const float4 v = spot;
-                    const float old[4] = {v.x, v.y, v.z, v.w};
-                    float unused[4], en[4], U[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) { unused[j] = 0.0f; U[j] = 0.0f; }
-                    if constexpr (ROUNDING == 1) {
-                        const int64_t gi = q.P.t.start + base + lane * 4;
-                        const Shift sf = make_shift(q.P.t);
-                        StepScalars R = S;
-                        // the keys of the ten rounds are worked out here and not held in registers over the turns
-                        asm volatile("" : "+s"(R.key0), "+s"(R.key1));
-                        if (sf.r) uniforms_shifted<false>(R, gi, (uint32_t)q.w, 0u, sf.r, U);
-                        else uniforms<4, false>(R, gi, (uint32_t)q.w, 0u, U);
-                    }
-                    uint32_t codes;
-                    worker_lane<ROUNDING>(old, sc.s, sc.inv, c, S.mu_bits, U, unused, en, codes);
-                    store_shifted(A.err[q.w] + q.P.t.start + base + lane * 4, nvalid, en);
-                    int slot; bool writes;
-                    const uint32_t planes = pack_planes(codes, S.code_bits, lane, slot, writes);
-                    store_chunk_words(A.codes[q.w], q.P.t, base, S.code_bits, planes, slot, writes);
+                    parked_chunk<ROUNDING, false>(A, c, q, sc, base, spot, q_err, q_codes);
                 }
-                spot = make_float4(p[k][0], p[k][1], p[k][2], p[k][3]);
+                spot = make_float4(p[0][k][0], p[0][k][1], p[0][k][2], p[0][k][3]);
+#pragma unroll
+                for (int h = 0; h + 1 < HELD; ++h)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) p[h][k][j] = p[h + 1][k][j];
                 asm volatile("" : : : "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (next != kNoUnit) {
 #pragma unroll
-                for (int k = 0; k < kParkedLoads; ++k)
+                for (int k = 0; k < LOADS; ++k)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        p[k0 + k][j] = g[k][j] + e[k][j];
-                        asm volatile("" : "+v"(p[k0 + k][j]) : : "memory");
+                        p[HELD - 1][k0 + k][j] = g[k][j] + e[k][j];
+                        asm volatile("" : "+v"(p[HELD - 1][k0 + k][j]) : : "memory");
                     }
             }
         });
@@ -1666,7 +1793,7 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
             for (int k = 0; k < kParkedChunks; ++k)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint32_t ab = f2u(p[k][j]) & 0x7fffffffu;
+                    const uint32_t ab = f2u(p[HELD - 1][k][j]) & 0x7fffffffu;
                     local = ab > local ? ab : local;
                 }
             const uint32_t bm = block_max<kParkedThreads>(local);
@@ -1677,11 +1804,13 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
             }
             word = bm;                          // of a layer of one unit
         }
-        item = other_item;
-        other_item = next;
         const uint32_t youngest = word;
-        word = other_word;
-        other_word = youngest;
+        item = younger[0];
+        word = younger_word[0];
+#pragma unroll
+        for (int h = 0; h + 1 < HELD; ++h) { younger[h] = younger[h + 1]; younger_word[h] = younger_word[h + 1]; }
+        younger[HELD - 1] = next;
+        younger_word[HELD - 1] = youngest;
     }
 }
 
@@ -2601,7 +2730,8 @@ static bool codes_overlap(const Launch& L, const WorkerPtrs& W, int first_worker
 // Two code buffers that overlap are left to the main pass, which gives them an order.
 bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call)
 {
-    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1, call)
+    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1, call,
+                                                   L.parked.longest)
         && !codes_overlap(L, W, first_worker, num);
 }
 
@@ -2621,8 +2751,14 @@ hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs
     A.num_units = (uint32_t)L.parked.num_units; A.total = A.num_units * (uint32_t)num;
     const unsigned lds = kParkedThreads * kParkedChunks * sizeof(float4);
     const dim3 grid(kParkedGroups), block(kParkedThreads);
-    if (S.rounding == 0) hipLaunchKernelGGL(k_parked<0>, grid, block, lds, L.stream, A);
-    else hipLaunchKernelGGL(k_parked<1>, grid, block, lds, L.stream, A);
+    const bool three = L.parked.longest > kParkedLongest;
+    if (S.rounding == 0) {
+        if (three) hipLaunchKernelGGL((k_parked<0, 2, 2>), grid, block, lds, L.stream, A);
+        else hipLaunchKernelGGL((k_parked<0, 1, 4>), grid, block, lds, L.stream, A);
+    } else {
+        if (three) hipLaunchKernelGGL((k_parked<1, 2, 2>), grid, block, lds, L.stream, A);
+        else hipLaunchKernelGGL((k_parked<1, 1, 4>), grid, block, lds, L.stream, A);
+    }
     return hipGetLastError();
 }
 

@@ -231,7 +231,7 @@ constexpr bool worth_by_worker(int64_t n, int64_t off_grid, int num, bool varian
 
 // ---- layers that the chip's registers hold (k_parked) -----------------------------------------------------------------
 // Unit u of a layer's n is its chunks u, u + n, ..., kParkedChunks at most, so that the workgroups of a layer walk it side
-// by side.  A workgroup holds two units.
+// by side.  A workgroup holds two units or, where a list has layers that need it, three.
 constexpr int kParkedThreads = 512;
 constexpr int kParkedChunk = kParkedThreads * 4, kParkedChunks = 8;
 
@@ -241,9 +241,13 @@ constexpr int parked_units(int64_t len)
     return (int)((chunks + kParkedChunks - 1) / kParkedChunks);
 }
 
-// Layers of up to 384 units (6.3 M elements).  The 512 workgroups of a launch (kParkedGroups, two per CU) hold two units each,
-// and a layer of nearly as many units as there are workgroups leaves none of them for its neighbours.  One worker's call of 85 M
-// elements, us, two passes / this way: layers of 36 units 260 / 210, 144 260 / 206, 256 259 / 206, 384 272 / 222, 512 257 / 284.
+// Layers of up to kParkedLongestOfThree: 1088 units, 17.8 M elements.  The 512 workgroups of a launch (kParkedGroups, two per CU) hold two or
+// three units each, of which one is being replaced, and a layer of nearly as many units as they hold beside it leaves none for its
+// neighbours.  The third unit costs loads in flight and a turn more that only loads, so it is there only for lists with a layer of
+// more than kParkedLongest elements (256 units).  One worker's call of 85 M elements, us, two passes / two units / three: layers of 36 units 260 / 202 /
+// 206, 144 260 / 194 / 202, 256 259 / 203, 300 259 / 209 / 202, 384 272 / 232 / 212, 512 257 / 262 / 209, 768 275 / 273 / 218, 1024 261 / 263 /
+// 209, 1100 (90 M) 277 / - / 242, 1280 (105 M) 323 / - / 291; step of 4 workers whose scale pass is the filtered one, 768 (88 M) 1348 / - /
+// 1257, 1024 (117 M) 1790 / - / 1650, 1100 (90 M) 1388 / - / 1383, 1280 (105 M) 1599 / - / 1623.
 constexpr int kParkedGroups = 512;
 // Polls for a scale, of about 0.7 us each, before a workgroup puts its unit aside: where the layer's units are all held, and
 // between two looks whether they are.
@@ -251,9 +255,10 @@ constexpr int kParkedPolls = 250, kPollsUnheld = 8;
 // Every wait ends, also where two calls for one worker overlap, which the boundary forbids, and their counts are wrong: this
 // many polls (about a second) at most, and for a scale that has to come a NaN in its place then.
 constexpr int kLastPolls = 1 << 20;
-constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
+constexpr int64_t kParkedLongest = (int64_t)256 * kParkedChunk * kParkedChunks;
+constexpr int64_t kParkedLongestOfThree = (int64_t)1088 * kParkedChunk * kParkedChunks;
 
-// Whether a step of num workers, or one worker's separate call (`call`), does the layers of up to kParkedLongest elements this way:
+// Whether a step of num workers, or one worker's separate call (`call`), does the layers of up to kParkedLongestOfThree elements this way:
 // `elems` in `units`, of the `all` elements whose scales have a pass of their own.  The launch starts by loading only and ends by
 // storing only, which costs it about 29 us (85 M elements in 206 us, 340 M in 738).  us, without / with, layers of 2^18 to 2^21
 // elements: step of one worker of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 /
@@ -269,13 +274,18 @@ constexpr int64_t kParkedLongest = (int64_t)384 * kParkedChunk * kParkedChunks;
 // layers of 5 M 165 / 166 and off the grid 191 / 196, 64 M 211 / 196; step of 2 workers of 24 M 286 / 293, 30 M 358 / 362, 4 of 8 M 159 /
 // 162, off the grid 168 / 178, of 16 M 306 / 286 and 380 / 317.  Beside longer layers, 8 workers, 6 M beside 12 M 612 / 627, off the
 // grid 684 / 737, 12 M beside 12 M 812 / 783 and 916 / 918, 4 workers 465 / 476 and 522 / 567.
-constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic, bool call = false)
+// Layers that need a third unit, whose start takes longer (longest: elements of the longest): step of one worker, one layer of 8 M 82.0 /
+// 83.8, two 160 / 150, one of 16 M 160 / 149; of 4, one of 8 M 158 / 151, 12 M 236 / 209, 16 M 308 / 268; one worker's call, two of 8 M
+// 56.5 / 55.6, three 82 / 78, one of 16 M 56.9 / 55.5; stochastic, 5 of 8 M, its call 136 / 133, step of 4 workers 753 / 630, 3 of 16 M
+// 899 / 798.
+constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic, bool call = false,
+                             int64_t longest = 0)
 {
     const int64_t work = elems * num, M = 1 << 20, turns = (units + kParkedGroups - 1) / kParkedGroups;
     const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
     const bool full_turns = 16 * units >= 15 * turns * kParkedGroups;
     const int64_t least = stochastic && elems < all ? 96 : !filled ? 72 : stochastic ? (call || num == 2 ? 64 : 48)
-                        : 2 * elems < all ? 48 : num > 1 ? 24 : !call ? 8 : full_turns ? 15 : 24;
+                        : 2 * elems < all ? 48 : num > 1 ? 24 : !call ? (longest > kParkedLongest ? 12 : 8) : full_turns ? 15 : 24;
     return work >= least * M && 4 * elems >= all;
 }
 

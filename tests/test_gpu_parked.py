@@ -179,3 +179,19 @@ def test_polls_are_checked():
     with pytest.raises(Exception):
         q.set_scale_polls(-2)
     q.set_scale_polls(2**31 - 1)            # accepted, as many as end in a bounded time are used
+
+
+@pytest.mark.parametrize("polls", [-1, 0, 3])
+@pytest.mark.parametrize("sizes", [[256 * UNIT + 1, 1001, 130 * UNIT - 5, 2047, 300 * UNIT],    # just beyond what two units serve
+                                   [1001, 1088 * UNIT]])                                        # the longest, off the grid
+@pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=4, k_x=6, rounding=1, seed=3)])
+def test_lists_whose_workgroups_hold_three_units(polls, sizes, cfgkw):
+    a, b = (_AnyState(sizes, False, workers=5, **cfgkw) for _ in range(2))
+    a.q.set_scale_polls(polls)
+    a.q.profile_enable()
+    for t in (1, 2):
+        a.step(t, False, True)
+        b.step(t, False, False)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+    assert a.q.get_status() == 0
+    assert a.q.profile_work()[0] == 0       # every layer was parked
