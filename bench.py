@@ -502,9 +502,11 @@ def run_fused(args, config, dev, steps, warmup, placement, headline):
     if variant_w:
         # first pass (dominant): per worker read g, m_i, v_i, e_i and write m_i, v_i, p = 28 B;
         # second pass: per worker read p, write e and the code; server read/write x and e^x, weight code
-        a_first = 28.0 * N
-        a_second = N * (8.0 + (1.0 + codes_read) * code_bits / 8.0) + 8.0 + (8.0 if weight_ef else 4.0) + wcode_bytes
-        roofline = {"bound": "hbm", "kernel": "k_moments_w (first pass of qadam_step_fused_w)",
+        # layers that stay on the chip between the two (k_parked) are read and written once, within the second part
+        a_first = 28.0 * N * scanned
+        a_second = N * (8.0 + 20.0 * (1.0 - scanned) + (1.0 + codes_read) * code_bits / 8.0) + 8.0 + (8.0 if weight_ef else 4.0) + wcode_bytes
+        roofline = {"bound": "hbm", "kernel": "k_moments_w (first pass of qadam_step_fused_w%s)" % (
+                        "; layers that are read once, %.1f %%: k_parked, k_layers" % (100 * (1 - scanned)) if scanned < 1 else ""),
                     "scope": "this kernel's launches only",
                     "achieved": gbs(a_first, scale_avg), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs(a_first, scale_avg) / HBM_PEAK_GBS, 4), "traffic": None,

@@ -46,8 +46,8 @@
  *     checks made before anything is enqueued: the buffers are untouched.  QADAM_EHIP means a kernel launch
  *     was refused by the runtime part way through the call: launches accepted before it still run, so the
  *     buffers of the call are then in an intermediate state (variant S: scales written, server state not yet
- *     advanced, the error buffers of some layers and workers perhaps; variant W: m_i, v_i already advanced and the error buffers holding the parked
- *     alpha_t m_i / sqrt(v_i + eps) + e_i instead of e_i) and the step cannot be repeated on them.
+ *     advanced, the error buffers of some layers and workers perhaps; variant W: m_i, v_i already advanced and the error buffers of some or all
+ *     layers holding alpha_t m_i / sqrt(v_i + eps) + e_i, or what the step leaves there, instead of e_i) and the step cannot be repeated on them.
  *     Non-finite scales (NaN/Inf in g + e) are data errors: they set a bit in the status word that
  *     qadam_get_status reads; the outputs of that layer are then unspecified (codes stay in range).
  *   - HIP graphs: the compute calls may be recorded into a graph (stream capture).  A replay repeats the

@@ -315,8 +315,12 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
         park_elems += n; park_units += parked_units(n);
         if (n > park_longest) park_longest = n;
     }
-    const bool parks_any = h->code_bits > 0 && (worth_parking(park_elems, park_units, scaled_elems, 1, cfg->rounding == 1, true, park_longest) ||
-                                                worth_parking(park_elems, park_units, scaled_elems, num_workers, cfg->rounding == 1, false, park_longest));
+    const bool stochastic = cfg->rounding == 1;
+    const bool parks_any = h->code_bits > 0 &&
+        (worth_parking(park_elems, park_units, scaled_elems, 1, stochastic, true, park_longest) ||
+         worth_parking(park_elems, park_units, scaled_elems, num_workers, stochastic, false, park_longest) ||
+         worth_parking_w(park_elems, park_units, scaled_elems, 1, stochastic, park_longest) ||
+         worth_parking_w(park_elems, park_units, scaled_elems, num_workers, stochastic, park_longest));
     std::vector<Tile> scaled_tiles, short_layers[kShortSizes];
     std::vector<int32_t> sample_tiles, scaled_begin, scaled_layers;
     std::vector<Tile> rest_tiles;
@@ -394,6 +398,10 @@ int qadam_init(qadam_handle_t* out, const qadam_config_t* cfg, const int64_t* se
     }
     h->code_words = word_off;
     h->max_row = h->scaled.shape.num_tiles * (int32_t)moment_cut(h->scaled.shape).parts;
+    if (parks_any) {
+        const int32_t with_units = rest_maxima(h->rest) + (int32_t)parked_units_of.size();
+        if (with_units > h->max_row) h->max_row = with_units;
+    }
 
     seg_tile_begin[num_segments] = (int32_t)tiles.size();
     h->num_tiles = (int32_t)tiles.size();
@@ -536,7 +544,7 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step, const 
     W.codes[worker] = static_cast<uint32_t*>(codes_dev); W.scales[worker] = scales_dev;
     const StepScalars S = make_scalars(h, step, 0.0f, 0.0f);
     Launch L = make_launch(h, stream);
-    const bool parked = use_parked(L, S, W, worker, 1, true);
+    const bool parked = use_parked(L, S, W, worker, 1, true, false);
     if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
@@ -545,7 +553,7 @@ int qadam_worker_quantize(qadam_handle_t h, int32_t worker, int64_t step, const 
     const bool filtered = recorded && (h->trust_errs == 2 || (h->trust_errs == 1 && L.scaled.shape.num_tiles >= kFilterMinTiles));
     if (h->trust_errs == 3 && recorded) QADAM_HIP(launch_check_error_bounds(L, W, worker, 1));
     BoundRecord record(h, worker, 1, W);
-    if (parked) QADAM_HIP(launch_parked(L, S, W, worker, 1));
+    if (parked) QADAM_HIP(launch_parked(L, S, W, worker, 1, false));
     if (filtered) QADAM_HIP(launch_amax_filtered(L, S, W, worker, 1));
     else QADAM_HIP(launch_amax(L, S, W, worker, 1));
     QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1));
@@ -660,7 +668,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
     sp.werr = idx ? nullptr : werr_dev; sp.wcodes = idx ? nullptr : wcodes_dev;
     const StepScalars S = make_scalars(h, step, lr, beta2);
     Launch L = make_launch(h, stream);
-    const bool parked = !idg && use_parked(L, S, W, 0, h->num_workers, false);
+    const bool parked = !idg && use_parked(L, S, W, 0, h->num_workers, false, false);
     if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
@@ -685,7 +693,7 @@ int qadam_step_fused(qadam_handle_t h, int64_t step, float lr, float beta2, cons
         QADAM_HIP(launch_reduce_scales(L, S, W, 0, h->num_workers));
         if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[1], L.stream));
         QADAM_HIP(launch_short_layers(L, S, W, sp, false));
-        if (parked) QADAM_HIP(launch_parked(L, S, W, 0, h->num_workers));
+        if (parked) QADAM_HIP(launch_parked(L, S, W, 0, h->num_workers, false));
         QADAM_HIP(launch_fused(L, S, W, sp));
         record.complete = !capturing;
         if (h->profile)
@@ -720,11 +728,14 @@ int qadam_worker_step_w(qadam_handle_t h, int32_t worker, int64_t step, float lr
     W.grad[worker] = grad_dev; W.err[worker] = err_dev; W.mw[worker] = mw_dev; W.vw[worker] = vw_dev;
     W.codes[worker] = static_cast<uint32_t*>(codes_dev); W.scales[worker] = scales_dev;
     const StepScalars S = make_scalars(h, step, lr, beta2);
-    const Launch L = make_launch(h, stream);
+    Launch L = make_launch(h, stream);
+    const bool parked = use_parked(L, S, W, worker, 1, true, true);
+    if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
     // pass 1: local moments, p = alpha m / sqrt(v + eps) + e parked in the error buffer, tile maxima
     BoundRecord record(h, worker, 1, W);
+    if (parked) QADAM_HIP(launch_parked(L, S, W, worker, 1, true));
     QADAM_HIP(launch_worker_moments_w(L, S, W, worker, 1));
     QADAM_HIP(launch_reduce_scales(L, S, W, worker, 1, moment_parts(L)));
     QADAM_HIP(launch_short_layers(L, S, W, worker, true));
@@ -758,7 +769,9 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     sp.x = x_dev; sp.m = nullptr; sp.v = nullptr;
     sp.werr = idx ? nullptr : werr_dev; sp.wcodes = idx ? nullptr : wcodes_dev;
     const StepScalars S = make_scalars(h, step, lr, beta2);
-    const Launch L = make_launch(h, stream);
+    Launch L = make_launch(h, stream);
+    const bool parked = !idg && use_parked(L, S, W, 0, h->num_workers, false, true);
+    if (parked) L = without_parked(L);
     bool capturing = false;
     QADAM_CHECK(check_capture(h, stream, &capturing));
     if (h->profile && !capturing) QADAM_HIP(hipEventRecord(h->ev[0], L.stream));
@@ -771,13 +784,14 @@ int qadam_step_fused_w(qadam_handle_t h, int64_t step, float lr, float beta2, co
     if (idg) QADAM_HIP(launch_plain_messages(L, S, W, sp, true));
     else {
         QADAM_HIP(launch_short_layers(L, S, W, sp, true));
+        if (parked) QADAM_HIP(launch_parked(L, S, W, 0, h->num_workers, true));
         QADAM_HIP(launch_fused_w(L, S, W, sp));
     }
     record.complete = !idg && !capturing;   // with the identity quantizer no scale, hence no bound, was produced
     if (h->profile && !capturing) {
         QADAM_HIP(hipEventRecord(h->ev[2], L.stream));
         const int64_t scanned = idg ? 0 : L.scaled.num_elems;
-        h->profile_work = {scanned, 0, scanned > 0 && step_by_worker(L, S, W, sp, true) ? scanned : 0};
+        h->profile_work = {scanned, 0, !idg && L.served.num_tiles > 0 && step_by_worker(L, S, W, sp, true) ? h->scaled.num_elems : 0};
         h->profile_valid = true;
     }
     return QADAM_OK;

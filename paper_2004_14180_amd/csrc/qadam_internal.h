@@ -135,6 +135,9 @@ struct Launch {
 // maxima per tile that the first pass of variant W leaves
 inline int moment_parts(const Launch& L) { return (int)moment_cut(L.scaled.shape).parts; }
 
+// maxima of one worker that a first pass over what k_parked leaves may write, in front of those of the units
+inline int rest_maxima(const Section& rest) { return rest.shape.num_tiles * (int)moment_cut(rest.shape).parts; }
+
 // the launch of what k_parked leaves
 inline Launch without_parked(const Launch& L)
 {
@@ -153,8 +156,8 @@ hipError_t launch_reduce_scales(const Launch& L, const StepScalars& S, const Wor
                                 int max_per_tile = 1);
 hipError_t launch_amax_filtered(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
 hipError_t launch_check_error_bounds(const Launch& L, const WorkerPtrs& W, int first_worker, int num);
-bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call);
-hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num);
+bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call, bool variant_w);
+hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool variant_w);
 hipError_t launch_worker_quantize(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int worker);
 // the short layers of the list, from the gradient (variant_w: through the local moments) to the codes, for one worker; or
 // the whole step of all workers

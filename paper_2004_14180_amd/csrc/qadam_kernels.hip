@@ -543,6 +543,18 @@ __device__ __forceinline__ void unif(const StepScalars& S, int64_t gi, uint32_t 
 // ------------------------------------------------------------------------------------------------
 // Server arithmetic on one lane: moments (Alg. 1, moment recursions) and the step alpha m / sqrt(v + eps).
 // ------------------------------------------------------------------------------------------------
+// of moments that have taken the step
+__device__ __forceinline__ float adam_quotient(const StepScalars& S, float m, float v)
+{
+    if (S.adam_flavor == 0) {
+        const float den = sqrtf(v + S.eps);
+        return (S.lr * m) / den;
+    } else {
+        const float den = (sqrtf(v) / S.sbc2) + S.eps;
+        return (S.lr1 * m) / den;
+    }
+}
+
 __device__ __forceinline__ float adam_step(const StepScalars& S, float gbar, float& m, float& v)
 {
     const float g2 = gbar * gbar;
@@ -550,13 +562,7 @@ __device__ __forceinline__ float adam_step(const StepScalars& S, float gbar, flo
     const float mn = (S.beta1 * m) + (S.omb1 * gbar);
     v = vn;
     m = mn;
-    if (S.adam_flavor == 0) {
-        const float den = sqrtf(vn + S.eps);
-        return (S.lr * mn) / den;
-    } else {
-        const float den = (sqrtf(vn) / S.sbc2) + S.eps;
-        return (S.lr1 * mn) / den;
-    }
+    return adam_quotient(S, mn, vn);
 }
 
 __device__ __forceinline__ float mean_over_workers(const StepScalars& S, float acc)
@@ -1322,7 +1328,8 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
 // The workgroups of a layer keep p = g + e on the chip, meet over the layer's scale and then quantize what they hold, so that
 // g and e are read once: 12.4 bytes per element for 20.4 of the two passes.  A workgroup holds two units or three, the oldest one in
 // LDS, the younger ones in registers.  Each turn it quantizes the oldest one chunk by chunk while the next unit is loaded and the
-// others move up, so that loads and stores mix and a layer's units have a turn or two to meet.  Bound by memory: 85 M elements, one
+// others move up, so that loads and stores mix and a layer's units have a turn or two to meet.  In variant W the local moments are
+// updated on the way, 28.4 bytes per element for 36.4.  Bound by memory: 85 M elements, one
 // worker 257 -> 194 us with two units, layers of 8 to 17 M elements 261 -> 209 with three; beyond the first and last turns 6.0 TB/s.
 // Layers of one unit each, which do not meet, take the same time.  Chunks whose loads are in flight together, two units, 2 / 4 / 8: 209 /
 // 206 / 220 us (8 spills); three units, 2 / 4 (4 spills): 211 / 228, where 1024 units meet 1706 / 1822; workgroups of 256 / 512 / 1024
@@ -1350,6 +1357,8 @@ struct ParkedArgs {
     float* err[QADAM_MAX_WORKERS];
     uint32_t* codes[QADAM_MAX_WORKERS];
     float* scales[QADAM_MAX_WORKERS];
+    float* mw[QADAM_MAX_WORKERS];   // variant W
+    float* vw[QADAM_MAX_WORKERS];
     uint32_t* maxima;       // rows of `row` maxima, one row per worker, one maximum per unit
     uint32_t* meeting;      // [N][meeting_words], zero between launches but for the launches counted
     uint32_t* aside;        // [N][num_units]: of a unit put aside, the one its workgroup put aside before it
@@ -1640,8 +1649,9 @@ __device__ __forceinline__ void parked_chunk(const ParkedArgs& A, const QgConst&
     }
 }
 
-// HELD: units in registers.  LOADS: chunks whose loads are in flight together.
-template <int ROUNDING, int HELD, int LOADS>
+// HELD: units in registers.  LOADS: chunks whose loads are in flight together.  W: p is the local update and the error, and the local
+// moments take their step; those of a unit put aside have taken it already.
+template <int ROUNDING, int HELD, int LOADS, bool W>
 __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
 {
     const StepScalars& S = A.S;
@@ -1696,85 +1706,108 @@ __global__ void __launch_bounds__(kParkedThreads, 4) k_parked(ParkedArgs A)
         const int n_stride = n.P.num_units * kParkedChunk, n_begin = n.unit * kParkedChunk;
         const bool q_whole = q_begin + (kParkedChunks - 1) * q_stride + kParkedChunk <= q.P.t.len;
         const bool n_whole = n_begin + (kParkedChunks - 1) * n_stride + kParkedChunk <= n.P.t.len;
-        const bool straight = item != kNoUnit && next != kNoUnit && q_whole && n_whole;
+        const bool straight = item != kNoUnit && next != kNoUnit && q_whole && n_whole && !(W && again);
         const float* n_grad = A.grad[n.w] + n.P.t.start;
         const float* n_err = A.err[n.w] + n.P.t.start;
         const Buf n_grad_buf = buffer_of(n_grad), n_err_buf = buffer_of(n_err);
         const Out q_err = out_of(A.err[q.w] + q.P.t.start), q_codes = out_of(A.codes[q.w] + q.P.t.code_word);
+        float* n_mw = nullptr;
+        float* n_vw = nullptr;
+        if constexpr (W) { n_mw = A.mw[n.w] + n.P.t.start; n_vw = A.vw[n.w] + n.P.t.start; }
+        const Buf n_mw_buf = buffer_of(n_mw), n_vw_buf = buffer_of(n_vw);
+        const Out n_mw_out = out_of(n_mw), n_vw_out = out_of(n_vw);
         static_for<kParkedChunks / LOADS>([&](auto part) {
             constexpr int k0 = decltype(part)::value * LOADS;
-            float g[LOADS][4], e[LOADS][4];
-            if (straight) {
-#pragma unroll
-                for (int k = 0; k < LOADS; ++k) {
-                    const int base = n_begin + (k0 + k) * n_stride;
-                    load_buffer(n_grad_buf, (uint32_t)threadIdx.x * 16u, base * 4, g[k]);
-                    load_buffer(n_err_buf, (uint32_t)threadIdx.x * 16u, base * 4, e[k]);
-                }
-                asm volatile("" : : : "memory");
-#pragma unroll
-                for (int k = k0; k < k0 + LOADS; ++k) {
-                    float4& spot = held[k * kParkedThreads + threadIdx.x];
-                    parked_chunk<ROUNDING, true>(A, c, q, sc, q_begin + k * q_stride + wave * 256, spot, q_err, q_codes);
-                    spot = make_float4(p[0][k][0], p[0][k][1], p[0][k][2], p[0][k][3]);
-#pragma unroll
-                    for (int h = 0; h + 1 < HELD; ++h)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) p[h][k][j] = p[h + 1][k][j];
-                    asm volatile("" : : : "memory");
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int k = 0; k < LOADS; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        p[HELD - 1][k0 + k][j] = g[k][j] + e[k][j];
-                        asm volatile("" : "+v"(p[HELD - 1][k0 + k][j]) : : "memory");
-                    }
-                return;
-            }
-            if (next != kNoUnit) {
-                if (n_whole) {
-#pragma unroll
-                    for (int k = 0; k < LOADS; ++k) {
-                        const int base = n_begin + (k0 + k) * n_stride;
-                        load_any(n_grad + base + mine, 4, g[k]);
-                        load_any(n_err + base + mine, 4, e[k]);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < LOADS; ++k) {
-                        const int base = n_begin + (k0 + k) * n_stride;
-                        const int nvalid = min(max(n.P.t.len - base - mine, 0), 4);
-                        load_any(n_grad + base + mine, nvalid, g[k]);
-                        load_any(n_err + base + mine, nvalid, e[k]);
-                    }
-                }
-            }
-            asm volatile("" : : : "memory");    // the loads are on their way before the arithmetic
-#pragma unroll
-            for (int k = k0; k < k0 + LOADS; ++k) {
-                float4& spot = held[k * kParkedThreads + threadIdx.x];
-                const int base = q_begin + k * q_stride + wave * 256;
-                if (item != kNoUnit && (q_whole || base < q.P.t.len)) {
-                    parked_chunk<ROUNDING, false>(A, c, q, sc, base, spot, q_err, q_codes);
-                }
-                spot = make_float4(p[0][k][0], p[0][k][1], p[0][k][2], p[0][k][3]);
+            float g[LOADS][4], e[LOADS][4], mv[LOADS][4], vv[LOADS][4];
+            // the younger units move up, the oldest of them to LDS
+            auto move_up = [&](int k) {
+                held[k * kParkedThreads + threadIdx.x] = make_float4(p[0][k][0], p[0][k][1], p[0][k][2], p[0][k][3]);
 #pragma unroll
                 for (int h = 0; h + 1 < HELD; ++h)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) p[h][k][j] = p[h + 1][k][j];
                 asm volatile("" : : : "memory");
                 __builtin_amdgcn_sched_barrier(0);
+            };
+            auto keep = [&](int k, int j, float v) {
+                p[HELD - 1][k0 + k][j] = v;
+                asm volatile("" : "+v"(p[HELD - 1][k0 + k][j]) : : "memory");
+            };
+            if (straight) {
+                const uint32_t at = threadIdx.x * 16u;
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k) {
+                    const int base = n_begin + (k0 + k) * n_stride;
+                    load_buffer(n_grad_buf, at, base * 4, g[k]);
+                    if constexpr (W) {
+                        load_buffer(n_mw_buf, at, base * 4, mv[k]);
+                        load_buffer(n_vw_buf, at, base * 4, vv[k]);
+                    }
+                    load_buffer(n_err_buf, at, base * 4, e[k]);
+                }
+                asm volatile("" : : : "memory");    // the loads are on their way before the arithmetic
+#pragma unroll
+                for (int k = k0; k < k0 + LOADS; ++k) {
+                    parked_chunk<ROUNDING, true>(A, c, q, sc, q_begin + k * q_stride + wave * 256, held[k * kParkedThreads + threadIdx.x],
+                                                 q_err, q_codes);
+                    move_up(k);
+                }
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if constexpr (W) keep(k, j, adam_step(S, g[k][j], mv[k][j], vv[k][j]) + e[k][j]);
+                        else keep(k, j, g[k][j] + e[k][j]);
+                    }
+                    if constexpr (W) {
+                        const int base = n_begin + (k0 + k) * n_stride;
+                        store_out(n_mw_out, at, base * 4, mv[k]);
+                        store_out(n_vw_out, at, base * 4, vv[k]);
+                    }
+                }
+                return;
             }
             if (next != kNoUnit) {
 #pragma unroll
-                for (int k = 0; k < LOADS; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        p[HELD - 1][k0 + k][j] = g[k][j] + e[k][j];
-                        asm volatile("" : "+v"(p[HELD - 1][k0 + k][j]) : : "memory");
+                for (int k = 0; k < LOADS; ++k) {
+                    const int base = n_begin + (k0 + k) * n_stride;
+                    const int nvalid = n_whole ? 4 : min(max(n.P.t.len - base - mine, 0), 4);
+                    load_any(n_grad + base + mine, nvalid, g[k]);
+                    if constexpr (W) {
+                        load_any(n_mw + base + mine, nvalid, mv[k]);
+                        load_any(n_vw + base + mine, nvalid, vv[k]);
                     }
+                    load_any(n_err + base + mine, nvalid, e[k]);
+                }
+            }
+            asm volatile("" : : : "memory");
+#pragma unroll
+            for (int k = k0; k < k0 + LOADS; ++k) {
+                const int base = q_begin + k * q_stride + wave * 256;
+                if (item != kNoUnit && (q_whole || base < q.P.t.len))
+                    parked_chunk<ROUNDING, false>(A, c, q, sc, base, held[k * kParkedThreads + threadIdx.x], q_err, q_codes);
+                move_up(k);
+            }
+            if (next != kNoUnit) {
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k) {
+                    if constexpr (W) {
+                        const int base = n_begin + (k0 + k) * n_stride;
+                        const int nvalid = n_whole ? 4 : min(max(n.P.t.len - base - mine, 0), 4);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float u = again ? adam_quotient(S, mv[k][j], vv[k][j]) : adam_step(S, g[k][j], mv[k][j], vv[k][j]);
+                            keep(k, j, j < nvalid ? u + e[k][j] : 0.0f);
+                        }
+                        if (!again) {
+                            store_shifted(n_mw + base + mine, nvalid, mv[k]);
+                            store_shifted(n_vw + base + mine, nvalid, vv[k]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) keep(k, j, g[k][j] + e[k][j]);
+                    }
+                }
             }
         });
         if (item != kNoUnit) {
@@ -2728,37 +2761,51 @@ static bool codes_overlap(const Launch& L, const WorkerPtrs& W, int first_worker
 }
 
 // Two code buffers that overlap are left to the main pass, which gives them an order.
-bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call)
+bool use_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool call, bool variant_w)
 {
-    return L.parked.num_units > 0 && worth_parking(L.parked.num_elems, L.parked.num_units, L.scaled.num_elems, num, S.rounding == 1, call,
-                                                   L.parked.longest)
-        && !codes_overlap(L, W, first_worker, num);
+    const Parked& P = L.parked;
+    const bool worth = variant_w ? worth_parking_w(P.num_elems, P.num_units, L.scaled.num_elems, num, S.rounding == 1, P.longest)
+                                 : worth_parking(P.num_elems, P.num_units, L.scaled.num_elems, num, S.rounding == 1, call, P.longest);
+    return P.num_units > 0 && worth && !codes_overlap(L, W, first_worker, num);
 }
 
-hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num)
+template <int ROUNDING, int HELD, int LOADS, bool W>
+static void launch_parked(const ParkedArgs& A, hipStream_t stream)
+{
+    const unsigned lds = kParkedThreads * kParkedChunks * sizeof(float4);
+    hipLaunchKernelGGL((k_parked<ROUNDING, HELD, LOADS, W>), dim3(kParkedGroups), dim3(kParkedThreads), lds, stream, A);
+}
+
+template <int ROUNDING>
+static void launch_parked(const ParkedArgs& A, bool three, bool variant_w, hipStream_t stream)
+{
+    if (variant_w) {
+        if (three) launch_parked<ROUNDING, 2, 1, true>(A, stream);
+        else launch_parked<ROUNDING, 1, 2, true>(A, stream);
+    } else {
+        if (three) launch_parked<ROUNDING, 2, 2, false>(A, stream);
+        else launch_parked<ROUNDING, 1, 4, false>(A, stream);
+    }
+}
+
+hipError_t launch_parked(const Launch& L, const StepScalars& S, const WorkerPtrs& W, int first_worker, int num, bool variant_w)
 {
     if (L.parked.num_units == 0) return hipSuccess;
     ParkedArgs A;
     A.units = L.parked.units; A.layers = L.parked.layers; A.S = S;
     for (int i = 0; i < QADAM_MAX_WORKERS; ++i) {
         A.grad[i] = W.grad[i]; A.err[i] = W.err[i]; A.codes[i] = W.codes[i]; A.scales[i] = W.scales[i];
+        A.mw[i] = W.mw[i]; A.vw[i] = W.vw[i];
     }
-    A.row = L.max_row; A.maxima = L.tile_max + L.rest.shape.num_tiles;
+    A.row = L.max_row; A.maxima = L.tile_max + rest_maxima(L.rest);
     A.meeting = L.parked.meeting; A.aside = L.parked.aside; A.meeting_words = L.parked.meeting_words;
     A.inv_scales = L.inv_scales; A.err_bound = L.err_bound; A.bound_factor = residual_bound_factor(S);
     A.num_segments = L.num_segments; A.first_worker = first_worker; A.polls = L.parked.polls;
     A.status = L.status;
     A.num_units = (uint32_t)L.parked.num_units; A.total = A.num_units * (uint32_t)num;
-    const unsigned lds = kParkedThreads * kParkedChunks * sizeof(float4);
-    const dim3 grid(kParkedGroups), block(kParkedThreads);
     const bool three = L.parked.longest > kParkedLongest;
-    if (S.rounding == 0) {
-        if (three) hipLaunchKernelGGL((k_parked<0, 2, 2>), grid, block, lds, L.stream, A);
-        else hipLaunchKernelGGL((k_parked<0, 1, 4>), grid, block, lds, L.stream, A);
-    } else {
-        if (three) hipLaunchKernelGGL((k_parked<1, 2, 2>), grid, block, lds, L.stream, A);
-        else hipLaunchKernelGGL((k_parked<1, 1, 4>), grid, block, lds, L.stream, A);
-    }
+    if (S.rounding == 0) launch_parked<0>(A, three, variant_w, L.stream);
+    else launch_parked<1>(A, three, variant_w, L.stream);
     return hipGetLastError();
 }
 

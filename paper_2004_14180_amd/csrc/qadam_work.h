@@ -289,6 +289,22 @@ constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num,
     return work >= least * M && 4 * elems >= all;
 }
 
+// The same for variant W, a worker's separate call being a step of one.  It saves 8 of 36 bytes per element, so parking pays later.  us
+// per step, two passes / parked.  Layers of 36 units: one worker of 16 M (2^20) elements 147 / 148, 24 M 213 / 219, 47 M 419 / 405, 94 M
+// 853 / 812; 2 of 12 M 181 / 181; 4 of 8 M 223 / 225, 12 M 330 / 323, 24 M 654 / 602; 8 of 4 M 213 / 216, 8 M 421 / 399; 16 of 2 M 247 / 231;
+// off the grid 4 of 12 M 373 / 360, 8 of 8 M 480 / 447; one worker's call of 24 M 148 / 156, 47 M 292 / 277.  Layers that need a third unit: 4
+// workers, one of 8 M 228 / 235, 12 M 334 / 327, 16 M 428 / 432, two of 5 M 265 / 269, five 651 / 600, three of 8 M 668 / 625, of 16 M 1383 /
+// 1205; 8, four of 16 M 3451 / 3000; 5 of 7.3 M 253 / 270.  Stochastic: 3 of 17 M 386 / 398, 4 of 12 M 341 / 342, 24 M 676 / 607.  Units mostly
+// empty, 4000 layers of 5000 and 4 workers 629 / 660.  Beside a longer layer, 4 workers: 9 M beside 23 M 971 / 980, 20 M beside 31 M 1479 /
+// 1449.
+constexpr bool worth_parking_w(int64_t elems, int64_t units, int64_t all, int num, bool stochastic, int64_t longest)
+{
+    const int64_t work = elems * num, M = 1 << 20;
+    const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
+    const int64_t least = longest > kParkedLongest ? 80 : stochastic ? 72 : num >= 4 ? 40 : 48;
+    return filled && work >= least * M && 3 * elems >= all;
+}
+
 // The meeting place of a layer's workgroups: a word that counts arrivals and departures, and copies of the published scale
 // for up to eight of them each to poll, every one in a line of its own.  Words.
 constexpr int kMeetingLine = 32;

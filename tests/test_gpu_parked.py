@@ -195,3 +195,44 @@ def test_lists_whose_workgroups_hold_three_units(polls, sizes, cfgkw):
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
     assert a.q.get_status() == 0
     assert a.q.profile_work()[0] == 0       # every layer was parked
+
+
+@pytest.mark.parametrize("polls", [-1, 0, 3])
+@pytest.mark.parametrize("sizes,workers", [(_sizes(9 * M // 2), N),                             # 72 M, units of every filling
+                                           ([256 * UNIT + 1, 1001, 130 * UNIT - 5, 2047, 300 * UNIT], 8),   # three units
+                                           ([1001, 1088 * UNIT], 8)])                           # the longest, off the grid
+@pytest.mark.parametrize("cfgkw", [dict(k_g=2, k_x=6), dict(k_g=0, k_x=14, weight_ef=0, adam_flavor=1),
+                                   dict(k_g=4, k_x=6, rounding=1, seed=3)])
+def test_variant_w_gives_the_bits_of_the_separate_calls(polls, sizes, workers, cfgkw):
+    """Units put aside find their local moments advanced when they are loaded again."""
+    a, b = (_AnyState(sizes, True, workers=workers, **cfgkw) for _ in range(2))
+    a.q.set_scale_polls(polls)
+    a.q.profile_enable()
+    for t in (1, 2):
+        a.step(t, True, True)
+        b.step(t, True, False)
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
+    assert a.q.get_status() == 0
+    assert a.q.profile_work()[0] == 0
+
+
+@pytest.mark.parametrize("sizes", [[36 * UNIT - 7] * 85 + [0, 3], [2000 * UNIT, 1000 * UNIT, 300 * UNIT, 5]])
+def test_variant_w_one_workers_call(sizes):
+    """One worker's call that parks its layers, the second list's beside a longer one, against plain tensor operations: moments and
+    scales bit for bit, residuals within half the widest gap of the grid."""
+    a, b = _AnyState(sizes, True, workers=1), _AnyState(sizes, True, workers=1)
+    for t in (1, 2):
+        a.step(t, True, False)
+        g, m, v = b.g[0], b.m[0], b.v[0]
+        f = lambda c: torch.tensor(c, dtype=torch.float32, device="cuda")  # noqa: E731
+        b1, b2, one = f(0.9), f(0.999), f(1.0)
+        v.copy_((b2 * v) + ((one - b2) * (g * g)))
+        m.copy_((b1 * m) + ((one - b1) * g))
+        assert torch.equal(_bits(a.v[0]), _bits(v)) and torch.equal(_bits(a.m[0]), _bits(m)), t
+        p = (f(1e-3) * m) / torch.sqrt(v + f(b.cfg.eps)) + b.e[0]
+        at = 0
+        for l, n in enumerate(sizes):
+            assert a.scales[0][l] == (p[at:at + n].abs().max() if n else 0.0), (t, l)
+            at += n
+        b.e[0].copy_(a.e[0])        # every next step begins from the same state
+        assert (a.e[0].abs() <= 0.2501 * a.scales[0].repeat_interleave(torch.tensor(sizes, device="cuda"))).all()

@@ -276,6 +276,22 @@ def test_lines_of_parking_for_a_separate_call_and_stochastic_rounding(tmp_path):
     CHECK(worth_parking(12 * M, 768, 24 * M, 8, true) && !worth_parking(12 * M - 1, 768, 24 * M, 8, true), "beside longer layers");""")
 
 
+def test_lines_of_parking_in_variant_w(tmp_path):
+    _run(tmp_path, """
+    const int64_t M = 1 << 20, unit = kParkedChunk * kParkedChunks;
+    auto parks = [](int64_t elems, int64_t all, int num, bool stochastic, int64_t longest) {
+        return worth_parking_w(elems, (elems + unit - 1) / unit, all, num, stochastic, longest);
+    };
+    CHECK(parks(48 * M, 48 * M, 1, false, M) && !parks(48 * M - 1, 48 * M, 1, false, M), "one worker");
+    CHECK(parks(10 * M, 30 * M, 4, false, M) && !parks(10 * M - 1, 10 * M, 4, false, M) && !parks(10 * M, 30 * M + 1, 4, false, M), "four workers");
+    CHECK(parks(18 * M, 18 * M, 4, true, M) && !parks(18 * M - 1, 18 * M, 4, true, M), "stochastic");
+    CHECK(parks(20 * M, 20 * M, 4, false, kParkedLongest + 1) && !parks(20 * M - 1, 20 * M, 4, false, kParkedLongest + 1), "three units");
+    CHECK(!worth_parking_w(20 * M, 4000, 20 * M, 4, false, 5000), "mostly empty units");
+    for (int num = 1; num <= 32; ++num)
+        for (int64_t units = 1; units <= 2 * kParkedGroups; ++units)
+            CHECK(!worth_parking_w(units * unit, units, units * unit, num, false, M) || units * num >= kParkedGroups, "a unit for every workgroup");""")
+
+
 def _c_list(sizes):
     return "{" + ", ".join("%d" % n for n in sizes) + "}"
 
