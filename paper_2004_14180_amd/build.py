@@ -1,4 +1,4 @@
-"""Compile the gfx950 shared library (``libqadam_hip.so``) in-tree with hipcc."""
+"""Compile the gfx950 shared library (``libqadam_hip.so``) and the binding's native part (``_args.so``) in-tree."""
 from __future__ import annotations
 
 import os
@@ -87,6 +87,28 @@ def device_resource_usage(source: str = "qadam_kernels.hip") -> dict:
     return out
 
 
+ARGS_SRC = os.path.join(CSRC, "qadam_args.cpp")
+ARGS = os.path.join(HERE, "_args.so")
+
+
+def build_args(verbose: bool = True) -> str:
+    """The binding's native part: checks of torch tensors and the calls with their addresses."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"]]
+    lib = os.path.join(base, "lib")
+    tmp = ARGS + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *["-isystem" + i for i in inc], "-o", tmp, ARGS_SRC, "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, ARGS)
+    return ARGS
+
+
 def build_library(verbose: bool = True) -> str:
     srcs = []
     for s in SOURCES:
@@ -98,6 +120,7 @@ def build_library(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
+    build_args(verbose)
     return LIB
 
 

@@ -63,3 +63,45 @@ def test_the_current_stream_is_used():
     with torch.cuda.stream(s):
         assert _stream(None) == s.cuda_stream
     assert _stream(s) == s.cuda_stream
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("form", ["parameter", "subclass", "tuple", "generator-made list", "longer", "numpy numbers", "a stream"])
+def test_other_forms_give_the_common_forms_result(form):
+    """What the native calls do not take goes through the checks in Python, with the same outcome."""
+    q = QAdam(configs()[0], np.array([0, 1000, P]), N)
+
+    def step(put):
+        torch.manual_seed(0)
+        f = lambda n: torch.randn(n, device="cuda")  # noqa: E731
+        g, e = [f(P) for _ in range(N)], [torch.zeros(P, device="cuda") for _ in range(N)]
+        c = [torch.zeros(q.grad_code_bytes() // 4, dtype=torch.int32, device="cuda") for _ in range(N)]
+        s = [torch.zeros(2, device="cuda") for _ in range(N)]
+        x, m, v, w = f(P), torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
+        wc, lr, stream = torch.zeros(P, dtype=torch.int8, device="cuda"), 1e-3, None
+        if put == "parameter":
+            g = [torch.nn.Parameter(t) for t in g]
+        elif put == "subclass":
+            g[1] = g[1].as_subclass(_Sub)
+        elif put == "tuple":
+            g, s = tuple(g), tuple(s)
+        elif put == "generator-made list":
+            g = list(t for t in g)
+        elif put == "longer":
+            g[0] = torch.cat([g[0], f(5)])
+        elif put == "numpy numbers":
+            lr = np.float64(lr)
+        elif put == "a stream":
+            torch.cuda.synchronize()
+            stream = torch.cuda.Stream()
+        q.step_fused(1, lr, 0.999, g, e, c, s, x, m, v, w, wc, stream=stream)
+        torch.cuda.synchronize()
+        return e + c + list(s) + [x, m, v, w, wc]
+
+    assert all(torch.equal(a, b) for a, b in zip(step(form), step(None)))
+    q.close()
+    with pytest.raises(Exception):
+        step(None)                      # a closed handle stays refused

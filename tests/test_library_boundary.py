@@ -95,3 +95,24 @@ def test_kernels_keep_their_arguments_out_of_scratch_and_the_main_pass_its_occup
     main = [u for name, u in usage.items() if "k_fusedILi0ELi4ELb0" in name]
     assert len(main) == 1
     assert main[0]["scratch_bytes"] == 0 and main[0]["vgprs"] <= 96 and main[0]["waves_per_simd"] >= 5, main[0]
+
+
+def test_native_calls_leave_other_forms_to_the_python_checks(lib):
+    """None, and nothing called: the entry points of this plan are address 0."""
+    import torch
+    from paper_2004_14180_amd import binding
+    native = binding._native
+    plan = native.plan(0, 2, 10, 1, 16, 10, 1, 0, 0, 0, 0, 0)
+    t = torch.zeros(16)
+    two = [t, t]
+    for p in (None, plan):
+        assert native.worker_quantize(p, -1, 0, 0, 1, t, t, t, t) is None
+        assert native.server_step(p, -1, 0, 1, 1e-3, 0.9, two, two, t, t, t) is None
+        assert native.weight_quantize(p, -1, 0, 1, t, t, t) is None
+        assert native.step_fused(p, -1, 0, 1, 1e-3, 0.9, two, two, two, two, t, t, t, t, t) is None
+        assert native.step_fused_w(p, -1, 0, 1, 1e-3, 0.9, two, two, two, two, two, two, t, t, t) is None
+        assert native.step_fused(p, 0, 0, 2**70, "a", None, [t], two, iter(two), None, t, t, t, None, t) is None
+    assert native.quantize_segment(0, -1, 0, 2, 10, t, t, t, t) is None
+    for bad in (lambda: native.step_fused(plan), lambda: native.plan(1, 2), lambda: native.plan(0, 33, *[0] * 10)):
+        with pytest.raises(TypeError):
+            bad()
