@@ -858,24 +858,45 @@ __device__ __forceinline__ uint32_t fold_maxima(const uint32_t* __restrict__ par
     return local;
 }
 
-// The same, folded by one wavefront; `first`: the wavefront writes it out if its tile `ti` is the layer's first.
-__device__ __forceinline__ Scale folded_scale(const Fold& F, int row, const Tile& t, int ti, bool first, float* scales)
+// The same, folded by one wavefront from the maxima t0 .. t1 of a row.  In two steps, so that loads for several workers can be under
+// way together: each lane's share, then the scale; `first`: the wavefront writes it out if its tile `ti` is the layer's first.
+struct FoldRange {
+    int t0, t1;
+};
+
+__device__ __forceinline__ FoldRange fold_range(const Fold& F, const Tile& t)
 {
-    const int t0 = F.seg_tile_begin ? F.seg_tile_begin[t.seg] * F.per_tile : 0;
-    const int t1 = F.seg_tile_begin ? F.seg_tile_begin[t.seg + 1] * F.per_tile : F.row;
+    FoldRange r;
+    r.t0 = F.seg_tile_begin ? F.seg_tile_begin[t.seg] * F.per_tile : 0;
+    r.t1 = F.seg_tile_begin ? F.seg_tile_begin[t.seg + 1] * F.per_tile : F.row;
+    return r;
+}
+
+__device__ __forceinline__ uint32_t fold_share(const Fold& F, int row, const FoldRange& r)
+{
     const uint32_t* part = F.tile_max + (size_t)row * F.row;
     // Four loads in flight where a lane has several (one after the other / eight / four: one worker's call of 512 tiles
     // 13.5 / 12.3 / 12.4 us, 768 tiles 17.7 / 15.8 / 15.5; step of 4 workers of 16 tiles, one load each, 12.8 / 13.1 / 12.7).
-    uint32_t local = 0;
-    if (t1 - t0 > 64) local = fold_maxima<64, 4>(part, t0, t1, (int)threadIdx.x);
-    else if (t0 + (int)threadIdx.x < t1) local = part[t0 + (int)threadIdx.x];
-    const Scale r = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(local)));
-    if (first && ti * F.per_tile == t0 && threadIdx.x == 0) {
+    if (r.t1 - r.t0 > 64) return fold_maxima<64, 4>(part, r.t0, r.t1, (int)threadIdx.x);
+    return r.t0 + (int)threadIdx.x < r.t1 ? part[r.t0 + (int)threadIdx.x] : 0u;
+}
+
+__device__ __forceinline__ Scale folded_scale(const Fold& F, int row, const Tile& t, int ti, const FoldRange& range, uint32_t share,
+                                              bool first, float* scales)
+{
+    const Scale r = make_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(share)));
+    if (first && ti * F.per_tile == range.t0 && threadIdx.x == 0) {
         scales[t.seg] = r.s;
         F.inv_scales[(size_t)row * F.num_segments + t.seg] = r.inv;
         F.err_bound[(size_t)row * F.num_segments + t.seg] = residual_bound(r.s, F.bound_factor);
     }
     return r;
+}
+
+__device__ __forceinline__ Scale folded_scale(const Fold& F, int row, const Tile& t, int ti, bool first, float* scales)
+{
+    const FoldRange range = fold_range(F, t);
+    return folded_scale(F, row, t, ti, range, fold_share(F, row, range), first, scales);
 }
 
 __device__ __forceinline__ void check_scale(float s, uint32_t* status)
@@ -2176,6 +2197,8 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
     const int N = S.num_workers;
     const Shift sf = make_shift(t);
     const int part_end = min(t.len, part_begin + part_len);
+    FoldRange range;
+    if constexpr (FOLD) range = fold_range(A.fold, t);
     for (int base = part_begin; base < part_end; base += WAVE_ELEMS) {
         const int off = base + lane * V;
         const int nvalid = FULL ? V : min(max(t.len - off, 0), V);
@@ -2205,13 +2228,21 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
                     ld<V, SH>(A.err[i0 + u], gi, nvalid, sf, e[u]);
                 }
             }
+            uint32_t share[U];
+            if constexpr (FOLD) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (U > 1 && i0 + u >= N) break;
+                    share[u] = fold_share(A.fold, i0 + u, range);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = i0 + u;
                 if (U > 1 && i >= N) break;
                 Scale sc;
                 if constexpr (FOLD) {
-                    sc = folded_scale(A.fold, i, t, ti, base == 0, A.scales[i]);
+                    sc = folded_scale(A.fold, i, t, ti, range, share[u], base == 0, A.scales[i]);
                     if (base == 0) check_scale(sc.s, A.status);
                 } else {
                     sc = stored_scale(A.fold, i, t, A.scales[i]);
@@ -2237,10 +2268,18 @@ __device__ __forceinline__ void fused_part(const FusedArgs& A, const Tile& t, in
         for (int i = 0; i < N; ++i) check_scale(A.scales[i][t.seg], A.status);
 }
 
+// U: workers whose loads are in flight together.  4: the scales are there.  Else the pass folds them itself, for all U workers' layers at
+// once, in whole pieces and in the ends of layers: few wavefronts, each a chain of loads, so that what is under way together decides.
+// Beyond about 256 tiles, which few workers alone reach, the registers of five cost more.  us per step, one after the other / two / five
+// together: ragged lists of 51 k elements, 4 workers 15.1 / 14.8 / 14.6, 8 21.1 / 19.3 / 19.1, 16 33.7 / 29.8 / 28.4; one layer of 16 tiles, 2
+// workers 10.9 / 10.7 / 10.9, 4 12.7 / 12.2 / 12.1, 8 16.8 / 15.5 / 15.2, 16 26.2 / 22.4 / 21.5; of 128, 3 13.0 / 13.1 / 13.0, 5 15.7 / 15.6 /
+// 15.4; of 256, 2 16.3 / 16.8 / 19.8, 4 22.4 / 20.3 / 25.1; variant W, ragged, 8 workers 20.8 / 18.8 / 18.3.
+constexpr int kFoldFew = 2, kFoldMany = 5;
+
 template <int ROUNDING, int U, bool W>
 __global__ void __launch_bounds__(64) k_fused(FusedArgs A)
 {
-    constexpr bool FOLD = U == 1;
+    constexpr bool FOLD = U != 4;
     const uint32_t item = wave_item(A.items);
     if (item >= A.items.count) return;
     const int ti = (int)(item / A.items.cut.parts);
@@ -2251,10 +2290,10 @@ __global__ void __launch_bounds__(64) k_fused(FusedArgs A)
     const bool full = part_begin + part_len <= t.len;
     if (t.flags & kTileUnaligned) {
         if (full) fused_part<ROUNDING, 4, W, true, FOLD, U, true>(A, t, ti, part_begin, part_len);
-        else fused_part<ROUNDING, 4, W, true, FOLD, 1, false>(A, t, ti, part_begin, part_len);
+        else fused_part<ROUNDING, 4, W, true, FOLD, FOLD ? U : 1, false>(A, t, ti, part_begin, part_len);
     } else {
         if (full) fused_part<ROUNDING, 4, W, false, FOLD, U, true>(A, t, ti, part_begin, part_len);
-        else fused_part<ROUNDING, 4, W, false, FOLD, 1, false>(A, t, ti, part_begin, part_len);
+        else fused_part<ROUNDING, 4, W, false, FOLD, FOLD ? U : 1, false>(A, t, ti, part_begin, part_len);
     }
 }
 
@@ -3045,11 +3084,13 @@ static hipError_t launch_fused_any(const Launch& L, const StepScalars& S, const 
     A.items = wave_items(L.scaled.shape, 256);
     const dim3 grid = wave_grid(A.items), block(64);
     const unsigned lds = variant_w ? 0u : kMainPassLds;
-    // U = 4, or the variant that folds the scales, one worker at a time
-#define QADAM_LAUNCH_FUSED(R, WV)                                                                                  \
-    do {                                                                                                           \
-        if (A.fold.tile_max) hipLaunchKernelGGL((k_fused<R, 1, WV>), grid, block, 0, L.stream, A);                 \
-        else hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, lds, L.stream, A);                              \
+    const bool fold = A.fold.tile_max != nullptr;
+#define QADAM_LAUNCH_FUSED(R, WV)                                                                                   \
+    do {                                                                                                            \
+        if (!fold) hipLaunchKernelGGL((k_fused<R, 4, WV>), grid, block, lds, L.stream, A);                          \
+        else if (S.num_workers == 1) hipLaunchKernelGGL((k_fused<R, 1, WV>), grid, block, 0, L.stream, A);          \
+        else if (S.num_workers <= 4) hipLaunchKernelGGL((k_fused<R, kFoldFew, WV>), grid, block, 0, L.stream, A);   \
+        else hipLaunchKernelGGL((k_fused<R, kFoldMany, WV>), grid, block, 0, L.stream, A);                          \
     } while (0)
     if (S.rounding == 0) {
         if (variant_w) QADAM_LAUNCH_FUSED(0, true); else QADAM_LAUNCH_FUSED(0, false);
