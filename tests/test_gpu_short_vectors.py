@@ -43,6 +43,19 @@ def test_each_side_of_the_longest_folded_layer(N, longest, others, fused):
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
 
 
+@pytest.mark.parametrize("N", [3, 5, 6])
+@pytest.mark.parametrize("w", [False, True])
+def test_folded_workers_beyond_whole_groups(N, w):
+    """Two or five workers are folded together: the last group is not whole.  Layers of more than 64 maxima and of one, and the ends of
+    layers, which are folded the same way."""
+    sizes = [66 * T + 9, 1, 255, T, 700]
+    if w:
+        _worker_moments(N, 70, sizes)
+    else:
+        rep, st = _custom(sizes, N, 2, seed=N, trust=2)
+        assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+
+
 @pytest.mark.parametrize("N,tiles", [(2, 128), (8, 129), (4, 255), (4, 257)])
 def test_worker_moments_each_side_of_the_fold(N, tiles):
     """Variant W leaves four maxima per tile: ends of a layer in each quarter of its last tile."""
