@@ -236,3 +236,18 @@ def test_variant_w_one_workers_call(sizes):
             at += n
         b.e[0].copy_(a.e[0])        # every next step begins from the same state
         assert (a.e[0].abs() <= 0.2501 * a.scales[0].repeat_interleave(torch.tensor(sizes, device="cuda"))).all()
+
+
+@pytest.mark.parametrize("sizes", [_sizes(40 * M // N), [1001, 300 * UNIT, 20 * UNIT]])    # two units, three
+def test_captured_step_of_variant_w_is_the_eager_one(sizes):
+    w = N if sizes[0] == 1 else 2 * N
+    a, b = (_AnyState(sizes, True, workers=w) for _ in range(2))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        a.step(1, True, True)
+    for t in (1, 2, 3):
+        graph.replay()
+        b.step(1, True, True)
+        torch.cuda.synchronize()
+        assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
