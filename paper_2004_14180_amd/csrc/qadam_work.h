@@ -275,9 +275,10 @@ constexpr int64_t kParkedLongestOfThree = (int64_t)1088 * kParkedChunk * kParked
 // 162, off the grid 168 / 178, of 16 M 306 / 286 and 380 / 317.  Beside longer layers, 8 workers, 6 M beside 12 M 612 / 627, off the
 // grid 684 / 737, 12 M beside 12 M 812 / 783 and 916 / 918, 4 workers 465 / 476 and 522 / 567.
 // Layers that need a third unit, whose start takes longer (longest: elements of the longest): step of one worker, one layer of 8 M 82.0 /
-// 83.8, two 160 / 150, one of 16 M 160 / 149; of 4, one of 8 M 158 / 151, 12 M 236 / 209, 16 M 308 / 268; one worker's call, two of 8 M
-// 56.5 / 55.6, three 82 / 78, one of 16 M 56.9 / 55.5; stochastic, 5 of 8 M, its call 136 / 133, step of 4 workers 753 / 630, 3 of 16 M
-// 899 / 798.
+// 83.8, two 160 / 150, one of 16 M 160 / 149; of 4, one of 8 M 158 / 151, 12 M 236 / 209, 16 M 308 / 268; stochastic, 5 of 8 M, its
+// call 136 / 133, step of 4 workers 753 / 630, 3 of 16 M 899 / 798.  One worker's call, alone and then each of four at once on
+// streams of their own, whose launches have few workgroups for many units: two layers of 8 M 57 / 59 and 55 / 69, one of 16 M 56 / 58 and
+// 56 / 71; two of 12 M 82 / 76 and 82 / 88, two of 16 M 108 / 99 and 106 / 119, three 157 / 137 and 158 / 169, five 257 / 208 and 259 / 249.
 constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num, bool stochastic, bool call = false,
                              int64_t longest = 0)
 {
@@ -285,7 +286,8 @@ constexpr bool worth_parking(int64_t elems, int64_t units, int64_t all, int num,
     const bool filled = units * kParkedChunk * kParkedChunks <= 2 * elems;
     const bool full_turns = 16 * units >= 15 * turns * kParkedGroups;
     const int64_t least = stochastic && elems < all ? 96 : !filled ? 72 : stochastic ? (call || num == 2 ? 64 : 48)
-                        : 2 * elems < all ? 48 : num > 1 ? 24 : !call ? (longest > kParkedLongest ? 12 : 8) : full_turns ? 15 : 24;
+                        : 2 * elems < all ? 48 : num > 1 ? 24 : !call ? (longest > kParkedLongest ? 12 : 8)
+                        : full_turns && longest <= kParkedLongest ? 15 : 24;
     return work >= least * M && 4 * elems >= all;
 }
 

@@ -268,9 +268,13 @@ def test_where_the_whole_step_goes_by_worker(tmp_path):
 def test_lines_of_parking_for_a_separate_call_and_stochastic_rounding(tmp_path):
     _run(tmp_path, """
     const int64_t M = 1 << 20, unit = kParkedChunk * kParkedChunks;
-    auto call = [&](int64_t elems, bool stochastic) { return worth_parking(elems, (elems + unit - 1) / unit, elems, 1, stochastic, true); };
+    auto call = [&](int64_t elems, bool stochastic, int64_t longest = 1 << 20) {
+        return worth_parking(elems, (elems + unit - 1) / unit, elems, 1, stochastic, true, longest);
+    };
     CHECK(!call(8 * M, false) && !call(12 * M, false) && !call(20 * M, false) && !call(22 * M, false), "turns partly empty, or one");
     CHECK(call(15 * M, false) && call(16 * M, false) && !call(16 * M + 1, false) && call(24 * M, false) && call(25 * M, false), "full turns, many");
+    CHECK(call(16 * M, false, kParkedLongest) && !call(16 * M, false, kParkedLongest + 1) && !call(24 * M - 1, false, 16 * M) &&
+          call(24 * M, false, 16 * M), "a call whose layers need a third unit");
     CHECK(call(64 * M, true) && !call(64 * M - 1, true), "stochastic");
     CHECK(worth_parking(32 * M, 2048, 32 * M, 2, true) && !worth_parking(32 * M - 1, 2048, 32 * M, 2, true), "two workers");
     CHECK(worth_parking(12 * M, 768, 24 * M, 8, true) && !worth_parking(12 * M - 1, 768, 24 * M, 8, true), "beside longer layers");""")
