@@ -7,7 +7,9 @@ CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -74,12 +76,33 @@ class QAdamConfig:
 
 _lib = None
 _torch = None             # set with _lib
-_native = None            # set with _lib: the calls with tensors of the common form (csrc/qadam_args.cpp)
+_native = None            # set with _lib: the calls with tensors of the common form (csrc/qadam_args.cpp), or _Unavailable
 _segment = 0              # ... the address of qadam_quantize_segment_noalloc
 
 
 def library_path() -> str:
     return _LIB_PATH
+
+
+class _Unavailable:
+    """In place of the native calls where they were not built for this Python and torch: takes no call, so that all go through the
+    checks in Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(torch):
+    try:
+        native = importlib.import_module("._args", __package__)
+        built_for = getattr(native, "torch_version", None)
+        if built_for != str(torch.__version__):
+            raise ImportError("built for torch %s, this is %s" % (built_for, torch.__version__))
+        return native
+    except ImportError as e:
+        warnings.warn("the binding's native part is not used (%s): buffers are checked in Python, which costs a call of a short vector up "
+                      "to 13 us; build it with `python paper_2004_14180_amd/build.py`" % e, stacklevel=3)
+        return _Unavailable()
 
 
 def load_library():
@@ -95,7 +118,6 @@ def load_library():
     # process must end up with ONE runtime shared by torch (device memory, streams) and this library.
     # Loaded the other way round, the library's HIP calls fail with "no ROCm-capable device".
     import torch
-    from . import _args         # built with the library; missing like it, it raises
     lib = C.CDLL(_LIB_PATH)
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
     lib.qadam_init.argtypes = [C.POINTER(vp), C.POINTER(_Config), C.POINTER(i64), i32, i32]
@@ -127,7 +149,7 @@ def load_library():
     lib.qadam_profile_work.argtypes = [vp, C.POINTER(_ProfileWork)]
     lib.qadam_quantize_segment_noalloc.argtypes = [i32, i64, vp, vp, vp, vp, vp]
     lib.qadam_arena_layout.argtypes = [vp, C.c_size_t, i32, C.POINTER(_Arena)]
-    _native, _segment = _args, _address(lib.qadam_quantize_segment_noalloc)
+    _native, _segment = _load_native(torch), _address(lib.qadam_quantize_segment_noalloc)
     _lib, _torch = lib, torch
     return lib
 

@@ -257,4 +257,10 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_args", "Calls of the library wit
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__args(void) { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__args(void)
+{
+    PyObject* m = PyModule_Create(&kModule);
+    // tensors are read through inlined code of this version
+    if (m && PyModule_AddStringConstant(m, "torch_version", QADAM_TORCH_VERSION) < 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2004_14180_amd import QAdam
+from paper_2004_14180_amd import QAdam, binding
 from paper_2004_14180_amd.binding import _stream
 from parity_util import configs
 
@@ -69,8 +69,8 @@ class _Sub(torch.Tensor):
     pass
 
 
-@pytest.mark.parametrize("form", ["parameter", "subclass", "tuple", "generator-made list", "longer", "numpy numbers", "a stream"])
-def test_other_forms_give_the_common_forms_result(form):
+@pytest.mark.parametrize("form", ["parameter", "subclass", "tuple", "generator-made list", "longer", "numpy numbers", "a stream", "no native part"])
+def test_other_forms_give_the_common_forms_result(form, monkeypatch):
     """What the native calls do not take goes through the checks in Python, with the same outcome."""
     q = QAdam(configs()[0], np.array([0, 1000, P]), N)
 
@@ -97,8 +97,12 @@ def test_other_forms_give_the_common_forms_result(form):
         elif put == "a stream":
             torch.cuda.synchronize()
             stream = torch.cuda.Stream()
+        elif put == "no native part":
+            monkeypatch.setattr(binding, "_native", binding._Unavailable())
         q.step_fused(1, lr, 0.999, g, e, c, s, x, m, v, w, wc, stream=stream)
         torch.cuda.synchronize()
+        monkeypatch.undo()
+        assert not isinstance(binding._native, binding._Unavailable)
         return e + c + list(s) + [x, m, v, w, wc]
 
     assert all(torch.equal(a, b) for a, b in zip(step(form), step(None)))

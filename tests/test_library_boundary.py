@@ -18,9 +18,11 @@ def _declared_functions():
 @pytest.fixture(scope="module")
 def lib():
     from paper_2004_14180_amd import binding
+    from paper_2004_14180_amd.build import ARGS, build_args, build_library
     if not os.path.exists(binding.library_path()):
-        from paper_2004_14180_amd.build import build_library
         build_library(verbose=False)
+    if not os.path.exists(ARGS):
+        build_args(verbose=False)
     return binding.load_library()
 
 
@@ -67,6 +69,32 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(binding, "_LIB_PATH", "/nonexistent/libqadam_hip.so")
     with pytest.raises(ImportError):
         binding.load_library()
+
+
+@pytest.mark.parametrize("why", ["missing", "another torch"])
+def test_without_its_native_part_the_binding_checks_in_python(lib, monkeypatch, why):
+    import importlib
+    import sys
+    import types
+    import warnings
+    import torch
+    from paper_2004_14180_amd import binding
+    name = "paper_2004_14180_amd._args"
+    assert importlib.import_module(name).torch_version == torch.__version__
+    other = types.ModuleType(name)
+    other.torch_version = "1.0"
+    monkeypatch.setitem(sys.modules, name, None if why == "missing" else other)
+    for n in ("_lib", "_native"):
+        monkeypatch.setattr(binding, n, None)
+    with pytest.warns(UserWarning, match="native part is not used"):
+        assert hasattr(binding.load_library(), "qadam_init")
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        binding.load_library()                          # said once
+    t = torch.zeros(16)
+    assert binding._native.plan(0, 1) is None and binding._native.quantize_segment(0, -1, 0, 2, 10, t, t, t, t) is None
+    with pytest.raises(ValueError, match="device tensor"):
+        binding.quantize_segment_noalloc(2, 10, t, t, t, t)
 
 
 def test_device_code_holds_no_packed_fp32_instructions():
