@@ -119,7 +119,8 @@ def test_random_layer_lists_and_settings(seed):
 RAGGED = [1, 3, 31, 33, 0, 255, 257, 4095, 4097, 5000, 0, 64, 8192, 2, 12289, 7]
 
 
-def _custom(sizes, N, steps, seed=1, cfgkw=None, fused=True, scale=1e-2, weight_quant=True, gsel=None, trust=0):
+def _custom(sizes, N, steps, seed=1, cfgkw=None, fused=True, scale=1e-2, weight_quant=True, gsel=None, trust=0, work=None):
+    """work: a list for what qadam_profile_work says of every step."""
     cfgkw = cfgkw or {}
     gcfg, ocfg = configs(**cfgkw)
     seg_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
@@ -127,6 +128,7 @@ def _custom(sizes, N, steps, seed=1, cfgkw=None, fused=True, scale=1e-2, weight_
     rng = np.random.default_rng(seed)
     q = QAdam(gcfg, seg_off, N)
     q.trust_error_buffers(trust)
+    q.profile_enable(work is not None)
     x0 = (rng.standard_normal(P) * 0.02).astype(np.float32)
     ds = DeviceState(q, torch.from_numpy(x0))
     hs = HostState(P, N, x0)
@@ -141,6 +143,8 @@ def _custom(sizes, N, steps, seed=1, cfgkw=None, fused=True, scale=1e-2, weight_
             ds.step_fused(t, 1e-3, 0.999)
         else:
             ds.step_unfused(t, 1e-3, 0.999, weight_quant=weight_quant)
+        if work is not None:
+            work.append(q.profile_work())
         out = oracle_step_layers(ocfg, seg_off, t, 1e-3, 0.999, grads, hs, weight_quant=weight_quant)
         compare_step(rep, ocfg, seg_off, ds, hs, out, weight_quant=weight_quant)
     st = q.get_status()

@@ -1,6 +1,6 @@
 """GPU parity of layers whose scale and quantization are one launch (k_parked): units of every filling, on and off the 16-byte
-grid, the longest layer, units that wait for their scale and units put aside, calls on two streams and beside other work,
-captured calls, non-finite scales."""
+grid, the longest layer, units that wait for their scale and units put aside, calls on several streams and beside other work,
+captured calls, non-finite scales.  The rules that choose are applied to these lists on the CPU in test_work_split.py."""
 import time
 
 import numpy as np
@@ -14,7 +14,8 @@ from test_gpu_parity import _custom
 pytestmark = pytest.mark.gpu
 
 M, N = 1 << 20, 16
-UNIT, LONGEST = 16384, 384 * 16384
+UNIT = 16384
+OF_TWO, LONGEST = 256 * UNIT, 1088 * UNIT       # what a launch that holds two units per workgroup serves, what one with three
 LEAST = 24 * M // N                     # elements from which the whole step of N workers parks its layers, twice that for stochastic
                                         # rounding; one worker's separate call: 24 M, 64 M
 
@@ -58,12 +59,21 @@ def test_some_units_of_a_layer_are_put_aside(polls):
         assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(a.state() + a.codes, b.state() + b.codes)), t
 
 
-@pytest.mark.parametrize("sizes,workers,trust", [([LONGEST, 2 * M, 1001, 0, 70001], 1, 0),      # all parked, an empty layer
-                                                 ([LONGEST + 1, 2 * M - 1, 7], 1, 0),           # not enough of them
-                                                 ([LONGEST + 1, 3, LONGEST - 1, 2 * M], 3, 2)])  # beside a longer one, filtered
-def test_against_the_oracle(sizes, workers, trust):
-    rep, st = _custom(sizes, workers, 2, seed=43, trust=trust)
+# sizes, workers, trust, elements whose scales have a pass of their own
+ORACLE = [([OF_TWO, 2 * M, 1001, 0, 70001, 2 * M], 1, 0, 0),                    # two units, all parked, an empty layer
+          ([OF_TWO, 2 * M, 1001, 0, 2 * M - 1002], 1, 0, 8 * M - 1),            # not enough of them
+          ([700 * UNIT, 0, OF_TWO + 3, 77], 1, 0, 0),                           # three units, all parked
+          ([OF_TWO + 1, 8 * M - 9, 7], 1, 0, 12 * M - 1),                       # not enough of them
+          ([LONGEST + 1, 3, OF_TWO, OF_TWO, OF_TWO - 5, 77], 4, 2, LONGEST + 1),        # two units, beside a longer layer, filtered
+          ([LONGEST + 1, 3, LONGEST - 1, 2 * M], 3, 2, LONGEST + 1)]                    # three
+
+
+@pytest.mark.parametrize("sizes,workers,trust,scanned", ORACLE)
+def test_against_the_oracle(sizes, workers, trust, scanned):
+    work = []
+    rep, st = _custom(sizes, workers, 2, seed=43, trust=trust, work=work)
     assert rep.ok() and st == 0 and rep.float_not_bit_exact == 0, rep.line()
+    assert [w[:2] for w in work] == [(scanned, 0), (scanned, scanned if trust else 0)]
 
 
 class _Calls:
@@ -132,7 +142,10 @@ def test_calls_on_two_streams_do_not_wait_for_workgroups_without_a_place():
     assert beside < 2.0 * alone, (alone, beside)
 
 
-@pytest.mark.parametrize("sizes", [[768 * UNIT, 768 * UNIT + 5], [1003, 1024 * UNIT, 1024 * UNIT, 300 * UNIT]])
+ON_FOUR_STREAMS = [[768 * UNIT, 768 * UNIT + 5], [1003, 1024 * UNIT, 1024 * UNIT, 300 * UNIT]]
+
+
+@pytest.mark.parametrize("sizes", ON_FOUR_STREAMS)
 def test_long_layers_on_four_streams_find_the_units_without_a_workgroup(sizes):
     """Three of four launches have a part of their workgroups on the chip, and a layer needs units that no workgroup has begun with.
     Where every workgroup looked for the first of them, a call took 1.5 to 1.6 times as long as alone; it takes up to 1.25
@@ -230,10 +243,14 @@ def test_variant_w_gives_the_bits_of_the_separate_calls(polls, sizes, workers, c
     assert a.q.profile_work()[0] == 0
 
 
-@pytest.mark.parametrize("sizes", [[36 * UNIT - 7] * 85 + [0, 3], [2000 * UNIT, 1000 * UNIT, 300 * UNIT, 5]])
+W_CALL = [36 * UNIT - 7] * 86 + [0, 3]
+W_CALL_OF_THREE = [2000 * UNIT, 1088 * UNIT] + [1024 * UNIT] * 4 + [5]         # beside a longer layer
+
+
+@pytest.mark.parametrize("sizes", [W_CALL, W_CALL_OF_THREE])
 def test_variant_w_one_workers_call(sizes):
-    """One worker's call that parks its layers, the second list's beside a longer one, against plain tensor operations: moments and
-    scales bit for bit, residuals within half the widest gap of the grid."""
+    """One worker's call that parks its layers, against plain tensor operations: moments and scales bit for bit, residuals within
+    half the widest gap of the grid."""
     a, b = _AnyState(sizes, True, workers=1), _AnyState(sizes, True, workers=1)
     for t in (1, 2):
         a.step(t, True, False)
@@ -250,6 +267,41 @@ def test_variant_w_one_workers_call(sizes):
             at += n
         b.e[0].copy_(a.e[0])        # every next step begins from the same state
         assert (a.e[0].abs() <= 0.2501 * a.scales[0].repeat_interleave(torch.tensor(sizes, device="cuda"))).all()
+
+
+def beside_longer(sizes):
+    """The list with a layer behind it that keeps variant W from parking any of them."""
+    return sizes + [2 * sum(sizes) + 1]
+
+
+W_CALLS = [(W_CALL, 0), (W_CALL_OF_THREE, 0), ([36 * UNIT - 7] * 130 + [1, 2050], 1), ([1001] + [1024 * UNIT] * 5, 1)]
+
+
+@pytest.mark.parametrize("streams", [1, 2])
+@pytest.mark.parametrize("polls", [-1, 3])
+@pytest.mark.parametrize("sizes,rounding", W_CALLS)
+def test_variant_w_calls_give_the_bits_of_two_passes(sizes, rounding, polls, streams):
+    """Two workers' calls, one after the other and on streams of their own, against those of a list whose first layers are the same and
+    are not parked."""
+    a, b = (_AnyState(s, True, workers=2, rounding=rounding, seed=3) for s in (sizes, beside_longer(sizes)))
+    P, L = sum(sizes), len(sizes)
+    a.q.set_scale_polls(polls)
+    for i in range(2):
+        for p, r in ((a.g, b.g), (a.e, b.e), (a.m, b.m), (a.v, b.v)):
+            r[i][:P].copy_(p[i])
+    on = [torch.cuda.Stream() for _ in range(2)] if streams == 2 else [torch.cuda.current_stream()] * 2
+    torch.cuda.synchronize()
+    for t in (1, 2):
+        for s, where in ((a, on), (b, [None, None])):
+            for i in (1, 0):
+                s.q.worker_step_w(i, t, 1e-3, 0.999, s.g[i], s.m[i], s.v[i], s.e[i], s.codes[i], s.scales[i], stream=where[i])
+        torch.cuda.synchronize()
+        for i in range(2):
+            for name, p, r in (("e", a.e, b.e), ("m", a.m, b.m), ("v", a.v, b.v)):
+                assert torch.equal(_bits(p[i]), _bits(r[i][:P])), (t, name, i)
+            assert torch.equal(_bits(a.scales[i]), _bits(b.scales[i][:L])), (t, i)
+            assert torch.equal(a.codes[i], b.codes[i][:a.codes[i].numel()]), (t, i)
+    assert a.q.get_status() == b.q.get_status() == 0
 
 
 @pytest.mark.parametrize("sizes", [_sizes(40 * M // N), [1001, 300 * UNIT, 20 * UNIT]])    # two units, three

@@ -186,22 +186,25 @@ def test_server_by_section_where_one_launch_would_be_sparse(tmp_path):
 
 
 def test_units_cover_a_parked_layer(tmp_path):
-    """Chunk c of a layer is in unit c mod n, and no unit has more chunks than a workgroup holds; the workgroups that are
-    there can hold the longest layer, its units fit the counts of arrivals and departures, and it has no more polled copies
-    of the scale than one wavefront writes."""
+    """Chunk c of a layer is in unit c mod n, and no unit has more chunks than a unit holds; the workgroups that are there, with
+    the two units or three that each holds, can hold the longest layer, its units fit the counts of arrivals and departures, and it has
+    no more polled copies of the scale than one wavefront writes."""
     _run(tmp_path, """
     const int unit = kParkedChunk * kParkedChunks;
     for (int64_t len : {(int64_t)1, (int64_t)kParkedChunk, (int64_t)kParkedChunk + 1, (int64_t)unit, (int64_t)unit + 1, (int64_t)9 * unit - 1,
-                        kParkedLongest - 1, kParkedLongest}) {
-        const int n = parked_units(len);
+                        kParkedLongest - 1, kParkedLongest, kParkedLongest + 1, (int64_t)512 * unit, (int64_t)512 * unit + 1,
+                        kParkedLongestOfThree - 1, kParkedLongestOfThree}) {
+        const int n = parked_units(len), held = len > kParkedLongest ? 3 : 2;
         const int64_t chunks = (len + kParkedChunk - 1) / kParkedChunk;
         for (int u = 0; u < n; ++u) CHECK((chunks - u + n - 1) / n >= 1 && (chunks - u + n - 1) / n <= kParkedChunks, "%lld", (long long)len);
-        CHECK(n < kParkedGroups && (unsigned)n <= kArrivals && (uint64_t)n * kDeparture < (1ull << 32), "%lld", (long long)len);
+        CHECK(n < held * kParkedGroups && (held == 3 || n < kParkedGroups) && (unsigned)n <= kArrivals && (uint64_t)n * kDeparture < (1ull << 32), "%lld", (long long)len);
         CHECK(meeting_copies(n) >= 1 && meeting_copies(n) <= 64, "%lld", (long long)len);
         CHECK(meeting_words(n) == (n > 1 ? (1 + meeting_copies(n)) * kMeetingLine : 0), "%lld", (long long)len);
     }
     const int64_t M = 1 << 20;
     CHECK(worth_parking(8 * M, 512, 8 * M, 1, false) && !worth_parking(8 * M - 1, 512, 8 * M, 1, false), "one worker");
+    CHECK(worth_parking(12 * M, 768, 12 * M, 1, false, false, kParkedLongest + 1) && !worth_parking(12 * M - 1, 768, 12 * M, 1, false, false, kParkedLongest + 1) &&
+          worth_parking(8 * M, 512, 8 * M, 1, false, false, kParkedLongest), "one worker, three units");
     CHECK(worth_parking(6 * M, 384, 12 * M, 4, false) && !worth_parking(6 * M - 1, 384, 6 * M, 4, false), "four workers");
     CHECK(worth_parking(12 * M, 768, 48 * M, 4, false) && !worth_parking(12 * M - 1, 768, 24 * M, 4, false), "beside a longer layer");
     CHECK(!worth_parking(12 * M, 768, 48 * M + 1, 4, false), "beside a much longer layer");
@@ -305,17 +308,22 @@ def test_the_lists_of_the_gpu_tests_lie_on_both_sides_of_the_rules(tmp_path):
     import test_gpu_by_worker as by
     import test_gpu_parked as parked
     body = """
-    struct Counts { int64_t all, elems, units, off; };
+    struct Counts { int64_t all, elems, units, off, longest; };
     auto count = [](std::initializer_list<int64_t> sizes) {
         Counts c{};
         for (int64_t n : sizes) {
             if (c.all % 4 != 0) c.off += n;
-            if (n <= kParkedLongest) { c.elems += n; c.units += parked_units(n); }
+            if (n <= kParkedLongestOfThree) { c.elems += n; c.units += parked_units(n); c.longest = n > c.longest ? n : c.longest; }
             c.all += n;
         }
         return c;
     };
-    auto parks = [](const Counts& c, int num, bool stochastic) { return worth_parking(c.elems, c.units, c.all, num, stochastic); };"""
+    auto parks = [](const Counts& c, int num, bool stochastic, bool call = false) {
+        return worth_parking(c.elems, c.units, c.all, num, stochastic, call, c.longest);
+    };
+    auto parks_w = [](const Counts& c, int num, bool stochastic) {
+        return worth_parking_w(c.elems, c.units, c.all, num, stochastic, c.longest);
+    };"""
     for kind in by.LAST:
         for more in (0, 1):
             body += """
@@ -329,7 +337,15 @@ def test_the_lists_of_the_gpu_tests_lie_on_both_sides_of_the_rules(tmp_path):
             body += """
     CHECK(parks(count(%s), %d, %d) == %d, "parked, %d");""" % (
                 _c_list(parked._sizes((1 + stochastic) * parked.LEAST - less)), parked.N, stochastic, 1 - less, less)
-    body += """
-    CHECK(worth_parking(%d, %d, %d, 1, false, true), "separate calls");""" % (
-        sum(parked.SIZES), sum((n + parked.UNIT - 1) // parked.UNIT for n in parked.SIZES), sum(parked.SIZES))
+    for sizes in (parked.SIZES, *parked.ON_FOUR_STREAMS):
+        body += """
+    CHECK(parks(count(%s), 1, false, true), "separate calls");""" % _c_list(sizes)
+    for sizes, workers, _, scanned in parked.ORACLE:
+        body += """
+    { const Counts c = count(%s); CHECK((parks(c, %d, false) ? c.all - c.elems : c.all) == %d, "against the oracle"); }""" % (
+            _c_list(sizes), workers, scanned)
+    for sizes, stochastic in parked.W_CALLS:
+        body += """
+    CHECK(parks_w(count(%s), 1, %d) && !parks_w(count(%s), 1, %d), "one worker's call of variant W");""" % (
+            _c_list(sizes), stochastic, _c_list(parked.beside_longer(sizes)), stochastic)
     _run(tmp_path, body)
