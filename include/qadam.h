@@ -19,8 +19,8 @@
  * paper's Algorithms 2-3 keep the moments on the workers and quantize the Adam update instead
  * ("variant W"); the entry points ending in _w implement that placement with the same kernels.
  *
- * All arithmetic is IEEE binary32, one rounding per operation (no fused multiply-add), subnormals
- * kept, division and square root correctly rounded; integer codes are therefore reproducible bit
+ * All arithmetic is IEEE binary32, one rounding per operation (a multiply-add appears only where its
+ * product is exact, so that it rounds as the two operations do), subnormals kept, division and square root correctly rounded; integer codes are therefore reproducible bit
  * for bit by a plain CPU implementation of the same formulas.
  *
  * Conventions

@@ -310,9 +310,10 @@ class QAdam:
             raise ValueError("%s is required" % name)
         if len(ts) != self.num_workers:
             raise ValueError("%s: expected %d tensors (one per worker), got %d" % (name, self.num_workers, len(ts)))
-        # A step of a short vector is bound by the host, and most of the host's work is these checks (51 k parameters,
-        # 4 workers: 21 buffers, 32.3 -> 20.2 us per step): the common form of a buffer passes in one expression, any
-        # other goes to _buf, which takes the other types and words the refusal.
+        # For the calls that the native part does not take: server_apply_w, a step with an identity quantizer, another form of a buffer,
+        # no native part.  These checks are most of the host's work there (51 k parameters, 4 workers: 21 buffers, 32.3 -> 20.2 us
+        # per step): the common form of a buffer passes in one expression, any other goes to _buf, which takes the other types
+        # and words the refusal.
         dtype, size = (_torch.float32, 1) if kind == "f32" else (_torch.int32, 4)
         dev = _torch._C._cuda_getDevice() if _torch.cuda.is_initialized() else -1
         addrs = [t.data_ptr() if t is not None and t.dtype is dtype and t.is_cuda and t.get_device() == dev
@@ -322,7 +323,8 @@ class QAdam:
 
     # the calls ---------------------------------------------------------------------------------
     # us per step of a short vector, checks in Python / native: 51 k parameters, 4 workers, 21 buffers 20.4 / 14.6; one worker of 2^20, two
-    # calls 18.9 / 14.0; of the host alone 19.9 / 7.4 and 19.5 / 10.2, the handle-free call 5.0 / 3.6.
+    # calls 18.9 / 14.0; of the host alone 19.9 / 7.4 and 19.5 / 10.2, the handle-free call 5.0 / 3.6.  Variant W's separate calls and the
+    # decoders are checked in Python alone.
     def worker_quantize(self, worker, step, grad, err, codes, scales, stream=None):
         rc = _native.worker_quantize(self._plan, *_device_and_stream(stream), worker, step, grad, err, codes, scales)
         if rc is not None:

@@ -26,7 +26,7 @@ HIPCC_FLAGS = [
     # time.  The compiler reads such a struct straight from the kernel-argument segment only if a use scan of
     # bounded length succeeds (default 300 uses); the fused kernel, with its piece of a tile instantiated four
     # times (whole or not, on or off the 16-byte grid), has more, and past the bound the whole 1.2 KB struct is copied to per-lane scratch memory
-    # at kernel entry.  tests/test_library_boundary.py checks that no kernel has a scratch segment.
+    # at kernel entry.  tests/test_library_boundary.py checks that no kernel has more than 64 bytes of scratch per lane.
     "-mllvm", "-instcombine-max-copied-from-constant-users=4000",
     "-Wall", "-Wno-unused-function",
 ]

@@ -1351,11 +1351,13 @@ __global__ void __launch_bounds__(kSegmentThreads) k_segment(SegmentArgs A)
 // LDS, the younger ones in registers.  Each turn it quantizes the oldest one chunk by chunk while the next unit is loaded and the
 // others move up, so that loads and stores mix and a layer's units have a turn or two to meet.  In variant W the local moments are
 // updated on the way, 28.4 bytes per element for 36.4.  Bound by memory: 85 M elements, one
-// worker 257 -> 194 us with two units, layers of 8 to 17 M elements 261 -> 209 with three; beyond the first and last turns 6.0 TB/s.
-// Layers of one unit each, which do not meet, take the same time.  Chunks whose loads are in flight together, two units, 2 / 4 / 8: 209 /
-// 206 / 220 us (8 spills); three units, 2 / 4 (4 spills): 211 / 228, where 1024 units meet 1706 / 1822; workgroups of 256 / 512 / 1024
-// threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded, waited for and stored in turn 229.  A workgroup's
-// first unit is the one of its own number, the others are drawn from a counter in the order of the layers: all dealt out beforehand
+// worker 257 -> 194 us with two units, layers of 8 to 17 M elements 261 -> 209 with three; beyond the first and last turns 6.45 TB/s
+// with two units and 5.92 with three, whose loads in flight are fewer, in variant W 5.80 and 5.64.
+// Layers of one unit each, which do not meet, take the same time.  Measured with guarded stores in every turn (206 us): chunks whose loads
+// are in flight together, two units, 2 / 4 / 8: 209 / 206 / 220 us (8 spills); three units, 2 / 4 (4 spills): 211 / 228, where 1024 units
+// meet 1706 / 1822; workgroups of 256 / 512 / 1024 threads 205 / 206 / 207; half as many workgroups 253; one unit per workgroup, loaded,
+// waited for and stored in turn 229.  The forms with three units and those of variant W have 8 to 52 bytes of scratch per lane; with
+// three units one word or up to four are stored there before the first turn and read once in a turn, with two none.  A workgroup's first unit is the one of its own number, the others are drawn from a counter in the order of the layers: all dealt out beforehand
 // they end 10 us later, all drawn they begin 4 us later, as 512 draws at once take that long.
 // A turn that quantizes a whole unit and loads a whole one runs straight through, without a guard around a store: where paths with and
 // without stores join, the wait for the loads becomes one for everything (two units, layers of 144 units 200 / 194).  The maxima of a layer

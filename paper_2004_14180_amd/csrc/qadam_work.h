@@ -244,7 +244,8 @@ constexpr int parked_units(int64_t len)
 // Layers of up to kParkedLongestOfThree: 1088 units, 17.8 M elements.  The 512 workgroups of a launch (kParkedGroups, two per CU) hold two or
 // three units each, of which one is being replaced, and a layer of nearly as many units as they hold beside it leaves none for its
 // neighbours.  The third unit costs loads in flight and a turn more that only loads, so it is there only for lists with a layer of
-// more than kParkedLongest elements (256 units).  One worker's call of 85 M elements, us, two passes / two units / three: layers of 36 units 260 / 202 /
+// more than kParkedLongest elements (256 units).  The line is one for all calls and lies where the step whose scale pass is the filtered
+// one stops gaining; a call with the full pass would gain up to 10 % beyond it.  One worker's call of 85 M elements, us, two passes / two units / three: layers of 36 units 260 / 202 /
 // 206, 144 260 / 194 / 202, 256 259 / 203, 300 259 / 209 / 202, 384 272 / 232 / 212, 512 257 / 262 / 209, 768 275 / 273 / 218, 1024 261 / 263 /
 // 209, 1100 (90 M) 277 / - / 242, 1280 (105 M) 323 / - / 291; step of 4 workers whose scale pass is the filtered one, 768 (88 M) 1348 / - /
 // 1257, 1024 (117 M) 1790 / - / 1650, 1100 (90 M) 1388 / - / 1383, 1280 (105 M) 1599 / - / 1623.
@@ -260,8 +261,9 @@ constexpr int64_t kParkedLongestOfThree = (int64_t)1088 * kParkedChunk * kParked
 
 // Whether a step of num workers, or one worker's separate call (`call`), does the layers of up to kParkedLongestOfThree elements this way:
 // `elems` in `units`, of the `all` elements whose scales have a pass of their own.  The launch starts by loading only and ends by
-// storing only, which costs it about 29 us (85 M elements in 206 us, 340 M in 738).  us, without / with, layers of 2^18 to 2^21
-// elements: step of one worker of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 /
+// storing only, which costs it about 30 us with two units (layers of 144 units, 85 M elements in 193 us, 340 M in 682), 34 with three
+// (1024 units, 84 M in 209, 336 M in 735).  The figures from here to "a third unit" are of turns with guarded stores, 5 % slower at 85 M.
+// us, without / with, layers of 2^18 to 2^21 elements: step of one worker of 4 M (2^20) 37.0 / 47.0, 8 M 83.1 / 79.2, 16 M 156 / 147, 64 M 559 / 517; 4 workers of 4 M 80.8 /
 // 82.6, 8 M 155 / 141, 32 M 599 / 482; 8 of 2 M 71.0 / 71.9, 4 M 137 / 121, 32 M 1020 / 755.  A unit costs about the same however few
 // elements it has: 4000 layers of 5000, one worker's call 69.4 / 78.8, step of 4 workers 404 / 395; 500 of 10000 and 100, 4 workers
 // 107 / 123, 3000 times 609 / 513; 1000 of 20000 375 / 338.  Beside a long layer the step goes worker by worker for its sake: one of
@@ -308,7 +310,8 @@ constexpr bool worth_parking_w(int64_t elems, int64_t units, int64_t all, int nu
 }
 
 // The meeting place of a layer's workgroups: a word that counts arrivals and departures, and copies of the published scale
-// for up to eight of them each to poll, every one in a line of its own.  Words.
+// to poll, every one in a line of its own, for up to eight of them each in layers of up to 512 units and 17 in the longest: one
+// wavefront writes all copies.  Words.
 constexpr int kMeetingLine = 32;
 constexpr uint32_t kArrivals = 0xffffu, kDeparture = 0x10000u;
 // In front of a worker's meeting places: the counts of a launch, and the claims of the workgroups' first units.

@@ -155,7 +155,7 @@ def test_long_layers_on_four_streams_find_the_units_without_a_workgroup(sizes):
     one.run(alone), many.run(beside)
     assert all(torch.equal(_bits(p), _bits(r)) for p, r in zip(one.state(), many.state()))
     a, b = (min(one.run(streams, 10) for _ in range(4)) for streams in (alone, beside))
-    assert b < 1.37 * a, (a, b)
+    assert b < 1.42 * a, (a, b)
 
 
 def test_overlapping_code_buffers_do_not_change_the_step():
